@@ -310,3 +310,28 @@ def test_device_gate_refuses_late_sgd_steps_and_the_factors_keep_their_bits():
     assert _same_bits(got_P, P32) and _same_bits(got_Q, Q32)
     P64, Q64 = osgd.sgd(r.row_ptr, r.item, r.rating, P0, Q0, gamma, lam, K, B)
     assert np.abs(got_P - P64).max() <= TOL64 and np.abs(got_Q - Q64).max() <= TOL64
+
+
+def _dense(pairs, n_users, n_items, seed):
+    pairs = sorted(set(pairs))
+    row_ptr = np.zeros(n_users + 1, np.int64)
+    np.add.at(row_ptr, np.array([u for u, _ in pairs]) + 1, 1)
+    rating = np.random.default_rng(seed).uniform(1, 5, len(pairs)).astype(np.float32)
+    return wl.Ratings(n_users, n_items, len(pairs), np.cumsum(row_ptr).astype(np.int32), np.array([i for _, i in pairs], np.int32), rating)
+
+
+# where the layout in rounds can go wrong: a batch of one rating, full batches and one more (128, 129), one chain (a single
+# user or item), no chain at all (a diagonal: 256 rows and the most LDS), a grid, cells without ratings, and both sides of
+# the mean cell size (256) from which on the ratings are worked on one after the other
+@pytest.mark.parametrize("F", [16, 32, 64])
+@pytest.mark.parametrize("shape,B", [((1, 1), 1), ((1, 128), 1), ((1, 129), 1), ((129, 1), 1), ("diagonal", 1), ((16, 16), 1), ((1, 257), 1),
+                                     ((33, 31), 2), ((9, 7), 7)])
+def test_rounds_of_a_batch_match_the_oracle(shape, B, F):
+    print("case", shape, B, F, flush=True)
+    pairs = [(k, k) for k in range(128)] if shape == "diagonal" else [(u, i) for u in range(shape[0]) for i in range(shape[1])]
+    n_users, n_items = max(u for u, _ in pairs) + 3, max(i for _, i in pairs) + 2
+    r = _dense(pairs, n_users, n_items, seed=len(pairs))
+    P0, Q0 = wl.initial_factors(n_users, n_items, F, seed=F)
+    P, Q, _ = _run(r, P0, Q0, F, 0.02, 0.03, 3, B)
+    P32, Q32 = osgd.sgd(r.row_ptr, r.item, r.rating, P0, Q0, 0.02, 0.03, 3, B, ordered_fp32=True)
+    assert _same_bits(P, P32) and _same_bits(Q, Q32)
