@@ -7,19 +7,20 @@
 // clock for a fixed time.
 
 #include <algorithm>
+#include <cmath>
 #include <new>
+#include <type_traits>
 
 #include "common.h"
 
 namespace {
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
-typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
+typedef __attribute__((address_space(3))) char* LdsBytes;
+__device__ __forceinline__ LdsBytes lds_at(uint32_t address) { return reinterpret_cast<LdsBytes>(address); }
 
-constexpr int BM = 256, BN = 128, BK = 64;     // workgroup tile
-constexpr int kThreads = 512;                  // 8 wavefronts as 4 x 2, each 64 x 64 of C
-constexpr int kLdsRow = BK + 8;                // bf16 elements per LDS row: 128 B of data + 16 B pad, which spreads
-                                               // the rows one 16-byte-per-lane LDS access touches over the banks
+constexpr int BK = 64;                         // K of a k-tile: 128 bytes of a row
 constexpr int kXcds = 8;
 
 __device__ __forceinline__ uint16_t f32_to_bf16_rne(float x)
@@ -29,88 +30,230 @@ __device__ __forceinline__ uint16_t f32_to_bf16_rne(float x)
     return (uint16_t)(u >> 16);
 }
 
-// C[M, N] = A[M, K] * B[N, K]^T, bf16 in / bf16 out, fp32 accumulate.  M multiple of 256, N of 128, K of 64.
-// Per k-tile: the registers holding the tile go to LDS, the next tile's global loads are issued into the same
-// registers, and the tile is multiplied out of LDS (4 k-steps of v_mfma_f32_32x32x16_bf16, 2 x 2 MFMA tiles per
-// wavefront).  Two workgroups share a CU (54 KB of LDS and 128 registers per lane each), so one multiplies while
-// the other sits at its barrier.  The staging registers are named scalars on purpose: as small private arrays
-// they are moved to LDS or scratch by the compiler and the kernel runs three times slower.
-// Workgroups are dealt round-robin over the 8 XCDs by the hardware; the tile map undoes that so that each XCD
-// walks a contiguous run of tiles (same A rows, consecutive B columns) and reuses its own L2.
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 4)))
+__device__ __forceinline__ uint32_t two_bf16(float lo, float hi)
+{
+    typedef float f2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 b2 __attribute__((ext_vector_type(2)));
+    const f2 x = {lo, hi};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(x, b2));        // nearest even
+}
+
+// The instruction scheduler keeps what stands on either side of this apart.
+__device__ __forceinline__ void keep_order() { __builtin_amdgcn_sched_barrier(0); }
+
+// A barrier without the wait for all loads in flight that __syncthreads() brings along.
+__device__ __forceinline__ void plain_barrier()
+{
+    keep_order();
+    asm volatile("s_barrier" ::: "memory");
+    keep_order();
+}
+
+// Global memory to LDS, 16 bytes a lane, without passing through registers: lane l's bytes go to LDS address m0 + 16 l.
+// (Written as assembly so that the compiler does not wait for every load in flight before each read of LDS: which loads
+// have to be here is counted by hand, wait_loads.)
+__device__ __forceinline__ void aim_lds(uint32_t lds) { asm volatile("s_mov_b32 m0, %0" ::"s"(lds) : "memory"); }
+__device__ __forceinline__ void load_to_lds(uint32_t lane_offset, const char* g)
+{
+    asm volatile("global_load_lds_dwordx4 %0, %1" ::"v"(lane_offset), "s"(g) : "memory");
+}
+template <int kLeft> __device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(%0)" ::"i"(kLeft) : "memory"); }
+
+// LDS of a group of four wavefronts: five slots, each large enough for one operand's k-tile.
+constexpr uint32_t slot_bytes(int BM, int BN) { return (uint32_t)(BM > BN ? BM : BN) * BK * 2; }
+
+// C[M, N] = A[M, K] * B[N, K]^T, bf16 in / bf16 out, fp32 accumulate.  M multiple of BM, N of BN, K of 64.
+//
+// One workgroup per BM x BN tile; its four wavefronts (2 x 2) hold a quarter each, as 16 x 16 blocks of
+// v_mfma_f32_16x16x32_bf16 in place in the accumulator registers.  (The instruction is written as assembly: left to itself
+// the compiler moves 256 registers of accumulators around.)  With kSplit = 4, sixteen wavefronts: four such groups with a
+// quarter of K each, whose sums are added up in LDS at the end.
+//
+// A and B pass through LDS in k-tiles of 64, in slots of a ring of five (A of k-tile t in slot 2 t mod 5, B in the next), one
+// operand two k-tiles ahead.  A k-tile is worked on in two halves of K = 32.  First half: the MFMAs of the half whose
+// fragments are in registers, the other half's fragments being read from LDS, A of k-tile t + 2 asked for.  Then the one
+// barrier of a k-tile: every wavefront has read all of k-tile t, and k-tile t + 1 has landed.  Second half: its
+// MFMAs, the first fragments of k-tile t + 1, and B of k-tile t + 2 into the slot A of t was in.  Reads and loads stand between
+// the MFMAs one by one, so that a SIMD's only wavefront keeps its matrix core busy.
+//
+// Rows of 128 bytes are loaded whole (eight lanes a row; 64-byte pieces cost 10 %).  Inside a row, 16-byte chunk c sits
+// at place c ^ h: h = (row / 2) mod 8 for A, and for B, whose fragments take rows 8 q + r and 8 q + 4 + r for lanes 4 q + r, bits
+// 1, 3 and 4 of the row.  Sixteen-byte reads are served for lanes 0-3, 12-15, 20-23, 24-27 together (and so on), and with
+// these h they hit 64 different banks (no conflict counted; with row mod 8 every read took twice as long).
+// The operands are swapped in the MFMA (B first), which leaves a lane four consecutive columns of one row, and with B's rows
+// taken as above eight, so that rows of C are written in pieces of 64 bytes.
+//
+// What bounds it: on large products the matrix cores are busy 66 - 88 % of the time at 1.8 - 2.1 GHz, to which the chip
+// lowers its clock under this load (2.4 GHz otherwise); writing C takes 3 - 6 us a tile with all compute units at it at
+// once.  Measured, bf16 values uniform in [-1/8, 1/8):
+//   8192 x 8192 x 8192     720 us  1530 TFLOP/s      2048 x 16384 x 4096   179 - 207 us  1330 - 1540 TFLOP/s
+//   2048 x 4096 x 16384    200 us  1370              16384 x 4096 x 2048   195 - 212 us  1300 - 1410
+//   512 x 768 x 1024       6.6 us   123              (before: 20.4 us; the other shapes 850 - 1000 TFLOP/s with 256 x 128 tiles,
+//   staged through registers, and two barriers per k-tile)
+template <int BM, int BN, int kSplit>
+__global__ __launch_bounds__(256 * kSplit) __attribute__((amdgpu_waves_per_eu(kSplit > 1 ? kSplit : BM * BN >= 32768 ? 1 : 2, kSplit > 1 ? kSplit : BM * BN >= 32768 ? 1 : 2)))
 void k_gemm_bf16_nt(const uint16_t* __restrict__ A, const uint16_t* __restrict__ B, uint16_t* __restrict__ C, int M, int N, int K)
 {
-    constexpr int kPiecesPerRow = BK / 8, kRowsPerPass = kThreads / kPiecesPerRow;     // 8 pieces of 16 B, 64 rows
-    __shared__ __align__(16) uint16_t sA[BM * kLdsRow];
-    __shared__ __align__(16) uint16_t sB[BN * kLdsRow];
+    constexpr int NI = BM / 32, NJ = BN / 32;              // 16 x 16 blocks of a wavefront's quarter
+    constexpr uint32_t kSlot = slot_bytes(BM, BN);
+    __shared__ __align__(1024) char lds[5 * kSlot * kSplit];
+    static_assert(sizeof(lds) <= 163840, "LDS of a compute unit");
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave_all = __builtin_amdgcn_readfirstlane(tid >> 6), wave = wave_all & 3, group = wave_all >> 2;
     const int wm = wave >> 1, wn = wave & 1;
-    const int tiles_n = N / BN, n_tiles = (int)gridDim.x;
-    int tile = (int)blockIdx.x;
-    if (n_tiles % kXcds == 0) tile = (tile % kXcds) * (n_tiles / kXcds) + tile / kXcds;
-    const int bm = (tile / tiles_n) * BM, bn = (tile % tiles_n) * BN;
+    const uint32_t lds0 = (uint32_t)reinterpret_cast<uintptr_t>((LdsBytes)lds), base = lds0 + group * 5 * kSlot;
+    asm volatile("" ::"s"(lds0) : "memory");               // (the array is written behind the compiler's back)
 
-    const int ld_row = tid / kPiecesPerRow, ld_k = (tid % kPiecesPerRow) * 8;
-    const uint16_t* gA = A + (size_t)(bm + ld_row) * K + ld_k;
-    const uint16_t* gB = B + (size_t)(bn + ld_row) * K + ld_k;
-    const size_t step = (size_t)kRowsPerPass * K;
-
-    f32x16 acc00, acc01, acc10, acc11;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) { acc00[r] = 0.0f; acc01[r] = 0.0f; acc10[r] = 0.0f; acc11[r] = 0.0f; }
-
-    uint4 a0 = *reinterpret_cast<const uint4*>(gA), a1 = *reinterpret_cast<const uint4*>(gA + step);
-    uint4 a2 = *reinterpret_cast<const uint4*>(gA + 2 * step), a3 = *reinterpret_cast<const uint4*>(gA + 3 * step);
-    uint4 b0 = *reinterpret_cast<const uint4*>(gB), b1 = *reinterpret_cast<const uint4*>(gB + step);
-
-    const int frag_row = lane & 31, frag_k = (lane >> 5) * 8;
-    uint16_t* wA = &sA[ld_row * kLdsRow + ld_k];
-    uint16_t* wB = &sB[ld_row * kLdsRow + ld_k];
-    const uint16_t* rA = &sA[(wm * 64 + frag_row) * kLdsRow + frag_k];
-    const uint16_t* rB = &sB[(wn * 64 + frag_row) * kLdsRow + frag_k];
-    constexpr int kPass = kRowsPerPass * kLdsRow;
-    for (int k0 = 0; k0 < K; k0 += BK) {
-        __syncthreads();                       // previous tile fully consumed
-        *reinterpret_cast<uint4*>(wA) = a0;
-        *reinterpret_cast<uint4*>(wA + kPass) = a1;
-        *reinterpret_cast<uint4*>(wA + 2 * kPass) = a2;
-        *reinterpret_cast<uint4*>(wA + 3 * kPass) = a3;
-        *reinterpret_cast<uint4*>(wB) = b0;
-        *reinterpret_cast<uint4*>(wB + kPass) = b1;
-        __syncthreads();
-        if (k0 + BK < K) {                     // fetch the next tile while this one is multiplied
-            const uint16_t* pA = gA + k0 + BK;
-            const uint16_t* pB = gB + k0 + BK;
-            a0 = *reinterpret_cast<const uint4*>(pA);
-            a1 = *reinterpret_cast<const uint4*>(pA + step);
-            a2 = *reinterpret_cast<const uint4*>(pA + 2 * step);
-            a3 = *reinterpret_cast<const uint4*>(pA + 3 * step);
-            b0 = *reinterpret_cast<const uint4*>(pB);
-            b1 = *reinterpret_cast<const uint4*>(pB + step);
-        }
-#pragma unroll
-        for (int kk = 0; kk < BK; kk += 16) {
-            const bf16x8 fa0 = *reinterpret_cast<const bf16x8*>(rA + kk);
-            const bf16x8 fa1 = *reinterpret_cast<const bf16x8*>(rA + 32 * kLdsRow + kk);
-            const bf16x8 fb0 = *reinterpret_cast<const bf16x8*>(rB + kk);
-            const bf16x8 fb1 = *reinterpret_cast<const bf16x8*>(rB + 32 * kLdsRow + kk);
-            acc00 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa0, fb0, acc00, 0, 0, 0);
-            acc01 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa0, fb1, acc01, 0, 0, 0);
-            acc10 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa1, fb0, acc10, 0, 0, 0);
-            acc11 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa1, fb1, acc11, 0, 0, 0);
-        }
+    // The tile of this workgroup.  Workgroups are dealt round-robin over the XCDs; every XCD gets a contiguous run of
+    // tiles, which go through bands of 1024 rows of C column by column: 32 tiles side by side on an XCD then read few rows
+    // and columns, through its own L2.
+    int bm, bn;
+    {
+        constexpr int kBand = 1024 / BM;
+        const int tiles_m = M / BM, tiles_n = N / BN, n = tiles_m * tiles_n;
+        const int xcd = (int)blockIdx.x % kXcds, q = n / kXcds, r = n % kXcds;
+        const int id = xcd * q + (xcd < r ? xcd : r) + (int)blockIdx.x / kXcds;
+        const int band = id / (kBand * tiles_n), rows = tiles_m - band * kBand < kBand ? tiles_m - band * kBand : kBand, in = id - band * kBand * tiles_n;
+        bm = (band * kBand + in % rows) * BM;
+        bn = in / rows * BN;
     }
+    const size_t row_bytes = (size_t)K * 2, rows8 = 8 * row_bytes;
+    const int nk_all = K / BK, nk_most = (nk_all + kSplit - 1) / kSplit;       // k-tiles of all groups, of a group
+    const int k0 = group * nk_most < nk_all ? group * nk_most : nk_all, nk = nk_all - k0 < nk_most ? nk_all - k0 : nk_most;
 
-    // accumulator layout of the 32 x 32 MFMA: lane l holds column l % 32, rows 8 * (r / 4) + 4 * (l / 32) + r % 4
-    const int col = bn + wn * 64 + (lane & 31), row_in = (lane >> 5) * 4;
+    // loads: eight rows a load, lane l the chunk for place l % 8 of row l / 8 (chunk = place ^ h)
+    const int lrow = lane >> 3, place = lane & 7;
+    constexpr int kVarA = 2, kVarB = NJ < 4 ? NJ : 4;      // h over the loads of a wavefront: so many different ones
+    uint32_t vA[kVarA], vB[kVarB];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        const int row = bm + wm * 64 + 8 * (r >> 2) + row_in + (r & 3);
-        C[(size_t)row * N + col] = f32_to_bf16_rne(acc00[r]);
-        C[(size_t)row * N + col + 32] = f32_to_bf16_rne(acc01[r]);
-        C[(size_t)(row + 32) * N + col] = f32_to_bf16_rne(acc10[r]);
-        C[(size_t)(row + 32) * N + col + 32] = f32_to_bf16_rne(acc11[r]);
+    for (int j = 0; j < kVarA; ++j) vA[j] = lrow * (uint32_t)row_bytes + (uint32_t)(place ^ (lrow >> 1) ^ (4 * j)) * 16;
+#pragma unroll
+    for (int j = 0; j < kVarB; ++j) vB[j] = lrow * (uint32_t)row_bytes + (uint32_t)(place ^ (((lrow >> 1) & 1) | (((wave * (BN / 4) / 8) + j) & 3) << 1)) * 16;
+    const char* gA = reinterpret_cast<const char*>(A) + (size_t)(bm + wave * (BM / 4)) * row_bytes + (size_t)k0 * (BK * 2);
+    const char* gB = reinterpret_cast<const char*>(B) + (size_t)(bn + wave * (BN / 4)) * row_bytes + (size_t)k0 * (BK * 2);
+    auto advance = [&] { gA += BK * 2; gB += BK * 2; };      // (they point at k-tile t + 2)
+
+    f32x4 acc[NI][NJ];
+
+    // fragments: lane l holds k 8 (l / 16) .. + 7 of a block's row l % 16
+    const int fr = lane & 15, kq = lane >> 4;
+    const uint32_t hA = (uint32_t)(fr >> 1) & 7, hB = ((uint32_t)(fr >> 1) & 1) | (uint32_t)(fr >> 2) << 1;
+    const uint32_t rowA = base + (uint32_t)(wm * (BM / 2) + fr) * 128, rowB = base + (uint32_t)(wn * (BN / 2) + (fr >> 2) * 8 + (fr & 3)) * 128;
+    const uint32_t rA[2] = {rowA + (kq ^ hA) * 16, rowA + ((kq | 4) ^ hA) * 16}, rB[2] = {rowB + (kq ^ hB) * 16, rowB + ((kq | 4) ^ hB) * 16};
+    struct Fragments { bf16x8 a[NI], b[NJ]; };
+    typedef const __attribute__((address_space(3))) bf16x8* LdsFragment;
+    auto read = [&](Fragments& f, int half, uint32_t slot_a, uint32_t slot_b, int w) {
+        if (w < NI) f.a[w] = *reinterpret_cast<LdsFragment>(lds_at(rA[half] + slot_a) + w * 2048);
+        else f.b[w - NI] = *reinterpret_cast<LdsFragment>(lds_at(rB[half] + slot_b) + (w - NI) / 2 * 4096 + (w - NI) % 2 * 512);
+    };
+    // one half of a k-tile: the MFMAs on `now`; reads into `next`; one operand's loads, eight rows each
+    auto half_tile = [&](Fragments& now, Fragments& next, int half, uint32_t slot_a, uint32_t slot_b, const char* g, uint32_t slot, auto is_b, auto loads) {
+        constexpr bool kB = decltype(is_b)::value, kLoad = decltype(loads)::value;
+        constexpr int kMfma = NI * NJ, kReads = NI + NJ, kLoads = kB ? NJ : NI, kEvery = kMfma / kLoads;
+        constexpr int kReadEvery = 3 * kMfma / 4 / kReads > 0 ? 3 * kMfma / 4 / kReads : 1;
+        const uint32_t to = base + slot + wave * ((kB ? BN : BM) * 32);
+#pragma unroll
+        for (int i = 0; i < NI; ++i)
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) {
+                const int m = i * NJ + j, d = m / kEvery;
+                asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc[i][j]) : "v"(now.b[j]), "v"(now.a[i]));
+                keep_order();
+                if (m % kReadEvery == 0 && m / kReadEvery < kReads) { read(next, half, slot_a, slot_b, m / kReadEvery); keep_order(); }
+                const uint32_t v = kB ? vB[d % kVarB] : vA[d % kVarA];
+                if (!kLoad) continue;
+                if (kEvery >= 4) {                         // (m0 is set one MFMA before it is used: a load may not follow at once)
+                    if (m % kEvery == kEvery - 3) { aim_lds(to + d * 1024); keep_order(); }
+                    if (m % kEvery == kEvery - 2) { load_to_lds(v, g); g += rows8; keep_order(); }
+                } else if (m % kEvery == kEvery - 1) {
+                    aim_lds(to + d * 1024);
+                    asm volatile("s_nop 0");
+                    load_to_lds(v, g);
+                    g += rows8;
+                    keep_order();
+                }
+            }
+    };
+    auto two_on = [&](uint32_t slot) { const uint32_t x = slot + 2 * kSlot; return x >= 5 * kSlot ? x - 5 * kSlot : x; };
+
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        if (t < nk) {
+#pragma unroll
+            for (int j = 0; j < NI; ++j) { aim_lds(base + 2 * t * kSlot + wave * (BM * 32) + j * 1024); asm volatile("s_nop 0"); load_to_lds(vA[j % kVarA], gA + j * rows8); }
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) { aim_lds(base + (2 * t + 1) * kSlot + wave * (BN * 32) + j * 1024); asm volatile("s_nop 0"); load_to_lds(vB[j % kVarB], gB + j * rows8); }
+        }
+        advance();
+    }
+    if (nk > 1) wait_loads<NI + NJ>();
+    else wait_loads<0>();
+    plain_barrier();
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    Fragments f0, f1;
+#pragma unroll
+    for (int w = 0; w < NI + NJ; ++w) read(f0, 0, 0, kSlot, w);
+    uint32_t slot_a = 0, slot_b = kSlot;
+    auto k_tile = [&](auto loads) {
+        const uint32_t next_a = two_on(slot_a), next_b = two_on(slot_b);
+        keep_order();
+        half_tile(f0, f1, 1, slot_a, slot_b, gA, two_on(next_a), std::false_type{}, loads);
+        keep_order();
+        static_assert(NI <= 8, "as a load count of the wait below");
+        // no read of LDS outstanding, and no load but the NI just asked for
+        if (decltype(loads)::value) __builtin_amdgcn_s_waitcnt(0x0070 | NI);
+        else __builtin_amdgcn_s_waitcnt(0x0070);
+        plain_barrier();
+        half_tile(f1, f0, 0, next_a, next_b, gB, slot_a, std::true_type{}, loads);
+        slot_a = next_a; slot_b = next_b;
+    };
+    int t = 0;
+    for (; t + 2 < nk; ++t) { k_tile(std::true_type{}); advance(); }
+    for (; t < nk; ++t) k_tile(std::false_type{});         // (reads of a k-tile behind the last are not used)
+    if constexpr (kSplit > 1)
+        for (; t < nk_most; ++t) plain_barrier();          // (a group with fewer k-tiles than the others)
+    wait_loads<0>();
+    keep_order();
+    asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");      // (the last MFMA's results, unknown to the compiler as such)
+    keep_order();
+
+    // block (i, j) of the quarter, lane l, element r: row 16 i + l % 16, column 32 (j / 2) + 8 (l / 16) + 4 (j % 2) + r
+    int again = threadIdx.x;                                // (made anew: what is only used here shall not hold registers in the loop)
+    asm volatile("" : "+v"(again));
+    const int out_row = wm * (BM / 2) + (again & 15), out_col = wn * (BN / 2) + ((again >> 4) & 3) * 8;
+    if constexpr (kSplit == 1) {
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            uint16_t* row = C + (size_t)(bm + out_row + i * 16) * N + bn + out_col;
+#pragma unroll
+            for (int h = 0; h < NJ / 2; ++h) {
+                const f32x4 x = acc[i][2 * h], y = acc[i][2 * h + 1];
+                *reinterpret_cast<uint4*>(row + h * 32) = make_uint4(two_bf16(x[0], x[1]), two_bf16(x[2], x[3]), two_bf16(y[0], y[1]), two_bf16(y[2], y[3]));
+            }
+        }
+    } else {
+        constexpr uint32_t kPitch = (BN + 4) * 4;
+        static_assert(BM * kPitch <= 5 * kSlot, "a group's sums fit its slots");
+        typedef __attribute__((address_space(3))) f32x4* LdsSums;
+        plain_barrier();                                    // every group is done with its slots
+#pragma unroll
+        for (int i = 0; i < NI; ++i)
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) {
+                const uint32_t row = out_row + i * 16, col = out_col + j / 2 * 32 + j % 2 * 4;
+                *reinterpret_cast<LdsSums>(lds_at(base + row * kPitch + col * 4)) = acc[i][j];
+            }
+        __syncthreads();
+        for (uint32_t x = tid; x < BM * BN / 4; x += 256 * kSplit) {
+            const uint32_t row = x / (BN / 4), col = x % (BN / 4) * 4;
+            f32x4 s = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+            for (int g = 0; g < kSplit; ++g) s += *reinterpret_cast<LdsSums>(lds_at(lds0 + g * 5 * kSlot + row * kPitch + col * 4));
+            *reinterpret_cast<uint2*>(C + (size_t)(bm + row) * N + bn + col) = make_uint2(two_bf16(s[0], s[1]), two_bf16(s[2], s[3]));
+        }
     }
 }
 
@@ -202,11 +345,48 @@ uint64_t plan_gpt(fr_load* l, bool fill_lists)
     return off;
 }
 
+// Tiles and what they were measured to take, in us: `start` to begin and end a workgroup, and per k-tile `alone` with few
+// workgroups on the chip, `full` with one on every compute unit (shared L2, lower clock), and `more` for every further one per
+// compute unit.  Where one workgroup fills a compute unit (side_by_side 1) a part of a round costs a round; others overlap.
+// 2048 x 4096 x 4096, for instance, takes 75 us in 128 tiles of 256 x 256, 55 in 256 of 128 x 256 and 58 in 512 of
+// 128 x 128; 512 x 768 x 1024 from operands that are in no L2 takes 22.9 us in 6 tiles of 256 x 256, 8.1 in 96 of 64 x 64 and 6.6
+// if four parts of K are worked on side by side as well (with K = 512: 15.3, 4.0 and 5.1).
+struct GemmTile { int bm, bn, side_by_side; float start, alone, full, more; };
+constexpr GemmTile kTiles[] = {
+    {256, 256, 1, 7.0f, 0.97f, 1.39f, 1.39f}, {128, 256, 1, 4.6f, 0.57f, 0.80f, 0.80f}, {128, 128, 2, 3.3f, 0.33f, 0.46f, 0.43f},
+    {64, 128, 2, 2.8f, 0.24f, 0.35f, 0.28f}, {64, 64, 4, 2.6f, 0.26f, 0.36f, 0.20f},  {64, 64, 1, 3.9f, 0.134f, 0.20f, 0.20f},    // (the last: kSplit 4)
+};
+
+float gemm_estimate(const GemmTile& T, int M, int N, int K, int cus)
+{
+    const float u = (float)((double)(M / T.bm) * (double)(N / T.bn) / cus), nk = (float)(K / BK);
+    if (T.side_by_side > 1) return T.start * std::max(1.0f, u / T.side_by_side) + nk * (u <= 1.0f ? T.alone + (T.full - T.alone) * u : T.full + (u - 1.0f) * T.more);
+    const float rounds = std::floor(u), rest = u - rounds;
+    return (rounds + (rest > 0.0f ? 1.0f : 0.0f)) * T.start + nk * (rounds * T.full + (rest > 0.0f ? T.alone + (T.full - T.alone) * rest : 0.0f));
+}
+
 int gemm_launch(const void* A, const void* B, void* C, int M, int N, int K, hipStream_t stream)
 {
-    const unsigned grid = (unsigned)((M / BM) * (N / BN));
-    hipLaunchKernelGGL(k_gemm_bf16_nt, dim3(grid), dim3(kThreads), 0, stream, (const uint16_t*)A, (const uint16_t*)B,
-                       (uint16_t*)C, M, N, K);
+    int device = 0, cus = 0;
+    if (hipGetDevice(&device) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess || cus <= 0) return FR_ERR_HIP;
+    int best = 0;
+    float least = gemm_estimate(kTiles[0], M, N, K, cus);
+    for (int k = 1; k < (int)(sizeof(kTiles) / sizeof(kTiles[0])); ++k) {
+        const float us = gemm_estimate(kTiles[k], M, N, K, cus);
+        if (us < least) { least = us; best = k; }
+    }
+    const unsigned grid = (unsigned)(M / kTiles[best].bm) * (unsigned)(N / kTiles[best].bn);
+    auto go = [&](auto kernel, unsigned threads) {
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), 0, stream, (const uint16_t*)A, (const uint16_t*)B, (uint16_t*)C, M, N, K);
+    };
+    switch (best) {
+    case 0: go(k_gemm_bf16_nt<256, 256, 1>, 256); break;
+    case 1: go(k_gemm_bf16_nt<128, 256, 1>, 256); break;
+    case 2: go(k_gemm_bf16_nt<128, 128, 1>, 256); break;
+    case 3: go(k_gemm_bf16_nt<64, 128, 1>, 256); break;
+    case 4: go(k_gemm_bf16_nt<64, 64, 1>, 256); break;
+    default: go(k_gemm_bf16_nt<64, 64, 4>, 1024); break;
+    }
     return hipGetLastError() == hipSuccess ? FR_OK : FR_ERR_HIP;
 }
 
@@ -252,7 +432,7 @@ int fr_gemm_bf16(const void* A, const void* B, void* C, int32_t M, int32_t N, in
     if (!A || !B || !C || M <= 0 || N <= 0 || K <= 0) return FR_ERR_ARG;
     if (M % 256 || N % 256 || K % 64) return FR_ERR_ARG;
     if (((uintptr_t)A | (uintptr_t)B | (uintptr_t)C) & 15) return FR_ERR_ARG;
-    if ((uint64_t)(M / BM) * (uint64_t)(N / BN) > 0x7fffffffull) return FR_ERR_ARG;
+    if ((uint64_t)(M / 64) * (uint64_t)(N / 64) > 0x7fffffffull) return FR_ERR_ARG;
     return gemm_launch(A, B, C, M, N, K, (hipStream_t)stream);
 }
 
