@@ -257,6 +257,95 @@ void k_gemm_bf16_nt(const uint16_t* __restrict__ A, const uint16_t* __restrict__
     }
 }
 
+// The same product with a few k-tiles and many tiles: then it is writing C that takes the time, and what counts is how much of
+// it two workgroups of eight wavefronts keep on its way.  (8192 x 16384 with K = 64: 60 us; the kernel above 91 us with its best tile,
+// whose two workgroups per compute unit hold half as much of C.  K = 256: 113 and 134; K = 512: 183 and 176.)
+// Per k-tile: the registers holding the tile go to LDS, the next tile's global loads are issued into the same
+// registers, and the tile is multiplied out of LDS (4 k-steps of v_mfma_f32_32x32x16_bf16, 2 x 2 MFMA tiles per
+// wavefront).  Two workgroups share a CU (54 KB of LDS and 128 registers per lane each), so one multiplies while
+// the other sits at its barrier.  The staging registers are named scalars on purpose: as small private arrays
+// they are moved to LDS or scratch by the compiler and the kernel runs three times slower.
+typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
+constexpr int kShortM = 256, kShortN = 128, kThreads = 512;      // 8 wavefronts as 4 x 2, each 64 x 64 of C
+constexpr int kLdsRow = BK + 8;                // bf16 elements per LDS row: 128 B of data + 16 B pad, which spreads
+                                               // the rows one 16-byte-per-lane LDS access touches over the banks
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 4)))
+void k_gemm_bf16_nt_short(const uint16_t* __restrict__ A, const uint16_t* __restrict__ B, uint16_t* __restrict__ C, int M, int N, int K)
+{
+    constexpr int kPiecesPerRow = BK / 8, kRowsPerPass = kThreads / kPiecesPerRow;     // 8 pieces of 16 B, 64 rows
+    __shared__ __align__(16) uint16_t sA[kShortM * kLdsRow];
+    __shared__ __align__(16) uint16_t sB[kShortN * kLdsRow];
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int wm = wave >> 1, wn = wave & 1;
+    const int tiles_n = N / kShortN, n_tiles = (int)gridDim.x;
+    int tile = (int)blockIdx.x;
+    if (n_tiles % kXcds == 0) tile = (tile % kXcds) * (n_tiles / kXcds) + tile / kXcds;
+    const int bm = (tile / tiles_n) * kShortM, bn = (tile % tiles_n) * kShortN;
+
+    const int ld_row = tid / kPiecesPerRow, ld_k = (tid % kPiecesPerRow) * 8;
+    const uint16_t* gA = A + (size_t)(bm + ld_row) * K + ld_k;
+    const uint16_t* gB = B + (size_t)(bn + ld_row) * K + ld_k;
+    const size_t step = (size_t)kRowsPerPass * K;
+
+    f32x16 acc00, acc01, acc10, acc11;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) { acc00[r] = 0.0f; acc01[r] = 0.0f; acc10[r] = 0.0f; acc11[r] = 0.0f; }
+
+    uint4 a0 = *reinterpret_cast<const uint4*>(gA), a1 = *reinterpret_cast<const uint4*>(gA + step);
+    uint4 a2 = *reinterpret_cast<const uint4*>(gA + 2 * step), a3 = *reinterpret_cast<const uint4*>(gA + 3 * step);
+    uint4 b0 = *reinterpret_cast<const uint4*>(gB), b1 = *reinterpret_cast<const uint4*>(gB + step);
+
+    const int frag_row = lane & 31, frag_k = (lane >> 5) * 8;
+    uint16_t* wA = &sA[ld_row * kLdsRow + ld_k];
+    uint16_t* wB = &sB[ld_row * kLdsRow + ld_k];
+    const uint16_t* rA = &sA[(wm * 64 + frag_row) * kLdsRow + frag_k];
+    const uint16_t* rB = &sB[(wn * 64 + frag_row) * kLdsRow + frag_k];
+    constexpr int kPass = kRowsPerPass * kLdsRow;
+    for (int k0 = 0; k0 < K; k0 += BK) {
+        __syncthreads();                       // previous tile fully consumed
+        *reinterpret_cast<uint4*>(wA) = a0;
+        *reinterpret_cast<uint4*>(wA + kPass) = a1;
+        *reinterpret_cast<uint4*>(wA + 2 * kPass) = a2;
+        *reinterpret_cast<uint4*>(wA + 3 * kPass) = a3;
+        *reinterpret_cast<uint4*>(wB) = b0;
+        *reinterpret_cast<uint4*>(wB + kPass) = b1;
+        __syncthreads();
+        if (k0 + BK < K) {                     // fetch the next tile while this one is multiplied
+            const uint16_t* pA = gA + k0 + BK;
+            const uint16_t* pB = gB + k0 + BK;
+            a0 = *reinterpret_cast<const uint4*>(pA);
+            a1 = *reinterpret_cast<const uint4*>(pA + step);
+            a2 = *reinterpret_cast<const uint4*>(pA + 2 * step);
+            a3 = *reinterpret_cast<const uint4*>(pA + 3 * step);
+            b0 = *reinterpret_cast<const uint4*>(pB);
+            b1 = *reinterpret_cast<const uint4*>(pB + step);
+        }
+#pragma unroll
+        for (int kk = 0; kk < BK; kk += 16) {
+            const bf16x8 fa0 = *reinterpret_cast<const bf16x8*>(rA + kk);
+            const bf16x8 fa1 = *reinterpret_cast<const bf16x8*>(rA + 32 * kLdsRow + kk);
+            const bf16x8 fb0 = *reinterpret_cast<const bf16x8*>(rB + kk);
+            const bf16x8 fb1 = *reinterpret_cast<const bf16x8*>(rB + 32 * kLdsRow + kk);
+            acc00 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa0, fb0, acc00, 0, 0, 0);
+            acc01 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa0, fb1, acc01, 0, 0, 0);
+            acc10 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa1, fb0, acc10, 0, 0, 0);
+            acc11 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa1, fb1, acc11, 0, 0, 0);
+        }
+    }
+
+    // accumulator layout of the 32 x 32 MFMA: lane l holds column l % 32, rows 8 * (r / 4) + 4 * (l / 32) + r % 4
+    const int col = bn + wn * 64 + (lane & 31), row_in = (lane >> 5) * 4;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const int row = bm + wm * 64 + 8 * (r >> 2) + row_in + (r & 3);
+        C[(size_t)row * N + col] = f32_to_bf16_rne(acc00[r]);
+        C[(size_t)row * N + col + 32] = f32_to_bf16_rne(acc01[r]);
+        C[(size_t)(row + 32) * N + col] = f32_to_bf16_rne(acc10[r]);
+        C[(size_t)(row + 32) * N + col + 32] = f32_to_bf16_rne(acc11[r]);
+    }
+}
+
 // Seeded fill: bf16 values uniform in [-1/8, 1/8) from a counter-based 64-bit mixer.
 __global__ __launch_bounds__(256) void k_fill_bf16(uint16_t* __restrict__ p, uint64_t n, uint64_t seed)
 {
@@ -353,16 +442,20 @@ uint64_t plan_gpt(fr_load* l, bool fill_lists)
 // if four parts of K are worked on side by side as well (with K = 512: 15.3, 4.0 and 5.1).
 struct GemmTile { int bm, bn, side_by_side; float start, alone, full, more; };
 constexpr GemmTile kTiles[] = {
-    {256, 256, 1, 7.0f, 0.97f, 1.39f, 1.39f}, {128, 256, 1, 4.6f, 0.57f, 0.80f, 0.80f}, {128, 128, 2, 3.3f, 0.33f, 0.46f, 0.43f},
-    {64, 128, 2, 2.8f, 0.24f, 0.35f, 0.28f}, {64, 64, 4, 2.6f, 0.26f, 0.36f, 0.20f},  {64, 64, 1, 3.9f, 0.134f, 0.20f, 0.20f},    // (the last: kSplit 4)
+    {256, 256, 1, 8.5f, 0.97f, 1.39f, 1.39f}, {128, 256, 1, 5.7f, 0.57f, 0.80f, 0.80f}, {128, 128, 2, 5.1f, 0.33f, 0.46f, 0.43f},
+    {64, 128, 2, 2.7f, 0.24f, 0.35f, 0.28f}, {64, 64, 4, 2.6f, 0.22f, 0.30f, 0.28f},
+    {64, 64, 1, 3.9f, 0.134f, 0.20f, 0.20f},                       // kSplit 4
+    {kShortM, kShortN, 2, 4.8f, 1.0f, 1.1f, 1.0f},                 // k_gemm_bf16_nt_short
 };
 
 float gemm_estimate(const GemmTile& T, int M, int N, int K, int cus)
 {
-    const float u = (float)((double)(M / T.bm) * (double)(N / T.bn) / cus), nk = (float)(K / BK);
-    if (T.side_by_side > 1) return T.start * std::max(1.0f, u / T.side_by_side) + nk * (u <= 1.0f ? T.alone + (T.full - T.alone) * u : T.full + (u - 1.0f) * T.more);
-    const float rounds = std::floor(u), rest = u - rounds;
-    return (rounds + (rest > 0.0f ? 1.0f : 0.0f)) * T.start + nk * (rounds * T.full + (rest > 0.0f ? T.alone + (T.full - T.alone) * rest : 0.0f));
+    const float u = (float)((double)(M / T.bm) * (double)(N / T.bn) / cus), nk = (float)(K / BK), rounds = std::floor(u), rest = u - rounds;
+    if (T.side_by_side == 1)
+        return (rounds + (rest > 0.0f ? 1.0f : 0.0f)) * T.start + nk * (rounds * T.full + (rest > 0.0f ? T.alone + (T.full - T.alone) * rest : 0.0f));
+    // (the compute units with one workgroup more than the others set the time, though less than if all had as many)
+    const float v = u <= 1.0f ? u : 0.35f * u + 0.65f * std::ceil(u);
+    return T.start * std::max(1.0f, v / T.side_by_side) + nk * (v <= 1.0f ? T.alone + (T.full - T.alone) * v : T.full + (v - 1.0f) * T.more);
 }
 
 int gemm_launch(const void* A, const void* B, void* C, int M, int N, int K, hipStream_t stream)
@@ -385,7 +478,8 @@ int gemm_launch(const void* A, const void* B, void* C, int M, int N, int K, hipS
     case 2: go(k_gemm_bf16_nt<128, 128, 1>, 256); break;
     case 3: go(k_gemm_bf16_nt<64, 128, 1>, 256); break;
     case 4: go(k_gemm_bf16_nt<64, 64, 1>, 256); break;
-    default: go(k_gemm_bf16_nt<64, 64, 4>, 1024); break;
+    case 5: go(k_gemm_bf16_nt<64, 64, 4>, 1024); break;
+    default: go(k_gemm_bf16_nt_short, kThreads); break;
     }
     return hipGetLastError() == hipSuccess ? FR_OK : FR_ERR_HIP;
 }

@@ -37,10 +37,11 @@ def test_gemm_matches_oracle(M, N, K):
     assert np.mean(got == nearest) > 0.98
 
 
-# every tile shape where the choice by size takes it, with ragged counts: 64 x 64 (one k-tile; few tiles of a small K), 64 x 64 with
-# K in four parts (k-tiles that do not divide by four), 64 x 128, 128 x 128, 128 x 256 and 256 x 256 with bands that are cut short
+# every kernel where the choice by size takes it, with ragged counts: 64 x 64 (one k-tile; few tiles of a small K), 64 x 64 with
+# K in four parts (k-tiles that do not divide by four), 64 x 128, 128 x 128, 128 x 256, 256 x 256 with bands that are cut short, and
+# the one for a short K and many tiles
 @pytest.mark.parametrize("M,N,K", [(256, 256, 64), (512, 768, 448), (256, 512, 2624), (512, 256, 4160), (1024, 1536, 512),
-                                   (1280, 1536, 1216), (1792, 2304, 832), (2048, 4096, 1088), (4352, 3840, 1216)])
+                                   (1280, 1536, 1216), (2048, 4096, 320), (2048, 4096, 1088), (4352, 3840, 1216), (3328, 4608, 64)])
 def test_every_tile_shape_matches_oracle(M, N, K):
     test_gemm_matches_oracle(M, N, K)
 
