@@ -12,6 +12,7 @@
 #include <rocprim/rocprim.hpp>
 
 #include <algorithm>
+#include <cmath>
 
 #include "pr_layout.h"
 
@@ -474,16 +475,22 @@ int pr_build_layout(PrLayout* L, int64_t V, int64_t E, const int32_t* row_ptr, c
         // two pieces per slot and every piece is a tile of its own, so that the many light tiles at the end fill
         // the gaps the heavy ones leave; below that there are no more tiles than slots, light pieces share tiles, and
         // `body` is the smallest (to 2 %) that achieves it.
-        const uint64_t slots = (uint64_t)cus * (rows_per_part == kRowsSmall ? 2 : 1);
         std::vector<uint64_t> w(Qe);
-        uint64_t total = 0;
-        for (uint32_t j = 0; j < Qe; ++j) { w[j] = weight_at(eoff_host[j + 1]) - weight_at(eoff_host[j]); total += w[j]; }
+        uint64_t total = 0, heaviest = 0;
+        for (uint32_t j = 0; j < Qe; ++j) {
+            w[j] = weight_at(eoff_host[j + 1]) - weight_at(eoff_host[j]);
+            total += w[j];
+            heaviest = std::max(heaviest, w[j]);
+        }
+        const bool alone = rows_per_part == kRowsLarge || (2 * Qe <= cus && total <= (uint64_t)cus * cus * kGatherAloneShare);   // one workgroup a unit
+        const uint64_t slots = (uint64_t)cus * (alone ? 1 : 2);
         const uint64_t share = (total + slots - 1) / slots;
         const uint64_t fine = share >= kGatherFineShare ? 2 : 1;
+        const uint64_t least = std::max<uint64_t>(kMinTileEdges * kGatherEdgeWeight, (uint64_t)((double)kMergeBalance * std::sqrt((double)heaviest)));
         std::vector<GatherPiece> pieces;
         std::vector<uint64_t> piece_w;
         std::vector<uint2> tiles;
-        uint64_t body = std::max<uint64_t>(kMinTileEdges * kGatherEdgeWeight, (total + slots * fine - 1) / (slots * fine));
+        uint64_t body = std::max<uint64_t>(least, (total + slots * fine - 1) / (slots * fine));
         for (int round = 0; round < 400; ++round, body += body / 50 + 1) {
             pieces.clear(); piece_w.clear(); tiles.clear();
             L->ri.assign(Q, RangeInfo{kRangeEmpty, 0});
@@ -642,8 +649,10 @@ int pr_build_layout(PrLayout* L, int64_t V, int64_t E, const int32_t* row_ptr, c
             }
             if (open) stiles.push_back(make_uint2(first, n));
         };
-        const uint64_t slots = (uint64_t)cus * (src_per_part == kSrcSmall ? 2 : 1);
-        const uint64_t all = weight_before((uint64_t)V), least = kMinTileMessages * kScatterMessageWeight;
+        const uint64_t all = weight_before((uint64_t)V);
+        const uint64_t least = std::max<uint64_t>(kMinTileMessages * kScatterMessageWeight, (uint64_t)((double)kPieceBalance * std::sqrt((double)all)));
+        const bool alone = src_per_part == kSrcLarge || all <= (uint64_t)cus * cus * kScatterAloneShare;            // one workgroup a unit
+        const uint64_t slots = (uint64_t)cus * (alone ? 1 : 2);
         const uint64_t share = (all + slots - 1) / slots;
         const uint64_t fine = share >= kScatterFineShare ? 2 : 1;
         const uint64_t start = std::max<uint64_t>(least, (all + slots * fine - 1) / (slots * fine));

@@ -92,6 +92,30 @@ def test_every_partition_size(rows, srcs):
     assert np.array_equal(got.view(np.uint32), ref.cpu().numpy().view(np.uint32))
 
 
+# around the sizes where the tile rule changes: one tile, a few, one workgroup per compute unit, two per compute unit
+# (more ranges than half the units, or a heavier sweep)
+@pytest.mark.parametrize("n,edges,tiles", [(300, 2400, (1, 1)), (16_384, 700_001, (2, 256)), (300_007, 4_000_001, (100, 256)), (1_200_007, 9_000_000, (200, 512))])
+def test_small_sweeps_have_a_workgroup_per_compute_unit(n, edges, tiles):
+    src, dst = graphs.rmat_edges((n - 1).bit_length(), edges, seed=31)
+    g = graphs.csr_from_edges(n, src % n, dst % n)
+    rp, col, od = _dev(g.row_ptr, torch.int32), _dev(g.col, torch.int32), _dev(g.out_degree, torch.int32)
+    bits = []
+    for step in (0, 5):
+        print("case V=%d E=%d tiles per launch %d" % (n, edges, step), flush=True)
+        ranks = torch.zeros(n, dtype=torch.float32, device="cuda")
+        t = fr.PageRankTask(n, g.n_edges, rp, col, od, ranks, iterations=6)
+        t.fr_pagerank_run_standalone(0, torch.cuda.current_stream(), step)
+        info = t.fr_pagerank_info()
+        t.fr_pagerank_destroy()
+        bits.append(ranks.cpu().numpy())
+    assert tiles[0] <= info.gather_tiles <= tiles[1] and info.scatter_tiles <= info.scatter_slots, (info.gather_tiles, info.scatter_tiles)
+    assert np.array_equal(bits[0].view(np.uint32), bits[1].view(np.uint32))
+    want = pagerank(g.row_ptr, g.col, g.out_degree, 0.85, 6)
+    assert np.abs(bits[0].astype(np.float64) - want).max() <= TOL
+    big = want > 1.0 / n
+    assert (np.abs(bits[0][big] - want[big]) / want[big]).max() <= 1e-4
+
+
 def test_partition_sizes_other_than_the_two_supported_are_refused():
     g = graphs.rmat_csr(10, 3000, seed=8)
     rp, col, od = _dev(g.row_ptr, torch.int32), _dev(g.col, torch.int32), _dev(g.out_degree, torch.int32)
