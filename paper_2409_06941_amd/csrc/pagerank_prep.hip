@@ -1,11 +1,12 @@
 // Builds the partition-centric layout (pr_layout.h) of the PageRank side task on the GPU, once, in InitSideTask
 // (Section 4.1 of the paper: the transition that loads the task's context into GPU memory).
 //
-// Pipeline: check the CSR -> order the vertices by in-degree (radix sort; perm and its inverse) -> one 64-bit key
-// per edge (range, source, local row) in new ids -> radix sort -> message starts (flags, scan) -> messages per
-// source (histogram, scan) -> scatter tiles (host) -> id stream, message sources, edge offsets of the ranges ->
-// gather tiles and range classes (host) -> message range of every (scatter tile, range).  rocPRIM supplies the
-// device-wide sorts and scans; they run once per task and are not part of any iteration.
+// Pipeline: check the CSR -> order the vertices by in-degree (radix sorts; perm and its inverse) -> one 64-bit key
+// per edge (range, source, local row) in new ids, made in the order of the new rows -> stable radix sort by (range,
+// source) -> one pass over the sorted keys: message starts, messages per chunk and per source -> scans -> scatter tiles
+// (host) -> id stream, message sources, edge offsets of the ranges -> gather tiles and range classes (host) -> message
+// range of every (scatter tile, range).  rocPRIM supplies the device-wide sorts and scans; they run once per task and
+// are not part of any iteration.
 
 #include <cstring>
 
@@ -21,18 +22,6 @@ namespace {
 constexpr int kBlk = 256;
 
 inline unsigned blocks_for(uint64_t n) { return (unsigned)((n + kBlk - 1) / kBlk); }
-
-// Row that holds edge e: the v with row_ptr[v] <= e < row_ptr[v + 1].
-__device__ __forceinline__ int32_t row_of_edge(const int32_t* __restrict__ row_ptr, int64_t V, int64_t e)
-{
-    int64_t lo = 0, hi = V;            // first index in [0, V] whose row_ptr exceeds e
-    while (lo < hi) {
-        const int64_t mid = (lo + hi) >> 1;
-        if ((int64_t)row_ptr[mid] > e) hi = mid;
-        else lo = mid + 1;
-    }
-    return (int32_t)(lo - 1);
-}
 
 __global__ void k_set_i32(int32_t* p, int32_t value) { *p = value; }
 
@@ -61,75 +50,192 @@ __global__ __launch_bounds__(kBlk) void k_validate(int64_t V, int64_t E, const i
 // in one run at the very end that no scatter piece has to load.  (Breaking all ties by out-degree gives a few more
 // such runs and made the gather sweep 2 to 6 % slower on R-MAT graphs: rows of like out-degree are like in whom
 // they are pointed to by, and the ids of a wavefront's 64 edges then fall on fewer accumulators.)
-// Two sorts of 64-bit keys: by (out-degree falling, id), then by (in-degree falling, id or, without in-edges, the
-// rank in the first order).
-__global__ __launch_bounds__(kBlk) void k_vertex_keys_out(int64_t V, const int32_t* __restrict__ outdeg, uint64_t* __restrict__ keys)
+// Two stable sorts of keys (top - degree) << 32 | id by their upper half, made in the order of the ids; `top` is 2^bits - 1
+// with as many bits as a degree can have, so that a graph of 2^26 edges takes four passes of eight bits per sort (all 64
+// bits: eight).  The vertices without in-edges, which end the second order, are then put in the order of the first.
+__global__ __launch_bounds__(kBlk) void k_vertex_keys_out(int64_t V, uint32_t top, const int32_t* __restrict__ outdeg, uint64_t* __restrict__ keys)
 {
     const int64_t v = (int64_t)blockIdx.x * kBlk + threadIdx.x;
     if (v >= V) return;
-    const uint32_t d = (uint32_t)(outdeg[v] < 0 ? 0 : outdeg[v]);
-    keys[v] = ((uint64_t)(0x7fffffffu - d) << 32) | (uint64_t)(uint32_t)v;
+    const int32_t d = outdeg[v];
+    keys[v] = ((uint64_t)(top - ((uint32_t)(d < 0 ? 0 : d) < top ? (uint32_t)(d < 0 ? 0 : d) : top)) << 32) | (uint64_t)(uint32_t)v;
 }
 
-__global__ __launch_bounds__(kBlk) void k_vertex_keys_in(int64_t V, const int32_t* __restrict__ row_ptr, const uint64_t* __restrict__ by_out,
-                                                         uint64_t* __restrict__ keys)
+__global__ __launch_bounds__(kBlk) void k_vertex_keys_in(int64_t V, uint32_t top, const int32_t* __restrict__ row_ptr, uint64_t* __restrict__ keys)
 {
-    const int64_t i = (int64_t)blockIdx.x * kBlk + threadIdx.x;
-    if (i >= V) return;
-    uint32_t v = (uint32_t)(by_out[i] & 0xffffffffu);
-    if ((int64_t)v >= V) v = 0;                        // cannot happen: the keys hold 0 .. V-1
-    const uint32_t indeg = (uint32_t)(row_ptr[v + 1] - row_ptr[v]);
-    keys[i] = ((uint64_t)(0x7fffffffu - indeg) << 32) | (uint64_t)(indeg ? v : (uint32_t)i);
+    const int64_t v = (int64_t)blockIdx.x * kBlk + threadIdx.x;
+    if (v >= V) return;
+    keys[v] = ((uint64_t)(top - (uint32_t)(row_ptr[v + 1] - row_ptr[v])) << 32) | (uint64_t)(uint32_t)v;
 }
 
-// perm[new] = old, inv[old] = new, inv_out[new] = 1/outdeg (0 for dangling vertices)
-__global__ __launch_bounds__(kBlk) void k_perm(int64_t V, const uint64_t* __restrict__ sorted, const uint64_t* __restrict__ by_out,
+// A vertex without in-edges?  (its key of the first order)
+struct NoInEdges {
+    const int32_t* row_ptr;
+    __host__ __device__ bool operator()(uint64_t key) const
+    {
+        const uint32_t v = (uint32_t)key;
+        return row_ptr[v + 1] == row_ptr[v];
+    }
+};
+
+// perm[new] = old, inv[old] = new, inv_out[new] = 1/outdeg (0 for dangling vertices), indeg[new].  `sorted` is the second
+// order, `no_in` the vertices without in-edges in the first order (n_no_in[0] of them): they are the last of the order.
+__global__ __launch_bounds__(kBlk) void k_perm(int64_t V, const uint64_t* __restrict__ sorted, const uint64_t* __restrict__ no_in,
+                                               const uint32_t* __restrict__ n_no_in, const int32_t* __restrict__ row_ptr,
                                                const int32_t* __restrict__ outdeg, int32_t* __restrict__ perm, int32_t* __restrict__ inv,
-                                               float* __restrict__ inv_out)
+                                               float* __restrict__ inv_out, uint32_t* __restrict__ indeg)
 {
     const int64_t n = (int64_t)blockIdx.x * kBlk + threadIdx.x;
-    if (n >= V) return;
-    uint32_t old = (uint32_t)(sorted[n] & 0xffffffffu);          // the id, or for a vertex without in-edges its rank by out-degree
-    if ((int64_t)old >= V) old = 0;                    // cannot happen
-    if ((sorted[n] >> 32) == 0x7fffffffull) {
-        old = (uint32_t)(by_out[old] & 0xffffffffu);
-        if ((int64_t)old >= V) old = 0;                // cannot happen
-    }
+    if (n > V) return;
+    if (n == V) { indeg[n] = 0; return; }
+    const int64_t with_in = V - (int64_t)*n_no_in;
+    uint32_t old = (uint32_t)(n < with_in ? sorted[n] : no_in[n - with_in]);
+    if ((int64_t)old >= V) old = 0;                    // cannot happen: the keys hold 0 .. V-1
     perm[n] = (int32_t)old;
     inv[old] = (int32_t)n;
     const int32_t d = outdeg[old];
     inv_out[n] = d > 0 ? 1.0f / (float)d : 0.0f;
+    indeg[n] = (uint32_t)(row_ptr[old + 1] - row_ptr[old]);
 }
 
-__global__ __launch_bounds__(kBlk) void k_keys(int64_t V, int64_t E, const int32_t* __restrict__ row_ptr,
-                                               const int32_t* __restrict__ col, const int32_t* __restrict__ inv,
-                                               uint32_t rows_per_part, uint64_t* __restrict__ keys)
+// Last index n of [0, V) with first[n] <= p, for first[0] <= p < first[V] (first: rising).  A wavefront looks together,
+// 64 places at a time: four loads one after the other for 2^24 entries instead of 24.
+__device__ __forceinline__ uint32_t wave_find(const uint32_t* __restrict__ first, uint32_t V, uint32_t p)
 {
-    const int64_t e = (int64_t)blockIdx.x * kBlk + threadIdx.x;
-    if (e >= E) return;
-    const uint64_t v = (uint64_t)(uint32_t)inv[row_of_edge(row_ptr, V, e)];
-    const uint64_t u = (uint64_t)(uint32_t)inv[col[e]];
-    keys[e] = ((v / rows_per_part) << (kKeyLocalBits + kKeySrcBits)) | (u << kKeyLocalBits) | (v % rows_per_part);
+    const uint32_t lane = threadIdx.x & 63;
+    uint64_t lo = 0, hi = V;                           // first[lo] <= p < first[hi]
+    while (hi - lo > 1) {
+        const uint64_t step = (hi - lo + 63) / 64;
+        const uint64_t at = lo + (lane + 1) * step;
+        const uint32_t n = (uint32_t)__popcll(__ballot(at < hi && first[at] <= p));
+        lo += n * step;
+        hi = lo + step < hi ? lo + step : hi;
+    }
+    return (uint32_t)lo;
 }
 
-// 1 where edge e (in sorted order) is the first of its (partition, source) group, i.e. starts a message.
-__host__ __device__ __forceinline__ uint32_t flag_of(const uint64_t* __restrict__ keys, int64_t e)
+// One key per edge, range << (kKeyLocalBits + src_bits) | source << kKeyLocalBits | local row, in the order of the new
+// rows (`first`: edges before each), so that a stable sort by range and source leaves the rows of a source in order:
+// 30 of 64 bits to sort for 2^22 vertices, four passes.  A workgroup makes kKeyRun keys; the rows with edges come first
+// in the new order, so these lie in kKeyRun rows at most, whose starts are held in LDS.  Bound by the look-ups of inv[].
+// (2^26 edges: keys and sort 5.1 ms with a search of row_ptr per edge and all 54 bits of a key sorted.)
+constexpr uint32_t kKeyRun = 2048;
+__global__ __launch_bounds__(kBlk) void k_keys(uint32_t V, uint32_t E, const uint32_t* __restrict__ first, const int32_t* __restrict__ row_ptr,
+                                               const int32_t* __restrict__ perm, const int32_t* __restrict__ col, const int32_t* __restrict__ inv,
+                                               uint32_t rows_per_part, uint32_t src_bits, uint64_t* __restrict__ keys)
 {
-    return (e == 0 || (keys[e] >> kKeyLocalBits) != (keys[e - 1] >> kKeyLocalBits)) ? 1u : 0u;
+    __shared__ uint32_t row_first[kKeyRun + 1];        // edges before the run's rows, new order
+    __shared__ uint32_t row_old[kKeyRun];              // where their edges are in the caller's order
+    __shared__ uint32_t ends[2];
+    const uint32_t p0 = blockIdx.x * kKeyRun, p1 = E - p0 < kKeyRun ? E : p0 + kKeyRun;
+    if (threadIdx.x < 128) {
+        const uint32_t n = wave_find(first, V, threadIdx.x < 64 ? p0 : p1 - 1);
+        if ((threadIdx.x & 63) == 0) ends[threadIdx.x >> 6] = n;
+    }
+    __syncthreads();
+    const uint32_t n0 = ends[0], rows = ends[1] - n0 + 1 < kKeyRun ? ends[1] - n0 + 1 : kKeyRun;
+    for (uint32_t i = threadIdx.x; i < rows; i += kBlk) {
+        row_first[i] = first[n0 + i];
+        row_old[i] = (uint32_t)row_ptr[perm[n0 + i]];
+    }
+    __syncthreads();
+    constexpr int kEach = kKeyRun / kBlk;
+    uint32_t n[kEach], c[kEach];
+#pragma unroll
+    for (int k = 0; k < kEach; ++k) {
+        const uint32_t p = p0 + k * kBlk + threadIdx.x;
+        n[k] = 0; c[k] = 0;
+        if (p >= p1) continue;
+        uint32_t lo = 0, hi = rows;                    // row_first[lo] <= p
+        while (hi - lo > 1) {
+            const uint32_t mid = (lo + hi) >> 1;
+            if (row_first[mid] <= p) lo = mid;
+            else hi = mid;
+        }
+        n[k] = n0 + lo;
+        c[k] = (uint32_t)col[row_old[lo] + (p - row_first[lo])];
+    }
+#pragma unroll
+    for (int k = 0; k < kEach; ++k) c[k] = (uint32_t)inv[c[k]];
+#pragma unroll
+    for (int k = 0; k < kEach; ++k) {
+        const uint32_t p = p0 + k * kBlk + threadIdx.x;
+        if (p < p1)
+            keys[p] = ((uint64_t)(n[k] / rows_per_part) << (kKeyLocalBits + src_bits)) | ((uint64_t)c[k] << kKeyLocalBits) | (n[k] % rows_per_part);
+    }
 }
 
-struct FlagOf {
-    const uint64_t* keys;
-    __host__ __device__ uint32_t operator()(size_t e) const { return flag_of(keys, (int64_t)e); }
+// ---- the sorted keys, a chunk of kIdChunk edges per wavefront: lane l holds the edges at positions 64 j + l (row j)
+constexpr int kChunkRows = (int)(kIdChunk / 64);
+constexpr uint32_t kChunksPerBlock = kBlk / 64;
+
+struct ChunkKeys {
+    uint64_t key[kChunkRows];        // 0 beyond the last edge
+    uint64_t begins[kChunkRows];     // per row: which edges are the first of their (range, source) group, i.e. begin a message
+    uint64_t repeats[kChunkRows];    // which repeat their predecessor (same range, source and row: a multi-edge)
 };
 
-// Id stream and message sources.  Inside every chunk of kIdChunk ids the stream is stored transposed: stream
-// position r = 64 * j + lane of the chunk sits at slot 8 * lane + j, so that one 16-byte load hands a lane the
-// ids 64 apart and, for a fixed j, the 64 lanes of a wavefront hold 64 consecutive ids of the stream.
-__device__ __forceinline__ int64_t id_slot(int64_t e)
+__device__ __forceinline__ void read_chunk(ChunkKeys& K, uint32_t c, uint32_t E, const uint64_t* __restrict__ keys)
 {
-    const int64_t r = e % kIdChunk;
-    return e - r + (r % 64) * (kIdChunk / 64) + r / 64;
+    const uint32_t lane = threadIdx.x & 63;
+    const uint64_t e0 = (uint64_t)c * kIdChunk;
+#pragma unroll
+    for (int j = 0; j < kChunkRows; ++j) K.key[j] = e0 + 64 * j + lane < E ? keys[e0 + 64 * j + lane] : 0ull;
+    uint64_t before = e0 ? keys[e0 - 1] : ~0ull;       // (no key has all bits set)
+#pragma unroll
+    for (int j = 0; j < kChunkRows; ++j) {
+        const uint64_t k = K.key[j];
+        uint64_t prev = __shfl_up(k, 1, 64);
+        if (lane == 0) prev = before;
+        before = __shfl(k, 63, 64);
+        const bool held = e0 + 64 * j + lane < E;
+        K.begins[j] = __ballot(held && (k >> kKeyLocalBits) != (prev >> kKeyLocalBits));
+        K.repeats[j] = __ballot(held && k == prev);
+    }
+}
+
+// One pass over the keys: message-start records, messages and repeated edges per chunk, messages per source (cnt, zero
+// before; integer atomics).  A chunk's record, kStartWords 64-bit words: words 0 .. 7 = for row j (stream positions 64 j ..
+// 64 j + 63 of the chunk) the start bits of positions 1 .. 63 in bits 0 .. 62 (bit l set: position l + 1 begins a message);
+// words 8 .. 11 = eight 32-bit words, for the first position of each row four times the distance of its message from
+// message mbase[c] - 1 (0 .. 2048: a byte offset into the messages).  The message of position l of row j is then:
+// mbase[c] - 1 + first[j] / 4 + (set bits below l in word j).  Repeated edges, adjacent in the stream, hit one accumulator
+// from neighbouring lanes, which the LDS serialises; the tile cutter counts them.  Bound by the atomics: 2^26 edges 0.3 ms
+// (a pass each for records, numbering, repeats and counts, the records 64 keys a thread: 1.9 ms).
+__global__ __launch_bounds__(kBlk) void k_chunk_facts(uint32_t E, int64_t V, uint32_t n_chunks, uint32_t src_mask, const uint64_t* __restrict__ keys,
+                                                      uint64_t* __restrict__ starts, uint32_t* __restrict__ messages, uint32_t* __restrict__ rep,
+                                                      uint32_t* __restrict__ cnt)
+{
+    const uint32_t c = blockIdx.x * kChunksPerBlock + threadIdx.x / 64, lane = threadIdx.x & 63;
+    if (c > n_chunks) return;
+    if (c == n_chunks) {                               // (the scan's last element)
+        if (lane == 0) messages[c] = 0;
+        return;
+    }
+    ChunkKeys K;
+    read_chunk(K, c, E, keys);
+    uint64_t* rec = starts + (uint64_t)c * kStartWords;
+    uint32_t begun = 0, repeated = 0;
+    uint64_t word = 0;
+    uint32_t first = 0;
+#pragma unroll
+    for (int j = 0; j < kChunkRows; ++j) {
+        if (lane == (uint32_t)j) {
+            word = K.begins[j] >> 1;
+            first = (uint64_t)c * kIdChunk + 64 * j < E ? 4u * (begun + (uint32_t)(K.begins[j] & 1u)) : 0u;
+        }
+        begun += (uint32_t)__popcll(K.begins[j]);
+        repeated += (uint32_t)__popcll(K.repeats[j]);
+        if ((K.begins[j] >> lane) & 1u) {
+            const uint32_t u = (uint32_t)(K.key[j] >> kKeyLocalBits) & src_mask;
+            if ((int64_t)u < V) atomicAdd(&cnt[u], 1u);
+        }
+    }
+    if (lane < (uint32_t)kChunkRows) {
+        rec[lane] = word;
+        reinterpret_cast<uint32_t*>(rec + kChunkRows)[lane] = first;
+    }
+    if (lane == 0) { messages[c] = begun; rep[c] = repeated; }
 }
 
 // Scatter tile that holds source u: the t with ubound[t] <= u < ubound[t + 1].
@@ -144,88 +250,37 @@ __device__ __forceinline__ uint32_t tile_of_source(const uint32_t* __restrict__ 
     return lo ? lo - 1 : 0;
 }
 
-// cnt[u] += 1 for every message of source u (set-up only; integer atomics)
-__global__ __launch_bounds__(kBlk) void k_count_messages(int64_t E, int64_t V, const uint64_t* __restrict__ keys, uint32_t* __restrict__ cnt)
-{
-    const int64_t e = (int64_t)blockIdx.x * kBlk + threadIdx.x;
-    if (e >= E || !flag_of(keys, e)) return;
-    const uint32_t u = (uint32_t)((keys[e] >> kKeyLocalBits) & 0x7fffffffu);
-    if ((int64_t)u < V) atomicAdd(&cnt[u], 1u);
-}
-
 __global__ __launch_bounds__(kBlk) void k_zero_u32(uint64_t n, uint32_t* p)
 {
     const uint64_t i = (uint64_t)blockIdx.x * kBlk + threadIdx.x;
     if (i < n) p[i] = 0u;
 }
 
-__global__ __launch_bounds__(kBlk) void k_emit(int64_t E, int64_t padded, uint64_t M, const uint64_t* __restrict__ keys,
-                                               const uint32_t* __restrict__ incl, const uint32_t* __restrict__ ubound,
-                                               uint32_t n_tiles, uint32_t id_scale, uint16_t* __restrict__ ids16,
-                                               uint16_t* __restrict__ src16)
+// Id stream and message sources.  Inside every chunk of kIdChunk ids the stream is stored transposed: stream position
+// 64 j + l sits at slot 8 l + j, so that one 16-byte access is a lane's ids 64 apart and, for a fixed j, the 64 lanes of
+// a wavefront hold 64 consecutive ids of the stream.
+__global__ __launch_bounds__(kBlk) void k_emit(uint32_t E, uint32_t n_chunks, uint32_t M, uint32_t src_mask, const uint64_t* __restrict__ keys,
+                                               const uint32_t* __restrict__ mbase, const uint32_t* __restrict__ ubound, uint32_t n_tiles,
+                                               uint32_t id_scale, uint16_t* __restrict__ ids16, uint16_t* __restrict__ src16)
 {
-    const int64_t e = (int64_t)blockIdx.x * kBlk + threadIdx.x;
-    if (e >= padded) return;
-    if (e >= E) { ids16[id_slot(e)] = 0; return; }
-    const uint64_t k = keys[e];
-    const uint32_t f = flag_of(keys, e);
-    ids16[id_slot(e)] = (uint16_t)((k & ((1u << kKeyLocalBits) - 1)) * id_scale);
-    if (f) {
-        const uint64_t m = (uint64_t)incl[e] - 1;
-        const uint32_t u = (uint32_t)((k >> kKeyLocalBits) & 0x7fffffffu);
-        if (m < M) src16[m] = (uint16_t)(u - ubound[tile_of_source(ubound, n_tiles, u)]);
-    }
-}
-
-// Message-start record of chunk c, kStartWords 64-bit words: words 0 .. 7 = for row j (stream positions 64 j .. 64 j + 63
-// of the chunk) the start bits of positions 1 .. 63 in bits 0 .. 62 (bit l set: position l + 1 begins a message);
-// words 8 .. 11 = eight 32-bit words, for the first position of each row four times the distance of its message from
-// message mbase[c] - 1 (0 .. 2048: a byte offset into the messages).  The message of position l of row j is then:
-// mbase[c] - 1 + first[j] / 4 + (set bits below l in word j).
-__global__ __launch_bounds__(kBlk) void k_starts(int64_t E, uint64_t n_rows, const uint64_t* __restrict__ keys,
-                                                 const uint32_t* __restrict__ incl, uint64_t* __restrict__ starts)
-{
-    const uint64_t w = (uint64_t)blockIdx.x * kBlk + threadIdx.x;
-    if (w >= n_rows) return;
-    uint64_t bits = 0;
-    for (int l = 1; l < 64; ++l) {
-        const int64_t e = (int64_t)(w * 64) + l;
-        if (e < E && flag_of(keys, e)) bits |= 1ull << (l - 1);
-    }
-    const int64_t e0 = (int64_t)(w * 64);
-    uint64_t* rec = starts + (w / 8) * kStartWords;
-    rec[w % 8] = bits;
-    const int64_t ec = (int64_t)(w / 8) * kIdChunk;          // the chunk's first position
-    reinterpret_cast<uint32_t*>(rec + 8)[w % 8] = e0 < E ? 4u * (incl[e0] - (incl[ec] - flag_of(keys, ec))) : 0u;
-}
-
-__global__ __launch_bounds__(kBlk) void k_mbase(int64_t E, uint32_t n_chunks, uint32_t M, const uint64_t* __restrict__ keys,
-                                                const uint32_t* __restrict__ incl, uint32_t* __restrict__ mbase)
-{
-    const uint32_t c = blockIdx.x * kBlk + threadIdx.x;
-    if (c > n_chunks) return;
-    const int64_t e = (int64_t)c * kIdChunk;
-    mbase[c] = e < E ? incl[e] - flag_of(keys, e) : M;
-}
-
-// rep[c] = edges of chunk c that repeat their predecessor (same range, source and row: a multi-edge).  Adjacent in
-// the stream, they hit one accumulator from neighbouring lanes, which the LDS serialises; the tile cutter counts them.
-__global__ __launch_bounds__(kBlk) void k_chunk_repeats(int64_t E, uint32_t n_chunks, const uint64_t* __restrict__ keys,
-                                                        uint32_t* __restrict__ rep)
-{
-    const uint32_t c = blockIdx.x;
+    const uint32_t c = blockIdx.x * kChunksPerBlock + threadIdx.x / 64, lane = threadIdx.x & 63;
     if (c >= n_chunks) return;
-    __shared__ uint32_t total;
-    if (threadIdx.x == 0) total = 0;
-    __syncthreads();
-    uint32_t mine = 0;
-    for (uint32_t r = threadIdx.x; r < kIdChunk; r += kBlk) {
-        const int64_t e = (int64_t)c * kIdChunk + r;
-        if (e >= 1 && e < E && keys[e] == keys[e - 1]) ++mine;
+    ChunkKeys K;
+    read_chunk(K, c, E, keys);
+    uint32_t m0 = mbase[c];
+    uint32_t id[kChunkRows];
+#pragma unroll
+    for (int j = 0; j < kChunkRows; ++j) {
+        id[j] = ((uint32_t)K.key[j] & kLocalMask) * id_scale;
+        if ((K.begins[j] >> lane) & 1u) {
+            const uint32_t m = m0 + (uint32_t)__popcll(K.begins[j] & ((1ull << lane) - 1));
+            const uint32_t u = (uint32_t)(K.key[j] >> kKeyLocalBits) & src_mask;
+            if (m < M) src16[m] = (uint16_t)(u - ubound[tile_of_source(ubound, n_tiles, u)]);
+        }
+        m0 += (uint32_t)__popcll(K.begins[j]);
     }
-    if (mine) atomicAdd(&total, mine);
-    __syncthreads();
-    if (threadIdx.x == 0) rep[c] = total;
+    static_assert(kChunkRows == 8, "one 16-byte store a lane");
+    reinterpret_cast<uint4*>(ids16)[(uint64_t)c * 64 + lane] = make_uint4(id[0] | id[1] << 16, id[2] | id[3] << 16, id[4] | id[5] << 16, id[6] | id[7] << 16);
 }
 
 __device__ __forceinline__ int64_t lower_bound_key(const uint64_t* __restrict__ keys, int64_t E, uint64_t target)
@@ -239,28 +294,36 @@ __device__ __forceinline__ int64_t lower_bound_key(const uint64_t* __restrict__ 
     return lo;
 }
 
-__global__ __launch_bounds__(kBlk) void k_eoff(uint32_t Q, int64_t E, const uint64_t* __restrict__ keys, uint32_t* __restrict__ eoff)
+__global__ __launch_bounds__(kBlk) void k_eoff(uint32_t Q, int64_t E, uint32_t src_bits, const uint64_t* __restrict__ keys, uint32_t* __restrict__ eoff)
 {
     const uint32_t q = blockIdx.x * kBlk + threadIdx.x;
     if (q > Q) return;
-    eoff[q] = (uint32_t)lower_bound_key(keys, E, (uint64_t)q << (kKeyLocalBits + kKeySrcBits));
+    eoff[q] = (uint32_t)lower_bound_key(keys, E, (uint64_t)q << (kKeyLocalBits + src_bits));
+}
+
+// Message of edge e, from its chunk's record.
+__device__ __forceinline__ uint32_t message_of(uint32_t e, const uint64_t* __restrict__ starts, const uint32_t* __restrict__ mbase)
+{
+    const uint32_t c = e / kIdChunk, j = e % kIdChunk / 64, l = e % 64;
+    const uint64_t* rec = starts + (uint64_t)c * kStartWords;
+    return mbase[c] - 1 + reinterpret_cast<const uint32_t*>(rec + kChunkRows)[j] / 4 + (uint32_t)__popcll(rec[j] & ((1ull << l) - 1));
 }
 
 // bins[t * Qe + j] = message range of the edges of range j whose source lies in scatter tile t.
-// The first edge of a bin always starts a message, so "messages before it" = incl - 1 there.
-__global__ __launch_bounds__(kBlk) void k_bins(uint32_t n_tiles, uint32_t Qe, int64_t E, uint32_t M, const uint32_t* __restrict__ ubound,
-                                               const uint64_t* __restrict__ keys, const uint32_t* __restrict__ incl,
-                                               uint2* __restrict__ bins)
+// The first edge of a bin always begins a message, so its message is the first of the bin.
+__global__ __launch_bounds__(kBlk) void k_bins(uint32_t n_tiles, uint32_t Qe, int64_t E, uint32_t M, uint32_t src_bits, const uint32_t* __restrict__ ubound,
+                                               const uint64_t* __restrict__ keys, const uint64_t* __restrict__ starts,
+                                               const uint32_t* __restrict__ mbase, uint2* __restrict__ bins)
 {
     const uint64_t idx = (uint64_t)blockIdx.x * kBlk + threadIdx.x;
     if (idx >= (uint64_t)n_tiles * Qe) return;
     const uint64_t t = idx / Qe, j = idx % Qe;
-    const uint64_t base = j << (kKeyLocalBits + kKeySrcBits);
+    const uint64_t base = j << (kKeyLocalBits + src_bits);
     const int64_t lo = lower_bound_key(keys, E, base + ((uint64_t)ubound[t] << kKeyLocalBits));
     const int64_t hi = lower_bound_key(keys, E, base + ((uint64_t)ubound[t + 1] << kKeyLocalBits));
     uint2 r;
-    r.x = lo < E ? incl[lo] - 1 : M;
-    r.y = hi < E ? incl[hi] - 1 : M;
+    r.x = lo < E ? message_of((uint32_t)lo, starts, mbase) : M;
+    r.y = hi < E ? message_of((uint32_t)hi, starts, mbase) : M;
     if (r.y < r.x) r.y = r.x;
     bins[idx] = r;
 }
@@ -321,6 +384,9 @@ int pr_build_layout(PrLayout* L, int64_t V, int64_t E, const int32_t* row_ptr, c
     const int64_t padded = (int64_t)std::max<uint32_t>(L->n_chunks, 1) * kIdChunk;
     const uint32_t Q = L->Q;
     if ((uint64_t)Q >= (1ull << (63 - kKeyLocalBits - kKeySrcBits))) return FR_ERR_ARG;
+    uint32_t src_bits = 1;                             // (so that ubound = V as a key's source does not reach the range, V <= 2^src_bits
+    while (src_bits < (uint32_t)kKeySrcBits && (1ll << src_bits) <= V) ++src_bits;         // is not enough)
+    const uint32_t src_mask = (uint32_t)((1ull << src_bits) - 1);
 
     Scratch tmp{a, {}};
 
@@ -339,96 +405,109 @@ int pr_build_layout(PrLayout* L, int64_t V, int64_t E, const int32_t* row_ptr, c
     if (!keep(a, &L->perm, (uint64_t)V) || !keep(a, &L->inv_out, (uint64_t)V)) PREP_NEED((void*)nullptr);
     int32_t* inv = tmp.take<int32_t>((uint64_t)V);
     PREP_NEED(inv);
+    uint64_t* keys_a = nullptr;
+    uint64_t* keys_b = nullptr;
+    uint32_t* first = nullptr;                         // edges before each row, new order (V + 1)
     {
+        uint32_t degree_bits = 1;                      // an in-degree has at most these; a larger out-degree (the caller's array
+        while ((1ll << degree_bits) <= E && degree_bits < 31) ++degree_bits;      // is not held against the edges) counts as 2^bits - 1
+        const uint32_t top = (uint32_t)((1ull << degree_bits) - 1);
         uint64_t* by_out = tmp.take<uint64_t>((uint64_t)V);
         uint64_t* vk_a = tmp.take<uint64_t>((uint64_t)V);
         uint64_t* vk_b = tmp.take<uint64_t>((uint64_t)V);
         PREP_NEED(by_out); PREP_NEED(vk_a); PREP_NEED(vk_b);
-        size_t bytes = 0;
-        {
-            rocprim::double_buffer<uint64_t> probe(vk_a, vk_b);
-            PREP_HIP(rocprim::radix_sort_keys(nullptr, bytes, probe, (size_t)V, 0u, 64u, stream));
-        }
+        size_t sort_bytes = 0, select_bytes = 0, scan_bytes = 0;
+        uint32_t* n_no_in = reinterpret_cast<uint32_t*>(bad);        // (its check is done)
+        const NoInEdges no_in_edges{row_ptr};
+        rocprim::double_buffer<uint64_t> order(vk_a, vk_b);
+        PREP_HIP(rocprim::radix_sort_keys(nullptr, sort_bytes, order, (size_t)V, 32u, 32u + degree_bits, stream));
+        PREP_HIP(rocprim::select(nullptr, select_bytes, vk_a, by_out, n_no_in, (size_t)V, no_in_edges, stream));
+        PREP_HIP(rocprim::exclusive_scan(nullptr, scan_bytes, reinterpret_cast<uint32_t*>(vk_a), reinterpret_cast<uint32_t*>(vk_a), 0u, (size_t)V + 1, rocprim::plus<uint32_t>(), stream));
+        size_t bytes = std::max(sort_bytes, std::max(select_bytes, scan_bytes));
         void* t = tmp.take<uint8_t>(bytes);
         PREP_NEED(t);
-        hipLaunchKernelGGL(k_vertex_keys_out, dim3(blocks_for((uint64_t)V)), dim3(kBlk), 0, stream, V, out_degree, vk_a);
-        rocprim::double_buffer<uint64_t> first(vk_a, vk_b);
-        PREP_HIP(rocprim::radix_sort_keys(t, bytes, first, (size_t)V, 0u, 64u, stream));
-        PREP_HIP(hipMemcpyAsync(by_out, first.current(), (size_t)V * 8, hipMemcpyDeviceToDevice, stream));
-        hipLaunchKernelGGL(k_vertex_keys_in, dim3(blocks_for((uint64_t)V)), dim3(kBlk), 0, stream, V, row_ptr, by_out, vk_a);
-        rocprim::double_buffer<uint64_t> second(vk_a, vk_b);
-        PREP_HIP(rocprim::radix_sort_keys(t, bytes, second, (size_t)V, 0u, 64u, stream));
-        hipLaunchKernelGGL(k_perm, dim3(blocks_for((uint64_t)V)), dim3(kBlk), 0, stream, V, second.current(), by_out, out_degree, L->perm, inv, L->inv_out);
+        hipLaunchKernelGGL(k_vertex_keys_out, dim3(blocks_for((uint64_t)V)), dim3(kBlk), 0, stream, V, top, out_degree, vk_a);
+        PREP_HIP(rocprim::radix_sort_keys(t, sort_bytes, order, (size_t)V, 32u, 32u + degree_bits, stream));
+        PREP_HIP(rocprim::select(t, select_bytes, order.current(), by_out, n_no_in, (size_t)V, no_in_edges, stream));
+        order = rocprim::double_buffer<uint64_t>(vk_a, vk_b);
+        hipLaunchKernelGGL(k_vertex_keys_in, dim3(blocks_for((uint64_t)V)), dim3(kBlk), 0, stream, V, top, row_ptr, vk_a);
+        PREP_HIP(rocprim::radix_sort_keys(t, sort_bytes, order, (size_t)V, 32u, 32u + degree_bits, stream));
+        uint32_t* indeg = reinterpret_cast<uint32_t*>(order.alternate());          // V + 1 words where 2 V have room
+        hipLaunchKernelGGL(k_perm, dim3(blocks_for((uint64_t)V + 1)), dim3(kBlk), 0, stream, V, order.current(), by_out, n_no_in, row_ptr, out_degree, L->perm, inv, L->inv_out, indeg);
+        PREP_HIP(rocprim::exclusive_scan(t, scan_bytes, indeg, reinterpret_cast<uint32_t*>(by_out), 0u, (size_t)V + 1, rocprim::plus<uint32_t>(), stream));
         PREP_HIP(hipStreamSynchronize(stream));
-        tmp.drop(t); tmp.drop(vk_a); tmp.drop(vk_b); tmp.drop(by_out);
+        tmp.drop(t); tmp.drop(vk_a); tmp.drop(vk_b);
+        first = reinterpret_cast<uint32_t*>(by_out);
     }
 
     // ---- sort the edges by (range, source, local row); set-up scratch is returned as soon as it is done with
     uint64_t* keys = nullptr;
-    uint32_t* incl = nullptr;
     uint32_t M = 0;
     if (E > 0) {
-        uint64_t* keys_a = tmp.take<uint64_t>((uint64_t)E);
-        uint64_t* keys_b = tmp.take<uint64_t>((uint64_t)E);
-        PREP_NEED(keys_a); PREP_NEED(keys_b);
-        hipLaunchKernelGGL(k_keys, dim3(blocks_for((uint64_t)E)), dim3(kBlk), 0, stream, V, E, row_ptr, col, inv, rows_per_part, keys_a);
-        unsigned end_bit = kKeyLocalBits + kKeySrcBits;
-        while (end_bit < 63 && (1ull << (end_bit - kKeyLocalBits - kKeySrcBits)) < (uint64_t)Q) ++end_bit;
-        {
-            rocprim::double_buffer<uint64_t> db(keys_a, keys_b);
-            size_t bytes = 0;
-            PREP_HIP(rocprim::radix_sort_keys(nullptr, bytes, db, (size_t)E, 0u, end_bit, stream));
-            void* t = tmp.take<uint8_t>(bytes);
-            PREP_NEED(t);
-            PREP_HIP(rocprim::radix_sort_keys(t, bytes, db, (size_t)E, 0u, end_bit, stream));
-            PREP_HIP(hipStreamSynchronize(stream));
-            keys = db.current();
-            tmp.drop(t);
-            tmp.drop(keys == keys_a ? keys_b : keys_a);
-        }
-        incl = tmp.take<uint32_t>((uint64_t)E);
-        PREP_NEED(incl);
-        {
-            auto flags = rocprim::make_transform_iterator(rocprim::make_counting_iterator<size_t>(0), FlagOf{keys});
-            size_t bytes = 0;
-            PREP_HIP(rocprim::inclusive_scan(nullptr, bytes, flags, incl, (size_t)E, rocprim::plus<uint32_t>(), stream));
-            void* t = tmp.take<uint8_t>(bytes);
-            PREP_NEED(t);
-            PREP_HIP(rocprim::inclusive_scan(t, bytes, flags, incl, (size_t)E, rocprim::plus<uint32_t>(), stream));
-            PREP_HIP(hipMemcpyAsync(&M, incl + (E - 1), 4, hipMemcpyDeviceToHost, stream));
-            PREP_HIP(hipStreamSynchronize(stream));
-            tmp.drop(t);
-        }
+        keys_a = tmp.take<uint64_t>((uint64_t)E);
+        PREP_NEED(keys_a);
+        hipLaunchKernelGGL(k_keys, dim3((unsigned)((E + kKeyRun - 1) / kKeyRun)), dim3(kBlk), 0, stream, (uint32_t)V, (uint32_t)E, first, row_ptr, L->perm, col, inv,
+                           rows_per_part, src_bits, keys_a);
+        PREP_HIP(hipStreamSynchronize(stream));
+        tmp.drop(first); tmp.drop(inv);
+        first = nullptr; inv = nullptr;
+        keys_b = tmp.take<uint64_t>((uint64_t)E);
+        PREP_NEED(keys_b);
+        unsigned end_bit = kKeyLocalBits + src_bits;
+        while (end_bit < 63 && (1ull << (end_bit - kKeyLocalBits - src_bits)) < (uint64_t)Q) ++end_bit;
+        rocprim::double_buffer<uint64_t> db(keys_a, keys_b);
+        size_t bytes = 0;
+        PREP_HIP(rocprim::radix_sort_keys(nullptr, bytes, db, (size_t)E, (unsigned)kKeyLocalBits, end_bit, stream));
+        void* t = tmp.take<uint8_t>(bytes);
+        PREP_NEED(t);
+        PREP_HIP(rocprim::radix_sort_keys(t, bytes, db, (size_t)E, (unsigned)kKeyLocalBits, end_bit, stream));
+        PREP_HIP(hipStreamSynchronize(stream));
+        keys = db.current();
+        tmp.drop(t);
+        tmp.drop(keys == keys_a ? keys_b : keys_a);
+    } else {
+        tmp.drop(first); tmp.drop(inv);
     }
-    tmp.drop(inv);
-    L->M = M;
 
     // ---- scatter pieces: source intervals of about equal numbers of messages
     std::vector<uint32_t> cum((size_t)V + 1, 0u);            // messages of the sources before u
+    std::vector<uint32_t> rep_host(L->n_chunks), mbase_host((size_t)L->n_chunks + 1, 0u);
+    if (!keep(a, &L->starts, (uint64_t)padded / kIdChunk * kStartWords) || !keep(a, &L->mbase, (uint64_t)L->n_chunks + 1))
+        PREP_NEED((void*)nullptr);
     if (E > 0) {
         uint32_t* cnt = tmp.take<uint32_t>((uint64_t)V + 1);
         uint32_t* cum_dev = tmp.take<uint32_t>((uint64_t)V + 1);
-        PREP_NEED(cnt); PREP_NEED(cum_dev);
+        uint32_t* messages = tmp.take<uint32_t>((uint64_t)L->n_chunks + 1);
+        uint32_t* rep = tmp.take<uint32_t>((uint64_t)L->n_chunks);
+        PREP_NEED(cnt); PREP_NEED(cum_dev); PREP_NEED(messages); PREP_NEED(rep);
         hipLaunchKernelGGL(k_zero_u32, dim3(blocks_for((uint64_t)V + 1)), dim3(kBlk), 0, stream, (uint64_t)V + 1, cnt);
-        hipLaunchKernelGGL(k_count_messages, dim3(blocks_for((uint64_t)E)), dim3(kBlk), 0, stream, E, V, keys, cnt);
-        size_t bytes = 0;
+        hipLaunchKernelGGL(k_chunk_facts, dim3(L->n_chunks / kChunksPerBlock + 1), dim3(kBlk), 0, stream, (uint32_t)E, V, L->n_chunks, src_mask, keys, L->starts,
+                           messages, rep, cnt);
+        size_t bytes = 0, bytes_m = 0;
         PREP_HIP(rocprim::exclusive_scan(nullptr, bytes, cnt, cum_dev, 0u, (size_t)V + 1, rocprim::plus<uint32_t>(), stream));
-        void* t = tmp.take<uint8_t>(bytes);
+        PREP_HIP(rocprim::exclusive_scan(nullptr, bytes_m, messages, L->mbase, 0u, (size_t)L->n_chunks + 1, rocprim::plus<uint32_t>(), stream));
+        void* t = tmp.take<uint8_t>(std::max(bytes, bytes_m));
         PREP_NEED(t);
+        PREP_HIP(rocprim::exclusive_scan(t, bytes_m, messages, L->mbase, 0u, (size_t)L->n_chunks + 1, rocprim::plus<uint32_t>(), stream));
         PREP_HIP(rocprim::exclusive_scan(t, bytes, cnt, cum_dev, 0u, (size_t)V + 1, rocprim::plus<uint32_t>(), stream));
         PREP_HIP(hipMemcpyAsync(cum.data(), cum_dev, ((size_t)V + 1) * 4, hipMemcpyDeviceToHost, stream));
+        PREP_HIP(hipMemcpyAsync(rep_host.data(), rep, (size_t)L->n_chunks * 4, hipMemcpyDeviceToHost, stream));
+        PREP_HIP(hipMemcpyAsync(mbase_host.data(), L->mbase, ((size_t)L->n_chunks + 1) * 4, hipMemcpyDeviceToHost, stream));
         PREP_HIP(hipStreamSynchronize(stream));
-        tmp.drop(t); tmp.drop(cnt); tmp.drop(cum_dev);
+        tmp.drop(t); tmp.drop(rep); tmp.drop(messages); tmp.drop(cnt); tmp.drop(cum_dev);
+        M = mbase_host[L->n_chunks];
         if (cum[(size_t)V] != M) return FR_ERR_ARG;
+    } else {
+        PREP_HIP(hipMemcpyAsync(L->mbase, mbase_host.data(), 4, hipMemcpyHostToDevice, stream));
     }
+    L->M = M;
+
     // ---- the arrays that stay
-    if (!keep(a, &L->ids16, (uint64_t)padded) || !keep(a, &L->starts, (uint64_t)padded / kIdChunk * kStartWords) || !keep(a, &L->mbase, (uint64_t)L->n_chunks + 1) || !keep(a, &L->src16, ((uint64_t)M + 15) / 8 * 8))     // read eight at a time
+    if (!keep(a, &L->ids16, (uint64_t)padded) || !keep(a, &L->src16, ((uint64_t)M + 15) / 8 * 8))     // read eight at a time
         PREP_NEED((void*)nullptr);
     uint32_t* eoff = tmp.take<uint32_t>((uint64_t)Q + 1);
     PREP_NEED(eoff);
-    hipLaunchKernelGGL(k_starts, dim3(blocks_for((uint64_t)padded / 64)), dim3(kBlk), 0, stream, E, (uint64_t)padded / 64, keys, incl, L->starts);
-    hipLaunchKernelGGL(k_mbase, dim3(blocks_for((uint64_t)L->n_chunks + 1)), dim3(kBlk), 0, stream, E, L->n_chunks, M, keys, incl, L->mbase);
-    hipLaunchKernelGGL(k_eoff, dim3(blocks_for((uint64_t)Q + 1)), dim3(kBlk), 0, stream, Q, E, keys, eoff);
+    hipLaunchKernelGGL(k_eoff, dim3(blocks_for((uint64_t)Q + 1)), dim3(kBlk), 0, stream, Q, E, src_bits, keys, eoff);
     std::vector<uint32_t> eoff_host((size_t)Q + 1);
     PREP_HIP(hipMemcpyAsync(eoff_host.data(), eoff, ((size_t)Q + 1) * 4, hipMemcpyDeviceToHost, stream));
     PREP_HIP(hipStreamSynchronize(stream));
@@ -444,14 +523,6 @@ int pr_build_layout(PrLayout* L, int64_t V, int64_t E, const int32_t* row_ptr, c
     // repeated edge kGatherRepeatWeight more (measured on single tiles: 0.09 ns, 0.18 ns and 0.28 ns a piece)
     std::vector<uint64_t> wcum((size_t)L->n_chunks + 1, 0);
     if (E > 0) {
-        uint32_t* rep = tmp.take<uint32_t>((uint64_t)L->n_chunks);
-        PREP_NEED(rep);
-        hipLaunchKernelGGL(k_chunk_repeats, dim3(L->n_chunks), dim3(kBlk), 0, stream, E, L->n_chunks, keys, rep);
-        std::vector<uint32_t> rep_host(L->n_chunks), mbase_host((size_t)L->n_chunks + 1);
-        PREP_HIP(hipMemcpyAsync(rep_host.data(), rep, (size_t)L->n_chunks * 4, hipMemcpyDeviceToHost, stream));
-        PREP_HIP(hipMemcpyAsync(mbase_host.data(), L->mbase, ((size_t)L->n_chunks + 1) * 4, hipMemcpyDeviceToHost, stream));
-        PREP_HIP(hipStreamSynchronize(stream));
-        tmp.drop(rep);
         for (uint32_t c = 0; c < L->n_chunks; ++c) {
             const uint64_t edges = std::min<uint64_t>(kIdChunk, (uint64_t)E - (uint64_t)c * kIdChunk);
             wcum[c + 1] = wcum[c] + kGatherEdgeWeight * edges + kGatherMessageWeight * (uint64_t)(mbase_host[c + 1] - mbase_host[c]) +
@@ -694,8 +765,9 @@ int pr_build_layout(PrLayout* L, int64_t V, int64_t E, const int32_t* row_ptr, c
     uint32_t* ubound_dev = tmp.take<uint32_t>(ubound.size());
     PREP_NEED(ubound_dev);
     PREP_HIP(hipMemcpyAsync(ubound_dev, ubound.data(), ubound.size() * 4, hipMemcpyHostToDevice, stream));
-    hipLaunchKernelGGL(k_emit, dim3(blocks_for((uint64_t)padded)), dim3(kBlk), 0, stream, E, padded, (uint64_t)M, keys, incl,
-                       ubound_dev, L->n_spieces, id_scale_for(rows_per_part), L->ids16, L->src16);
+    if (E > 0)
+        hipLaunchKernelGGL(k_emit, dim3((L->n_chunks + kChunksPerBlock - 1) / kChunksPerBlock), dim3(kBlk), 0, stream, (uint32_t)E, L->n_chunks, M, src_mask, keys,
+                           L->mbase, ubound_dev, L->n_spieces, id_scale_for(rows_per_part), L->ids16, L->src16);
 
     // ---- what the cost model needs of every scatter tile
     L->sp.clear(); L->st.clear(); L->st_msgs.clear(); L->st_rows.clear();
@@ -730,8 +802,8 @@ int pr_build_layout(PrLayout* L, int64_t V, int64_t E, const int32_t* row_ptr, c
         !keep(a, &L->finish_ranges, (uint64_t)L->n_finish))
         PREP_NEED((void*)nullptr);
     if (Qe)
-        hipLaunchKernelGGL(k_bins, dim3(blocks_for((uint64_t)L->n_spieces * Qe)), dim3(kBlk), 0, stream, L->n_spieces, Qe, E, M, ubound_dev,
-                           keys, incl, L->bins);
+        hipLaunchKernelGGL(k_bins, dim3(blocks_for((uint64_t)L->n_spieces * Qe)), dim3(kBlk), 0, stream, L->n_spieces, Qe, E, M, src_bits, ubound_dev,
+                           keys, L->starts, L->mbase, L->bins);
     PREP_HIP(hipGetLastError());
     PREP_HIP(hipMemcpyAsync(L->range_info, L->ri.data(), (size_t)Q * sizeof(RangeInfo), hipMemcpyHostToDevice, stream));
     PREP_HIP(hipMemcpyAsync(L->gather_pieces, L->gp.data(), (size_t)L->n_pieces * sizeof(GatherPiece), hipMemcpyHostToDevice, stream));

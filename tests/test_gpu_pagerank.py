@@ -116,6 +116,17 @@ def test_small_sweeps_have_a_workgroup_per_compute_unit(n, edges, tiles):
     assert (np.abs(bits[0][big] - want[big]) / want[big]).max() <= 1e-4
 
 
+# the layout is built in runs of 2048 keys and chunks of 512 edges, four chunks a workgroup
+@pytest.mark.parametrize("edges", [1, 511, 513, 2047, 2048, 2049, 4097])
+@pytest.mark.parametrize("n", [2, 700, 9000])
+def test_layout_of_edge_counts_around_its_runs(n, edges):
+    rng = np.random.default_rng(edges)
+    src, dst = rng.integers(0, n, edges), rng.integers(0, max(1, n // 2), edges)
+    src[edges // 2:] = src[:edges - edges // 2]          # repeated edges among them
+    dst[edges // 2:] = dst[:edges - edges // 2]
+    _check(graphs.csr_from_edges(n, src, dst), iterations=4)
+
+
 def test_partition_sizes_other_than_the_two_supported_are_refused():
     g = graphs.rmat_csr(10, 3000, seed=8)
     rp, col, od = _dev(g.row_ptr, torch.int32), _dev(g.col, torch.int32), _dev(g.out_degree, torch.int32)
