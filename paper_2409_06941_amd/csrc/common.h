@@ -17,12 +17,16 @@ struct fr_alloc {
     int device = 0;
     int hip_error = 0;
     uint64_t peak = 0;
-    struct Block { void* ptr; uint64_t bytes; };
+    bool pooled = false;                 // set-up scratch comes from, and goes back to, the pool of kept blocks
+    struct Block { void* ptr; uint64_t bytes; uint64_t room; };      // room: the size of a block of the pool (0: not one)
     std::vector<Block> blocks;
 };
 
 void fr_alloc_reset(fr_alloc* a, uint64_t limit, bool host_only, int device);
 void fr_alloc_release(fr_alloc* a);   // frees every block handed out
+// Memory a task needs while it is set up, and counts only that long.  Given back with fr_alloc_free, by a caller that has
+// waited for the work that used it.
+void* fr_alloc_scratch(fr_alloc* a, size_t bytes);
 
 // Stage-load kernels (gemm.hip).
 int fr_busywait_launch(uint64_t ns, int wall_clock_khz, hipStream_t stream);

@@ -1246,6 +1246,7 @@ int fr_pagerank_run_standalone(void* user, int32_t device_id, void* stream_v, ui
     FR_HIP_TRY(hipSetDevice(device_id), p->hip_error);
     if (!p->inited) {
         fr_alloc_reset(&p->own, p->d.mem_limit_bytes, false, device_id);
+        p->own.pooled = true;
         int rc = pr_init(p, &p->own, stream_v);
         if (rc != FR_OK) {
             const bool oom = p->own.oom;

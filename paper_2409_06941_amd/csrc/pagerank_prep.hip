@@ -250,6 +250,20 @@ __device__ __forceinline__ uint32_t tile_of_source(const uint32_t* __restrict__ 
     return lo ? lo - 1 : 0;
 }
 
+// What the host needs of the messages per source to cut the scatter sweep: which sources send any (a bit each), and the
+// messages before every kFineSources-th source of all beyond the first kHeadSources (cum: before every source).  With
+// falling in-degree the sources of very many messages are among the first, whose messages the host gets one by one.
+// (2^22 vertices: the whole array is a 16 MB copy to memory the host has to touch first, and a walk over it.)
+constexpr uint64_t kHeadSources = 1u << 18, kFineSources = 16;
+__global__ __launch_bounds__(kBlk) void k_source_facts(uint64_t V, const uint32_t* __restrict__ cnt, const uint32_t* __restrict__ cum,
+                                                       uint64_t* __restrict__ sends, uint32_t* __restrict__ fine)
+{
+    const uint64_t u = (uint64_t)blockIdx.x * kBlk + threadIdx.x;
+    const uint64_t any = __ballot(u < V && cnt[u] != 0);
+    if ((threadIdx.x & 63) == 0 && u < V) sends[u / 64] = any;
+    if (u >= kHeadSources && u < V && u % kFineSources == 0) fine[(u - kHeadSources) / kFineSources] = cum[u];
+}
+
 __global__ __launch_bounds__(kBlk) void k_zero_u32(uint64_t n, uint32_t* p)
 {
     const uint64_t i = (uint64_t)blockIdx.x * kBlk + threadIdx.x;
@@ -330,11 +344,12 @@ __global__ __launch_bounds__(kBlk) void k_bins(uint32_t n_tiles, uint32_t Qe, in
 
 struct Scratch {
     fr_alloc* a;
+    hipStream_t stream;
     std::vector<void*> held;
     template <typename T>
     T* take(uint64_t count)
     {
-        void* p = fr_alloc_device(a, (size_t)(count ? count : 1) * sizeof(T));
+        void* p = fr_alloc_scratch(a, (size_t)(count ? count : 1) * sizeof(T));
         if (p) held.push_back(p);
         return static_cast<T*>(p);
     }
@@ -345,7 +360,32 @@ struct Scratch {
     }
     ~Scratch()
     {
+        if (!held.empty()) (void)hipStreamSynchronize(stream);       // (an early return may leave work that uses them)
         for (void* p : held) (void)fr_alloc_free(a, p);
+    }
+};
+
+// Several arrays in one block of the allocator, each on a 256-byte boundary: what they count as is what they would as
+// blocks of their own, at the price of one allocation (10 to 300 us each, and as much to give back).
+struct Carve {
+    uint64_t bytes = 0;
+    struct Part { void** where; uint64_t at; };
+    std::vector<Part> parts;
+    template <typename T>
+    void add(T** out, uint64_t count)
+    {
+        parts.push_back({reinterpret_cast<void**>(out), bytes});
+        bytes += ((count ? count : 1) * sizeof(T) + 255) / 256 * 256;
+    }
+    void place(void* base)
+    {
+        for (const Part& x : parts) *x.where = static_cast<char*>(base) + x.at;
+    }
+    bool keep(fr_alloc* a)
+    {
+        void* base = fr_alloc_device(a, (size_t)bytes);
+        if (base) place(base);
+        return base != nullptr;
     }
 };
 
@@ -388,7 +428,7 @@ int pr_build_layout(PrLayout* L, int64_t V, int64_t E, const int32_t* row_ptr, c
     while (src_bits < (uint32_t)kKeySrcBits && (1ll << src_bits) <= V) ++src_bits;         // is not enough)
     const uint32_t src_mask = (uint32_t)((1ull << src_bits) - 1);
 
-    Scratch tmp{a, {}};
+    Scratch tmp{a, stream, {}};
 
     // ---- refuse a malformed CSR before anything indexes with it
     int32_t* bad = tmp.take<int32_t>(1);
@@ -402,30 +442,48 @@ int pr_build_layout(PrLayout* L, int64_t V, int64_t E, const int32_t* row_ptr, c
     if (bad_host) return FR_ERR_ARG;
 
     // ---- vertices in order of falling in-degree; those without in-edges by falling out-degree
+    // The keys' two buffers are taken first; while the second is unused, what is needed to order the vertices and to make
+    // the keys lies in it, if it has room (E of about 4 V; else it has blocks of its own, given back as soon as they are done with).
     if (!keep(a, &L->perm, (uint64_t)V) || !keep(a, &L->inv_out, (uint64_t)V)) PREP_NEED((void*)nullptr);
-    int32_t* inv = tmp.take<int32_t>((uint64_t)V);
-    PREP_NEED(inv);
+    int32_t* inv = nullptr;
     uint64_t* keys_a = nullptr;
     uint64_t* keys_b = nullptr;
     uint32_t* first = nullptr;                         // edges before each row, new order (V + 1)
+    void* vertex_block = nullptr;
     {
         uint32_t degree_bits = 1;                      // an in-degree has at most these; a larger out-degree (the caller's array
         while ((1ll << degree_bits) <= E && degree_bits < 31) ++degree_bits;      // is not held against the edges) counts as 2^bits - 1
         const uint32_t top = (uint32_t)((1ull << degree_bits) - 1);
-        uint64_t* by_out = tmp.take<uint64_t>((uint64_t)V);
-        uint64_t* vk_a = tmp.take<uint64_t>((uint64_t)V);
-        uint64_t* vk_b = tmp.take<uint64_t>((uint64_t)V);
-        PREP_NEED(by_out); PREP_NEED(vk_a); PREP_NEED(vk_b);
+        uint64_t *by_out = nullptr, *vk_a = nullptr, *vk_b = nullptr;
+        uint8_t* t = nullptr;
         size_t sort_bytes = 0, select_bytes = 0, scan_bytes = 0;
         uint32_t* n_no_in = reinterpret_cast<uint32_t*>(bad);        // (its check is done)
         const NoInEdges no_in_edges{row_ptr};
-        rocprim::double_buffer<uint64_t> order(vk_a, vk_b);
-        PREP_HIP(rocprim::radix_sort_keys(nullptr, sort_bytes, order, (size_t)V, 32u, 32u + degree_bits, stream));
+        {
+            rocprim::double_buffer<uint64_t> probe(vk_a, vk_b);
+            PREP_HIP(rocprim::radix_sort_keys(nullptr, sort_bytes, probe, (size_t)V, 32u, 32u + degree_bits, stream));
+        }
         PREP_HIP(rocprim::select(nullptr, select_bytes, vk_a, by_out, n_no_in, (size_t)V, no_in_edges, stream));
-        PREP_HIP(rocprim::exclusive_scan(nullptr, scan_bytes, reinterpret_cast<uint32_t*>(vk_a), reinterpret_cast<uint32_t*>(vk_a), 0u, (size_t)V + 1, rocprim::plus<uint32_t>(), stream));
-        size_t bytes = std::max(sort_bytes, std::max(select_bytes, scan_bytes));
-        void* t = tmp.take<uint8_t>(bytes);
-        PREP_NEED(t);
+        PREP_HIP(rocprim::exclusive_scan(nullptr, scan_bytes, first, first, 0u, (size_t)V + 1, rocprim::plus<uint32_t>(), stream));
+        Carve longer, parts;                           // what the keys are made from, and what is only needed for the order
+        longer.add(&inv, (uint64_t)V); longer.add(&by_out, (uint64_t)V);
+        parts.add(&vk_a, (uint64_t)V); parts.add(&vk_b, (uint64_t)V);
+        parts.add(&t, std::max(sort_bytes, std::max(select_bytes, scan_bytes)));
+        void* order_block = nullptr;
+        if (longer.bytes + parts.bytes <= (uint64_t)E * 8) {
+            keys_a = tmp.take<uint64_t>((uint64_t)E);
+            keys_b = tmp.take<uint64_t>((uint64_t)E);
+            PREP_NEED(keys_a); PREP_NEED(keys_b);
+            longer.place(keys_b);
+            parts.place(reinterpret_cast<char*>(keys_b) + longer.bytes);
+        } else {
+            vertex_block = tmp.take<uint8_t>(longer.bytes);
+            order_block = tmp.take<uint8_t>(parts.bytes);
+            PREP_NEED(vertex_block); PREP_NEED(order_block);
+            longer.place(vertex_block);
+            parts.place(order_block);
+        }
+        rocprim::double_buffer<uint64_t> order(vk_a, vk_b);
         hipLaunchKernelGGL(k_vertex_keys_out, dim3(blocks_for((uint64_t)V)), dim3(kBlk), 0, stream, V, top, out_degree, vk_a);
         PREP_HIP(rocprim::radix_sort_keys(t, sort_bytes, order, (size_t)V, 32u, 32u + degree_bits, stream));
         PREP_HIP(rocprim::select(t, select_bytes, order.current(), by_out, n_no_in, (size_t)V, no_in_edges, stream));
@@ -434,25 +492,28 @@ int pr_build_layout(PrLayout* L, int64_t V, int64_t E, const int32_t* row_ptr, c
         PREP_HIP(rocprim::radix_sort_keys(t, sort_bytes, order, (size_t)V, 32u, 32u + degree_bits, stream));
         uint32_t* indeg = reinterpret_cast<uint32_t*>(order.alternate());          // V + 1 words where 2 V have room
         hipLaunchKernelGGL(k_perm, dim3(blocks_for((uint64_t)V + 1)), dim3(kBlk), 0, stream, V, order.current(), by_out, n_no_in, row_ptr, out_degree, L->perm, inv, L->inv_out, indeg);
-        PREP_HIP(rocprim::exclusive_scan(t, scan_bytes, indeg, reinterpret_cast<uint32_t*>(by_out), 0u, (size_t)V + 1, rocprim::plus<uint32_t>(), stream));
-        PREP_HIP(hipStreamSynchronize(stream));
-        tmp.drop(t); tmp.drop(vk_a); tmp.drop(vk_b);
         first = reinterpret_cast<uint32_t*>(by_out);
+        PREP_HIP(rocprim::exclusive_scan(t, scan_bytes, indeg, first, 0u, (size_t)V + 1, rocprim::plus<uint32_t>(), stream));
+        if (order_block) {
+            PREP_HIP(hipStreamSynchronize(stream));
+            tmp.drop(order_block);
+        }
     }
 
     // ---- sort the edges by (range, source, local row); set-up scratch is returned as soon as it is done with
     uint64_t* keys = nullptr;
     uint32_t M = 0;
     if (E > 0) {
-        keys_a = tmp.take<uint64_t>((uint64_t)E);
+        if (!keys_a) keys_a = tmp.take<uint64_t>((uint64_t)E);
         PREP_NEED(keys_a);
         hipLaunchKernelGGL(k_keys, dim3((unsigned)((E + kKeyRun - 1) / kKeyRun)), dim3(kBlk), 0, stream, (uint32_t)V, (uint32_t)E, first, row_ptr, L->perm, col, inv,
                            rows_per_part, src_bits, keys_a);
-        PREP_HIP(hipStreamSynchronize(stream));
-        tmp.drop(first); tmp.drop(inv);
-        first = nullptr; inv = nullptr;
-        keys_b = tmp.take<uint64_t>((uint64_t)E);
-        PREP_NEED(keys_b);
+        if (!keys_b) {
+            PREP_HIP(hipStreamSynchronize(stream));
+            tmp.drop(vertex_block);
+            keys_b = tmp.take<uint64_t>((uint64_t)E);
+            PREP_NEED(keys_b);
+        }
         unsigned end_bit = kKeyLocalBits + src_bits;
         while (end_bit < 63 && (1ull << (end_bit - kKeyLocalBits - src_bits)) < (uint64_t)Q) ++end_bit;
         rocprim::double_buffer<uint64_t> db(keys_a, keys_b);
@@ -466,45 +527,67 @@ int pr_build_layout(PrLayout* L, int64_t V, int64_t E, const int32_t* row_ptr, c
         tmp.drop(t);
         tmp.drop(keys == keys_a ? keys_b : keys_a);
     } else {
-        tmp.drop(first); tmp.drop(inv);
+        PREP_HIP(hipStreamSynchronize(stream));
+        tmp.drop(vertex_block);
     }
 
     // ---- scatter pieces: source intervals of about equal numbers of messages
-    std::vector<uint32_t> cum((size_t)V + 1, 0u);            // messages of the sources before u
-    std::vector<uint32_t> rep_host(L->n_chunks), mbase_host((size_t)L->n_chunks + 1, 0u);
-    if (!keep(a, &L->starts, (uint64_t)padded / kIdChunk * kStartWords) || !keep(a, &L->mbase, (uint64_t)L->n_chunks + 1))
-        PREP_NEED((void*)nullptr);
+    // (`cum`: messages before each of the first kHeadSources sources, then before every kFineSources-th; `sends`: a bit a source)
+    const uint64_t n_head = std::min<uint64_t>((uint64_t)V, kHeadSources), n_fine = ((uint64_t)V - n_head + kFineSources - 1) / kFineSources;
+    std::vector<uint32_t> cum(n_head + n_fine, 0u), rep_host(L->n_chunks), mbase_host((size_t)L->n_chunks + 1, 0u);
+    std::vector<uint64_t> sends(((uint64_t)V + 63) / 64, 0ull);
+    {
+        Carve kept;
+        kept.add(&L->starts, (uint64_t)padded / kIdChunk * kStartWords); kept.add(&L->mbase, (uint64_t)L->n_chunks + 1);
+        if (!kept.keep(a)) PREP_NEED((void*)nullptr);
+    }
     if (E > 0) {
-        uint32_t* cnt = tmp.take<uint32_t>((uint64_t)V + 1);
-        uint32_t* cum_dev = tmp.take<uint32_t>((uint64_t)V + 1);
-        uint32_t* messages = tmp.take<uint32_t>((uint64_t)L->n_chunks + 1);
-        uint32_t* rep = tmp.take<uint32_t>((uint64_t)L->n_chunks);
-        PREP_NEED(cnt); PREP_NEED(cum_dev); PREP_NEED(messages); PREP_NEED(rep);
-        hipLaunchKernelGGL(k_zero_u32, dim3(blocks_for((uint64_t)V + 1)), dim3(kBlk), 0, stream, (uint64_t)V + 1, cnt);
+        uint32_t *cnt = nullptr, *cum_dev = nullptr, *messages = nullptr, *rep = nullptr, *fine = nullptr;
+        uint64_t* sends_dev = nullptr;
+        uint8_t* t = nullptr;
+        size_t bytes = 0, bytes_m = 0;
+        PREP_HIP(rocprim::exclusive_scan(nullptr, bytes, cnt, cum_dev, 0u, (size_t)V, rocprim::plus<uint32_t>(), stream));
+        PREP_HIP(rocprim::exclusive_scan(nullptr, bytes_m, messages, L->mbase, 0u, (size_t)L->n_chunks + 1, rocprim::plus<uint32_t>(), stream));
+        Carve parts;
+        parts.add(&cnt, (uint64_t)V); parts.add(&cum_dev, (uint64_t)V); parts.add(&messages, (uint64_t)L->n_chunks + 1); parts.add(&rep, (uint64_t)L->n_chunks);
+        parts.add(&fine, n_fine); parts.add(&sends_dev, sends.size()); parts.add(&t, std::max(bytes, bytes_m));
+        void* block = tmp.take<uint8_t>(parts.bytes);
+        PREP_NEED(block);
+        parts.place(block);
+        hipLaunchKernelGGL(k_zero_u32, dim3(blocks_for((uint64_t)V)), dim3(kBlk), 0, stream, (uint64_t)V, cnt);
         hipLaunchKernelGGL(k_chunk_facts, dim3(L->n_chunks / kChunksPerBlock + 1), dim3(kBlk), 0, stream, (uint32_t)E, V, L->n_chunks, src_mask, keys, L->starts,
                            messages, rep, cnt);
-        size_t bytes = 0, bytes_m = 0;
-        PREP_HIP(rocprim::exclusive_scan(nullptr, bytes, cnt, cum_dev, 0u, (size_t)V + 1, rocprim::plus<uint32_t>(), stream));
-        PREP_HIP(rocprim::exclusive_scan(nullptr, bytes_m, messages, L->mbase, 0u, (size_t)L->n_chunks + 1, rocprim::plus<uint32_t>(), stream));
-        void* t = tmp.take<uint8_t>(std::max(bytes, bytes_m));
-        PREP_NEED(t);
         PREP_HIP(rocprim::exclusive_scan(t, bytes_m, messages, L->mbase, 0u, (size_t)L->n_chunks + 1, rocprim::plus<uint32_t>(), stream));
-        PREP_HIP(rocprim::exclusive_scan(t, bytes, cnt, cum_dev, 0u, (size_t)V + 1, rocprim::plus<uint32_t>(), stream));
-        PREP_HIP(hipMemcpyAsync(cum.data(), cum_dev, ((size_t)V + 1) * 4, hipMemcpyDeviceToHost, stream));
+        PREP_HIP(rocprim::exclusive_scan(t, bytes, cnt, cum_dev, 0u, (size_t)V, rocprim::plus<uint32_t>(), stream));
+        hipLaunchKernelGGL(k_source_facts, dim3(blocks_for((uint64_t)V)), dim3(kBlk), 0, stream, (uint64_t)V, cnt, cum_dev, sends_dev, fine);
+        uint32_t last[2] = {0, 0};
+        PREP_HIP(hipMemcpyAsync(cum.data(), cum_dev, n_head * 4, hipMemcpyDeviceToHost, stream));
+        if (n_fine) PREP_HIP(hipMemcpyAsync(cum.data() + n_head, fine, n_fine * 4, hipMemcpyDeviceToHost, stream));
+        PREP_HIP(hipMemcpyAsync(sends.data(), sends_dev, sends.size() * 8, hipMemcpyDeviceToHost, stream));
+        PREP_HIP(hipMemcpyAsync(&last[0], cum_dev + (V - 1), 4, hipMemcpyDeviceToHost, stream));
+        PREP_HIP(hipMemcpyAsync(&last[1], cnt + (V - 1), 4, hipMemcpyDeviceToHost, stream));
         PREP_HIP(hipMemcpyAsync(rep_host.data(), rep, (size_t)L->n_chunks * 4, hipMemcpyDeviceToHost, stream));
         PREP_HIP(hipMemcpyAsync(mbase_host.data(), L->mbase, ((size_t)L->n_chunks + 1) * 4, hipMemcpyDeviceToHost, stream));
         PREP_HIP(hipStreamSynchronize(stream));
-        tmp.drop(t); tmp.drop(rep); tmp.drop(messages); tmp.drop(cnt); tmp.drop(cum_dev);
+        tmp.drop(block);
         M = mbase_host[L->n_chunks];
-        if (cum[(size_t)V] != M) return FR_ERR_ARG;
+        if (last[0] + last[1] != M) return FR_ERR_ARG;
     } else {
         PREP_HIP(hipMemcpyAsync(L->mbase, mbase_host.data(), 4, hipMemcpyHostToDevice, stream));
     }
+    // messages of the sources before u: any u up to kHeadSources, beyond it a multiple of kFineSources or V
+    auto messages_before = [&](uint64_t u) -> uint64_t {
+        if (u >= (uint64_t)V) return M;
+        return u < n_head ? cum[u] : cum[n_head + (u - n_head) / kFineSources];
+    };
     L->M = M;
 
     // ---- the arrays that stay
-    if (!keep(a, &L->ids16, (uint64_t)padded) || !keep(a, &L->src16, ((uint64_t)M + 15) / 8 * 8))     // read eight at a time
-        PREP_NEED((void*)nullptr);
+    {
+        Carve kept;
+        kept.add(&L->ids16, (uint64_t)padded); kept.add(&L->src16, ((uint64_t)M + 15) / 8 * 8);     // (read eight at a time)
+        if (!kept.keep(a)) PREP_NEED((void*)nullptr);
+    }
     uint32_t* eoff = tmp.take<uint32_t>((uint64_t)Q + 1);
     PREP_NEED(eoff);
     hipLaunchKernelGGL(k_eoff, dim3(blocks_for((uint64_t)Q + 1)), dim3(kBlk), 0, stream, Q, E, src_bits, keys, eoff);
@@ -655,12 +738,23 @@ int pr_build_layout(PrLayout* L, int64_t V, int64_t E, const int32_t* row_ptr, c
             uint64_t first_voidable = std::min<uint64_t>((uint64_t)V, src_per_part);      // (the first piece always exists)
             for (uint32_t j = 0; j < Q; ++j)
                 if ((L->ri[j].cls_tiles & 3u) == kRangeMerged) first_voidable = std::max(first_voidable, std::min<uint64_t>((uint64_t)V, ((uint64_t)j + 1) * rows_per_part));
+            // (by words of 64 sources; beyond kHeadSources a run is cut to multiples of kFineSources)
             uint64_t run_start = first_voidable, rows = 0;
-            for (uint64_t u = first_voidable; u <= (uint64_t)V; ++u) {
-                if (u < (uint64_t)V && cum[u + 1] == cum[u]) continue;
-                if (u - run_start >= kVoidMin) { voids.push_back({run_start, u}); void_rows_before_void.push_back(rows); rows += u - run_start; }
-                run_start = u + 1;
+            auto end_run = [&](uint64_t lo, uint64_t hi) {
+                if (lo >= kHeadSources) lo = (lo + kFineSources - 1) / kFineSources * kFineSources;
+                if (hi > kHeadSources && hi < (uint64_t)V) hi = hi / kFineSources * kFineSources;
+                if (hi < lo + kVoidMin) return;
+                voids.push_back({lo, hi}); void_rows_before_void.push_back(rows);
+                rows += hi - lo;
+            };
+            for (uint64_t k = first_voidable / 64; k < sends.size(); ++k) {
+                uint64_t w = sends[k];
+                if (k == first_voidable / 64) w &= ~0ull << (first_voidable % 64);
+                if (!w) continue;
+                end_run(run_start, k * 64 + (uint64_t)__builtin_ctzll(w));
+                run_start = k * 64 + 64 - (uint64_t)__builtin_clzll(w);      // (shorter runs inside the word do not count)
             }
+            end_run(run_start, (uint64_t)V);
             void_rows_before_void.push_back(rows);
         }
         auto void_rows_before = [&](uint64_t u) -> uint64_t {        // rows of void runs among the sources before u
@@ -671,7 +765,7 @@ int pr_build_layout(PrLayout* L, int64_t V, int64_t E, const int32_t* row_ptr, c
         auto weight_before = [&](uint64_t u) -> uint64_t {
             const uint64_t j = std::min<uint64_t>(u / rows_per_part, Q);
             const uint64_t rows = rows_before[j] + (j < Q ? (u - j * rows_per_part) * per_row[j] : 0);
-            return kScatterMessageWeight * (uint64_t)cum[u] + kScatterRowWeight * (rows - void_rows_before(u));
+            return kScatterMessageWeight * messages_before(u) + kScatterRowWeight * (rows - void_rows_before(u));
         };
         auto cut = [&](uint64_t target) {
             ubound.clear(); piece_void.clear();
@@ -685,8 +779,23 @@ int pr_build_layout(PrLayout* L, int64_t V, int64_t E, const int32_t* row_ptr, c
                 }
                 uint64_t limit = std::min<uint64_t>((uint64_t)V, u + src_per_part);
                 if (vi < voids.size()) limit = std::min(limit, voids[vi].first);
+                if (limit > kHeadSources && limit < (uint64_t)V) limit = limit / kFineSources * kFineSources;
                 const uint64_t want = weight_before(u) + target;
                 uint64_t lo = u + 1, hi = limit;             // the first end in (u, limit] that reaches `want`, else limit
+                if (hi > kHeadSources) {                     // (beyond the head: the first multiple of kFineSources that does)
+                    const uint64_t from = std::max(kHeadSources, u);
+                    if (u < kHeadSources && weight_before(kHeadSources) >= want) {
+                        hi = kHeadSources;
+                    } else {
+                        uint64_t a_lo = from / kFineSources + 1, a_hi = (limit + kFineSources - 1) / kFineSources;      // (u is a multiple there)
+                        while (a_lo < a_hi) {
+                            const uint64_t mid = (a_lo + a_hi) / 2;
+                            if (weight_before(mid * kFineSources) >= want) a_hi = mid;
+                            else a_lo = mid + 1;
+                        }
+                        lo = hi = std::min(limit, a_lo * kFineSources);
+                    }
+                }
                 while (lo < hi) {
                     const uint64_t mid = (lo + hi) / 2;
                     if (weight_before(mid) >= want) hi = mid;
@@ -736,11 +845,19 @@ int pr_build_layout(PrLayout* L, int64_t V, int64_t E, const int32_t* row_ptr, c
             // the small kernel is faster without the loop over pieces: a tile per piece, if a target up to one
             // compute unit's share of the weight leaves few enough pieces
             const uint64_t most = std::max<uint64_t>(least, (all + cus - 1) / cus);
+            std::vector<uint64_t> targets;                   // (a larger target never leaves more pieces: bisection finds the first that fits)
             for (uint64_t target = start;; target = std::min(most, target + target / 50 + 1)) {
-                cut(target);
-                if (live_pieces() <= slots) { pack(0); done = true; break; }
+                targets.push_back(target);
                 if (target >= most) break;
             }
+            size_t lo = 0, hi = targets.size();
+            while (lo < hi) {
+                const size_t mid = (lo + hi) / 2;
+                cut(targets[mid]);
+                if (live_pieces() <= slots) hi = mid;
+                else lo = mid + 1;
+            }
+            if (lo < targets.size()) { cut(targets[lo]); pack(0); done = true; }
         }
         if (!done)
             for (uint64_t target = start;; target += target / 50 + 1) {
@@ -782,7 +899,7 @@ int pr_build_layout(PrLayout* L, int64_t V, int64_t E, const int32_t* row_ptr, c
                 partials += (hi - lo) * (L->ri[j].cls_tiles >> 2);
             }
             L->sp.push_back(ScatterPiece{(uint32_t)u0, (uint32_t)u1});
-            msgs[t] = (uint64_t)cum[u1] - cum[u0];
+            msgs[t] = messages_before(u1) - messages_before(u0);
             rows[t] = (u1 - u0) + partials;
         }
         for (const uint2& t : stiles) {
@@ -797,21 +914,30 @@ int pr_build_layout(PrLayout* L, int64_t V, int64_t E, const int32_t* row_ptr, c
     L->scatter_packed = false;
     for (const ScatterTile& t : L->st) L->scatter_packed = L->scatter_packed || t.p1 - t.p0 > 1;
 
-    if (!keep(a, &L->bins, (uint64_t)L->n_spieces * Qe) || !keep(a, &L->range_info, (uint64_t)Q) ||
-        !keep(a, &L->gather_pieces, (uint64_t)L->n_pieces) || !keep(a, &L->gather_tiles, (uint64_t)L->n_gather) || !keep(a, &L->scatter_pieces, (uint64_t)L->n_spieces) || !keep(a, &L->scatter_tiles, (uint64_t)L->n_scatter) ||
-        !keep(a, &L->finish_ranges, (uint64_t)L->n_finish))
-        PREP_NEED((void*)nullptr);
+    Carve tables;                                      // uploaded together
+    tables.add(&L->range_info, (uint64_t)Q); tables.add(&L->gather_pieces, (uint64_t)L->n_pieces); tables.add(&L->gather_tiles, (uint64_t)L->n_gather);
+    tables.add(&L->scatter_pieces, (uint64_t)L->n_spieces); tables.add(&L->scatter_tiles, (uint64_t)L->n_scatter); tables.add(&L->finish_ranges, (uint64_t)L->n_finish);
+    const uint64_t table_bytes = tables.bytes;
+    tables.add(&L->bins, (uint64_t)L->n_spieces * Qe);
+    if (!tables.keep(a)) PREP_NEED((void*)nullptr);
+    std::vector<char> packed(table_bytes, 0);
+    {
+        const char* base = reinterpret_cast<const char*>(L->range_info);
+        auto put = [&](const void* where, const void* from, size_t bytes) {
+            if (bytes) std::memcpy(packed.data() + (static_cast<const char*>(where) - base), from, bytes);
+        };
+        put(L->range_info, L->ri.data(), (size_t)Q * sizeof(RangeInfo));
+        put(L->gather_pieces, L->gp.data(), (size_t)L->n_pieces * sizeof(GatherPiece));
+        put(L->gather_tiles, L->gt.data(), (size_t)L->n_gather * sizeof(GatherTile));
+        put(L->scatter_pieces, L->sp.data(), (size_t)L->n_spieces * sizeof(ScatterPiece));
+        put(L->scatter_tiles, L->st.data(), (size_t)L->n_scatter * sizeof(ScatterTile));
+        put(L->finish_ranges, L->fin.data(), (size_t)L->n_finish * 4);
+    }
     if (Qe)
         hipLaunchKernelGGL(k_bins, dim3(blocks_for((uint64_t)L->n_spieces * Qe)), dim3(kBlk), 0, stream, L->n_spieces, Qe, E, M, src_bits, ubound_dev,
                            keys, L->starts, L->mbase, L->bins);
     PREP_HIP(hipGetLastError());
-    PREP_HIP(hipMemcpyAsync(L->range_info, L->ri.data(), (size_t)Q * sizeof(RangeInfo), hipMemcpyHostToDevice, stream));
-    PREP_HIP(hipMemcpyAsync(L->gather_pieces, L->gp.data(), (size_t)L->n_pieces * sizeof(GatherPiece), hipMemcpyHostToDevice, stream));
-    PREP_HIP(hipMemcpyAsync(L->gather_tiles, L->gt.data(), (size_t)L->n_gather * sizeof(GatherTile), hipMemcpyHostToDevice, stream));
-    PREP_HIP(hipMemcpyAsync(L->scatter_pieces, L->sp.data(), (size_t)L->n_spieces * sizeof(ScatterPiece), hipMemcpyHostToDevice, stream));
-    PREP_HIP(hipMemcpyAsync(L->scatter_tiles, L->st.data(), (size_t)L->n_scatter * sizeof(ScatterTile), hipMemcpyHostToDevice, stream));
-    if (L->n_finish)
-        PREP_HIP(hipMemcpyAsync(L->finish_ranges, L->fin.data(), (size_t)L->n_finish * 4, hipMemcpyHostToDevice, stream));
+    PREP_HIP(hipMemcpyAsync(L->range_info, packed.data(), table_bytes, hipMemcpyHostToDevice, stream));
     PREP_HIP(hipStreamSynchronize(stream));       // the host vectors and `tmp` go away after this
     return FR_OK;     // `tmp` returns the scratch blocks to the allocator
 }

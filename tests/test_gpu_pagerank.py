@@ -347,3 +347,38 @@ def test_malformed_csr_is_refused_before_any_kernel_uses_it():
         t.fr_pagerank_run_standalone(0, torch.cuda.current_stream())
     assert e.value.code == fr.FR_ERR_ARG
     t.fr_pagerank_destroy()
+
+
+# beyond 2^18 sources the scatter pieces are cut at multiples of 16 sources: few edges (runs of sources without messages
+# start and end anywhere), many (heavy sources on both sides of the line), vertices with and without room in the keys' buffer
+@pytest.mark.parametrize("n,edges", [(262_145, 300_000), (262_161, 3_000_000), (300_011, 90_001), (700_001, 6_000_000), (1_300_021, 200_000)])
+def test_scatter_pieces_beyond_the_first_sources(n, edges):
+    src, dst = graphs.rmat_edges((n - 1).bit_length(), edges, seed=17)
+    _check(graphs.csr_from_edges(n, src % n, dst % n), iterations=5)
+    # sources far down the in-degree order that send many messages, with empty runs between them
+    rng = np.random.default_rng(n)
+    heavy = rng.choice(n, 40, replace=False)
+    src = np.repeat(heavy, edges // 40)
+    _check(graphs.csr_from_edges(n, src, rng.integers(0, n, len(src))), iterations=4)
+
+
+def test_set_up_memory_kept_between_graphs_changes_nothing_and_is_given_back():
+    def ctx_life():
+        fr.Context(device_id=0).fr_destroy()             # gives kept blocks back
+
+    big, small = graphs.rmat_csr(16, 900_000, seed=41), graphs.rmat_csr(16, 800_000, seed=42)
+    ctx_life()
+    torch.cuda.synchronize()
+    want = _run(small, iterations=5)                     # nothing kept from a larger graph
+    ctx_life()
+    torch.cuda.empty_cache()
+    before = torch.cuda.mem_get_info()[0]
+    for g in (big, small, big):
+        got = _run(g, iterations=5)
+        if g is small:
+            assert np.array_equal(got.view(np.uint32), want.view(np.uint32))
+    torch.cuda.empty_cache()
+    kept = before - torch.cuda.mem_get_info()[0]
+    assert kept <= torch.cuda.mem_get_info()[1] // 64 + (64 << 20)
+    ctx_life()
+    assert before - torch.cuda.mem_get_info()[0] <= 4 << 20
