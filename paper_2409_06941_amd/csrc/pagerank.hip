@@ -364,14 +364,19 @@ __global__ void k_clear_sched(uint32_t* sched)
 
 // ---- S_k ----
 // One workgroup per scatter tile at a time: contrib of its sources sits in LDS, and for every range j the messages of bin
-// (tile, j) - a contiguous run [x, y) of message numbers - are written.  The unit of work is a GROUP of eight
-// consecutive message numbers, aligned to eight: one 16-byte load brings the eight sources, eight LDS reads their
-// contrib, two 16-byte stores write the messages (groups cut by the ends of a bin store element by element).
-// The groups of all bins of a batch are numbered consecutively (prefix sums in LDS) and dealt to the threads
-// round-robin, so bins of any length keep all lanes busy; a thread finds a group's bin by binary search.
-// The load for a thread's next group is issued before the current one is worked on.
+// (tile, j) - a contiguous run [x, y) of message numbers - are written.  The unit of work is a GROUP of four or eight
+// consecutive message numbers, aligned to as many: one 8- or 16-byte load brings the sources, LDS reads their contrib,
+// one or two 16-byte stores write the messages (groups cut by the ends of a bin store element by element).
+// The groups of all bins of a batch are numbered consecutively (prefix sums in LDS) and dealt to the threads, so bins of
+// any length keep all lanes busy; a thread finds a group's bin by binary search, and the loads of the groups a thread has
+// in flight are issued before the first is used.
+// Groups of four, dealt to the wavefronts in runs of up to kAhead * 64 lane by lane (a wavefront's store is 1 KB in one
+// piece, and the next 64 groups are mostly in the same bin), are for the large kernel and for launches that hand out
+// tiles, where the sweep is bound by its stores: uniform graph of 2^23 vertices / 2^28 edges on 64 units 1640 -> 1442 us
+// an iteration, skewed one of 2^24 / 2^28 362 -> 345.  One round of small tiles is bound by latency and has shorter bins;
+// groups of eight dealt round-robin search half as often (10^6 / 10^7: 30.4 us, groups of four 31.4; 3 x 10^6 / 6 x 10^7 on
+// 128 units: 123.0 and 125.9).
 constexpr uint32_t kDescBatch = 1024;       // bins per batch
-constexpr uint32_t kGroup = 8;
 
 // Exclusive prefix sums of one value per thread over the workgroup (kScatterBlock threads); out[i] = sum of the
 // values of threads < i for i <= kScatterBlock.  `wave_tot` holds kScatterWaves + 1 words.
@@ -398,40 +403,59 @@ __device__ __forceinline__ void block_exclusive_scan(uint32_t value, uint32_t* o
 }
 
 struct GroupRef {
-    uint32_t m0;      // first message number of the group (multiple of kGroup)
+    uint32_t m0;      // first message number of the group (a multiple of its size)
     uint32_t bin;     // its bin in the batch
 };
 
-// Group number k of the batch: its bin is the last one whose first group number is <= k.
-__device__ __forceinline__ GroupRef locate_group(uint32_t k, const uint32_t* gpre, const uint2* desc, uint32_t nb)
+// Group number k of the batch: its bin is the last one of [lo, hi) whose first group number is <= k (lo's is).
+__device__ __forceinline__ uint32_t find_bin(uint32_t k, const uint32_t* gpre, uint32_t lo, uint32_t hi)
 {
-    uint32_t lo = 0, hi = nb;
     while (hi - lo > 1) {
         const uint32_t mid = (lo + hi) >> 1;
         if (gpre[mid] <= k) lo = mid;
         else hi = mid;
     }
-    GroupRef g;
-    g.bin = lo;
-    g.m0 = (desc[lo].x / kGroup + (k - gpre[lo])) * kGroup;
-    return g;
+    return lo;
 }
 
-__device__ __forceinline__ void emit_group(const GroupRef& ref, const uint2* desc, const uint4& raw, const float* slice, uint32_t n,
+// The bin of a group 64 numbers on from one in bin `lo`: mostly the same, else within 64 bins unless there are empty ones.
+__device__ __forceinline__ uint32_t next_bin(uint32_t k, const uint32_t* gpre, uint32_t lo, uint32_t nb)
+{
+    if (k < gpre[lo + 1]) return lo;
+    const uint32_t near = lo + 65 < nb ? lo + 65 : nb;
+    return find_bin(k, gpre, lo + 1, gpre[near] > k ? near : nb);
+}
+
+template <uint32_t kGroup>
+struct GroupSources { uint32_t w[kGroup / 2]; };      // two 16-bit sources a word
+
+template <uint32_t kGroup>
+__device__ __forceinline__ GroupSources<kGroup> load_group(const uint16_t* __restrict__ src16, uint32_t m0)
+{
+    if constexpr (kGroup == 4) {
+        const uint2 r = reinterpret_cast<const uint2*>(src16)[m0 / 4];
+        return {{r.x, r.y}};
+    } else {
+        const uint4 r = reinterpret_cast<const uint4*>(src16)[m0 / 8];
+        return {{r.x, r.y, r.z, r.w}};
+    }
+}
+
+template <uint32_t kGroup>
+__device__ __forceinline__ void emit_group(const GroupRef& ref, const uint2* desc, const GroupSources<kGroup>& raw, const float* slice, uint32_t n,
                                            float* __restrict__ msg)
 {
     struct { uint32_t m0, x, y; } g = {ref.m0, desc[ref.bin].x, desc[ref.bin].y};
-    const uint32_t w[4] = {raw.x, raw.y, raw.z, raw.w};
     float val[kGroup];
 #pragma unroll
     for (int e = 0; e < (int)kGroup; ++e) {
-        const uint32_t src = (e & 1) ? (w[e >> 1] >> 16) : (w[e >> 1] & 0xffffu);
+        const uint32_t src = (e & 1) ? (raw.w[e >> 1] >> 16) : (raw.w[e >> 1] & 0xffffu);
         val[e] = src < n ? slice[src] : 0.0f;
     }
     if (g.m0 >= g.x && g.m0 + kGroup <= g.y) {
         float4* out = reinterpret_cast<float4*>(msg + g.m0);
-        out[0] = make_float4(val[0], val[1], val[2], val[3]);
-        out[1] = make_float4(val[4], val[5], val[6], val[7]);
+#pragma unroll
+        for (int e = 0; e < (int)kGroup; e += 4) out[e / 4] = make_float4(val[e], val[e + 1], val[e + 2], val[e + 3]);
     } else {
 #pragma unroll
         for (int e = 0; e < (int)kGroup; ++e)
@@ -463,7 +487,8 @@ void k_scatter(DevArgs A, GateArg G, uint32_t tile0, uint32_t n_tiles, int parit
         const float D = dangling_total(A.dpart + (size_t)parity * A.n_dpart, A.n_dpart);
         base = (1.0f - A.damping) / (float)A.V + A.damping * D / (float)A.V;
     }
-    const uint4* src8 = reinterpret_cast<const uint4*>(A.src16);
+    constexpr bool kRuns = kDynamic || kSrcPerPart == kSrcLarge;
+    constexpr uint32_t kGroup = kRuns ? 4 : 8;
     // rows a thread reads per round while the slice is filled (the small size has 64 registers per lane)
     constexpr int kFillRound = kSrcPerPart == kSrcSmall ? 4 : 16;
     uint32_t asked = kAskLater;          // thread 0: the answer to its question for the next tile
@@ -506,25 +531,34 @@ void k_scatter(DevArgs A, GateArg G, uint32_t tile0, uint32_t n_tiles, int parit
             }
             block_exclusive_scan(groups, gpre, wave_tot);
             const uint32_t total = gpre[kScatterBlock];
-            constexpr int kAhead = 4;                            // groups a thread has in flight
-            for (uint32_t k0 = threadIdx.x; k0 < total; k0 += kAhead * kScatterBlock) {
+            constexpr uint32_t kAhead = 4;                       // groups a thread has in flight, kApart numbers apart
+            constexpr uint32_t kApart = kRuns ? 64 : kScatterBlock;
+            // (runs are shorter where all wavefronts get some then)
+            const uint32_t ahead = !kRuns || total >= kAhead * kScatterBlock ? kAhead : (total + kScatterBlock - 1) / kScatterBlock;
+            const uint32_t k_first = kRuns ? (threadIdx.x / 64) * (ahead * 64) + threadIdx.x % 64 : threadIdx.x;
+            for (uint32_t k0 = k_first; k0 < total; k0 += ahead * kScatterBlock) {
                 // the question for the next tile goes out with the tile's last groups: put earlier, a workgroup on a
                 // heavy tile would book its next tile hundreds of microseconds before it is free to start it
                 if constexpr (kDynamic)
-                    if (threadIdx.x == 0 && last_piece && qb + kDescBatch >= Qe && k0 + kAhead * kScatterBlock >= total)
+                    if (threadIdx.x == 0 && last_piece && qb + kDescBatch >= Qe && k0 + ahead * kScatterBlock >= total)
                         asked = ask_if_time(A.sched, G);
                 GroupRef ref[kAhead];
-                uint4 raw[kAhead];
+                GroupSources<kGroup> raw[kAhead];
+                uint32_t bin = 0;
 #pragma unroll
-                for (int a = 0; a < kAhead; ++a) {
-                    const uint32_t k = k0 + a * kScatterBlock;
+                for (uint32_t a = 0; a < kAhead; ++a) {
+                    const uint32_t k = k0 + a * kApart;
                     ref[a] = GroupRef{0, 0};
-                    raw[a] = make_uint4(0, 0, 0, 0);
-                    if (k < total) { ref[a] = locate_group(k, gpre, desc, nb); raw[a] = src8[ref[a].m0 / kGroup]; }
+                    raw[a] = GroupSources<kGroup>{};
+                    if (a < ahead && k < total) {
+                        bin = !kRuns || a == 0 ? find_bin(k, gpre, 0, nb) : next_bin(k, gpre, bin, nb);
+                        ref[a] = GroupRef{(desc[bin].x / kGroup + (k - gpre[bin])) * kGroup, bin};
+                        raw[a] = load_group<kGroup>(A.src16, ref[a].m0);
+                    }
                 }
 #pragma unroll
-                for (int a = 0; a < kAhead; ++a)
-                    if (k0 + a * kScatterBlock < total) emit_group(ref[a], desc, raw[a], slice, n, A.msg);
+                for (uint32_t a = 0; a < kAhead; ++a)
+                    if (a < ahead && k0 + a * kApart < total) emit_group<kGroup>(ref[a], desc, raw[a], slice, n, A.msg);
             }
         }
     };
