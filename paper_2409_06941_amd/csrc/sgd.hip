@@ -251,7 +251,7 @@ __global__ __launch_bounds__(kSgdBlock) void k_sgd(SgdArgs A, GateArg G, uint32_
             ask_ids(i0);
         }
         __syncthreads();
-        if (threadIdx.x < 64) {
+        if (threadIdx.x < 64 && H.rounds) {                             // (a cell without ratings has no entries to read)
             const LdsBytes at = reinterpret_cast<LdsBytes>((uint32_t)((n_rows + 1) * (F * 4)));
             run_rounds<F, lanes_for(F)>(at, H.rounds, A.gamma, A.gl);
         }

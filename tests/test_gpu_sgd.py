@@ -106,6 +106,20 @@ def test_no_ratings_leaves_the_factors_alone():
     assert _same_bits(P, P0) and _same_bits(Q, Q0)
 
 
+# A cell without ratings has no entries: nothing may be read from its LDS, which holds what an earlier workgroup left, or is
+# none at all where no cell of the task has ratings (the factors keep their bits either way; what this runs is the path)
+@pytest.mark.parametrize("F", [16, 32, 64])
+@pytest.mark.parametrize("pairs,B", [([], 4), ([(3, 2)], 4), ([(0, 0), (0, 1), (5, 6)], 7), ([(k, (5 * k) % 40) for k in range(40)], 40)])
+def test_cells_without_ratings_are_left_alone(pairs, B, F):
+    print("case", len(pairs), B, F, flush=True)
+    r = _dense(pairs, 41, 41, seed=3)
+    P0, Q0 = wl.initial_factors(41, 41, F, seed=F)
+    P, Q, info = _run(r, P0, Q0, F, 0.02, 0.03, 3, B)
+    assert info.blocks == B and info.largest_cell <= len(pairs) < B * B      # most cells have none
+    P32, Q32 = osgd.sgd(r.row_ptr, r.item, r.rating, P0, Q0, 0.02, 0.03, 3, B, ordered_fp32=True)
+    assert _same_bits(P, P32) and _same_bits(Q, Q32)
+
+
 def test_malformed_ratings_are_refused():
     r = wl.rmat_ratings(6, 500, seed=8)
     P0, Q0 = wl.initial_factors(r.n_users, r.n_items, 16, seed=1)
@@ -315,7 +329,7 @@ def test_device_gate_refuses_late_sgd_steps_and_the_factors_keep_their_bits():
 def _dense(pairs, n_users, n_items, seed):
     pairs = sorted(set(pairs))
     row_ptr = np.zeros(n_users + 1, np.int64)
-    np.add.at(row_ptr, np.array([u for u, _ in pairs]) + 1, 1)
+    np.add.at(row_ptr, np.array([u for u, _ in pairs], np.int64) + 1, 1)
     rating = np.random.default_rng(seed).uniform(1, 5, len(pairs)).astype(np.float32)
     return wl.Ratings(n_users, n_items, len(pairs), np.cumsum(row_ptr).astype(np.int32), np.array([i for _, i in pairs], np.int32), rating)
 
