@@ -28,6 +28,11 @@ void fr_alloc_release(fr_alloc* a);   // frees every block handed out
 // waited for the work that used it.
 void* fr_alloc_scratch(fr_alloc* a, size_t bytes);
 
+// A set-up that has a smaller layout to fall back on: fr_alloc_mark before it takes memory for the larger one; if memory runs
+// out, fr_alloc_back_to (the stream has been waited for) frees what was handed out since and forgets that it ran out.
+size_t fr_alloc_mark(const fr_alloc* a);
+void fr_alloc_back_to(fr_alloc* a, size_t mark);
+
 // Stage-load kernels (gemm.hip).
 int fr_busywait_launch(uint64_t ns, int wall_clock_khz, hipStream_t stream);
 int fr_alufill_launch(uint64_t ns, int wall_clock_khz, uint32_t workgroups, hipStream_t stream);

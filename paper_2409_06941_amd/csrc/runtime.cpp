@@ -783,6 +783,15 @@ void fr_alloc_release(fr_alloc* a)
     a->used = 0;
 }
 
+size_t fr_alloc_mark(const fr_alloc* a) { return a->blocks.size(); }
+
+void fr_alloc_back_to(fr_alloc* a, size_t mark)
+{
+    while (a->blocks.size() > mark) (void)fr_alloc_free(a, a->blocks.back().ptr);
+    a->oom = false;
+    a->hip_error = 0;
+}
+
 void* fr_alloc_scratch(fr_alloc* a, size_t bytes)
 {
     if (!a || !a->pooled || a->host_only) return fr_alloc_device(a, bytes);

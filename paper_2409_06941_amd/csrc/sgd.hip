@@ -718,6 +718,8 @@ int sgd_lay_out_rounds(SgdTask* p, fr_alloc* a, hipStream_t stream, const uint32
     const uint32_t n_cells = p->B * p->B;
     const int F = p->d.factors;
     std::vector<MoreBatch> more;
+    std::vector<uint4> heads_host;
+    struct Wait { hipStream_t stream; ~Wait() { (void)hipStreamSynchronize(stream); } } wait{stream};      // (an early return may leave work)
     for (uint32_t c = 0; c < n_cells; ++c) {
         if (p->cells[c + 1] < p->cells[c]) return FR_ERR_ARG;
         for (uint32_t e = p->cells[c]; p->cells[c + 1] - e > kBatch;) {
@@ -747,7 +749,7 @@ int sgd_lay_out_rounds(SgdTask* p, fr_alloc* a, hipStream_t stream, const uint32
         (void)fr_alloc_free(a, tmp);
     }
     uint64_t total = 0;
-    std::vector<uint4> heads_host(n_batches);
+    heads_host.resize(n_batches);
     SGD_HIP(hipMemcpyAsync(&total, before + n_batches, 8, hipMemcpyDeviceToHost, stream));
     SGD_HIP(hipMemcpyAsync(heads_host.data(), heads, (size_t)n_batches * sizeof(uint4), hipMemcpyDeviceToHost, stream));
     SGD_HIP(hipStreamSynchronize(stream));
@@ -769,6 +771,21 @@ int sgd_lay_out_rounds(SgdTask* p, fr_alloc* a, hipStream_t stream, const uint32
     (void)fr_alloc_free(a, heads);
     if (F == 64) SGD_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_sgd<64>), hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLds));
     p->args.records = records; p->args.entries = entries; p->args.stride = stride;
+    return FR_OK;
+}
+
+// Ratings in the order of the cells, for k_sgd_chain.
+int sgd_lay_out_chain(SgdTask* p, fr_alloc* a, hipStream_t stream, const uint32_t* cell_ptr, const uint32_t* index, const uint32_t* user_of)
+{
+    const int64_t E = p->d.n_ratings;
+    const uint64_t n = (uint64_t)std::max<int64_t>(1, E);
+    uint64_t* keys = static_cast<uint64_t*>(fr_alloc_device(a, n * 8));
+    float* sorted = static_cast<float*>(fr_alloc_device(a, n * 4));
+    SGD_NEED(keys); SGD_NEED(sorted);
+    if (E > 0)
+        hipLaunchKernelGGL(k_sgd_stream, dim3((unsigned)((E + 255) / 256)), dim3(256), 0, stream, E, index, user_of, p->d.item, p->d.rating, keys, sorted);
+    SGD_HIP(hipStreamSynchronize(stream));
+    p->args.keys = keys; p->args.rating = sorted; p->args.cell_ptr = cell_ptr;
     return FR_OK;
 }
 
@@ -859,17 +876,26 @@ int sgd_init(void* user, fr_alloc* a, void* stream_v)
 
     SgdArgs& A = p->args;
     A = SgdArgs{};
-    if ((uint64_t)E > (uint64_t)kLongCell * n_cells) {
-        uint64_t* keys = static_cast<uint64_t*>(fr_alloc_device(a, n * 8));
-        float* sorted = static_cast<float*>(fr_alloc_device(a, n * 4));
-        SGD_NEED(keys); SGD_NEED(sorted);
-        hipLaunchKernelGGL(k_sgd_stream, dim3((unsigned)((E + 255) / 256)), dim3(256), 0, stream, E, index, user_of, p->d.item, p->d.rating, keys, sorted);
-        SGD_HIP(hipStreamSynchronize(stream));
-        A.keys = keys; A.rating = sorted; A.cell_ptr = cell_ptr;
-    } else {
+    // Rounds, or where the cells are long, or the task's limit (or the device) has no room for the rounds' layout, one rating
+    // after the other: that needs no more memory than the sort before it did.
+    bool rounds = (uint64_t)E <= (uint64_t)kLongCell * n_cells;
+    if (rounds) {
+        const size_t mark = fr_alloc_mark(a);
         int rc = sgd_lay_out_rounds(p, a, stream, cell_ptr, index, user_of);
-        if (rc != FR_OK) return rc;
+        if (rc != FR_OK && a->oom) {
+            fr_alloc_back_to(a, mark);
+            A = SgdArgs{};
+            p->lds_bytes = 0;
+            rounds = false;
+        } else if (rc != FR_OK) {
+            return rc;
+        }
+    }
+    if (rounds) {
         (void)fr_alloc_free(a, cell_ptr);
+    } else {
+        int rc = sgd_lay_out_chain(p, a, stream, cell_ptr, index, user_of);
+        if (rc != FR_OK) return rc;
     }
     (void)fr_alloc_free(a, user_of); (void)fr_alloc_free(a, index);
     p->prefix.assign((size_t)B * B + 1, 0);

@@ -334,6 +334,42 @@ def _dense(pairs, n_users, n_items, seed):
     return wl.Ratings(n_users, n_items, len(pairs), np.cumsum(row_ptr).astype(np.int32), np.array([i for _, i in pairs], np.int32), rating)
 
 
+def _limits(r, F, B, seed=4):
+    """What the task's own buffers come to beside the caller's, under a limit: (resident, peak), and the factors."""
+    P0, Q0 = wl.initial_factors(r.n_users, r.n_items, F, seed=seed)
+    caller = 4 * (r.n_users + 1) + 8 * r.n_ratings + 4 * F * (r.n_users + r.n_items)
+
+    def run(own_limit):
+        P, Q = _dev(P0), _dev(Q0)
+        t = _task(r, P, Q, F, 0.02, 0.03, 2, B, mem_limit_bytes=caller + own_limit)
+        try:
+            t.fr_sgd_run_standalone(0, torch.cuda.current_stream())
+            info = t.fr_sgd_info()
+        finally:
+            t.fr_sgd_destroy()
+        return info.bytes_resident - caller, info.bytes_peak - caller, P.cpu().numpy(), Q.cpu().numpy()
+    return run
+
+
+@pytest.mark.parametrize("F,B", [(16, 64), (64, 64), (32, 40)])
+def test_a_limit_without_room_for_the_rounds_takes_the_small_layout(F, B):
+    # 20 bytes a rating for the sort (and its scratch) and 4 per cell are what the ratings in a row need, 12 of them for good
+    r = wl.rmat_ratings(13, 300_000, seed=12)
+    run = _limits(r, F, B)
+    resident, peak, P, Q = run(1 << 40)
+    assert resident > 16 * r.n_ratings                            # rounds
+    enough = 32 * r.n_ratings + 4 * B * B + (1 << 17)
+    assert peak > enough                                          # (else this test looks at nothing)
+    for limit in (enough, peak - 1):
+        print("case", F, B, limit, flush=True)
+        small, small_peak, P2, Q2 = run(limit)
+        assert small <= 12 * r.n_ratings + 4 * B * B + 8 * B + 4096 and small_peak <= limit
+        assert _same_bits(P, P2) and _same_bits(Q, Q2)
+    with pytest.raises(fr.FreeRideError) as e:
+        run(19 * r.n_ratings)
+    assert e.value.code == fr.FR_ERR_OOM
+
+
 # where the layout in rounds can go wrong: a batch of one rating, full batches and one more (128, 129), one chain (a single
 # user or item), no chain at all (a diagonal: 256 rows and the most LDS), a grid, cells without ratings, and both sides of
 # the mean cell size (256) from which on the ratings are worked on one after the other
