@@ -37,6 +37,7 @@ constexpr uint32_t kBatch = 128;                 // ratings of a cell that are w
 constexpr uint32_t kMaxRounds = 2 * kBatch;      // a rating is at most two rounds behind the last one before it
 constexpr uint32_t kLongCell = 2 * kBatch;       // mean ratings of a cell up to which cells are worked on in rounds
 constexpr int kAhead = 2;                        // long cells: ratings whose rows are in flight ahead of the one being worked on (>= 2)
+constexpr uint64_t kMostBytes = 128;              // per rating that the rounds' layout may take for good (see k_sgd_chain)
 constexpr uint32_t kMaxBlocks = 1024;
 constexpr int64_t kMaxIds = (1ll << 27) - 1024;
 constexpr uint32_t kNoBatch = 0xffffffffu;
@@ -275,9 +276,12 @@ __global__ __launch_bounds__(kSgdBlock) void k_sgd(SgdArgs A, GateArg G, uint32_
 }
 
 // Cells of more than kLongCell ratings on average - a caller that asks for fewer blocks than the library would make, or more
-// than 2^28 ratings - are worked on by a group of F lanes per cell, lane l holding dimension l, its ratings one after the
-// other, straight from the matrices.  (12 bytes per rating where the rounds' layout takes 31 on the benchmark's ratings: memory
-// is what a side task is given least of.  It is the slower of the two: 0.23 us per rating of a cell where a batch of 128 takes
+// than 2^28 ratings -, cells whose layout in rounds would take more than kMostBytes per rating, and tasks whose limit has no room
+// for that layout are worked on by a group of F lanes per cell, lane l holding dimension l, its ratings one after the
+// other, straight from the matrices.  (12 bytes per rating where the rounds' layout takes 29 on the benchmark's ratings: memory
+// is what a side task is given least of.  A batch's record has the stride of the batch with most rows, so many cells with few
+// ratings and one with 128 in 256 rows cost 1040 bytes each: 1024 x 1024 cells of a million ratings 750 MB.  The blocks the
+// library makes by itself leave 25 to 50 bytes per rating.  It is the slower of the two: 0.23 us per rating of a cell where a batch of 128 takes
 // some 10 us in rounds.)  What a rating costs is the latency of fetching its rows.  The loop therefore looks two ratings
 // ahead (and three for the keys): while rating x - 2 is being worked
 // on, the rows of rating x are requested, unless they are held in registers by then (same user / same item as
@@ -711,7 +715,8 @@ int sgd_launch(SgdTask* p, uint32_t seg, uint32_t tile0, uint32_t tile1, hipStre
 #define SGD_HIP(expr) do { hipError_t e__ = (expr); if (e__ != hipSuccess) { p->hip_error = (int)e__; return FR_ERR_HIP; } } while (0)
 #define SGD_NEED(ptr) do { if (!(ptr)) return a->hip_error ? FR_ERR_HIP : FR_ERR_OOM; } while (0)
 
-// The cells' programs: laid out once to learn their sizes, then written.
+// The cells' programs: laid out once to learn their sizes, then written.  FR_ERR_OOM also where they take more than kMostBytes
+// per rating.
 int sgd_lay_out_rounds(SgdTask* p, fr_alloc* a, hipStream_t stream, const uint32_t* cell_ptr, const uint32_t* index, const uint32_t* user_of)
 {
     const uint64_t n = (uint64_t)std::max<int64_t>(1, p->d.n_ratings);
@@ -761,6 +766,7 @@ int sgd_lay_out_rounds(SgdTask* p, fr_alloc* a, hipStream_t stream, const uint32
         if (h.y) p->lds_bytes = std::max<uint32_t>(p->lds_bytes, (h.y + 3) * slots * (uint32_t)sizeof(SlotEntry) + (rows + 1) * row_bytes);
     }
     const uint32_t stride = 1 + (most_rows + 3) / 4;
+    if (((uint64_t)n_batches * stride + total) * sizeof(uint4) > kMostBytes * n) return FR_ERR_OOM;
     uint4* records = static_cast<uint4*>(fr_alloc_device(a, (uint64_t)n_batches * stride * sizeof(uint4)));
     uint4* entries = static_cast<uint4*>(fr_alloc_device(a, std::max<uint64_t>(1, total) * sizeof(uint4)));
     SGD_NEED(records); SGD_NEED(entries);
@@ -876,13 +882,13 @@ int sgd_init(void* user, fr_alloc* a, void* stream_v)
 
     SgdArgs& A = p->args;
     A = SgdArgs{};
-    // Rounds, or where the cells are long, or the task's limit (or the device) has no room for the rounds' layout, one rating
-    // after the other: that needs no more memory than the sort before it did.
+    // Rounds, or where the cells are long, or the rounds' layout is out of proportion to the ratings or has no room in the task's
+    // limit (or on the device), one rating after the other: that needs no more memory than the sort before it did.
     bool rounds = (uint64_t)E <= (uint64_t)kLongCell * n_cells;
     if (rounds) {
         const size_t mark = fr_alloc_mark(a);
         int rc = sgd_lay_out_rounds(p, a, stream, cell_ptr, index, user_of);
-        if (rc != FR_OK && a->oom) {
+        if (rc == FR_ERR_OOM || (rc != FR_OK && a->oom)) {
             fr_alloc_back_to(a, mark);
             A = SgdArgs{};
             p->lds_bytes = 0;

@@ -370,6 +370,28 @@ def test_a_limit_without_room_for_the_rounds_takes_the_small_layout(F, B):
     assert e.value.code == fr.FR_ERR_OOM
 
 
+@pytest.mark.parametrize("dense", [True, False])
+@pytest.mark.parametrize("F", [16, 64])
+def test_sparse_cells_stay_small(F, dense):
+    B, n = 256, 1 << 13
+    rng = np.random.default_rng(5)
+    if dense:
+        # 128 ratings a block: the first 128 users and items, a diagonal, are cell (0, 0) with 256 rows, the longest record
+        # there is; the others are spread over the other cells, half of which have none
+        pairs = {(k, k) for k in range(128)}
+        while len(pairs) < 128 * B:
+            pairs |= set(zip(rng.integers(128, n, 2000).tolist(), rng.integers(128, n, 2000).tolist()))
+        r = _dense(sorted(pairs)[:128 * B], n, n, seed=9)
+    else:
+        r = wl.rmat_ratings(14, 240_000, seed=14)                 # about three a cell
+    print("case", F, r.n_ratings, flush=True)
+    resident, _, P, Q = _limits(r, F, B)(1 << 40)
+    assert resident <= 128 * r.n_ratings + (1 << 16)
+    P0, Q0 = wl.initial_factors(r.n_users, r.n_items, F, seed=4)
+    P32, Q32 = osgd.sgd(r.row_ptr, r.item, r.rating, P0, Q0, 0.02, 0.03, 2, B, ordered_fp32=True)
+    assert _same_bits(P, P32) and _same_bits(Q, Q32)
+
+
 # where the layout in rounds can go wrong: a batch of one rating, full batches and one more (128, 129), one chain (a single
 # user or item), no chain at all (a diagonal: 256 rows and the most LDS), a grid, cells without ratings, and both sides of
 # the mean cell size (256) from which on the ratings are worked on one after the other
