@@ -33,6 +33,9 @@ void* fr_alloc_scratch(fr_alloc* a, size_t bytes);
 size_t fr_alloc_mark(const fr_alloc* a);
 void fr_alloc_back_to(fr_alloc* a, size_t mark);
 
+// Compute units that `stream` may use: those of its mask, if it has one, else all of the current device's.
+uint32_t fr_stream_cus(hipStream_t stream);
+
 // Stage-load kernels (gemm.hip).
 int fr_busywait_launch(uint64_t ns, int wall_clock_khz, hipStream_t stream);
 int fr_alufill_launch(uint64_t ns, int wall_clock_khz, uint32_t workgroups, hipStream_t stream);

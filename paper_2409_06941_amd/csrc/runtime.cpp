@@ -783,6 +783,24 @@ void fr_alloc_release(fr_alloc* a)
     a->used = 0;
 }
 
+uint32_t fr_stream_cus(hipStream_t stream)
+{
+    int device = 0, cus = 0;
+    if (hipGetDevice(&device) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess || cus <= 0) {
+        (void)hipGetLastError();
+        cus = 256;
+    }
+    uint32_t mask[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    if (hipExtStreamGetCUMask(stream, 8, mask) == hipSuccess) {
+        int masked = 0;
+        for (uint32_t w : mask) masked += __builtin_popcount(w);
+        if (masked > 0 && masked < cus) cus = masked;
+    } else {
+        (void)hipGetLastError();          // a stream without a mask of its own
+    }
+    return (uint32_t)cus;
+}
+
 size_t fr_alloc_mark(const fr_alloc* a) { return a->blocks.size(); }
 
 void fr_alloc_back_to(fr_alloc* a, size_t mark)

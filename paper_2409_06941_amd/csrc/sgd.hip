@@ -29,13 +29,13 @@
 
 #include "common.h"
 #include "freeride_device.h"
+#include "sgd_rule.h"
 
 namespace {
 
 constexpr int kSgdBlock = 256;
-constexpr uint32_t kBatch = 128;                 // ratings of a cell that are worked on out of LDS at a time
+constexpr uint32_t kBatch = kSgdBatch;
 constexpr uint32_t kMaxRounds = 2 * kBatch;      // a rating is at most two rounds behind the last one before it
-constexpr uint32_t kLongCell = 2 * kBatch;       // mean ratings of a cell up to which cells are worked on in rounds
 constexpr int kAhead = 2;                        // long cells: ratings whose rows are in flight ahead of the one being worked on (>= 2)
 constexpr uint64_t kMostBytes = 128;              // per rating that the rounds' layout may take for good (see k_sgd_chain)
 constexpr uint32_t kMaxBlocks = 1024;
@@ -275,9 +275,9 @@ __global__ __launch_bounds__(kSgdBlock) void k_sgd(SgdArgs A, GateArg G, uint32_
     fr_gate_done(G.gate, G.slot);
 }
 
-// Cells of more than kLongCell ratings on average - a caller that asks for fewer blocks than the library would make, or more
-// than 2^28 ratings -, cells whose layout in rounds would take more than kMostBytes per rating, and tasks whose limit has no room
-// for that layout are worked on by a group of F lanes per cell, lane l holding dimension l, its ratings one after the
+// Cells of more than kSgdLongCell ratings on average - a caller that asks for fewer blocks than the library would make, or more
+// than 2^28 ratings -, cells of a few ratings and many cells on few compute units (sgd_rounds_pay), cells whose layout in rounds
+// would take more than kMostBytes per rating, and tasks whose limit has no room for that layout are worked on by a group of F lanes per cell, lane l holding dimension l, its ratings one after the
 // other, straight from the matrices.  (12 bytes per rating where the rounds' layout takes 29 on the benchmark's ratings: memory
 // is what a side task is given least of.  A batch's record has the stride of the batch with most rows, so many cells with few
 // ratings and one with 128 in 256 rows cost 1040 bytes each: 1024 x 1024 cells of a million ratings 750 MB.  The blocks the
@@ -880,11 +880,23 @@ int sgd_init(void* user, fr_alloc* a, void* stream_v)
     (void)fr_alloc_free(a, index == index_a ? index_b : index_a);
     if (p->cells[0] != 0 || p->cells[n_cells] != (uint32_t)E) return FR_ERR_ARG;
 
+    p->prefix.assign((size_t)B * B + 1, 0);
+    p->max_cell = 0;
+    p->chain_ratings = 0;
+    uint32_t stratum_max = 0;
+    for (size_t c = 0; c < (size_t)B * B; ++c) {
+        if (p->cells[c + 1] < p->cells[c]) return FR_ERR_ARG;
+        const uint32_t len = p->cells[c + 1] - p->cells[c];
+        p->max_cell = std::max(p->max_cell, len);
+        stratum_max = std::max(stratum_max, len);
+        if ((c + 1) % B == 0) { p->chain_ratings += stratum_max; stratum_max = 0; }
+        p->prefix[c + 1] = p->prefix[c] + ceil_fs_to_ns((unsigned __int128)len * p->d.fs_per_rating);
+    }
     SgdArgs& A = p->args;
     A = SgdArgs{};
-    // Rounds, or where the cells are long, or the rounds' layout is out of proportion to the ratings or has no room in the task's
+    // Rounds, or where they do not pay, or the rounds' layout is out of proportion to the ratings or has no room in the task's
     // limit (or on the device), one rating after the other: that needs no more memory than the sort before it did.
-    bool rounds = (uint64_t)E <= (uint64_t)kLongCell * n_cells;
+    bool rounds = sgd_rounds_pay((uint64_t)E, B, p->chain_ratings, F, fr_stream_cus(stream));
     if (rounds) {
         const size_t mark = fr_alloc_mark(a);
         int rc = sgd_lay_out_rounds(p, a, stream, cell_ptr, index, user_of);
@@ -904,18 +916,6 @@ int sgd_init(void* user, fr_alloc* a, void* stream_v)
         if (rc != FR_OK) return rc;
     }
     (void)fr_alloc_free(a, user_of); (void)fr_alloc_free(a, index);
-    p->prefix.assign((size_t)B * B + 1, 0);
-    p->max_cell = 0;
-    p->chain_ratings = 0;
-    uint32_t stratum_max = 0;
-    for (size_t c = 0; c < (size_t)B * B; ++c) {
-        if (p->cells[c + 1] < p->cells[c]) return FR_ERR_ARG;
-        const uint32_t len = p->cells[c + 1] - p->cells[c];
-        p->max_cell = std::max(p->max_cell, len);
-        stratum_max = std::max(stratum_max, len);
-        if ((c + 1) % B == 0) { p->chain_ratings += stratum_max; stratum_max = 0; }
-        p->prefix[c + 1] = p->prefix[c] + ceil_fs_to_ns((unsigned __int128)len * p->d.fs_per_rating);
-    }
     A.P = p->d.P; A.Q = p->d.Q;
     A.gamma = p->d.gamma; A.gl = p->d.gamma * p->d.lambda;
     p->footprint_after = fr_alloc_used(a);

@@ -1,0 +1,59 @@
+"""The rules by which the library chooses among its kernels, compiled for the host: which side of each measured line a call
+falls on, over the sizes on both sides of it."""
+import ctypes
+import os
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2409_06941_amd", "csrc")
+
+
+def _compile(tmp_path_factory, name, code):
+    d = tmp_path_factory.mktemp(name)
+    src, lib = d / (name + ".cpp"), d / (name + ".so")
+    src.write_text(code)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-shared", "-fPIC", "-pthread", "-I", CSRC, str(src), "-o", str(lib)], check=True)
+    return ctypes.CDLL(str(lib))
+
+
+@pytest.fixture(scope="module")
+def sgd(tmp_path_factory):
+    L = _compile(tmp_path_factory, "sgd_rule", '''#include "sgd_rule.h"
+extern "C" int pay(uint64_t ratings, uint32_t B, uint64_t chain, int F, uint32_t cus) { return sgd_rounds_pay(ratings, B, chain, F, cus); }
+''')
+    L.pay.argtypes = [ctypes.c_uint64, ctypes.c_uint32, ctypes.c_uint64, ctypes.c_int, ctypes.c_uint32]
+    return lambda ratings, B, chain, F, cus: bool(L.pay(ratings, B, int(chain * B), F, cus))
+
+
+# (ratings, blocks, mean over the strata of their largest cell, factors, compute units, ms one after the other, ms in rounds)
+MEASURED = [
+    (16_253, 1024, 2.5, 64, 256, 2.45, 4.01), (125_091, 1024, 4.5, 16, 256, 2.68, 3.69), (1_043_634, 1024, 6.6, 64, 256, 4.18, 4.77),
+    (3_108_417, 1024, 14.5, 64, 256, 6.79, 5.75), (2_079_384, 1024, 10.4, 16, 256, 5.42, 4.56), (3_108_417, 1024, 14.5, 16, 256, 6.77, 4.85),
+    (16_084_561, 512, 131.9, 64, 256, 25.3, 8.46), (16_084_561, 512, 131.9, 64, 32, 29.7, 22.0), (16_084_561, 512, 131.9, 64, 16, 34.8, 38.9),
+    (16_084_561, 512, 131.9, 64, 8, 56.4, 72.5), (16_084_561, 512, 131.9, 16, 16, 27.6, 12.3), (1_801_150, 1024, 14.2, 64, 32, 7.32, 22.3),
+    (1_801_150, 1024, 14.2, 16, 32, 6.42, 12.0), (1_801_150, 256, 61.3, 64, 32, 5.97, 3.28), (1_801_150, 256, 61.3, 64, 8, 7.67, 8.93),
+    (1_801_150, 128, 170.8, 64, 8, 8.67, 6.97), (255_238, 64, 90.5, 64, 256, 1.94, 0.594), (255_238, 64, 90.5, 16, 16, 1.91, 0.492),
+    (128_491_641, 1024, 272.0, 64, 64, 125.2, 79.7), (128_491_641, 1024, 272.0, 32, 32, 128.7, 67.2), (16_084_561, 512, 131.9, 64, 24, 31.1, 27.9),
+    (1_801_150, 1024, 14.2, 32, 32, 6.98, 17.7), (16_084_561, 512, 131.9, 32, 8, 35.5, 32.8), (1_801_150, 256, 61.3, 32, 16, 6.20, 3.68),
+    (293, 16, 3.4, 16, 256, 0.047, 0.053), (1139, 16, 10.3, 64, 256, 0.077, 0.064), (39, 2, 10.5, 64, 256, 0.0097, 0.0079),
+]
+
+
+def test_sgd_takes_the_faster_side_of_every_measured_size(sgd):
+    for ratings, B, chain, F, cus, in_a_row, rounds in MEASURED:
+        assert sgd(ratings, B, chain, F, cus) == (rounds < in_a_row), (ratings, B, F, cus)
+
+
+def test_sgd_blocks_the_library_makes_are_worked_on_in_rounds(sgd):
+    for ratings in (40, 500, 13_920, 132_749, 922_110, 16_084_561, 1 << 27):
+        B = 1024
+        while B > 1 and ratings // (B * B) < 32:
+            B //= 2
+        mean = ratings / B / B
+        for F in (16, 32, 64):
+            for cus in (64, 128, 256):
+                if mean <= 256:
+                    assert sgd(ratings, B, 1.2 * mean, F, cus), (ratings, F, cus)
+    assert not sgd(257, 1, 257, 16, 256)                        # beyond 256 ratings a cell on average
+    assert not sgd(0, 4, 0, 16, 256) and not sgd(0, 1, 0, 64, 256)
