@@ -58,13 +58,20 @@ static_assert(sizeof(SlotEntry) == 16, "read as one 16-byte word");
 struct SgdArgs {
     const uint4* records;        // the first batch of cell s * B + a at that index, then the further batches of long cells
     const uint4* entries;
+    float* P;
+    float* Q;
     uint32_t stride;             // 16-byte words of a record
-    const uint64_t* keys;        // long cells: user << 32 | item and rating in the order of the cells, and the cells' starts
+    float gamma, gl;             // gl = gamma * lambda, rounded once
+};
+
+// (arguments of its own: in one struct with those above they lie behind a cache line's end, and a launch takes 0.15 us more)
+struct ChainArgs {
+    const uint64_t* keys;        // user << 32 | item and rating in the order of the cells, and the cells' starts
     const float* rating;
     const uint32_t* cell_ptr;
     float* P;
     float* Q;
-    float gamma, gl;             // gl = gamma * lambda, rounded once
+    float gamma, gl;
 };
 
 struct GateArg {
@@ -307,7 +314,7 @@ __device__ __forceinline__ float chain_sum(float t)
 }
 
 template <int F>
-__global__ __launch_bounds__(kSgdBlock) void k_sgd_chain(SgdArgs A, GateArg G, uint32_t cell0, uint32_t n_cells)
+__global__ __launch_bounds__(kSgdBlock) void k_sgd_chain(ChainArgs A, GateArg G, uint32_t cell0, uint32_t n_cells)
 {
     if (!fr_gate_admit(G.gate, G.slot, G.need_ticks)) return;
     const uint32_t g = (blockIdx.x * kSgdBlock + threadIdx.x) / F, l = threadIdx.x % F;
@@ -682,6 +689,7 @@ struct SgdTask {
     uint64_t chain_ratings = 0;           // sum over the strata of their largest cell
     uint64_t footprint_after = 0, footprint_peak = 0;
     SgdArgs args{};
+    ChainArgs chain{};                    // keys: NULL if the ratings are worked on in rounds
     bool inited = false, registered = false;
     fr_alloc own;                         // used by the standalone run only
     int hip_error = 0;
@@ -698,9 +706,9 @@ int sgd_launch(SgdTask* p, uint32_t seg, uint32_t tile0, uint32_t tile1, hipStre
     auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(n), dim3(kSgdBlock), p->lds_bytes, stream, p->args, G, cell0); };
     auto go_chain = [&](auto kernel) {
         const unsigned grid = (unsigned)(((uint64_t)n * F + kSgdBlock - 1) / kSgdBlock);
-        hipLaunchKernelGGL(kernel, dim3(grid), dim3(kSgdBlock), 0, stream, p->args, G, cell0, n);
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(kSgdBlock), 0, stream, p->chain, G, cell0, n);
     };
-    if (p->args.keys) {
+    if (p->chain.keys) {
         if (F == 64) go_chain(k_sgd_chain<64>);
         else if (F == 32) go_chain(k_sgd_chain<32>);
         else go_chain(k_sgd_chain<16>);
@@ -791,7 +799,7 @@ int sgd_lay_out_chain(SgdTask* p, fr_alloc* a, hipStream_t stream, const uint32_
     if (E > 0)
         hipLaunchKernelGGL(k_sgd_stream, dim3((unsigned)((E + 255) / 256)), dim3(256), 0, stream, E, index, user_of, p->d.item, p->d.rating, keys, sorted);
     SGD_HIP(hipStreamSynchronize(stream));
-    p->args.keys = keys; p->args.rating = sorted; p->args.cell_ptr = cell_ptr;
+    p->chain.keys = keys; p->chain.rating = sorted; p->chain.cell_ptr = cell_ptr;
     return FR_OK;
 }
 
@@ -892,8 +900,8 @@ int sgd_init(void* user, fr_alloc* a, void* stream_v)
         if ((c + 1) % B == 0) { p->chain_ratings += stratum_max; stratum_max = 0; }
         p->prefix[c + 1] = p->prefix[c] + ceil_fs_to_ns((unsigned __int128)len * p->d.fs_per_rating);
     }
-    SgdArgs& A = p->args;
-    A = SgdArgs{};
+    p->args = SgdArgs{};
+    p->chain = ChainArgs{};
     // Rounds, or where they do not pay, or the rounds' layout is out of proportion to the ratings or has no room in the task's
     // limit (or on the device), one rating after the other: that needs no more memory than the sort before it did.
     bool rounds = sgd_rounds_pay((uint64_t)E, B, p->chain_ratings, F, fr_stream_cus(stream));
@@ -902,7 +910,6 @@ int sgd_init(void* user, fr_alloc* a, void* stream_v)
         int rc = sgd_lay_out_rounds(p, a, stream, cell_ptr, index, user_of);
         if (rc == FR_ERR_OOM || (rc != FR_OK && a->oom)) {
             fr_alloc_back_to(a, mark);
-            A = SgdArgs{};
             p->lds_bytes = 0;
             rounds = false;
         } else if (rc != FR_OK) {
@@ -916,8 +923,9 @@ int sgd_init(void* user, fr_alloc* a, void* stream_v)
         if (rc != FR_OK) return rc;
     }
     (void)fr_alloc_free(a, user_of); (void)fr_alloc_free(a, index);
-    A.P = p->d.P; A.Q = p->d.Q;
-    A.gamma = p->d.gamma; A.gl = p->d.gamma * p->d.lambda;
+    auto shared = [&](auto& A) { A.P = p->d.P; A.Q = p->d.Q; A.gamma = p->d.gamma; A.gl = p->d.gamma * p->d.lambda; };
+    shared(p->args);
+    shared(p->chain);
     p->footprint_after = fr_alloc_used(a);
     p->footprint_peak = fr_alloc_peak(a);
     p->run = 0; p->seg = 0; p->tile = 0;
