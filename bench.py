@@ -27,7 +27,7 @@ HBM_PEAK_GBS = 8000.0        # MI355X HBM3E, published
 PARITY_TOL_ABS = 1e-5        # max |gpu - oracle| (fp32 ranks against the fp64 oracle)
 PARITY_TOL_REL = 1e-4        # the same relative to the rank, over ranks above 1/V
 KERNEL_SOURCES = ("paper_2409_06941_amd/csrc/pagerank.hip", "paper_2409_06941_amd/csrc/pagerank_prep.hip",
-                  "paper_2409_06941_amd/csrc/pr_layout.h")
+                  "paper_2409_06941_amd/csrc/pr_layout.h", "paper_2409_06941_amd/csrc/pr_rules.h")
 
 
 def log(*a):

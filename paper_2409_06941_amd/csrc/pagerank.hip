@@ -26,6 +26,7 @@
 #include <cstring>
 #include <mutex>
 #include <new>
+#include <type_traits>
 
 #include "freeride_device.h"
 #include "pr_layout.h"
@@ -370,12 +371,8 @@ __global__ void k_clear_sched(uint32_t* sched)
 // The groups of all bins of a batch are numbered consecutively (prefix sums in LDS) and dealt to the threads, so bins of
 // any length keep all lanes busy; a thread finds a group's bin by binary search, and the loads of the groups a thread has
 // in flight are issued before the first is used.
-// Groups of four, dealt to the wavefronts in runs of up to kAhead * 64 lane by lane (a wavefront's store is 1 KB in one
-// piece, and the next 64 groups are mostly in the same bin), are for the large kernel and for launches that hand out
-// tiles, where the sweep is bound by its stores: uniform graph of 2^23 vertices / 2^28 edges on 64 units 1640 -> 1442 us
-// an iteration, skewed one of 2^24 / 2^28 362 -> 345.  One round of small tiles is bound by latency and has shorter bins;
-// groups of eight dealt round-robin search half as often (10^6 / 10^7: 30.4 us, groups of four 31.4; 3 x 10^6 / 6 x 10^7 on
-// 128 units: 123.0 and 125.9).
+// Groups of four are dealt to the wavefronts in runs of up to kAhead * 64 lane by lane (a wavefront's store is 1 KB in one
+// piece, and the next 64 groups are mostly in the same bin), groups of eight round-robin; which: scatter_in_runs.
 constexpr uint32_t kDescBatch = 1024;       // bins per batch
 
 // Exclusive prefix sums of one value per thread over the workgroup (kScatterBlock threads); out[i] = sum of the
@@ -467,9 +464,10 @@ __device__ __forceinline__ void emit_group(const GroupRef& ref, const uint2* des
 // (two workgroups of the small size share a CU: 8 wavefronts per SIMD, hence at most 64 registers per lane)
 // kPacked: some tile has more than one piece (kept apart: the loop over pieces costs the small size registers it
 // does not have).
+// kRuns: groups of four in runs (see above).
 // kDynamic: the launch has more tiles than workgroups (else a workgroup's one tile is all it does, and the code of
 // the hand-out, which costs registers too, is left out).
-template <uint32_t kSrcPerPart, bool kPacked, bool kDynamic>
+template <uint32_t kSrcPerPart, bool kPacked, bool kDynamic, bool kRuns>
 __global__ __launch_bounds__(kScatterBlock) __attribute__((amdgpu_waves_per_eu(kSrcPerPart == kSrcSmall ? 8 : 4, kSrcPerPart == kSrcSmall ? 8 : 4)))
 void k_scatter(DevArgs A, GateArg G, uint32_t tile0, uint32_t n_tiles, int parity, int first)
 {
@@ -487,7 +485,6 @@ void k_scatter(DevArgs A, GateArg G, uint32_t tile0, uint32_t n_tiles, int parit
         const float D = dangling_total(A.dpart + (size_t)parity * A.n_dpart, A.n_dpart);
         base = (1.0f - A.damping) / (float)A.V + A.damping * D / (float)A.V;
     }
-    constexpr bool kRuns = kDynamic || kSrcPerPart == kSrcLarge;
     constexpr uint32_t kGroup = kRuns ? 4 : 8;
     // rows a thread reads per round while the slice is filled (the small size has 64 registers per lane)
     constexpr int kFillRound = kSrcPerPart == kSrcSmall ? 4 : 16;
@@ -946,13 +943,15 @@ int pr_launch(PrTask* p, uint32_t g, uint32_t tile0, uint32_t tile1, hipStream_t
             const uint32_t grid = std::min(n, p->L.scatter_slots);
             const bool packed = p->L.scatter_packed, dynamic = n > grid;
             auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(grid), dim3(kScatterBlock), 0, stream, args, G, tile0, n, parity, first); };
-            if (p->L.src_per_part == kSrcLarge) {
-                if (packed) { if (dynamic) go(k_scatter<kSrcLarge, true, true>); else go(k_scatter<kSrcLarge, true, false>); }
-                else { if (dynamic) go(k_scatter<kSrcLarge, false, true>); else go(k_scatter<kSrcLarge, false, false>); }
-            } else {
-                if (packed) { if (dynamic) go(k_scatter<kSrcSmall, true, true>); else go(k_scatter<kSrcSmall, true, false>); }
-                else { if (dynamic) go(k_scatter<kSrcSmall, false, true>); else go(k_scatter<kSrcSmall, false, false>); }
-            }
+            const bool runs = scatter_in_runs(p->L.src_per_part, p->d.n_vertices, p->L.cus, dynamic);
+            auto go_as = [&](auto packs) {
+                constexpr bool kPacked = decltype(packs)::value;
+                if (p->L.src_per_part == kSrcSmall) { if (runs) go(k_scatter<kSrcSmall, kPacked, true, true>); else go(k_scatter<kSrcSmall, kPacked, false, false>); }
+                else if (runs) { if (dynamic) go(k_scatter<kSrcLarge, kPacked, true, true>); else go(k_scatter<kSrcLarge, kPacked, false, true>); }
+                else { if (dynamic) go(k_scatter<kSrcLarge, kPacked, true, false>); else go(k_scatter<kSrcLarge, kPacked, false, false>); }
+            };
+            if (packed) go_as(std::true_type{});
+            else go_as(std::false_type{});
         } else {
             const int parity = (int)(k & 1u), final_pass = (k + 1 == K) ? 1 : 0;
             const uint32_t grid = std::min(n, p->L.gather_slots);

@@ -701,6 +701,7 @@ int pr_build_layout(PrLayout* L, int64_t V, int64_t E, const int32_t* row_ptr, c
             L->gt_edges.push_back(esum);
         }
     }
+    L->cus = cus;
     L->gather_slots = cus * (rows_per_part == kRowsSmall ? 2u : 1u);
     L->scatter_slots = cus * (src_per_part == kSrcSmall ? 2u : 1u);
     L->n_pieces = (uint32_t)L->gp.size();

@@ -50,11 +50,8 @@
 #include <vector>
 
 #include "common.h"
+#include "pr_rules.h"
 
-constexpr uint32_t kRowsSmall = 8192, kRowsLarge = 16384;   // destination rows per range (8 B each in LDS)
-constexpr uint32_t kSrcSmall = 16384, kSrcLarge = 32768;    // source vertices per scatter partition (4 B each in LDS)
-constexpr int64_t kLargeRowsFrom = int64_t(1) << 22;        // vertex counts from which the large sizes are used
-constexpr int64_t kLargeSrcFrom = int64_t(1) << 24;
 constexpr uint32_t kIdChunk = 512;           // ids per wavefront step (8 per lane, 64 apart)
 constexpr uint32_t kStartWords = 12;         // 64-bit words of a chunk's message-start record
 constexpr int kKeyLocalBits = 15;            // sort key = range << 46 | source << 15 | local row
@@ -121,6 +118,7 @@ struct PrLayout {
     uint32_t n_pieces = 0;           // gather pieces: runs of edges of one range
     uint32_t n_spieces = 0;          // scatter pieces: intervals of sources
     uint32_t n_gather = 0, n_scatter = 0;   // tiles (= pieces)
+    uint32_t cus = 0;                               // compute units the sweeps are cut for
     uint32_t gather_slots = 0, scatter_slots = 0;   // workgroups of a sweep that run side by side
     uint32_t n_merged = 0;           // ranges cut into several gather pieces
     uint32_t n_partials = 0;         // gather pieces of merged ranges = rows of partial sums

@@ -116,6 +116,31 @@ def test_small_sweeps_have_a_workgroup_per_compute_unit(n, edges, tiles):
     assert (np.abs(bits[0][big] - want[big]) / want[big]).max() <= 1e-4
 
 
+# the large scatter kernel on few units, where its groups are of eight: one round of tiles, steps, and tiles handed out
+@pytest.mark.parametrize("V,E,rows,cus", [(120_007, 1_500_001, 16384, 64), (400_009, 14_000_001, 8192, 8)])
+def test_large_source_slices_on_few_units(V, E, rows, cus):
+    rng = np.random.default_rng(cus)
+    g = graphs.csr_from_edges(V, np.arange(E) % V, rng.integers(0, V, E))
+    rp, col, od = _dev(g.row_ptr, torch.int32), _dev(g.col, torch.int32), _dev(g.out_degree, torch.int32)
+    ctx = fr.Context(device_id=0, cu_count=cus)
+    bits = []
+    for step in (0, 3):
+        print("case V=%d E=%d units %d tiles per launch %d" % (V, E, cus, step), flush=True)
+        ranks = torch.zeros(V, dtype=torch.float32, device="cuda")
+        torch.cuda.synchronize()
+        t = fr.PageRankTask(V, E, rp, col, od, ranks, iterations=4, rows_per_partition=rows, sources_per_partition=32768)
+        t.fr_pagerank_run_standalone(0, ctx.fr_side_stream(), step)
+        info = t.fr_pagerank_info()
+        t.fr_pagerank_destroy()
+        bits.append(ranks.cpu().numpy())
+    ctx.fr_destroy()
+    assert info.scatter_slots == cus and (info.scatter_tiles > cus) == (cus == 8), (info.scatter_tiles, info.scatter_slots)
+    assert np.array_equal(bits[0].view(np.uint32), bits[1].view(np.uint32))
+    want = pagerank(g.row_ptr, g.col, g.out_degree, 0.85, 4)
+    assert np.abs(bits[0].astype(np.float64) - want).max() <= TOL
+    assert (np.abs(bits[0] - want) / want).max() <= 1e-4
+
+
 # the layout is built in runs of 2048 keys and chunks of 512 edges, four chunks a workgroup
 @pytest.mark.parametrize("edges", [1, 511, 513, 2047, 2048, 2049, 4097])
 @pytest.mark.parametrize("n", [2, 700, 9000])

@@ -57,3 +57,26 @@ def test_sgd_blocks_the_library_makes_are_worked_on_in_rounds(sgd):
                     assert sgd(ratings, B, 1.2 * mean, F, cus), (ratings, F, cus)
     assert not sgd(257, 1, 257, 16, 256)                        # beyond 256 ratings a cell on average
     assert not sgd(0, 4, 0, 16, 256) and not sgd(0, 1, 0, 64, 256)
+
+
+@pytest.fixture(scope="module")
+def pr(tmp_path_factory):
+    L = _compile(tmp_path_factory, "pr_rules", '''#include "pr_rules.h"
+extern "C" int runs(uint32_t src, int64_t V, uint32_t cus, int hands_out) { return scatter_in_runs(src, V, cus, hands_out != 0); }
+''')
+    L.runs.argtypes = [ctypes.c_uint32, ctypes.c_int64, ctypes.c_uint32, ctypes.c_int]
+    return L
+
+
+# (sources a partition, vertices, compute units, more tiles than workgroups, us an iteration with groups of eight, of four)
+SCATTER_MEASURED = [
+    (16384, 1 << 23, 64, 1, 1640, 1442), (16384, 1_000_003, 256, 0, 30.4, 31.4), (16384, 3_000_000, 128, 0, 123.0, 125.9),
+    (32768, 1 << 24, 64, 1, 1815, 1968), (32768, 1 << 24, 64, 0, 326, 337), (32768, 1 << 25, 64, 0, 414, 439), (32768, 1 << 25, 64, 1, 932, 987),
+    (32768, 1 << 24, 256, 0, 367, 349), (32768, 1 << 24, 256, 1, 816, 752), (32768, 1 << 24, 128, 1, 1142, 1105), (32768, 1 << 24, 128, 0, 534, 519),
+    (32768, 3_000_000, 64, 0, 177, 187), (32768, 3_000_000, 256, 0, 83.0, 85.7), (32768, 1_000_003, 64, 0, 46.4, 48.6),
+]
+
+
+def test_scatter_groups_are_the_faster_ones_of_every_measured_size(pr):
+    for src, V, cus, hands_out, eight, four in SCATTER_MEASURED:
+        assert bool(pr.runs(src, V, cus, hands_out)) == (four < eight), (src, V, cus, hands_out)
