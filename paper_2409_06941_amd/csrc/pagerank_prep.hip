@@ -636,7 +636,7 @@ int pr_build_layout(PrLayout* L, int64_t V, int64_t E, const int32_t* row_ptr, c
             total += w[j];
             heaviest = std::max(heaviest, w[j]);
         }
-        const bool alone = rows_per_part == kRowsLarge || (2 * Qe <= cus && total <= (uint64_t)cus * cus * kGatherAloneShare);   // one workgroup a unit
+        const bool alone = gather_alone(rows_per_part, Qe, total, cus);                // one workgroup a unit
         const uint64_t slots = (uint64_t)cus * (alone ? 1 : 2);
         const uint64_t share = (total + slots - 1) / slots;
         const uint64_t fine = share >= kGatherFineShare ? 2 : 1;
@@ -832,7 +832,7 @@ int pr_build_layout(PrLayout* L, int64_t V, int64_t E, const int32_t* row_ptr, c
         };
         const uint64_t all = weight_before((uint64_t)V);
         const uint64_t least = std::max<uint64_t>(kMinTileMessages * kScatterMessageWeight, (uint64_t)((double)kPieceBalance * std::sqrt((double)all)));
-        const bool alone = src_per_part == kSrcLarge || all <= (uint64_t)cus * cus * kScatterAloneShare;            // one workgroup a unit
+        const bool alone = scatter_alone(src_per_part, all, cus);                      // one workgroup a unit
         const uint64_t slots = (uint64_t)cus * (alone ? 1 : 2);
         const uint64_t share = (all + slots - 1) / slots;
         const uint64_t fine = share >= kScatterFineShare ? 2 : 1;

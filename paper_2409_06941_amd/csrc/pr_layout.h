@@ -74,15 +74,6 @@ constexpr uint64_t kScatterMessageWeight = 1, kScatterRowWeight = 1, kScatterFix
 // 2^26 / 2^30 gains 20 % and 24 %, 2^22 / 2^26 loses in both; three, four or six pieces per slot are no better than two)
 constexpr uint64_t kGatherFineShare = 2000000, kScatterFineShare = 1000000;
 
-// The small kernels fit twice on a compute unit, but a sweep of a small graph is faster with one workgroup each: with
-// more, some units hold two and take twice as long as the others, and every piece of a merged range is one more row of
-// partial sums to write and to add up.  Gather: while there are two units or more per range (else light ranges share
-// workgroups badly: 10^6 vertices / 10^7 edges on 64 units 50.5 -> 58.0 us an iteration) and a unit's share is at most
-// kGatherAloneShare per unit (256 units: 10^6 vertices / 10^7 edges 34.9 -> 30.8 us, 3.8 x 10^7 edges 59.8 -> 56.2; on
-// few units each has more bandwidth to itself and needs two workgroups to use it: 64 units, 400 000 / 10^7 edges 47.5 ->
-// 51.0).  Scatter: up to kScatterAloneShare per unit (0.3 to 1.3 us of 25 to 40; beyond it one workgroup cannot keep a unit's
-// share of the bandwidth busy: 8 M vertices / 32 M edges 55.5 -> 63.0, 3 M / 60 M 83.9 -> 94.7).
-constexpr uint64_t kGatherAloneShare = 1600, kScatterAloneShare = 192;
 // Pieces of a range weigh at least kMergeBalance x sqrt(weight of the heaviest range): a row of a range cut into n pieces
 // costs the scatter sweep n loads, a piece costs the gather sweep its own weight, and the sum of both is least where
 // the pieces weigh as the root of the range (2^18 vertices / 2^22 edges: 162 pieces 22.8 us, 256 24.9, 313 28.9).

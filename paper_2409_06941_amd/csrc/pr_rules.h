@@ -23,4 +23,30 @@ inline bool scatter_in_runs(uint32_t src_per_part, int64_t V, uint32_t cus, bool
     return src_per_part == kSrcSmall ? hands_out : V >= kLargeSrcFrom && cus >= kRunsFromUnits;
 }
 
+// The small kernels fit twice on a compute unit, but a sweep of a small graph is faster with one workgroup each: with
+// more, some units hold two and take twice as long as the others, and every piece of a merged range is one more row of
+// partial sums to write and to add up.  Gather: while there are two units or more per range (else light ranges share
+// workgroups badly: 10^6 vertices / 10^7 edges on 64 units 50.5 -> 58.0 us an iteration) and a unit's share is at most
+// kGatherAloneShare per unit (256 units: 10^6 vertices / 10^7 edges 34.9 -> 30.8 us, 3.8 x 10^7 edges 59.8 -> 56.2; on
+// few units each has more bandwidth to itself and needs two workgroups to use it: 64 units, 400 000 / 10^7 edges 47.5 ->
+// 51.0).
+constexpr uint64_t kGatherAloneShare = 1600;
+inline bool gather_alone(uint32_t rows_per_part, uint32_t Qe, uint64_t total, uint32_t cus)
+{
+    return rows_per_part == kRowsLarge || (2 * Qe <= cus && total <= (uint64_t)cus * cus * kGatherAloneShare);
+}
+
+// Scatter: up to kScatterAloneShare (messages and values read) a unit per unit, or kScatterAloneLeast a unit on fewer than 171;
+// beyond it one workgroup cannot keep a unit's share of the bandwidth busy.  us an iteration, two a unit -> one, at these
+// thousands a unit:
+//   16 units: 9 18.1 -> 16.8, 22 27.5 -> 27.0, 53 64.8 -> 67.0, 84 40.0 -> 41.0   32: 9 18.6 -> 17.4, 22 24.8 -> 23.8, 72 116.7 -> 123.0
+//   64: 13 21.2 -> 19.6, 25 23.6 -> 22.0 and 30.5 -> 31.1, 44 69.8 -> 76.2, 72 35.6 -> 37.0
+//   128: 13 25.1 -> 23.2, 27 39.4 -> 38.0, 58 47.8 -> 57.5, 98 48.0 -> 50.0   256: 17 33.5 -> 32.1, 29 39.6 -> 37.5, 49 41.8 -> 40.4, 72 55.5 -> 63.0
+constexpr uint64_t kScatterAloneShare = 192, kScatterAloneLeast = 32768;
+inline bool scatter_alone(uint32_t src_per_part, uint64_t all, uint32_t cus)
+{
+    const uint64_t share = cus * kScatterAloneShare > kScatterAloneLeast ? cus * kScatterAloneShare : kScatterAloneLeast;
+    return src_per_part == kSrcLarge || all <= cus * share;
+}
+
 #endif

@@ -63,8 +63,10 @@ def test_sgd_blocks_the_library_makes_are_worked_on_in_rounds(sgd):
 def pr(tmp_path_factory):
     L = _compile(tmp_path_factory, "pr_rules", '''#include "pr_rules.h"
 extern "C" int runs(uint32_t src, int64_t V, uint32_t cus, int hands_out) { return scatter_in_runs(src, V, cus, hands_out != 0); }
+extern "C" int s_alone(uint32_t src, uint64_t all, uint32_t cus) { return scatter_alone(src, all, cus); }
 ''')
     L.runs.argtypes = [ctypes.c_uint32, ctypes.c_int64, ctypes.c_uint32, ctypes.c_int]
+    L.s_alone.argtypes = [ctypes.c_uint32, ctypes.c_uint64, ctypes.c_uint32]
     return L
 
 
@@ -80,3 +82,16 @@ SCATTER_MEASURED = [
 def test_scatter_groups_are_the_faster_ones_of_every_measured_size(pr):
     for src, V, cus, hands_out, eight, four in SCATTER_MEASURED:
         assert bool(pr.runs(src, V, cus, hands_out)) == (four < eight), (src, V, cus, hands_out)
+
+
+# (thousands of messages and values a compute unit, units, us an iteration with two workgroups a unit, with one)
+SCATTER_ALONE = [(9, 16, 18.1, 16.8), (22, 16, 27.5, 27.0), (53, 16, 64.8, 67.0), (84, 16, 40.0, 41.0), (9, 32, 18.6, 17.4), (22, 32, 24.8, 23.8),
+                 (72, 32, 116.7, 123.0), (13, 64, 21.2, 19.6), (25, 64, 23.6, 22.0), (44, 64, 69.8, 76.2), (72, 64, 35.6, 37.0), (13, 128, 25.1, 23.2),
+                 (27, 128, 39.4, 38.0), (58, 128, 47.8, 57.5), (98, 128, 48.0, 50.0), (17, 256, 33.5, 32.1), (29, 256, 39.6, 37.5), (49, 256, 41.8, 40.4),
+                 (72, 256, 55.5, 63.0)]
+
+
+def test_scatter_workgroups_a_unit_are_the_faster_number(pr):
+    for share, cus, two, one in SCATTER_ALONE:
+        assert bool(pr.s_alone(16384, share * 1000 * cus, cus)) == (one < two), (share, cus)
+    assert pr.s_alone(32768, 1 << 40, 16)                       # the large kernel fits once
