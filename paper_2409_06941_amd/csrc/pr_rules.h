@@ -26,14 +26,16 @@ inline bool scatter_in_runs(uint32_t src_per_part, int64_t V, uint32_t cus, bool
 // The small kernels fit twice on a compute unit, but a sweep of a small graph is faster with one workgroup each: with
 // more, some units hold two and take twice as long as the others, and every piece of a merged range is one more row of
 // partial sums to write and to add up.  Gather: while there are two units or more per range (else light ranges share
-// workgroups badly: 10^6 vertices / 10^7 edges on 64 units 50.5 -> 58.0 us an iteration) and a unit's share is at most
-// kGatherAloneShare per unit (256 units: 10^6 vertices / 10^7 edges 34.9 -> 30.8 us, 3.8 x 10^7 edges 59.8 -> 56.2; on
-// few units each has more bandwidth to itself and needs two workgroups to use it: 64 units, 400 000 / 10^7 edges 47.5 ->
-// 51.0).
+// workgroups badly: 10^6 vertices / 10^7 edges on 64 units 50.5 -> 58.0 us an iteration) and a unit's share of the weight
+// (two an edge, and some for repeated ones) is at most kGatherAloneShare per unit, or that of 64 units on fewer.  (On few units each
+// has more bandwidth to itself and needs two workgroups to use it; but a sweep that makes fewer than two tiles of the least
+// size a unit leaves some units with two and some with one.)  us an iteration, two a unit -> one, at these thousands of edges a unit:
+//   16 units: 31 22.2 -> 19.6, 63 26.9 -> 28.8, 125 37.6 -> 42.9   32: 16 23.4 -> 18.6, 31 24.8 -> 21.3, 63 28.6 -> 29.3
+//   64: 31 26.8 -> 21.8, 66 35.6 -> 39.4   128: 33 28.4 -> 23.2, 78 39.1 -> 38.4   256: 39 34.9 -> 30.8, 63 43.5 -> 37.0, 148 59.8 -> 56.2
 constexpr uint64_t kGatherAloneShare = 1600;
 inline bool gather_alone(uint32_t rows_per_part, uint32_t Qe, uint64_t total, uint32_t cus)
 {
-    return rows_per_part == kRowsLarge || (2 * Qe <= cus && total <= (uint64_t)cus * cus * kGatherAloneShare);
+    return rows_per_part == kRowsLarge || (2 * Qe <= cus && total <= (uint64_t)cus * (cus < 64 ? 64 : cus) * kGatherAloneShare);
 }
 
 // Scatter: up to kScatterAloneShare (messages and values read) a unit per unit, or kScatterAloneLeast a unit on fewer than 171;

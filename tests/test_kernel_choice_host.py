@@ -63,9 +63,11 @@ def test_sgd_blocks_the_library_makes_are_worked_on_in_rounds(sgd):
 def pr(tmp_path_factory):
     L = _compile(tmp_path_factory, "pr_rules", '''#include "pr_rules.h"
 extern "C" int runs(uint32_t src, int64_t V, uint32_t cus, int hands_out) { return scatter_in_runs(src, V, cus, hands_out != 0); }
+extern "C" int g_alone(uint32_t rows, uint32_t Qe, uint64_t total, uint32_t cus) { return gather_alone(rows, Qe, total, cus); }
 extern "C" int s_alone(uint32_t src, uint64_t all, uint32_t cus) { return scatter_alone(src, all, cus); }
 ''')
     L.runs.argtypes = [ctypes.c_uint32, ctypes.c_int64, ctypes.c_uint32, ctypes.c_int]
+    L.g_alone.argtypes = [ctypes.c_uint32, ctypes.c_uint32, ctypes.c_uint64, ctypes.c_uint32]
     L.s_alone.argtypes = [ctypes.c_uint32, ctypes.c_uint64, ctypes.c_uint32]
     return L
 
@@ -95,3 +97,16 @@ def test_scatter_workgroups_a_unit_are_the_faster_number(pr):
     for share, cus, two, one in SCATTER_ALONE:
         assert bool(pr.s_alone(16384, share * 1000 * cus, cus)) == (one < two), (share, cus)
     assert pr.s_alone(32768, 1 << 40, 16)                       # the large kernel fits once
+
+
+# (thousands of weight a compute unit, ranges with edges, units, us an iteration with two workgroups a unit, with one)
+GATHER_ALONE = [(65, 2, 16, 22.2, 19.6), (130, 8, 16, 26.9, 28.8), (256, 8, 16, 37.6, 42.9), (33, 2, 32, 23.4, 18.6), (65, 8, 32, 24.8, 21.3),
+                (130, 13, 32, 28.6, 29.3), (65, 13, 64, 26.8, 21.8), (137, 32, 64, 35.6, 39.4), (68, 32, 128, 28.4, 23.2), (164, 64, 128, 39.1, 38.4),
+                (80, 64, 256, 34.9, 30.8), (130, 49, 256, 43.5, 37.0), (330, 64, 64, 50.5, 58.0), (260, 49, 128, 47.8, 53.4)]
+
+
+def test_gather_workgroups_a_unit_are_the_faster_number(pr):
+    for share, Qe, cus, two, one in GATHER_ALONE:
+        assert bool(pr.g_alone(8192, Qe, share * 1000 * cus, cus)) == (one < two), (share, cus)
+    assert pr.g_alone(16384, 1000, 1 << 40, 16)                 # the large kernel fits once
+    assert not pr.g_alone(8192, 9, 1000, 16)                    # fewer than two units a range
