@@ -831,7 +831,7 @@ int pr_build_layout(PrLayout* L, int64_t V, int64_t E, const int32_t* row_ptr, c
             if (open) stiles.push_back(make_uint2(first, n));
         };
         const uint64_t all = weight_before((uint64_t)V);
-        const uint64_t least = std::max<uint64_t>(kMinTileMessages * kScatterMessageWeight, (uint64_t)((double)kPieceBalance * std::sqrt((double)all)));
+        const uint64_t least = least_scatter_weight(all);
         const bool alone = scatter_alone(src_per_part, all, cus);                      // one workgroup a unit
         const uint64_t slots = (uint64_t)cus * (alone ? 1 : 2);
         const uint64_t share = (all + slots - 1) / slots;

@@ -60,7 +60,6 @@ static_assert(kRowsLarge <= (1u << kKeyLocalBits) && kSrcLarge <= 65536, "id fie
 constexpr int kKeySrcBits = 31;
 constexpr uint32_t kDefaultCus = 256;        // heavy ranges and source intervals are cut for this many workgroups side by side ...
 constexpr uint64_t kMinTileEdges = 24576;    // ... but no smaller than this (in weight: times kGatherEdgeWeight)
-constexpr uint64_t kMinTileMessages = 4096;
 // (2^14 vertices / 2^18 edges: 12 + 8 tiles of at least 32768 edges and 16384 messages take 18.6 us an iteration, 23 + 51
 // tiles 16.2, 45 + 95 tiles 16.6; a piece's fixed weight counts against a step's budget, so the gather sweep stays coarser)
 // weight of a gather tile = kGatherEdgeWeight * edges + kGatherMessageWeight * messages + kGatherRepeatWeight *
@@ -77,8 +76,7 @@ constexpr uint64_t kGatherFineShare = 2000000, kScatterFineShare = 1000000;
 // Pieces of a range weigh at least kMergeBalance x sqrt(weight of the heaviest range): a row of a range cut into n pieces
 // costs the scatter sweep n loads, a piece costs the gather sweep its own weight, and the sum of both is least where
 // the pieces weigh as the root of the range (2^18 vertices / 2^22 edges: 162 pieces 22.8 us, 256 24.9, 313 28.9).
-// Scatter pieces likewise, kPieceBalance x sqrt(weight of the sweep).
-constexpr uint64_t kMergeBalance = 29, kPieceBalance = 6;
+constexpr uint64_t kMergeBalance = 29;
 
 // An id is stored as the byte offset of its row's 8-byte accumulator, or half of it where that needs 17 bits.
 constexpr uint32_t id_scale_for(uint32_t rows_per_part) { return rows_per_part <= 8192 ? 8u : 4u; }

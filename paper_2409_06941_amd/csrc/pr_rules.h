@@ -2,6 +2,7 @@
 #ifndef FR_PR_RULES_H
 #define FR_PR_RULES_H
 
+#include <cmath>
 #include <cstdint>
 
 constexpr uint32_t kRowsSmall = 8192, kRowsLarge = 16384;   // destination rows per range (8 B each in LDS)
@@ -49,6 +50,18 @@ inline bool scatter_alone(uint32_t src_per_part, uint64_t all, uint32_t cus)
 {
     const uint64_t share = cus * kScatterAloneShare > kScatterAloneLeast ? cus * kScatterAloneShare : kScatterAloneLeast;
     return src_per_part == kSrcLarge || all <= cus * share;
+}
+
+// Scatter pieces weigh at least kMinTileMessages, or kPieceBalance x the root of the sweep's weight (as pieces of a range do); a
+// sweep of up to kOneTileMessages is one tile: what a second one saves in stores it costs in start-up and in dangling sums.
+// us an iteration, tiles of at least 4096 -> one tile: 4096 vertices / 16 384 edges (weight 8200) 15.3 -> 14.7, 5000 / 20 000
+// (10 000) 15.9 -> 15.2; 10 000 / 40 000 (26 000) 15.9 -> 17.0 with three tiles and 17.6 with two.
+constexpr uint64_t kMinTileMessages = 4096, kOneTileMessages = 16384, kPieceBalance = 6;
+inline uint64_t least_scatter_weight(uint64_t all)
+{
+    if (all <= kOneTileMessages) return all ? all : 1;
+    const uint64_t balance = (uint64_t)((double)kPieceBalance * std::sqrt((double)all));
+    return balance > kMinTileMessages ? balance : kMinTileMessages;
 }
 
 #endif

@@ -94,7 +94,7 @@ def test_every_partition_size(rows, srcs):
 
 # around the sizes where the tile rule changes: one tile, a few, one workgroup per compute unit, two per compute unit
 # (more ranges than half the units, or a heavier sweep)
-@pytest.mark.parametrize("n,edges,tiles", [(300, 2400, (1, 1)), (16_384, 700_001, (2, 256)), (300_007, 4_000_001, (100, 256)), (1_200_007, 9_000_000, (200, 512))])
+@pytest.mark.parametrize("n,edges,tiles", [(300, 2400, (1, 1)), (5_000, 20_000, (1, 1)), (16_384, 700_001, (2, 256)), (300_007, 4_000_001, (100, 256)), (1_200_007, 9_000_000, (200, 512))])
 def test_small_sweeps_have_a_workgroup_per_compute_unit(n, edges, tiles):
     src, dst = graphs.rmat_edges((n - 1).bit_length(), edges, seed=31)
     g = graphs.csr_from_edges(n, src % n, dst % n)
@@ -108,6 +108,7 @@ def test_small_sweeps_have_a_workgroup_per_compute_unit(n, edges, tiles):
         info = t.fr_pagerank_info()
         t.fr_pagerank_destroy()
         bits.append(ranks.cpu().numpy())
+    assert n > 5_000 or info.scatter_tiles == 1                  # a sweep of few messages is not cut
     assert tiles[0] <= info.gather_tiles <= tiles[1] and info.scatter_tiles <= info.scatter_slots, (info.gather_tiles, info.scatter_tiles)
     assert np.array_equal(bits[0].view(np.uint32), bits[1].view(np.uint32))
     want = pagerank(g.row_ptr, g.col, g.out_degree, 0.85, 6)

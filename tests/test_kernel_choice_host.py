@@ -64,10 +64,12 @@ def pr(tmp_path_factory):
     L = _compile(tmp_path_factory, "pr_rules", '''#include "pr_rules.h"
 extern "C" int runs(uint32_t src, int64_t V, uint32_t cus, int hands_out) { return scatter_in_runs(src, V, cus, hands_out != 0); }
 extern "C" int g_alone(uint32_t rows, uint32_t Qe, uint64_t total, uint32_t cus) { return gather_alone(rows, Qe, total, cus); }
+extern "C" uint64_t least(uint64_t all) { return least_scatter_weight(all); }
 extern "C" int s_alone(uint32_t src, uint64_t all, uint32_t cus) { return scatter_alone(src, all, cus); }
 ''')
     L.runs.argtypes = [ctypes.c_uint32, ctypes.c_int64, ctypes.c_uint32, ctypes.c_int]
     L.g_alone.argtypes = [ctypes.c_uint32, ctypes.c_uint32, ctypes.c_uint64, ctypes.c_uint32]
+    L.least.argtypes, L.least.restype = [ctypes.c_uint64], ctypes.c_uint64
     L.s_alone.argtypes = [ctypes.c_uint32, ctypes.c_uint64, ctypes.c_uint32]
     return L
 
@@ -110,3 +112,11 @@ def test_gather_workgroups_a_unit_are_the_faster_number(pr):
         assert bool(pr.g_alone(8192, Qe, share * 1000 * cus, cus)) == (one < two), (share, cus)
     assert pr.g_alone(16384, 1000, 1 << 40, 16)                 # the large kernel fits once
     assert not pr.g_alone(8192, 9, 1000, 16)                    # fewer than two units a range
+
+
+def test_least_scatter_tile(pr):
+    assert pr.least(0) == 1 and pr.least(1) == 1
+    for all_ in (300, 8200, 10_000, 16_384):
+        assert pr.least(all_) == all_                           # one tile
+    assert pr.least(16_385) == pr.least(26_000) == 4096         # several
+    assert pr.least(1 << 26) == 6 * 8192
