@@ -356,7 +356,9 @@ typedef struct fr_pagerank_info_t {
     uint32_t sources_per_partition; /* most source vertices of a scatter tile                               */
     uint32_t partial_rows;        /* gather pieces of merged ranges (rows of fp32 partial sums)             */
     uint64_t bytes_resident;      /* booked against the limit after init (caller buffers included)          */
-    uint64_t bytes_peak;          /* highest amount booked during init (set-up scratch included)            */
+    uint64_t bytes_peak;          /* highest amount booked during init (set-up scratch included): what a limit has to hold;
+                                     a standalone run without a limit below the device's memory may hold scratch blocks
+                                     up to a quarter larger than what is booked for them                    */
     uint32_t scatter_slots;       /* workgroups of a scatter launch / of a gather launch that run side by side on  */
     uint32_t gather_slots;        /* the stream's compute units: a step of more tiles runs in rounds, and plan_step
                                      cuts a step that does not reach its segment's end to whole rounds             */

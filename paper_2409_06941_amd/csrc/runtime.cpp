@@ -15,6 +15,7 @@
 #include <thread>
 
 #include "common.h"
+#include "scratch_pool.h"
 #include "freeride_device.h"
 
 namespace {
@@ -703,68 +704,27 @@ namespace {
 // Set-up scratch kept for the next set-up of a standalone run (tasks of a context take and give back theirs as they go:
 // what they leave belongs to the stage).  Fresh device memory has to be cleared by the driver, at about 30 GB/s once the
 // memory that was free at first has been used: a new graph of 2^26 edges took 1.7 GB of it, 18.5 ms a graph at first and
-// 51 ms from the 110th on.  At most 1/64 of the device's memory and kPoolBlocks blocks are kept, none longer than
-// kPoolKeepNs unused; all are given back when a context is destroyed or an allocation fails.
-struct PoolBlock { int device; void* ptr; uint64_t room, since; };
-constexpr size_t kPoolBlocks = 8;
-constexpr uint64_t kPoolKeepNs = 5000000000ull;
-std::mutex g_pool_mu;
-std::vector<PoolBlock> g_pool;           // oldest first
-
-void pool_free_locked(size_t i)
+// 51 ms from the 110th on.  At most 1/64 of the device's memory and kBlocks blocks are kept, none longer than
+// kKeepNs unused; all are given back when a context is destroyed or an allocation fails.
+uint64_t total_memory()
 {
-    (void)hipFree(g_pool[i].ptr);
-    g_pool.erase(g_pool.begin() + (long)i);
-}
-
-void pool_trim(bool all)
-{
-    std::lock_guard<std::mutex> lk(g_pool_mu);
-    while (!g_pool.empty() && (all || now_ns() - g_pool.front().since > kPoolKeepNs)) pool_free_locked(0);
-}
-
-// A kept block of at least `bytes`, and no more than a quarter more; NULL if there is none.
-void* pool_take(int device, uint64_t bytes, uint64_t* room)
-{
-    pool_trim(false);
-    std::lock_guard<std::mutex> lk(g_pool_mu);
-    size_t best = g_pool.size();
-    for (size_t i = 0; i < g_pool.size(); ++i) {
-        const PoolBlock& b = g_pool[i];
-        if (b.device != device || b.room < bytes || b.room - bytes > bytes / 4) continue;
-        if (best == g_pool.size() || b.room < g_pool[best].room) best = i;
-    }
-    if (best == g_pool.size()) return nullptr;
-    void* p = g_pool[best].ptr;
-    *room = g_pool[best].room;
-    g_pool.erase(g_pool.begin() + (long)best);
-    return p;
-}
-
-void pool_give(int device, void* ptr, uint64_t room)
-{
-    pool_trim(false);
     size_t free_bytes = 0, total = 0;
-    if (hipMemGetInfo(&free_bytes, &total) != hipSuccess) total = 0;
-    std::lock_guard<std::mutex> lk(g_pool_mu);
-    if (room > total / 64) { (void)hipFree(ptr); return; }
-    for (;;) {
-        uint64_t held = 0;
-        size_t blocks = 0, oldest = g_pool.size();
-        for (size_t i = g_pool.size(); i-- > 0;)
-            if (g_pool[i].device == device) { held += g_pool[i].room; ++blocks; oldest = i; }
-        if (!blocks || (blocks < kPoolBlocks && held + room <= total / 64)) break;
-        pool_free_locked(oldest);
-    }
-    g_pool.push_back({device, ptr, room, now_ns()});
+    return hipMemGetInfo(&free_bytes, &total) == hipSuccess ? total : 0;
 }
+
+struct DeviceMemory {
+    static void free(void* p) { (void)hipFree(p); }
+    static uint64_t now_ns() { return ::now_ns(); }
+    static uint64_t keep_at_most(int) { return total_memory() / 64; }
+};
+ScratchPool<DeviceMemory> g_pool;
 
 hipError_t malloc_device(void** p, uint64_t bytes)
 {
     hipError_t e = hipMalloc(p, bytes);
     if (e == hipErrorOutOfMemory) {
         (void)hipGetLastError();
-        pool_trim(true);
+        g_pool.trim(true);
         e = hipMalloc(p, bytes);
     }
     return e;
@@ -778,7 +738,7 @@ void fr_alloc_release(fr_alloc* a)
         if (a->host_only) std::free(b.ptr);
         else (void)hipFree(b.ptr);           // (of the pool or not: the set-up that took it failed)
     }
-    if (!a->host_only) pool_trim(false);
+    if (!a->host_only) g_pool.trim(false);
     a->blocks.clear();
     a->used = 0;
 }
@@ -817,7 +777,7 @@ void* fr_alloc_scratch(fr_alloc* a, size_t bytes)
     const uint64_t rounded = std::max<uint64_t>(256, ((uint64_t)bytes + 255) & ~255ull);
     if (rounded > a->limit || a->used > a->limit - rounded) { a->oom = true; return nullptr; }
     uint64_t room = rounded;
-    void* p = pool_take(a->device, rounded, &room);
+    void* p = g_pool.take(a->device, rounded, most_room(a->limit, total_memory(), rounded), &room);
     if (!p) {
         hipError_t e = malloc_device(&p, rounded);
         if (e != hipSuccess) { a->hip_error = (int)e; a->oom = true; return nullptr; }
@@ -857,7 +817,7 @@ int fr_alloc_free(fr_alloc* a, void* p)
     for (size_t i = 0; i < a->blocks.size(); ++i) {
         if (a->blocks[i].ptr != p) continue;
         if (a->host_only) std::free(p);
-        else if (a->blocks[i].room) pool_give(a->device, p, a->blocks[i].room);
+        else if (a->blocks[i].room) g_pool.give(a->device, p, a->blocks[i].room);
         else (void)hipFree(p);
         a->used -= a->blocks[i].bytes;
         a->blocks.erase(a->blocks.begin() + (long)i);
@@ -931,7 +891,7 @@ int fr_create(const fr_config* cfg, fr_ctx** out)
 int fr_destroy(fr_ctx* c)
 {
     if (!c) return FR_ERR_ARG;
-    if (!c->host_only) pool_trim(true);
+    if (!c->host_only) g_pool.trim(true);
     c->abort_steps.store(true);
     c->end_requested.store(true);
     c->quit.store(true, std::memory_order_release);

@@ -1,0 +1,94 @@
+"""The pool of kept set-up memory (csrc/scratch_pool.h), compiled for the host on memory that only counts: what it may hand out
+and keep, and what it gives back when."""
+import ctypes
+import os
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2409_06941_amd", "csrc")
+
+CODE = r'''
+#include "scratch_pool.h"
+#include <atomic>
+#include <set>
+static std::atomic<uint64_t> g_now{0}, g_most{1000};
+static std::vector<uint64_t> g_freed;          // in the order they were freed
+struct Mem {
+    static void free(void* p) { g_freed.push_back((uint64_t)(uintptr_t)p); }
+    static uint64_t now_ns() { return g_now; }
+    static uint64_t keep_at_most(int) { return g_most; }
+};
+static ScratchPool<Mem>* pool = new ScratchPool<Mem>();
+extern "C" {
+void reset(uint64_t most) { delete pool; pool = new ScratchPool<Mem>(); g_now = 0; g_most = most; g_freed.clear(); }
+void set_now(uint64_t s) { g_now = s * 1000000000ull; }
+uint64_t take(int device, uint64_t bytes, uint64_t most) { uint64_t room = 0; return pool->take(device, bytes, most, &room) ? room : 0; }
+void give(int device, uint64_t id, uint64_t room) { pool->give(device, (void*)(uintptr_t)id, room); }
+void trim(int all) { pool->trim(all != 0); }
+uint64_t freed(uint64_t k) { return k < g_freed.size() ? g_freed[k] : 0; }
+uint64_t most(uint64_t limit, uint64_t total, uint64_t bytes) { return most_room(limit, total, bytes); }
+}
+'''
+
+
+def _build(tmp_path_factory, name, code, *flags):
+    d = tmp_path_factory.mktemp(name)
+    src, out = d / (name + ".cpp"), d / name
+    src.write_text(code)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-pthread", "-I", CSRC, *flags, str(src), "-o", str(out)], check=True)
+    return str(out)
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    L = ctypes.CDLL(_build(tmp_path_factory, "pool.so", CODE, "-shared", "-fPIC"))
+    u64 = ctypes.c_uint64
+    for name, args in (("reset", [u64]), ("set_now", [u64]), ("take", [ctypes.c_int, u64, u64]), ("give", [ctypes.c_int, u64, u64]),
+                       ("freed", [u64]), ("most", [u64, u64, u64])):
+        getattr(L, name).argtypes = args
+        getattr(L, name).restype = u64
+    return L
+
+
+def _freed(L):
+    out = []
+    while L.freed(len(out)):
+        out.append(L.freed(len(out)))
+    return out
+
+
+def test_a_task_with_a_limit_gets_blocks_of_the_size_that_is_booked(lib):
+    total = 1 << 38
+    assert lib.most(1 << 40, total, 1000) == 1250                 # no limit of its own: up to a quarter more
+    assert lib.most(total - 1, total, 1000) == 1000 and lib.most(1 << 40, 0, 1000) == 1000
+    lib.reset(10_000)
+    lib.give(0, 1, 1200)
+    assert lib.take(0, 1000, lib.most(total - 1, total, 1000)) == 0
+    assert lib.take(0, 1000, lib.most(total, total, 1000)) == 1200
+    lib.give(0, 1, 1000)
+    assert lib.take(0, 1000, lib.most(1, total, 1000)) == 1000
+
+
+def test_blocks_are_bounded_in_number_and_bytes_and_age(lib):
+    lib.reset(1000)
+    lib.give(0, 1, 1001)                                          # more than may be kept at all
+    assert _freed(lib) == [1]
+    lib.give(0, 2, 600); lib.give(0, 3, 300); lib.give(1, 4, 1000)
+    lib.give(0, 5, 200)                                           # 1100: the oldest of that device goes
+    assert _freed(lib) == [1, 2]
+    for k in range(6):
+        lib.give(0, 10 + k, 10)                                   # eight blocks of device 0
+    assert _freed(lib) == [1, 2]
+    lib.give(0, 20, 10)
+    assert _freed(lib) == [1, 2, 3]
+    assert lib.take(0, 150, 199) == 0 and lib.take(2, 10, 10) == 0 and lib.take(0, 150, 200) == 200
+    assert lib.take(1, 900, 1000) == 1000
+    lib.set_now(6)
+    lib.trim(0)
+    assert sorted(_freed(lib)[3:]) == [10, 11, 12, 13, 14, 15, 20]
+    lib.give(0, 30, 10)
+    lib.trim(0)
+    assert len(_freed(lib)) == 10
+    lib.trim(1)
+    assert _freed(lib)[-1] == 30
