@@ -738,7 +738,7 @@ void fr_alloc_release(fr_alloc* a)
         if (a->host_only) std::free(b.ptr);
         else (void)hipFree(b.ptr);           // (of the pool or not: the set-up that took it failed)
     }
-    if (!a->host_only) g_pool.trim(false);
+    if (a->pooled) g_pool.trim(false);       // (a task of a context has no part in the pool, and is stopped under the context's lock)
     a->blocks.clear();
     a->used = 0;
 }
@@ -891,7 +891,6 @@ int fr_create(const fr_config* cfg, fr_ctx** out)
 int fr_destroy(fr_ctx* c)
 {
     if (!c) return FR_ERR_ARG;
-    if (!c->host_only) g_pool.trim(true);
     c->abort_steps.store(true);
     c->end_requested.store(true);
     c->quit.store(true, std::memory_order_release);
@@ -910,6 +909,7 @@ int fr_destroy(fr_ctx* c)
     if (c->side) { (void)hipStreamSynchronize(c->side); (void)hipStreamDestroy(c->side); }
     if (c->tail_event) (void)hipEventDestroy(c->tail_event);
     if (c->gate) (void)hipFree(c->gate);
+    if (!c->host_only) g_pool.trim(true);                // (last: it waits for the device, and the worker is gone by now)
     delete c;
     return FR_OK;
 }

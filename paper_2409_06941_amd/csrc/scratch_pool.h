@@ -6,7 +6,6 @@
 #include <cstddef>
 #include <cstdint>
 #include <mutex>
-#include <vector>
 
 // The largest block that may serve a request of `bytes`: a task without a limit of its own (one beyond the device's `total`) may
 // be handed up to a quarter more than it asked for; one with a limit gets the size that is booked against it, so that the limit
@@ -24,53 +23,65 @@ public:
     {
         trim(false);
         std::lock_guard<std::mutex> lk(mu_);
-        size_t best = kept_.size();
-        for (size_t i = 0; i < kept_.size(); ++i) {
+        size_t best = n_;
+        for (size_t i = 0; i < n_; ++i) {
             const Block& b = kept_[i];
             if (b.device != device || b.room < bytes || b.room > most) continue;
-            if (best == kept_.size() || b.room < kept_[best].room) best = i;
+            if (best == n_ || b.room < kept_[best].room) best = i;
         }
-        if (best == kept_.size()) return nullptr;
-        void* p = kept_[best].ptr;
+        if (best == n_) return nullptr;
         *room = kept_[best].room;
-        kept_.erase(kept_.begin() + (long)best);
-        return p;
+        return remove(best);
     }
 
     void give(int device, void* ptr, uint64_t room)
     {
         trim(false);
         const uint64_t most = Mem::keep_at_most(device);
+        Freed freed;
         std::lock_guard<std::mutex> lk(mu_);
-        if (room > most) { Mem::free(ptr); return; }
+        if (room > most) { freed.add(ptr); return; }
         for (;;) {
             uint64_t held = 0;
-            size_t blocks = 0, oldest = kept_.size();
-            for (size_t i = kept_.size(); i-- > 0;)
+            size_t blocks = 0, oldest = n_;
+            for (size_t i = n_; i-- > 0;)
                 if (kept_[i].device == device) { held += kept_[i].room; ++blocks; oldest = i; }
-            if (!blocks || (blocks < kBlocks && held + room <= most)) break;
-            free_locked(oldest);
+            if (n_ < kAll && (!blocks || (blocks < kBlocks && held + room <= most))) break;
+            freed.add(remove(oldest < n_ ? oldest : 0));
         }
-        kept_.push_back({device, ptr, room, Mem::now_ns()});
+        kept_[n_++] = {device, ptr, room, Mem::now_ns()};
     }
 
     void trim(bool all)
     {
+        Freed freed;
         std::lock_guard<std::mutex> lk(mu_);
-        while (!kept_.empty() && (all || Mem::now_ns() - kept_.front().since > kKeepNs)) free_locked(0);
+        while (n_ && (all || Mem::now_ns() - kept_[0].since > kKeepNs)) freed.add(remove(0));
     }
 
 private:
+    static constexpr size_t kAll = 8 * kBlocks;             // of all devices
+
     struct Block { int device; void* ptr; uint64_t room, since; };
 
-    void free_locked(size_t i)
+    // What left the pool under the lock, freed after it: giving memory back waits for the device.
+    struct Freed {
+        void* p[kAll + 1];
+        size_t n = 0;
+        void add(void* ptr) { p[n++] = ptr; }
+        ~Freed() { for (size_t i = 0; i < n; ++i) Mem::free(p[i]); }
+    };
+
+    void* remove(size_t i)
     {
-        Mem::free(kept_[i].ptr);
-        kept_.erase(kept_.begin() + (long)i);
+        void* p = kept_[i].ptr;
+        for (--n_; i < n_; ++i) kept_[i] = kept_[i + 1];
+        return p;
     }
 
     std::mutex mu_;
-    std::vector<Block> kept_;               // oldest first
+    Block kept_[kAll];                      // oldest first
+    size_t n_ = 0;
 };
 
 #endif

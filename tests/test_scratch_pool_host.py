@@ -11,7 +11,7 @@ CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
 CODE = r'''
 #include "scratch_pool.h"
 #include <atomic>
-#include <set>
+#include <vector>
 static std::atomic<uint64_t> g_now{0}, g_most{1000};
 static std::vector<uint64_t> g_freed;          // in the order they were freed
 struct Mem {
@@ -92,3 +92,75 @@ def test_blocks_are_bounded_in_number_and_bytes_and_age(lib):
     assert len(_freed(lib)) == 10
     lib.trim(1)
     assert _freed(lib)[-1] == 30
+
+
+def test_memory_is_freed_outside_the_pools_lock(tmp_path_factory):
+    # giving memory back waits for the device: a thread that only wants a block must not wait for that
+    exe = _build(tmp_path_factory, "pool_lock", r'''
+#include "scratch_pool.h"
+#include <cstdio>
+static uint64_t g_now = 0;
+static void on_free();
+struct Mem {
+    static void free(void*) { on_free(); }
+    static uint64_t now_ns() { return g_now; }
+    static uint64_t keep_at_most(int) { return 100; }
+};
+static ScratchPool<Mem> pool;
+static int frees = 0;
+static void on_free() { ++frees; uint64_t room = 0; (void)pool.take(9, 1, 1, &room); }       // hangs if the lock is held
+int main()
+{
+    pool.give(0, (void*)1, 101);                                 // too large
+    for (uintptr_t k = 2; k < 12; ++k) pool.give(0, (void*)k, 10);        // too many
+    pool.give(0, (void*)20, 90);                                 // too much
+    g_now = ScratchPool<Mem>::kKeepNs + 1;
+    pool.trim(false);                                            // too old
+    pool.give(0, (void*)21, 1);
+    pool.trim(true);
+    std::printf("%d\n", frees);
+    return 0;
+}
+''')
+    out = subprocess.run([exe], capture_output=True, text=True, timeout=20, check=True).stdout
+    assert int(out) == 1 + 10 + 1 + 1
+
+
+def test_threads_never_share_a_block(tmp_path_factory):
+    exe = _build(tmp_path_factory, "pool_threads", r'''
+#include "scratch_pool.h"
+#include <atomic>
+#include <cstdio>
+#include <thread>
+#include <vector>
+static std::atomic<int> owners[4096];
+static std::atomic<int> live{0}, bad{0};
+struct Mem {
+    static void free(void* p) { if (owners[(uintptr_t)p].fetch_add(1) != 0) ++bad; --live; }       // (a freed block is never used again)
+    static uint64_t now_ns() { return 0; }
+    static uint64_t keep_at_most(int) { return 6; }
+};
+static ScratchPool<Mem> pool;
+int main()
+{
+    std::atomic<uintptr_t> next{1};
+    std::vector<std::thread> t;
+    for (int k = 0; k < 8; ++k)
+        t.emplace_back([&, k] {
+            for (int i = 0; i < 400; ++i) {
+                uint64_t room = 1;
+                void* p = pool.take(k % 3, 1, 1, &room);
+                if (!p) { p = (void*)next.fetch_add(1); ++live; }
+                if (owners[(uintptr_t)p].fetch_add(1) != 0) ++bad;
+                owners[(uintptr_t)p].fetch_sub(1);
+                pool.give(k % 3, p, room);
+                if (i % 97 == 0) pool.trim(true);
+            }
+        });
+    for (auto& x : t) x.join();
+    pool.trim(true);
+    std::printf("%d %d\n", bad.load(), live.load());
+    return 0;
+}
+''')
+    assert subprocess.run([exe], capture_output=True, text=True, timeout=60, check=True).stdout.split() == ["0", "0"]
