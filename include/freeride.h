@@ -388,6 +388,14 @@ int fr_pagerank_tile_weights(void* user, int32_t seg_kind, uint64_t* weights_hos
 int fr_pagerank_run_standalone(void* user, int32_t device_id, void* stream, uint32_t max_tiles_per_launch,
                                uint64_t* phase_ns_out);
 /*
+ * A program that sets up standalone PageRank tasks one after the other (less than five seconds from one set-up to the
+ * next) leaves set-up scratch with the library for the next one, at most 1/64 of the device's memory, also when every
+ * task is destroyed.  It is given back when a context is made or destroyed, when an allocation of the library fails, after
+ * five seconds without use at the next set-up, and by this call, which a program makes when it is done setting up
+ * graphs and another allocator is to have the memory.  *bytes_out (may be NULL) receives the bytes given back.
+ */
+int fr_scratch_release(uint64_t* bytes_out);
+/*
  * For callers that cannot allocate device memory (code under HIP graph capture, tight serving loops, harnesses that
  * forbid it): the same run as fr_pagerank_run_standalone with the same kernels and tiles, hence the same bits in
  * ranks_out, but the run's working memory (messages, contributions, dangling partials, partial sums) lies in a

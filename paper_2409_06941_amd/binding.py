@@ -134,6 +134,7 @@ SIGNATURES = {
     "fr_alloc_device": (C.c_void_p, [C.c_void_p, C.c_size_t]),
     "fr_alloc_charge": (C.c_int, [C.c_void_p, C.c_size_t]),
     "fr_alloc_free": (C.c_int, [C.c_void_p, C.c_void_p]),
+    "fr_scratch_release": (C.c_int, [C.POINTER(C.c_uint64)]),
     "fr_alloc_used": (C.c_uint64, [C.c_void_p]),
     "fr_alloc_peak": (C.c_uint64, [C.c_void_p]),
     "fr_bubble_begin": (C.c_int, [C.c_void_p, C.c_uint64, C.c_uint64]),
@@ -222,6 +223,13 @@ def _stream(s):
 
 def fr_now_ns():
     return lib().fr_now_ns()
+
+
+def fr_scratch_release():
+    """Gives kept set-up scratch back to the device; returns the bytes."""
+    out = C.c_uint64()
+    _check(lib().fr_scratch_release(C.byref(out)), "fr_scratch_release")
+    return out.value
 
 
 def fr_chunk_fit(prefix, tile0, budget_ns, launch_cost_ns):

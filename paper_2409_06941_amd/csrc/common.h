@@ -17,7 +17,8 @@ struct fr_alloc {
     int device = 0;
     int hip_error = 0;
     uint64_t peak = 0;
-    bool pooled = false;                 // set-up scratch comes from, and goes back to, the pool of kept blocks
+    bool pooled = false;                 // set-up scratch may come from, and go back to, the pool of kept blocks ...
+    int series = -1;                     // ... if the set-up follows another one (-1: not asked yet)
     struct Block { void* ptr; uint64_t bytes; uint64_t room; };      // room: the size of a block of the pool (0: not one)
     std::vector<Block> blocks;
 };

@@ -696,16 +696,19 @@ void enforce_check(fr_ctx* c)
 void fr_alloc_reset(fr_alloc* a, uint64_t limit, bool host_only, int device)
 {
     a->limit = limit; a->used = 0; a->oom = false; a->host_only = host_only; a->device = device;
-    a->hip_error = 0; a->peak = 0; a->pooled = false; a->blocks.clear();
+    a->hip_error = 0; a->peak = 0; a->pooled = false; a->series = -1; a->blocks.clear();
 }
 
 namespace {
 
 // Set-up scratch kept for the next set-up of a standalone run (tasks of a context take and give back theirs as they go:
 // what they leave belongs to the stage).  Fresh device memory has to be cleared by the driver, at about 30 GB/s once the
-// memory that was free at first has been used: a new graph of 2^26 edges took 1.7 GB of it, 18.5 ms a graph at first and
-// 51 ms from the 110th on.  At most 1/64 of the device's memory and kBlocks blocks are kept, none longer than
-// kKeepNs unused; all are given back when a context is destroyed or an allocation fails.
+// memory that was free at first has been used: 2^22 vertices / 2^26 edges, made, run and destroyed over and over, take 8.4 ms
+// a graph with kept scratch and without it 10.0 for the first 120 and 40 from then on, with single ones of 0.1 to 2.6 s.
+// Only a program that sets up graph after graph gains by it, so only a set-up that begins within kKeepNs of the one before
+// takes part; then at most 1/64 of the device's memory and kBlocks blocks are kept.  There is no thread that watches their
+// age: a block unused for kKeepNs is given back by the next set-up, or the next task with kept scratch that is destroyed; all are when a context
+// is made or destroyed, when an allocation of the library fails, and by fr_scratch_release.
 uint64_t total_memory()
 {
     size_t free_bytes = 0, total = 0;
@@ -773,6 +776,8 @@ void fr_alloc_back_to(fr_alloc* a, size_t mark)
 void* fr_alloc_scratch(fr_alloc* a, size_t bytes)
 {
     if (!a || !a->pooled || a->host_only) return fr_alloc_device(a, bytes);
+    if (a->series < 0) a->series = g_pool.begins(a->device) ? 1 : 0;
+    if (!a->series) return fr_alloc_device(a, bytes);
     if (a->oom) return nullptr;
     const uint64_t rounded = std::max<uint64_t>(256, ((uint64_t)bytes + 255) & ~255ull);
     if (rounded > a->limit || a->used > a->limit - rounded) { a->oom = true; return nullptr; }
@@ -836,6 +841,13 @@ int fr_alloc_charge(fr_alloc* a, size_t bytes)
     return FR_OK;
 }
 
+int fr_scratch_release(uint64_t* bytes_out)
+{
+    const uint64_t bytes = g_pool.trim(true);
+    if (bytes_out) *bytes_out = bytes;
+    return FR_OK;
+}
+
 uint64_t fr_alloc_used(const fr_alloc* a) { return a ? a->used : 0; }
 uint64_t fr_alloc_peak(const fr_alloc* a) { return a ? a->peak : 0; }
 
@@ -855,6 +867,7 @@ int fr_create(const fr_config* cfg, fr_ctx** out)
         if (e != hipSuccess || cfg->device_id >= n) { c->hip_error = (int)e; delete c; return e != hipSuccess ? FR_ERR_HIP : FR_ERR_ARG; }
         e = hipSetDevice(cfg->device_id);
         if (e != hipSuccess) { delete c; return FR_ERR_HIP; }
+        (void)g_pool.trim(true);                          // (what is free now is the side tasks')
         uint32_t mask[8] = {0};
         bool masked = false;
         if (cfg->cu_count > 0 && cfg->cu_count < 256) {

@@ -18,6 +18,16 @@ public:
     static constexpr size_t kBlocks = 8;                    // of a device
     static constexpr uint64_t kKeepNs = 5000000000ull;
 
+    // A set-up begins on `device`: does it follow another one within kKeepNs?  (Only then is anything worth keeping for the next.)
+    bool begins(int device)
+    {
+        if (device < 0 || device >= (int)(sizeof(last_) / sizeof(last_[0]))) return false;
+        std::lock_guard<std::mutex> lk(mu_);
+        const uint64_t now = Mem::now_ns(), last = last_[device];
+        last_[device] = now ? now : 1;
+        return last != 0 && now - last <= kKeepNs;
+    }
+
     // A kept block of `bytes` to `most` bytes, the smallest there is; NULL if there is none.
     void* take(int device, uint64_t bytes, uint64_t most, uint64_t* room)
     {
@@ -52,11 +62,14 @@ public:
         kept_[n_++] = {device, ptr, room, Mem::now_ns()};
     }
 
-    void trim(bool all)
+    // Gives back what has been kept for longer than kKeepNs, or all of it; bytes given back.
+    uint64_t trim(bool all)
     {
         Freed freed;
         std::lock_guard<std::mutex> lk(mu_);
-        while (n_ && (all || Mem::now_ns() - kept_[0].since > kKeepNs)) freed.add(remove(0));
+        uint64_t bytes = 0;
+        while (n_ && (all || Mem::now_ns() - kept_[0].since > kKeepNs)) { bytes += kept_[0].room; freed.add(remove(0)); }
+        return bytes;
     }
 
 private:
@@ -82,6 +95,7 @@ private:
     std::mutex mu_;
     Block kept_[kAll];                      // oldest first
     size_t n_ = 0;
+    uint64_t last_[64] = {};                // when the last set-up of a device began; 0: there was none
 };
 
 #endif

@@ -1,4 +1,6 @@
 """GPU parity: the HIP PageRank path against the fp64 CPU oracle, element by element, through the C ABI."""
+import time
+
 import numpy as np
 import pytest
 
@@ -408,3 +410,45 @@ def test_set_up_memory_kept_between_graphs_changes_nothing_and_is_given_back():
     assert kept <= torch.cuda.mem_get_info()[1] // 64 + (64 << 20)
     ctx_life()
     assert before - torch.cuda.mem_get_info()[0] <= 4 << 20
+
+
+def test_set_up_memory_goes_back_without_a_context():
+    one, other = graphs.rmat_csr(16, 900_000, seed=43), graphs.rmat_csr(16, 800_000, seed=44)
+    fr.fr_scratch_release()
+    want = _run(other, iterations=3)
+    fr.fr_scratch_release()
+    torch.cuda.synchronize()
+    time.sleep(5.2)                                      # the set-ups before this are too long ago to be followed
+    torch.cuda.empty_cache()
+    before = torch.cuda.mem_get_info()[0]
+    _run(one, iterations=3)                              # a graph on its own leaves nothing behind
+    torch.cuda.empty_cache()
+    assert before - torch.cuda.mem_get_info()[0] <= 4 << 20
+    assert fr.fr_scratch_release() == 0
+    _run(one, iterations=3)                              # the second of a series does
+    got = _run(other, iterations=3)
+    assert np.array_equal(got.view(np.uint32), want.view(np.uint32))
+    held = fr.fr_scratch_release()
+    assert 8 * one.n_edges <= held <= torch.cuda.mem_get_info()[1] // 64
+    torch.cuda.empty_cache()
+    assert before - torch.cuda.mem_get_info()[0] <= 4 << 20
+    assert fr.fr_scratch_release() == 0
+
+
+def test_a_limit_holds_for_kept_set_up_memory_too():
+    # blocks kept from a graph a seventh larger serve a task without a limit, but not one whose limit is what it needs: that one
+    # gets blocks of its own sizes (and leaves them, beside those of the larger graph)
+    big, small = graphs.rmat_csr(16, 915_000, seed=45), graphs.rmat_csr(16, 800_000, seed=46)
+    fr.fr_scratch_release()
+    rp, col, od = _dev(small.row_ptr, torch.int32), _dev(small.col, torch.int32), _dev(small.out_degree, torch.int32)
+    held, peak = [], None
+    for limit in (1 << 40, None):
+        for g in (big, big):
+            _run(g, iterations=2)
+        ranks = torch.zeros(small.n_vertices, dtype=torch.float32, device="cuda")
+        t = fr.PageRankTask(small.n_vertices, small.n_edges, rp, col, od, ranks, iterations=2, mem_limit_bytes=limit or peak)
+        t.fr_pagerank_run_standalone(0, torch.cuda.current_stream())
+        peak = t.fr_pagerank_info().bytes_peak
+        t.fr_pagerank_destroy()
+        held.append(fr.fr_scratch_release())
+    assert held[1] >= held[0] + 8 * small.n_edges // 2, held

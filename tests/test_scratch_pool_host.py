@@ -25,7 +25,8 @@ void reset(uint64_t most) { delete pool; pool = new ScratchPool<Mem>(); g_now = 
 void set_now(uint64_t s) { g_now = s * 1000000000ull; }
 uint64_t take(int device, uint64_t bytes, uint64_t most) { uint64_t room = 0; return pool->take(device, bytes, most, &room) ? room : 0; }
 void give(int device, uint64_t id, uint64_t room) { pool->give(device, (void*)(uintptr_t)id, room); }
-void trim(int all) { pool->trim(all != 0); }
+uint64_t trim(int all) { return pool->trim(all != 0); }
+int begins(int device) { return pool->begins(device); }
 uint64_t freed(uint64_t k) { return k < g_freed.size() ? g_freed[k] : 0; }
 uint64_t most(uint64_t limit, uint64_t total, uint64_t bytes) { return most_room(limit, total, bytes); }
 }
@@ -45,7 +46,7 @@ def lib(tmp_path_factory):
     L = ctypes.CDLL(_build(tmp_path_factory, "pool.so", CODE, "-shared", "-fPIC"))
     u64 = ctypes.c_uint64
     for name, args in (("reset", [u64]), ("set_now", [u64]), ("take", [ctypes.c_int, u64, u64]), ("give", [ctypes.c_int, u64, u64]),
-                       ("freed", [u64]), ("most", [u64, u64, u64])):
+                       ("freed", [u64]), ("trim", [ctypes.c_int]), ("most", [u64, u64, u64])):
         getattr(L, name).argtypes = args
         getattr(L, name).restype = u64
     return L
@@ -92,6 +93,18 @@ def test_blocks_are_bounded_in_number_and_bytes_and_age(lib):
     assert len(_freed(lib)) == 10
     lib.trim(1)
     assert _freed(lib)[-1] == 30
+
+
+def test_only_a_set_up_that_follows_another_takes_part(lib):
+    lib.reset(1000)
+    lib.set_now(100)
+    assert not lib.begins(0)                                      # the first of the process
+    lib.set_now(105)
+    assert lib.begins(0) and not lib.begins(1)                    # within five seconds, on the same device
+    lib.set_now(111)
+    assert not lib.begins(0) and not lib.begins(-1) and not lib.begins(64)
+    lib.give(0, 1, 300); lib.give(1, 2, 400)
+    assert lib.trim(0) == 0 and lib.trim(1) == 700 and lib.trim(1) == 0
 
 
 def test_memory_is_freed_outside_the_pools_lock(tmp_path_factory):
