@@ -25,7 +25,7 @@ def is_stale() -> bool:
     if not os.path.exists(LIB):
         return True
     t = os.path.getmtime(LIB)
-    deps = sources() + [os.path.join(CSRC, "common.h"), os.path.join(CSRC, "pr_layout.h"), os.path.join(CSRC, "pr_rules.h"), os.path.join(CSRC, "sgd_rule.h"), os.path.join(CSRC, "scratch_pool.h"),
+    deps = sources() + [os.path.join(CSRC, "common.h"), os.path.join(CSRC, "pr_layout.h"), os.path.join(CSRC, "pr_rules.h"), os.path.join(CSRC, "sgd_rule.h"), os.path.join(CSRC, "gemm_tiles.h"), os.path.join(CSRC, "scratch_pool.h"),
                         os.path.join(ROOT, "include", "freeride.h"),
                         os.path.join(ROOT, "include", "freeride_device.h")]
     return any(os.path.getmtime(d) > t for d in deps)

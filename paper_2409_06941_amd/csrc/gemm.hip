@@ -12,6 +12,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "gemm_tiles.h"
 
 namespace {
 
@@ -20,7 +21,6 @@ typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 typedef __attribute__((address_space(3))) char* LdsBytes;
 __device__ __forceinline__ LdsBytes lds_at(uint32_t address) { return reinterpret_cast<LdsBytes>(address); }
 
-constexpr int BK = 64;                         // K of a k-tile: 128 bytes of a row
 constexpr int kXcds = 8;
 
 __device__ __forceinline__ uint16_t f32_to_bf16_rne(float x)
@@ -266,7 +266,7 @@ void k_gemm_bf16_nt(const uint16_t* __restrict__ A, const uint16_t* __restrict__
 // the other sits at its barrier.  The staging registers are named scalars on purpose: as small private arrays
 // they are moved to LDS or scratch by the compiler and the kernel runs three times slower.
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
-constexpr int kShortM = 256, kShortN = 128, kThreads = 512;      // 8 wavefronts as 4 x 2, each 64 x 64 of C
+constexpr int kThreads = 512;                  // 8 wavefronts as 4 x 2, each 64 x 64 of C
 constexpr int kLdsRow = BK + 8;                // bf16 elements per LDS row: 128 B of data + 16 B pad, which spreads
                                                // the rows one 16-byte-per-lane LDS access touches over the banks
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 4)))
@@ -434,40 +434,9 @@ uint64_t plan_gpt(fr_load* l, bool fill_lists)
     return off;
 }
 
-// Tiles and what they were measured to take, in us: `start` to begin and end a workgroup, and per k-tile `alone` with few
-// workgroups on the chip, `full` with one on every compute unit (shared L2, lower clock), and `more` for every further one per
-// compute unit.  Where one workgroup fills a compute unit (side_by_side 1) a part of a round costs a round; others overlap.
-// 2048 x 4096 x 4096, for instance, takes 75 us in 128 tiles of 256 x 256, 55 in 256 of 128 x 256 and 58 in 512 of
-// 128 x 128; 512 x 768 x 1024 from operands that are in no L2 takes 22.9 us in 6 tiles of 256 x 256, 8.1 in 96 of 64 x 64 and 6.6
-// if four parts of K are worked on side by side as well (with K = 512: 15.3, 4.0 and 5.1).
-struct GemmTile { int bm, bn, side_by_side; float start, alone, full, more; };
-constexpr GemmTile kTiles[] = {
-    {256, 256, 1, 8.5f, 0.97f, 1.39f, 1.39f}, {128, 256, 1, 5.7f, 0.57f, 0.80f, 0.80f}, {128, 128, 2, 5.1f, 0.33f, 0.46f, 0.43f},
-    {64, 128, 2, 2.7f, 0.24f, 0.35f, 0.28f}, {64, 64, 4, 2.6f, 0.22f, 0.30f, 0.28f},
-    {64, 64, 1, 3.9f, 0.134f, 0.20f, 0.20f},                       // kSplit 4
-    {kShortM, kShortN, 2, 4.8f, 1.0f, 1.1f, 1.0f},                 // k_gemm_bf16_nt_short
-};
-
-float gemm_estimate(const GemmTile& T, int M, int N, int K, int cus)
+// Tile `best` of kTiles.
+int gemm_launch_tile(int best, const void* A, const void* B, void* C, int M, int N, int K, hipStream_t stream)
 {
-    const float u = (float)((double)(M / T.bm) * (double)(N / T.bn) / cus), nk = (float)(K / BK), rounds = std::floor(u), rest = u - rounds;
-    if (T.side_by_side == 1)
-        return (rounds + (rest > 0.0f ? 1.0f : 0.0f)) * T.start + nk * (rounds * T.full + (rest > 0.0f ? T.alone + (T.full - T.alone) * rest : 0.0f));
-    // (the compute units with one workgroup more than the others set the time, though less than if all had as many)
-    const float v = u <= 1.0f ? u : 0.35f * u + 0.65f * std::ceil(u);
-    return T.start * std::max(1.0f, v / T.side_by_side) + nk * (v <= 1.0f ? T.alone + (T.full - T.alone) * v : T.full + (v - 1.0f) * T.more);
-}
-
-int gemm_launch(const void* A, const void* B, void* C, int M, int N, int K, hipStream_t stream)
-{
-    int device = 0, cus = 0;
-    if (hipGetDevice(&device) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess || cus <= 0) return FR_ERR_HIP;
-    int best = 0;
-    float least = gemm_estimate(kTiles[0], M, N, K, cus);
-    for (int k = 1; k < (int)(sizeof(kTiles) / sizeof(kTiles[0])); ++k) {
-        const float us = gemm_estimate(kTiles[k], M, N, K, cus);
-        if (us < least) { least = us; best = k; }
-    }
     const unsigned grid = (unsigned)(M / kTiles[best].bm) * (unsigned)(N / kTiles[best].bn);
     auto go = [&](auto kernel, unsigned threads) {
         hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), 0, stream, (const uint16_t*)A, (const uint16_t*)B, (uint16_t*)C, M, N, K);
@@ -484,6 +453,15 @@ int gemm_launch(const void* A, const void* B, void* C, int M, int N, int K, hipS
     return hipGetLastError() == hipSuccess ? FR_OK : FR_ERR_HIP;
 }
 
+int gemm_check(const void* A, const void* B, const void* C, int32_t M, int32_t N, int32_t K)
+{
+    if (!A || !B || !C || M <= 0 || N <= 0 || K <= 0) return FR_ERR_ARG;
+    if (M % 256 || N % 256 || K % 64) return FR_ERR_ARG;
+    if (((uintptr_t)A | (uintptr_t)B | (uintptr_t)C) & 15) return FR_ERR_ARG;
+    if ((uint64_t)(M / 64) * (uint64_t)(N / 64) > 0x7fffffffull) return FR_ERR_ARG;
+    return FR_OK;
+}
+
 // Part `part` of `parts` of a burst: the GEMMs of the layers [part * layers / parts, (part + 1) * layers / parts)
 // (the list holds the layers one after the other, the same number of GEMMs each), or that share of a busy-wait.
 int burst(fr_load* l, const std::vector<GemmShape>& list, uint64_t ns, hipStream_t stream, int part = 0, int parts = 1)
@@ -493,9 +471,10 @@ int burst(fr_load* l, const std::vector<GemmShape>& list, uint64_t ns, hipStream
     if (l->d.layers % parts != 0) return FR_ERR_ARG;
     const size_t per_layer = list.size() / (size_t)l->d.layers, layers = (size_t)l->d.layers / (size_t)parts;
     uint16_t* ws = static_cast<uint16_t*>(l->d.workspace);
+    const int cus = (int)fr_stream_cus(stream);
     for (size_t i = (size_t)part * layers * per_layer; i < ((size_t)part + 1) * layers * per_layer; ++i) {
         const GemmShape& g = list[i];
-        int rc = gemm_launch(ws + g.a_off, ws + g.b_off, ws + g.c_off, g.M, g.N, g.K, stream);
+        int rc = gemm_launch_tile(gemm_choose(g.M, g.N, g.K, cus), ws + g.a_off, ws + g.b_off, ws + g.c_off, g.M, g.N, g.K, stream);
         if (rc != FR_OK) return rc;
     }
     return FR_OK;
@@ -523,11 +502,17 @@ extern "C" {
 
 int fr_gemm_bf16(const void* A, const void* B, void* C, int32_t M, int32_t N, int32_t K, void* stream)
 {
-    if (!A || !B || !C || M <= 0 || N <= 0 || K <= 0) return FR_ERR_ARG;
-    if (M % 256 || N % 256 || K % 64) return FR_ERR_ARG;
-    if (((uintptr_t)A | (uintptr_t)B | (uintptr_t)C) & 15) return FR_ERR_ARG;
-    if ((uint64_t)(M / 64) * (uint64_t)(N / 64) > 0x7fffffffull) return FR_ERR_ARG;
-    return gemm_launch(A, B, C, M, N, K, (hipStream_t)stream);
+    int rc = gemm_check(A, B, C, M, N, K);
+    return rc != FR_OK ? rc : gemm_launch_tile(gemm_choose(M, N, K, (int)fr_stream_cus((hipStream_t)stream)), A, B, C, M, N, K, (hipStream_t)stream);
+}
+
+// fr_gemm_bf16 with the tile given (not part of the interface: the library's own tests and timings run every tile with it).
+int fr_gemm_bf16_tile(const void* A, const void* B, void* C, int32_t M, int32_t N, int32_t K, int32_t tile, void* stream)
+{
+    int rc = gemm_check(A, B, C, M, N, K);
+    if (rc != FR_OK) return rc;
+    if (tile < 0 || tile >= kGemmTiles) return FR_ERR_ARG;
+    return gemm_launch_tile(tile, A, B, C, M, N, K, (hipStream_t)stream);
 }
 
 int fr_load_workspace_bytes(const fr_load_desc* d, uint64_t* bytes_out)

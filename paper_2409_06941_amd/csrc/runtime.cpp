@@ -748,11 +748,22 @@ void fr_alloc_release(fr_alloc* a)
 
 uint32_t fr_stream_cus(hipStream_t stream)
 {
-    int device = 0, cus = 0;
-    if (hipGetDevice(&device) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess || cus <= 0) {
-        (void)hipGetLastError();
-        cus = 256;
+    // (a device's number of units never changes: asked for once; a stream's mask goes with the stream, and a handle may be used
+    // again for another one: asked for every time, 0.1 us)
+    static std::atomic<int> units[64];
+    int device = 0;
+    if (hipGetDevice(&device) != hipSuccess) { (void)hipGetLastError(); device = -1; }
+    const bool known = device >= 0 && device < 64;
+    int cus = known ? units[device].load(std::memory_order_relaxed) : 0;
+    if (cus <= 0) {
+        if (device < 0 || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess || cus <= 0) {
+            (void)hipGetLastError();
+            cus = 256;
+        } else if (known) {
+            units[device].store(cus, std::memory_order_relaxed);
+        }
     }
+    if (!stream) return (uint32_t)cus;    // the default stream has no mask
     uint32_t mask[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     if (hipExtStreamGetCUMask(stream, 8, mask) == hipSuccess) {
         int masked = 0;

@@ -46,6 +46,36 @@ def test_every_tile_shape_matches_oracle(M, N, K):
     test_gemm_matches_oracle(M, N, K)
 
 
+def test_streams_with_few_units_and_captured_graphs():
+    # the choice of a tile asks the stream for its units: a masked stream, and a stream that is capturing
+    M, N, K = 512, 2816, 320
+    a, b = gemm_inputs.operands(M, N, K, seed=3)
+    A, B = _to_dev_bf16(a), _to_dev_bf16(b)
+    Cm = torch.zeros((M, N), dtype=torch.int16, device="cuda")
+    want = gemm_nt(a, b)
+    bound = np.abs(want) * 2.0 ** -8 + K * K * 2.0 ** -24 + 1e-30
+
+    def check():
+        torch.cuda.synchronize()
+        got = gemm_inputs.bits_to_f32(Cm.cpu().numpy().view(np.uint16)).astype(np.float64)
+        assert np.all(np.abs(got - want) <= bound)
+        Cm.zero_()
+    for cus in (8, 64):
+        print("units", cus, flush=True)
+        ctx = fr.Context(device_id=0, cu_count=cus)
+        torch.cuda.synchronize()
+        fr.fr_gemm_bf16(A, B, Cm, M, N, K, ctx.fr_side_stream())
+        check()
+        ctx.fr_destroy()
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph):
+        fr.fr_gemm_bf16(A, B, Cm, M, N, K, torch.cuda.current_stream())
+    for _ in range(3):
+        graph.replay()
+        check()
+
+
 def test_identity_and_shape_errors():
     M = N = K = 256
     a, _ = gemm_inputs.operands(M, N, K, seed=1)

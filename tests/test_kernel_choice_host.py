@@ -120,3 +120,32 @@ def test_least_scatter_tile(pr):
         assert pr.least(all_) == all_                           # one tile
     assert pr.least(16_385) == pr.least(26_000) == 4096         # several
     assert pr.least(1 << 26) == 6 * 8192
+
+
+@pytest.fixture(scope="module")
+def gemm(tmp_path_factory):
+    L = _compile(tmp_path_factory, "gemm_tiles", '''#include "gemm_tiles.h"
+extern "C" int choose(int M, int N, int K, int cus) { return gemm_choose(M, N, K, cus); }
+extern "C" int tiles(void) { return kGemmTiles; }
+''')
+    return L
+
+
+# (compute units of the stream, (M, N, K), us with every tile, operands not in a cache)
+GEMM_MEASURED = [
+    (32, (256, 15616, 1216), [59.1, 92.6, 89.1, 132.1, 193.7, 226.1, 73.4]), (32, (512, 11008, 64), [24.9, 28.8, 21.5, 25.1, 37.4, 104.5, 15.7]),
+    (32, (256, 16384, 16384), [567.3, 912.0, 1034.4, 1638.0, 2518.4, 2432.0, 858.0]), (32, (1280, 3840, 192), [30.4, 30.1, 24.6, 30.2, 43.1, 98.0, 22.1]),
+    (64, (256, 15616, 1216), [31.7, 48.4, 47.5, 68.2, 100.4, 117.1, 38.2]), (64, (512, 11008, 64), [17.4, 15.9, 12.7, 14.9, 20.5, 54.8, 9.6]),
+    (64, (2048, 2048, 128), [10.4, 11.6, 9.4, 11.0, 15.8, 41.5, 8.3]), (64, (256, 16384, 16384), [301.8, 468.3, 530.9, 824.1, 1281.0, 1214.4, 434.1]),
+    (64, (512, 15104, 1024), [50.7, 73.1, 70.1, 106.6, 159.0, 185.1, 61.7]), (64, (1792, 4096, 640), [35.4, 46.6, 39.7, 51.3, 77.9, 111.7, 41.4]),
+    (128, (256, 15616, 1216), [31.7, 26.6, 26.6, 37.2, 51.9, 61.2, 28.8]), (128, (512, 11008, 64), [10.2, 11.5, 8.8, 9.2, 11.9, 28.8, 7.3]),
+    (128, (256, 16384, 16384), [300.6, 248.6, 280.6, 424.9, 646.5, 636.8, 335.7]), (128, (512, 15104, 1024), [28.3, 39.1, 39.7, 57.9, 85.9, 94.5, 34.0]),
+    (256, (256, 15616, 1216), [31.7, 26.6, 19.4, 21.7, 28.2, 32.5, 28.7]), (256, (2048, 2048, 128), [10.4, 7.1, 5.5, 5.1, 6.2, 12.3, 6.3]),
+    (256, (256, 16384, 16384), [318.9, 249.8, 204.2, 229.6, 331.6, 332.0, 342.9]), (256, (1792, 4096, 640), [20.7, 16.1, 15.1, 19.5, 25.5, 34.1, 17.8]),
+]
+
+
+def test_gemm_tiles_are_the_fast_ones_of_every_measured_size(gemm):
+    assert gemm.tiles() == 7
+    for cus, shape, us in GEMM_MEASURED:
+        assert us[gemm.choose(*shape, cus)] <= 1.1 * min(us), (cus, shape)
