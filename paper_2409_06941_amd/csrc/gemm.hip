@@ -511,7 +511,7 @@ int fr_gemm_bf16_tile(const void* A, const void* B, void* C, int32_t M, int32_t 
 {
     int rc = gemm_check(A, B, C, M, N, K);
     if (rc != FR_OK) return rc;
-    if (tile < 0 || tile >= kGemmTiles) return FR_ERR_ARG;
+    if (tile < 0 || tile >= kGemmTiles || (K > kRingMostK && tile != kGemmTiles - 1)) return FR_ERR_ARG;
     return gemm_launch_tile(tile, A, B, C, M, N, K, (hipStream_t)stream);
 }
 

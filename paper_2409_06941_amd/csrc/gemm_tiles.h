@@ -32,6 +32,9 @@ inline float gemm_estimate(const GemmTile& T, int M, int N, int K, int cus)
     return T.start * std::max(1.0f, v / T.side_by_side) + nk * (v <= 1.0f ? T.alone + (T.full - T.alone) * v : T.full + (v - 1.0f) * T.more);
 }
 
+// The ring kernels' loads reach eight rows from one address with a 32-bit offset: rows of up to 2^28 bytes.  A longer K takes
+// k_gemm_bf16_nt_short, whose addresses have 64 bits.
+constexpr int kRingMostK = 1 << 27;
 constexpr int kGemmTiles = (int)(sizeof(kTiles) / sizeof(kTiles[0]));
 
 // The tile (its place in kTiles) that takes least on `cus` compute units: those the stream may use.  (For all 256, on a stream of
@@ -39,6 +42,7 @@ constexpr int kGemmTiles = (int)(sizeof(kTiles) / sizeof(kTiles[0]));
 // throughout.)
 inline int gemm_choose(int M, int N, int K, int cus)
 {
+    if (K > kRingMostK) return kGemmTiles - 1;
     int best = 0;
     float least = gemm_estimate(kTiles[0], M, N, K, cus);
     for (int k = 1; k < kGemmTiles; ++k) {

@@ -149,3 +149,12 @@ def test_gemm_tiles_are_the_fast_ones_of_every_measured_size(gemm):
     assert gemm.tiles() == 7
     for cus, shape, us in GEMM_MEASURED:
         assert us[gemm.choose(*shape, cus)] <= 1.1 * min(us), (cus, shape)
+
+
+def test_gemm_rows_beyond_a_32_bit_offset_take_the_kernel_with_64_bit_addresses(gemm):
+    for cus in (16, 256):
+        for M, N in ((256, 256), (256, 512)):                   # (A and B may be one buffer: 2^29 values of K fit the memory)
+            for K in (306_783_424, 1 << 29, 2_147_483_584):
+                assert 7 * 2 * K + 112 >= 1 << 32 and gemm.choose(M, N, K, cus) == gemm.tiles() - 1
+            assert gemm.choose(M, N, (1 << 27) + 64, cus) == gemm.tiles() - 1
+            assert 0 <= gemm.choose(M, N, 1 << 27, cus) < gemm.tiles() - 1 and 7 * 2 * (1 << 27) + 112 < 1 << 31
