@@ -51,7 +51,8 @@ __device__ __forceinline__ void plain_barrier()
 
 // Global memory to LDS, 16 bytes a lane, without passing through registers: lane l's bytes go to LDS address m0 + 16 l.
 // (Written as assembly so that the compiler does not wait for every load in flight before each read of LDS: which loads
-// have to be here is counted by hand, wait_loads.)
+// have to be here is counted by hand, wait_loads.  m0 is a reserved register: the compiler keeps no value in it, and refuses it
+// in a list of clobbers; it would write it for an instruction of its own that needs it, of which there are none here.)
 __device__ __forceinline__ void aim_lds(uint32_t lds) { asm volatile("s_mov_b32 m0, %0" ::"s"(lds) : "memory"); }
 __device__ __forceinline__ void load_to_lds(uint32_t lane_offset, const char* g)
 {

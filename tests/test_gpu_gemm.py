@@ -1,4 +1,6 @@
 """GPU parity of the stage-load GEMM (bf16 MFMA, fp32 accumulate) against the fp64 oracle."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -37,13 +39,30 @@ def test_gemm_matches_oracle(M, N, K):
     assert np.mean(got == nearest) > 0.98
 
 
-# every kernel where the choice by size takes it, with ragged counts: 64 x 64 (one k-tile; few tiles of a small K), 64 x 64 with
-# K in four parts (k-tiles that do not divide by four), 64 x 128, 128 x 128, 128 x 256, 256 x 256 with bands that are cut short, and
-# the one for a short K and many tiles
+# sizes on both sides of the lines between the tiles as the choice draws them on 256 units, through the public call
 @pytest.mark.parametrize("M,N,K", [(256, 256, 64), (512, 768, 448), (256, 512, 2624), (512, 256, 4160), (1024, 1536, 512),
                                    (1280, 1536, 1216), (2048, 4096, 320), (2048, 4096, 1088), (4352, 3840, 1216), (3328, 4608, 64)])
 def test_every_tile_shape_matches_oracle(M, N, K):
     test_gemm_matches_oracle(M, N, K)
+
+
+# every tile, whatever the choice would be: one, two and three k-tiles, odd and even counts, counts that do not divide by
+# four (K in four parts), and a band of rows that is cut short
+@pytest.mark.parametrize("tile", range(7))
+@pytest.mark.parametrize("M,N,K", [(256, 256, 64), (256, 512, 128), (512, 256, 192), (256, 256, 320), (512, 768, 448), (1280, 512, 512), (256, 256, 1216)])
+def test_each_tile_matches_oracle(tile, M, N, K):
+    print("gemm tile", tile, M, N, K, flush=True)
+    a, b = gemm_inputs.operands(M, N, K, seed=M + N + K)
+    A, B = _to_dev_bf16(a), _to_dev_bf16(b)
+    Cm = torch.zeros((M, N), dtype=torch.int16, device="cuda")
+    f = fr.lib().fr_gemm_bf16_tile
+    f.argtypes = [ctypes.c_void_p] * 3 + [ctypes.c_int32] * 4 + [ctypes.c_void_p]
+    assert f(A.data_ptr(), B.data_ptr(), Cm.data_ptr(), M, N, K, tile, torch.cuda.current_stream().cuda_stream) == fr.FR_OK
+    torch.cuda.synchronize()
+    got = gemm_inputs.bits_to_f32(Cm.cpu().numpy().view(np.uint16)).astype(np.float64)
+    want = gemm_nt(a, b)
+    assert np.all(np.abs(got - want) <= np.abs(want) * 2.0 ** -8 + K * K * 2.0 ** -24 + 1e-30)      # as in test_gemm_matches_oracle
+    assert f(A.data_ptr(), B.data_ptr(), Cm.data_ptr(), M, N, K, 7, None) == fr.FR_ERR_ARG
 
 
 def test_streams_with_few_units_and_captured_graphs():
