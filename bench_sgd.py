@@ -11,6 +11,23 @@ import time
 HBM_PEAK_GBS = 8000.0        # MI355X HBM3E, published
 
 
+def group_ratios(events, chunk_kind, launch_ns):
+    """Measured over modelled time of every timing group (consecutive steps of one bubble, the last of which has the time).  The
+    log's modelled_ns has the context's launch cost in it, which is no part of the model that the ratio corrects."""
+    ratios, group = [], []
+    for e in events:
+        if e.kind != chunk_kind:
+            group = []
+            continue
+        if group and group[-1].bubble != e.bubble:
+            group = []
+        group.append(e)
+        if e.measured_ns > 0:
+            ratios.append(e.measured_ns / sum(x.modelled_ns - launch_ns for x in group))
+            group = []
+    return ratios
+
+
 def run(args, stage_load, log):
     import numpy as np
     import torch
@@ -75,24 +92,15 @@ def run(args, stage_load, log):
 
     # second profiling pass, in place: what the steps cost inside real bubbles (launch gaps included) against what the
     # derated standalone model says; the final model is the measured cost plus a margin
-    ctx, task, tid = start_task(5_000, model)
+    calibration_launch_ns = 5_000
+    ctx, task, tid = start_task(calibration_launch_ns, model)
     for _ in range(3):
         stage.fr_stage_run_epoch(ctx)
     time.sleep(0.02)
     ctx.fr_event_log_clear()
     stage.fr_stage_run_epoch(ctx)
     time.sleep(0.02)
-    ratios, group = [], []
-    for e in ctx.fr_event_log(1 << 18):
-        if e.kind != fr.FR_EV_CHUNK:
-            group = []
-            continue
-        if group and group[-1].bubble != e.bubble:
-            group = []
-        group.append(e)
-        if e.measured_ns > 0:
-            ratios.append(e.measured_ns / sum(x.modelled_ns for x in group))
-            group = []
+    ratios = group_ratios(ctx.fr_event_log(1 << 18), fr.FR_EV_CHUNK, calibration_launch_ns)
     ctx.fr_task_stop(tid); task.fr_sgd_destroy(); ctx.fr_destroy()
     in_bubble = statistics.quantiles(ratios, n=4)[2] if len(ratios) >= 4 else 1.0      # upper quartile: strata differ
     log("in-bubble step cost = model x %.3f (%d timing groups of %d steps, min %.3f max %.3f)" %
@@ -157,7 +165,7 @@ def run(args, stage_load, log):
         "standalone_iteration_ms": ns / 1e6, "largest_cell": info.largest_cell,
         "roofline": {"kernel": "k_sgd<%d>" % F, "bound": "hbm", "achieved": gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": gbs / HBM_PEAK_GBS, "traffic": None, "bytes_per_rating": bytes_per_rating,
-                     "note": "latency-bound: one sequential chain of updates per cell, %d cells side by side" % B},
+                     "note": "latency-bound: the longest chain of updates linked by a user or an item in one of %d cells side by side" % B},
     }
     if not args.no_cpu_baseline:
         from oracle import sgd as osgd

@@ -2,6 +2,9 @@
 import os
 import subprocess
 import sys
+from types import SimpleNamespace
+
+import bench_sgd
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -21,3 +24,12 @@ def test_more_than_one_gpu_is_refused_with_a_message():
     r = _bench("--gpus", "2")
     assert r.returncode != 0
     assert "one GPU" in (r.stdout + r.stderr)
+
+
+def test_sgd_calibration_leaves_the_launch_cost_out_of_the_model():
+    # steps of 14 us, modelled at 20 and logged with 5 for the launch: the model is to be scaled by 14 / 20, not by 14 / 25 (which
+    # is a bubble planned a fifth too full)
+    def step(bubble, measured=0, kind=1):
+        return SimpleNamespace(kind=kind, bubble=bubble, modelled_ns=25_000, measured_ns=measured)
+    log = [step(0), step(0), step(0, 42_000), step(0), step(0, kind=2), step(0), step(0, 28_000), step(0), step(1), step(1, 28_000)]
+    assert bench_sgd.group_ratios(log, 1, 5_000) == [0.7, 0.7, 0.7]
