@@ -84,8 +84,9 @@ constexpr uint32_t slot_bytes(int BM, int BN) { return (uint32_t)(BM > BN ? BM :
 // The operands are swapped in the MFMA (B first), which leaves a lane four consecutive columns of one row, and with B's rows
 // taken as above eight, so that rows of C are written in pieces of 64 bytes.
 //
-// What bounds it: on large products the matrix cores are busy 66 - 88 % of the time at 1.8 - 2.1 GHz, to which the chip
-// lowers its clock under this load (2.4 GHz otherwise); writing C takes 3 - 6 us a tile with all compute units at it at
+// What bounds it: on large products the matrix cores are busy 68 - 76 % of the time with tiles of 256 x 256 and 48 - 51 % with 128 x
+// 256 (counted in the bursts of the stage load), at 1.8 - 2.05 GHz, to which the chip lowers its clock under this load (2.4 GHz
+// otherwise); writing C takes 3 - 6 us a tile with all compute units at it at
 // once.  Measured, bf16 values uniform in [-1/8, 1/8):
 //   8192 x 8192 x 8192     720 us  1530 TFLOP/s      2048 x 16384 x 4096   179 - 207 us  1330 - 1540 TFLOP/s
 //   2048 x 4096 x 16384    200 us  1370              16384 x 4096 x 2048   195 - 212 us  1300 - 1410

@@ -975,23 +975,6 @@ bool take(fr_alloc* a, T** out, uint64_t count)
     return *out != nullptr;
 }
 
-// Compute units the stream may use (its CU mask, if it has one): the sweeps are cut into that many tiles.
-uint32_t stream_cus(hipStream_t stream)
-{
-    int device = 0, cus = 0;
-    if (hipGetDevice(&device) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess || cus <= 0)
-        cus = (int)kDefaultCus;
-    uint32_t mask[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    if (hipExtStreamGetCUMask(stream, 8, mask) == hipSuccess) {
-        int masked = 0;
-        for (uint32_t w : mask) masked += __builtin_popcount(w);
-        if (masked > 0 && masked < cus) cus = masked;
-    } else {
-        (void)hipGetLastError();          // a stream without a mask of its own
-    }
-    return (uint32_t)cus;
-}
-
 int pr_init(void* user, fr_alloc* a, void* stream_v)
 {
     PrTask* p = static_cast<PrTask*>(user);
@@ -1002,7 +985,7 @@ int pr_init(void* user, fr_alloc* a, void* stream_v)
     const uint64_t caller = 4ull * (uint64_t)(V + 1) + 4ull * (uint64_t)E + 4ull * (uint64_t)V + 4ull * (uint64_t)V;
     if (fr_alloc_charge(a, caller) != FR_OK) return FR_ERR_OOM;
     int rc = pr_build_layout(&p->L, V, E, p->d.row_ptr, p->d.col, p->d.out_degree, p->d.rows_per_partition,
-                             p->d.sources_per_partition, stream_cus(stream), a, stream, &p->hip_error);
+                             p->d.sources_per_partition, fr_stream_cus(stream), a, stream, &p->hip_error);
     if (rc != FR_OK) return rc;
     PrLayout& L = p->L;
     // dangling partials: one slot per range (V0), or one per gather piece followed by one per scatter piece

@@ -54,10 +54,10 @@
 
 constexpr uint32_t kIdChunk = 512;           // ids per wavefront step (8 per lane, 64 apart)
 constexpr uint32_t kStartWords = 12;         // 64-bit words of a chunk's message-start record
-constexpr int kKeyLocalBits = 15;            // sort key = range << 46 | source << 15 | local row
+constexpr int kKeyLocalBits = 15;            // sort key = range << (15 + bits of a source) | source << 15 | local row
 constexpr uint32_t kLocalMask = (1u << kKeyLocalBits) - 1;
 static_assert(kRowsLarge <= (1u << kKeyLocalBits) && kSrcLarge <= 65536, "id fields");
-constexpr int kKeySrcBits = 31;
+constexpr int kKeySrcBits = 31;             // of a source, at most
 constexpr uint32_t kDefaultCus = 256;        // heavy ranges and source intervals are cut for this many workgroups side by side ...
 constexpr uint64_t kMinTileEdges = 24576;    // ... but no smaller than this (in weight: times kGatherEdgeWeight)
 // (2^14 vertices / 2^18 edges: 12 + 8 tiles of at least 32768 edges and 16384 messages take 18.6 us an iteration, 23 + 51

@@ -153,12 +153,13 @@ typedef float float4_any __attribute__((ext_vector_type(4), aligned(4)));
 // side by side in one wavefront, laid out once by k_sgd_schedule.  All four wavefronts bring the batch's rows to LDS, the
 // first one works through the rounds, all four write the rows back.
 // What bounds it: the longest chain of a stratum (16.1 M ratings, 512 x 512 cells, 64 factors: 85 updates, where its largest
-// cell has 109 ratings and a mean cell 61), at 95 ns a round: one wavefront's instructions, some forty, and the latency of
-// the sum's dependent moves.  Hence 32 lanes with two factors each (90.7 rounds) and not 16 with four (87.5 rounds of half as
-// many instructions again), rows fetched from LDS a round ahead, before the stores of the round that is being computed,
-// and the row of a chain handed on in registers.  A stratum takes 16.4 us there: 8.6 us of rounds, the rest is fetching and
-// storing 42 000 rows (21 MB, 2.8 TB/s) and the launch.  An iteration of 512 strata takes 8.6 ms; one rating after the other
-// straight from memory, as k_sgd_chain does it, it took 23.7 ms (16 factors, 300 000 ratings in 64 x 64 cells: 0.47 and 2.0 ms).
+// cell has 109 ratings and a mean cell 61), at 105 ns a round with 64 factors, 94 with 32, 80 with 16 (a cell that is one chain of
+// n ratings takes 2.2 us + n rounds): one wavefront's instructions, some forty, and the latency of the sum's dependent moves.
+// Hence 32 lanes with two factors each (90.7 rounds) and not 16 with four (87.5 rounds of half as many instructions again),
+// rows fetched from LDS a round ahead, before the stores of the round that is being computed, and the row of a chain handed on
+// in registers.  A stratum takes 15 us there, of which the rounds are some 9.5; the rest is fetching and storing 42 000 rows (21 MB) and the
+// launch.  An iteration of 512 strata takes 7.7 ms; one rating after the other straight from memory, as k_sgd_chain does it, it
+// took 21.9 ms (16 factors, 300 000 ratings in 64 x 64 cells: 0.46 and 1.9 ms).
 template <int F, int kLanes>
 __device__ __forceinline__ void run_rounds(LdsBytes entries, uint32_t rounds, float gamma, float gl)
 {
