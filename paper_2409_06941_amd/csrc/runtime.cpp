@@ -709,16 +709,25 @@ namespace {
 // takes part; then at most 1/64 of the device's memory and kBlocks blocks are kept.  There is no thread that watches their
 // age: a block unused for kKeepNs is given back by the next set-up, or the next task with kept scratch that is destroyed; all are when a context
 // is made or destroyed, when an allocation of the library fails, and by fr_scratch_release.
-uint64_t total_memory()
+// (it never changes: asked for once a device)
+uint64_t total_memory(int device)
 {
-    size_t free_bytes = 0, total = 0;
-    return hipMemGetInfo(&free_bytes, &total) == hipSuccess ? total : 0;
+    static std::atomic<uint64_t> known[64];
+    if (device < 0 || device >= 64) return 0;
+    uint64_t bytes = known[device].load(std::memory_order_relaxed);
+    if (!bytes) {
+        size_t total = 0;
+        if (hipDeviceTotalMem(&total, device) != hipSuccess) { (void)hipGetLastError(); return 0; }
+        bytes = total;
+        known[device].store(bytes, std::memory_order_relaxed);
+    }
+    return bytes;
 }
 
 struct DeviceMemory {
     static void free(void* p) { (void)hipFree(p); }
     static uint64_t now_ns() { return ::now_ns(); }
-    static uint64_t keep_at_most(int) { return total_memory() / 64; }
+    static uint64_t keep_at_most(int device) { return total_memory(device) / 64; }
 };
 ScratchPool<DeviceMemory> g_pool;
 
@@ -793,7 +802,7 @@ void* fr_alloc_scratch(fr_alloc* a, size_t bytes)
     const uint64_t rounded = std::max<uint64_t>(256, ((uint64_t)bytes + 255) & ~255ull);
     if (rounded > a->limit || a->used > a->limit - rounded) { a->oom = true; return nullptr; }
     uint64_t room = rounded;
-    void* p = g_pool.take(a->device, rounded, most_room(a->limit, total_memory(), rounded), &room);
+    void* p = g_pool.take(a->device, rounded, most_room(a->limit, total_memory(a->device), rounded), &room);
     if (!p) {
         hipError_t e = malloc_device(&p, rounded);
         if (e != hipSuccess) { a->hip_error = (int)e; a->oom = true; return nullptr; }
