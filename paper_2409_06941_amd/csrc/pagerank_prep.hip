@@ -628,7 +628,7 @@ int pr_build_layout(PrLayout* L, int64_t V, int64_t E, const int32_t* row_ptr, c
         // sweep is long against what a tile costs to start and to end (kGatherFineShare), heavy ranges are cut for
         // two pieces per slot and every piece is a tile of its own, so that the many light tiles at the end fill
         // the gaps the heavy ones leave; below that there are no more tiles than slots, light pieces share tiles, and
-        // `body` is the smallest (to 2 %) that achieves it.
+        // `body` is the smallest (to 2 %) that achieves it (least_gather_weight, kLeastGatherOfTwo).
         std::vector<uint64_t> w(Qe);
         uint64_t total = 0, heaviest = 0;
         for (uint32_t j = 0; j < Qe; ++j) {
@@ -640,12 +640,12 @@ int pr_build_layout(PrLayout* L, int64_t V, int64_t E, const int32_t* row_ptr, c
         const uint64_t slots = (uint64_t)cus * (alone ? 1 : 2);
         const uint64_t share = (total + slots - 1) / slots;
         const uint64_t fine = share >= kGatherFineShare ? 2 : 1;
-        const uint64_t least = std::max<uint64_t>(kMinTileEdges * kGatherEdgeWeight, (uint64_t)((double)kMergeBalance * std::sqrt((double)heaviest)));
+        const uint64_t least = least_gather_weight(rows_per_part, heaviest);
         std::vector<GatherPiece> pieces;
         std::vector<uint64_t> piece_w;
         std::vector<uint2> tiles;
         uint64_t body = std::max<uint64_t>(least, (total + slots * fine - 1) / (slots * fine));
-        for (int round = 0; round < 400; ++round, body += body / 50 + 1) {
+        for (int round = 0; round < 400; ++round) {
             pieces.clear(); piece_w.clear(); tiles.clear();
             L->ri.assign(Q, RangeInfo{kRangeEmpty, 0});
             L->fin.clear();
@@ -688,7 +688,10 @@ int pr_build_layout(PrLayout* L, int64_t V, int64_t E, const int32_t* row_ptr, c
                 in_tile += piece_w[i];
             }
             tiles.push_back(make_uint2(first, (uint32_t)pieces.size()));
-            if (fine > 1 || tiles.size() <= slots) break;
+            if (fine > 1) break;
+            if (!alone && tiles.size() > cus && body < kLeastGatherOfTwo) { body = kLeastGatherOfTwo; continue; }      // some units have two
+            if (tiles.size() <= slots) break;
+            body += body / 50 + 1;
         }
         for (uint32_t j = Qe; j < Q; ++j) L->fin.push_back(j);
         L->gp = pieces;

@@ -58,10 +58,7 @@ constexpr int kKeyLocalBits = 15;            // sort key = range << (15 + bits o
 constexpr uint32_t kLocalMask = (1u << kKeyLocalBits) - 1;
 static_assert(kRowsLarge <= (1u << kKeyLocalBits) && kSrcLarge <= 65536, "id fields");
 constexpr int kKeySrcBits = 31;             // of a source, at most
-constexpr uint32_t kDefaultCus = 256;        // heavy ranges and source intervals are cut for this many workgroups side by side ...
-constexpr uint64_t kMinTileEdges = 24576;    // ... but no smaller than this (in weight: times kGatherEdgeWeight)
-// (2^14 vertices / 2^18 edges: 12 + 8 tiles of at least 32768 edges and 16384 messages take 18.6 us an iteration, 23 + 51
-// tiles 16.2, 45 + 95 tiles 16.6; a piece's fixed weight counts against a step's budget, so the gather sweep stays coarser)
+constexpr uint32_t kDefaultCus = 256;        // heavy ranges and source intervals are cut for this many workgroups side by side
 // weight of a gather tile = kGatherEdgeWeight * edges + kGatherMessageWeight * messages + kGatherRepeatWeight *
 // repeated edges + kTileFixedWeight
 constexpr uint64_t kGatherEdgeWeight = 2, kGatherMessageWeight = 0, kGatherRepeatWeight = 6, kTileFixedWeight = 147456;
@@ -72,11 +69,6 @@ constexpr uint64_t kScatterMessageWeight = 1, kScatterRowWeight = 1, kScatterFix
 // piece a tile (measured: 2^24 vertices / 2^28 edges gains 15 % in the gather sweep and nothing in the scatter sweep,
 // 2^26 / 2^30 gains 20 % and 24 %, 2^22 / 2^26 loses in both; three, four or six pieces per slot are no better than two)
 constexpr uint64_t kGatherFineShare = 2000000, kScatterFineShare = 1000000;
-
-// Pieces of a range weigh at least kMergeBalance x sqrt(weight of the heaviest range): a row of a range cut into n pieces
-// costs the scatter sweep n loads, a piece costs the gather sweep its own weight, and the sum of both is least where
-// the pieces weigh as the root of the range (2^18 vertices / 2^22 edges: 162 pieces 22.8 us, 256 24.9, 313 28.9).
-constexpr uint64_t kMergeBalance = 29;
 
 // An id is stored as the byte offset of its row's 8-byte accumulator, or half of it where that needs 17 bits.
 constexpr uint32_t id_scale_for(uint32_t rows_per_part) { return rows_per_part <= 8192 ? 8u : 4u; }

@@ -39,6 +39,24 @@ inline bool gather_alone(uint32_t rows_per_part, uint32_t Qe, uint64_t total, ui
     return rows_per_part == kRowsLarge || (2 * Qe <= cus && total <= (uint64_t)cus * (cus < 64 ? 64 : cus) * kGatherAloneShare);
 }
 
+// Gather pieces weigh at least kLeastGather (two an edge, some for repeated ones), or kMergeBalance x the root of the heaviest
+// range's weight: a row of a range cut into n pieces costs the scatter sweep n loads, a piece costs the gather sweep its own
+// weight, and the sum of both is least where the pieces weigh as the root of the range (2^18 vertices / 2^22 edges: 162 pieces 22.8 us
+// an iteration, 256 24.9, 313 28.9).  (2^14 vertices / 2^18 edges: 12 + 8 tiles of at least 65536 and of 16384 messages 18.6 us, 23 + 51 tiles
+// 16.2, 45 + 95 tiles 16.6; a piece's fixed weight counts against a step's budget, so the gather sweep stays coarser.)
+// Where two workgroups share a unit and the sweep makes more tiles than there are units, light ranges would be cut in two for
+// nothing: pieces weigh kLeastGatherOfTwo there.  us an iteration, uniform graphs, 49152 -> 65536: 1.6 x 10^6 / 6.1 x 10^6 (315 -> 260
+// tiles) 37.6 -> 35.6, 2.5 x 10^6 / 8.5 x 10^6 (449 -> 378) 46.7 -> 43.6, on 64 units 600 000 / 1.8 x 10^6 (100 -> 86) 32.4 -> 31.4, on 128
+// 1.2 x 10^6 / 3.6 x 10^6 (199 -> 170) 36.4 -> 34.8.  Likewise with the large ranges, whose rows of partial sums are twice as long (skewed
+// 4.3 x 10^6 / 3 x 10^6 29.8 -> 29.4, 9 x 10^6 / 6.3 x 10^6 35.2 -> 35.8).  Partial sums count against the memory of the run that allocates
+// nothing: 3 x 10^6 / 9 x 10^6 took 54.2 MB of its 64 and takes 50.0.
+constexpr uint64_t kLeastGather = 49152, kLeastGatherOfTwo = 65536, kMergeBalance = 29;
+inline uint64_t least_gather_weight(uint32_t rows_per_part, uint64_t heaviest)
+{
+    const uint64_t least = rows_per_part == kRowsLarge ? kLeastGatherOfTwo : kLeastGather, balance = (uint64_t)((double)kMergeBalance * std::sqrt((double)heaviest));
+    return balance > least ? balance : least;
+}
+
 // Scatter: up to kScatterAloneShare (messages and values read) a unit per unit, or kScatterAloneLeast a unit on fewer than 171;
 // beyond it one workgroup cannot keep a unit's share of the bandwidth busy.  us an iteration, two a unit -> one, at these
 // thousands a unit:

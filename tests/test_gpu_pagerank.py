@@ -412,6 +412,33 @@ def test_set_up_memory_kept_between_graphs_changes_nothing_and_is_given_back():
     assert before - torch.cuda.mem_get_info()[0] <= 4 << 20
 
 
+# light ranges (weight: two an edge): pieces of at least 65536 where the sweep makes more of them than there are units, or
+# ranges are of 16384 rows; of 49152 where there are units enough
+@pytest.mark.parametrize("V,E,rows,cus,least", [(300_007, 900_001, 8192, 32, 65536), (300_007, 900_001, 16384, 256, 65536), (300_007, 900_001, 8192, 256, 49152)])
+def test_light_ranges_are_not_cut_for_nothing(V, E, rows, cus, least):
+    rng = np.random.default_rng(8)
+    edges = np.unique((np.arange(E) % V).astype(np.int64) * V + rng.integers(0, V, E))             # (none repeated)
+    g = graphs.csr_from_edges(V, edges // V, edges % V)
+    rp, col, od = _dev(g.row_ptr, torch.int32), _dev(g.col, torch.int32), _dev(g.out_degree, torch.int32)
+    ctx = fr.Context(device_id=0, cu_count=cus)
+    ranks = torch.zeros(V, dtype=torch.float32, device="cuda")
+    torch.cuda.synchronize()
+    t = fr.PageRankTask(V, g.n_edges, rp, col, od, ranks, iterations=4, rows_per_partition=rows)
+    t.fr_pagerank_run_standalone(0, ctx.fr_side_stream())
+    info = t.fr_pagerank_info()
+    t.fr_pagerank_destroy()
+    ctx.fr_destroy()
+    in_degree = np.sort(np.diff(g.row_ptr))[::-1]
+    weights = [2 * int(in_degree[r:r + rows].sum()) for r in range(0, V, rows)]
+    pieces = {k: [-(-w // k) for w in weights] for k in (49152, 65536)}              # (the last ranges have no edges)
+    assert sum(pieces[49152]) > sum(pieces[65536])               # (else this test looks at nothing)
+    print("case", V, E, rows, cus, info.gather_tiles, info.partial_rows, flush=True)
+    assert info.gather_tiles == sum(pieces[least]) and info.partial_rows == sum(n for n in pieces[least] if n > 1)
+    want = pagerank(g.row_ptr, g.col, g.out_degree, 0.85, 4)
+    got = ranks.cpu().numpy()
+    assert np.abs(got.astype(np.float64) - want).max() <= TOL and (np.abs(got - want) / want).max() <= 1e-4
+
+
 def test_set_up_memory_goes_back_without_a_context():
     one, other = graphs.rmat_csr(16, 900_000, seed=43), graphs.rmat_csr(16, 800_000, seed=44)
     fr.fr_scratch_release()

@@ -64,11 +64,13 @@ def pr(tmp_path_factory):
     L = _compile(tmp_path_factory, "pr_rules", '''#include "pr_rules.h"
 extern "C" int runs(uint32_t src, int64_t V, uint32_t cus, int hands_out) { return scatter_in_runs(src, V, cus, hands_out != 0); }
 extern "C" int g_alone(uint32_t rows, uint32_t Qe, uint64_t total, uint32_t cus) { return gather_alone(rows, Qe, total, cus); }
+extern "C" uint64_t g_least(uint32_t rows, uint64_t heaviest) { return least_gather_weight(rows, heaviest); }
 extern "C" uint64_t least(uint64_t all) { return least_scatter_weight(all); }
 extern "C" int s_alone(uint32_t src, uint64_t all, uint32_t cus) { return scatter_alone(src, all, cus); }
 ''')
     L.runs.argtypes = [ctypes.c_uint32, ctypes.c_int64, ctypes.c_uint32, ctypes.c_int]
     L.g_alone.argtypes = [ctypes.c_uint32, ctypes.c_uint32, ctypes.c_uint64, ctypes.c_uint32]
+    L.g_least.argtypes, L.g_least.restype = [ctypes.c_uint32, ctypes.c_uint64], ctypes.c_uint64
     L.least.argtypes, L.least.restype = [ctypes.c_uint64], ctypes.c_uint64
     L.s_alone.argtypes = [ctypes.c_uint32, ctypes.c_uint64, ctypes.c_uint32]
     return L
@@ -112,6 +114,11 @@ def test_gather_workgroups_a_unit_are_the_faster_number(pr):
         assert bool(pr.g_alone(8192, Qe, share * 1000 * cus, cus)) == (one < two), (share, cus)
     assert pr.g_alone(16384, 1000, 1 << 40, 16)                 # the large kernel fits once
     assert not pr.g_alone(8192, 9, 1000, 16)                    # fewer than two units a range
+
+
+def test_least_gather_piece(pr):
+    for rows, least in ((8192, 49152), (16384, 65536)):
+        assert pr.g_least(rows, 0) == pr.g_least(rows, 2_800_000) == least and pr.g_least(rows, 1 << 24) == 29 * 4096
 
 
 def test_least_scatter_tile(pr):
