@@ -468,7 +468,9 @@ int pr_build_layout(PrLayout* L, int64_t V, int64_t E, const int32_t* row_ptr, c
         Carve longer, parts;                           // what the keys are made from, and what is only needed for the order
         longer.add(&inv, (uint64_t)V); longer.add(&by_out, (uint64_t)V);
         parts.add(&vk_a, (uint64_t)V); parts.add(&vk_b, (uint64_t)V);
-        parts.add(&t, std::max(sort_bytes, std::max(select_bytes, scan_bytes)));
+        // (the selection and the scan work in a key buffer that is free at the time; too few vertices for that: in `t`)
+        auto in_t = [&](size_t bytes) -> size_t { return bytes > (size_t)V * 8 ? bytes : 0; };
+        parts.add(&t, std::max(sort_bytes, std::max(in_t(select_bytes), in_t(scan_bytes))));
         void* order_block = nullptr;
         if (longer.bytes + parts.bytes <= (uint64_t)E * 8) {
             keys_a = tmp.take<uint64_t>((uint64_t)E);
@@ -486,14 +488,14 @@ int pr_build_layout(PrLayout* L, int64_t V, int64_t E, const int32_t* row_ptr, c
         rocprim::double_buffer<uint64_t> order(vk_a, vk_b);
         hipLaunchKernelGGL(k_vertex_keys_out, dim3(blocks_for((uint64_t)V)), dim3(kBlk), 0, stream, V, top, out_degree, vk_a);
         PREP_HIP(rocprim::radix_sort_keys(t, sort_bytes, order, (size_t)V, 32u, 32u + degree_bits, stream));
-        PREP_HIP(rocprim::select(t, select_bytes, order.current(), by_out, n_no_in, (size_t)V, no_in_edges, stream));
+        PREP_HIP(rocprim::select(in_t(select_bytes) ? (void*)t : (void*)order.alternate(), select_bytes, order.current(), by_out, n_no_in, (size_t)V, no_in_edges, stream));
         order = rocprim::double_buffer<uint64_t>(vk_a, vk_b);
         hipLaunchKernelGGL(k_vertex_keys_in, dim3(blocks_for((uint64_t)V)), dim3(kBlk), 0, stream, V, top, row_ptr, vk_a);
         PREP_HIP(rocprim::radix_sort_keys(t, sort_bytes, order, (size_t)V, 32u, 32u + degree_bits, stream));
         uint32_t* indeg = reinterpret_cast<uint32_t*>(order.alternate());          // V + 1 words where 2 V have room
         hipLaunchKernelGGL(k_perm, dim3(blocks_for((uint64_t)V + 1)), dim3(kBlk), 0, stream, V, order.current(), by_out, n_no_in, row_ptr, out_degree, L->perm, inv, L->inv_out, indeg);
         first = reinterpret_cast<uint32_t*>(by_out);
-        PREP_HIP(rocprim::exclusive_scan(t, scan_bytes, indeg, first, 0u, (size_t)V + 1, rocprim::plus<uint32_t>(), stream));
+        PREP_HIP(rocprim::exclusive_scan(in_t(scan_bytes) ? (void*)t : (void*)order.current(), scan_bytes, indeg, first, 0u, (size_t)V + 1, rocprim::plus<uint32_t>(), stream));
         if (order_block) {
             PREP_HIP(hipStreamSynchronize(stream));
             tmp.drop(order_block);

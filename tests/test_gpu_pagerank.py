@@ -439,6 +439,24 @@ def test_light_ranges_are_not_cut_for_nothing(V, E, rows, cus, least):
     assert np.abs(got.astype(np.float64) - want).max() <= TOL and (np.abs(got - want) / want).max() <= 1e-4
 
 
+# more vertices than edges: while the vertices are ordered a task holds 36 bytes a vertex beside the caller's buffers, and
+# what the sort works in (less than 2 KB at these sizes)
+@pytest.mark.parametrize("V,E", [(20_000, 10_000), (100_000, 70_000)])
+def test_a_limit_of_what_ordering_the_vertices_takes_is_enough(V, E):
+    rng = np.random.default_rng(9)
+    g = graphs.csr_from_edges(V, rng.integers(0, V, E), rng.integers(0, V, E))
+    rp, col, od = _dev(g.row_ptr, torch.int32), _dev(g.col, torch.int32), _dev(g.out_degree, torch.int32)
+    ranks = torch.zeros(V, dtype=torch.float32, device="cuda")
+    torch.cuda.synchronize()
+    limit = 4 * (V + 1) + 4 * E + 8 * V + 36 * V + 2048
+    t = fr.PageRankTask(V, E, rp, col, od, ranks, iterations=3, mem_limit_bytes=limit)
+    t.fr_pagerank_run_standalone(0, torch.cuda.current_stream())
+    assert t.fr_pagerank_info().bytes_peak <= limit
+    t.fr_pagerank_destroy()
+    want = pagerank(g.row_ptr, g.col, g.out_degree, 0.85, 3)
+    assert np.abs(ranks.cpu().numpy().astype(np.float64) - want).max() <= TOL
+
+
 def test_set_up_memory_goes_back_without_a_context():
     one, other = graphs.rmat_csr(16, 900_000, seed=43), graphs.rmat_csr(16, 800_000, seed=44)
     fr.fr_scratch_release()
