@@ -65,23 +65,40 @@ __device__ __forceinline__ float block_sum(float x, float* lds /* one float per 
     return s;
 }
 
-// D = sum of dpart[0 .. n).  Every wavefront adds the whole array up by itself, in one fixed order (lane l takes
-// the elements l, l + 64, l + 128, ... into four running sums in turn; the four are joined pairwise, the lanes by
-// a butterfly), so all wavefronts of all kernels get the same bits, and no barrier stands between the loads of
-// the array and the loads of the work that follows: the sum is only waited for where it is first used.
-__device__ __forceinline__ float dangling_total(const float* __restrict__ dpart, uint32_t n)
+// D = sum of dpart[0 .. n), n >= 1, in one order whatever the kernel: strand i (of kStrands) is the sum of the elements i,
+// i + kStrands, i + 2 kStrands, ... in turn, the strands of a group of 64 are joined by a butterfly, the groups one after the
+// other.  A workgroup of the sweeps has a thread for every strand, so that up to 1024 partials are one load a thread, asked
+// for before the tile's record; the sum is put together behind the next barrier.  (Every wavefront for itself, as it was
+// before, the compiler waited for every fourth element a lane and for each of the last three in front of the tile's first
+// load: 10^6 vertices / 10^7 edges 32.0 -> 31.4 us an iteration, 2^22 / 2^26 77.0 -> 76.2.)
+constexpr uint32_t kStrands = 1024;
+__device__ __forceinline__ float dangling_strand(const float* __restrict__ dpart, uint32_t n, uint32_t i)
 {
-    const uint32_t lane = threadIdx.x & 63;
-    float s0 = 0.0f, s1 = 0.0f, s2 = 0.0f, s3 = 0.0f;
-    uint32_t i = lane;
-    for (; i + 192 < n; i += 256) {
-        const float a = dpart[i], b = dpart[i + 64], c = dpart[i + 128], d = dpart[i + 192];
-        s0 += a; s1 += b; s2 += c; s3 += d;
+    float s = dpart[i < n ? i : n - 1];
+    s = i < n ? s : 0.0f;
+    for (uint32_t j = i + kStrands; j < n; j += 4 * kStrands) {
+        float x[4];
+#pragma unroll
+        for (uint32_t k = 0; k < 4; ++k) x[k] = dpart[j + k * kStrands < n ? j + k * kStrands : n - 1];
+#pragma unroll
+        for (uint32_t k = 0; k < 4; ++k) s += j + k * kStrands < n ? x[k] : 0.0f;
     }
-    if (i < n) s0 += dpart[i];
-    if (i + 64 < n) s1 += dpart[i + 64];
-    if (i + 128 < n) s2 += dpart[i + 128];
-    return wave_sum((s0 + s1) + (s2 + s3));
+    return s;
+}
+
+// The wavefront's strands (64 consecutive ones) go to their group's word; after a barrier the groups are added up.
+__device__ __forceinline__ void dangling_group(float strand, uint32_t first, float* groups)
+{
+    const float s = wave_sum(strand);
+    if ((threadIdx.x & 63) == 0) groups[first / 64] = s;
+}
+
+__device__ __forceinline__ float dangling_total(const float* groups)
+{
+    float D = 0.0f;
+#pragma unroll
+    for (uint32_t g = 0; g < kStrands / 64; ++g) D += groups[g];
+    return D;
 }
 
 struct DevArgs {
@@ -476,14 +493,17 @@ void k_scatter(DevArgs A, GateArg G, uint32_t tile0, uint32_t n_tiles, int parit
     __shared__ uint32_t gpre[kScatterBlock + 1];          // groups before each bin of the batch; [kScatterBlock] = all
     __shared__ uint32_t wave_tot[kScatterWaves + 1];
     __shared__ float red[kScatterWaves];
+    __shared__ float groups[kStrands / 64];
     __shared__ uint32_t next_local;
     static_assert(kDescBatch <= kScatterBlock, "one bin per thread");
+    static_assert(kScatterBlock == kStrands, "a thread per strand");
     if (!fr_gate_admit(G.gate, G.slot, kDynamic ? G.tile_ticks : G.need_ticks)) return;
     const uint32_t Qe = A.Qe;
     float base = 0.0f;
     if (!first) {
-        const float D = dangling_total(A.dpart + (size_t)parity * A.n_dpart, A.n_dpart);
-        base = (1.0f - A.damping) / (float)A.V + A.damping * D / (float)A.V;
+        dangling_group(dangling_strand(A.dpart + (size_t)parity * A.n_dpart, A.n_dpart, threadIdx.x), threadIdx.x & ~63u, groups);
+        __syncthreads();
+        base = (1.0f - A.damping) / (float)A.V + A.damping * dangling_total(groups) / (float)A.V;
     }
     constexpr uint32_t kGroup = kRuns ? 4 : 8;
     // rows a thread reads per round while the slice is filled (the small size has 64 registers per lane)
@@ -618,174 +638,162 @@ __device__ __forceinline__ uint32_t id_of(const uint4& raw, int j)
 }
 
 // One workgroup per gather tile; it takes the tile's pieces one after the other, the accumulators of the piece's
-// range (one u64 per row) in LDS.  Per step a wavefront takes one chunk of 512 ids (8 per lane).  The loop is a
-// three-stage software pipeline over the wavefront's chunks, so that no step waits on a load it has just issued:
-//   A  ids, message-start record and message base of the chunk two steps on are requested;
-//   B  this step's chunk (ids now here): the start bits tell every id which message it belongs to; the
-//      messages are requested (64 consecutive ids per load, so the addresses are all but contiguous);
-//   C  the chunk of the step before (messages now here): each id adds its message, as a 64-bit fixed-point
-//      integer, to its row's accumulator with an LDS atomic.
-// Chunks that lie wholly inside the tile's edge range and whose messages cannot pass the end of the message array -
-// all but the first and last chunk of a tile - take a path without per-id checks (8 vector instructions per 64
-// edges instead of 25).  On a graph of 2^26 edges the sweep then moves its bytes at about 4.7 TB/s, which is what
-// the memory system gives this mix of streams: taking a sixth of the vector instructions out of the loop changed
-// nothing, a third or fourth buffer of messages in flight made it 6 to 9 % slower, and so did start records that
-// come through a vector load (one dword a lane, handed to the scalar side with readlane) instead of scalar loads.
+// range (one u64 per row) in LDS.  Per step a wavefront takes one chunk of 512 ids (8 per lane).  The chunks that lie wholly
+// inside the piece go through a pipeline without a branch in it, so that the compiler can count what is in flight:
+//   A  the chunk's start bits (through the scalar unit) are asked for two steps before its messages, its ids one;
+//   B  the start bits tell every id which message it belongs to, and the messages are requested (64 consecutive ids per load,
+//      so the addresses are all but contiguous): eight loads, one base address for the chunk and 32-bit offsets from it;
+//   C  the chunk of the step before (messages now here): each id adds its message, as a 64-bit fixed-point integer, to its
+//      row's accumulator with an LDS atomic.  An id is the byte offset of its row's accumulator divided by 8 / kIdScale, so
+//      any 16-bit value stays inside `acc` (the sink slot is its end).
+// Behind a wavefront's last chunk that one is asked for again: loads that nothing uses instead of conditions.  (With loads
+// under conditions, and checked and unchecked chunks in one loop, as it was before, the compiler waited for a chunk's messages
+// in the step that asked for them, and the small kernel for every start record as soon as it was requested.  us an iteration:
+// 2^14 vertices / 2^18 edges 17.2 -> 15.0, 10^6 / 10^7 31.4 -> 26.3, 2^22 / 2^26 76.2 -> 74.1, 2^24 / 2^28 343 -> 339.  What
+// bounds it on the large graphs is the memory's rate, on the small ones the chain record - ids - messages.)
+// The first and last chunk of a piece that is not cut on multiples of 512 go through a path with a check per id, before the
+// others, in the wavefronts that have fewest of those.
 // (two workgroups of the small size share a CU: 8 wavefronts per SIMD, hence at most 64 registers per lane)
 template <uint32_t kRowsPerPart, bool kDynamic>
 __global__ __launch_bounds__(kGatherBlock) __attribute__((amdgpu_waves_per_eu(kRowsPerPart == kRowsSmall ? 8 : 4, kRowsPerPart == kRowsSmall ? 8 : 4)))
 void k_gather(DevArgs A, GateArg G, uint32_t tile0, uint32_t n_tiles, int parity, int final_pass, const uint64_t* __restrict__ starts,
-              const uint32_t* __restrict__ mbase)
+              const uint32_t* __restrict__ mbase, const GatherTile* __restrict__ tiles, const GatherPiece* __restrict__ pieces)
 {
     constexpr uint32_t kAccSlots = kRowsPerPart;
     constexpr uint32_t kIdScale = id_scale_for(kRowsPerPart);
     static_assert(65535u * (8 / kIdScale) + 8 <= (kAccSlots + 1) * 8, "any id addresses a slot of acc");
-    __shared__ unsigned long long acc[kAccSlots + 1];            // + the sink slot
+    __shared__ __align__(16) unsigned long long acc[kAccSlots + 2];      // + the sink slot, and one to make pairs
     __shared__ float red[kGatherWaves];
+    __shared__ float groups[kStrands / 64];
     __shared__ uint32_t next_local;
+    static_assert(kGatherBlock == kStrands, "a thread per strand");
     if (!fr_gate_admit(G.gate, G.slot, kDynamic ? G.tile_ticks : G.need_ticks)) return;
-    const float D = dangling_total(A.dpart + (size_t)parity * A.n_dpart, A.n_dpart);
-    const float base = (1.0f - A.damping) / (float)A.V + A.damping * D / (float)A.V;
+    const float strand = dangling_strand(A.dpart + (size_t)parity * A.n_dpart, A.n_dpart, threadIdx.x);
     float* dnext = A.dpart + (size_t)(parity ^ 1) * A.n_dpart;
-    if (tile0 == 0 && blockIdx.x == 0 && !final_pass)            // slots no gather piece writes: the scatter tiles of the next sweep
-        for (uint32_t i = A.n_pieces + threadIdx.x; i < A.n_dpart; i += kGatherBlock) dnext[i] = 0.0f;     // fill theirs in, void pieces have none
+    const uint32_t lane = threadIdx.x & 63, wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     uint32_t local = blockIdx.x;
     do {
-    const uint4* rec = reinterpret_cast<const uint4*>(A.gather_tiles + tile0 + local);
-    const uint4 span = rec[0];                                   // x, y: the tile's pieces, worked on one after the other;
-    const uint4 span_more = rec[1];                              // then a copy of the first (saves a dependent load)
+    const GatherTile* tile = tiles + (tile0 + (uint32_t)__builtin_amdgcn_readfirstlane((int)local));
+    const uint32_t p0 = tile->p0, p1 = tile->p1;                 // the tile's pieces, worked on one after the other;
+    GatherPiece T = tile->first;                                 // with a copy of the first (saves a dependent load)
     uint32_t asked = 0;
-    for (uint32_t t = span.x; t < span.y; ++t) {
-    const GatherPiece T = t == span.x ? GatherPiece{span.z, span.w, span_more.x, span_more.y} : A.gather_pieces[t];
-    const uint32_t q = T.range;
-    const int64_t left = A.V - (int64_t)q * kRowsPerPart;
-    const uint32_t nrows = (uint32_t)(left < (int64_t)kRowsPerPart ? left : (int64_t)kRowsPerPart);
-    for (uint32_t i = threadIdx.x; i < kAccSlots + 1; i += kGatherBlock) acc[i] = 0ull;
+    for (uint32_t t = p0; t < p1; ++t) {
+    const GatherPiece T_next = pieces[t + 1 < p1 ? t + 1 : t];
+    for (uint32_t i = threadIdx.x; i < kAccSlots / 2 + 1; i += kGatherBlock) reinterpret_cast<ulonglong2*>(acc)[i] = make_ulonglong2(0ull, 0ull);
     __syncthreads();
 
     const uint32_t e0 = T.e0, e1 = T.e1 < (uint64_t)A.E ? T.e1 : (uint32_t)A.E;
-    const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const uint4* ids4 = reinterpret_cast<const uint4*>(A.ids16);
+    // a chunk's start bits (row j: bit l - 1 says that position l begins a message, bit 63 that position 0 does) and the number
+    // of messages begun before it; the same in all lanes of a wavefront, hence in scalar registers
+    struct Starts { uint64_t bits[8]; uint32_t mb; };
+    auto ask_starts = [&](Starts& S, uint32_t c) {
+        const uint64_t* rec = starts + (uint64_t)c * kStartWords;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) S.bits[j] = rec[j];
+        S.mb = mbase[c];
+    };
+    // The message of the id in lane l (position 64 j + l) is the message of the row's first id plus the messages begun at
+    // positions 1 .. l, which is what mbcnt counts in the row's word: as a distance from message mb - 1, in bytes
+    auto distances = [&](uint32_t (&at)[8], const Starts& S) {
+        uint32_t before = 0;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const uint32_t begun = __builtin_amdgcn_mbcnt_hi((uint32_t)(S.bits[j] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)S.bits[j], 0u));
+            at[j] = (begun << 2) + ((before + (uint32_t)(S.bits[j] >> 63)) << 2);
+            before += (uint32_t)__popcll(S.bits[j]);
+        }
+    };
+    const uint32_t f0 = (e0 + kIdChunk - 1) / kIdChunk, f1 = e1 / kIdChunk;      // chunks wholly inside: [f0, f1)
+    const uint32_t n_full = f1 > f0 ? f1 - f0 : 0;
     if (e1 > e0) {
-        const uint32_t c0 = e0 / kIdChunk, c1 = (e1 - 1) / kIdChunk;
-        const uint4* ids4 = reinterpret_cast<const uint4*>(A.ids16);
-        // Stage A's result: a chunk's ids, its message-start bits and the number of messages begun before it.  The
-        // chunk number is the same in all lanes of a wavefront; saying so lets the bits and the count come through
-        // the scalar unit, which leaves them where the arithmetic of stage B wants them.  There are kRing of these:
-        // a buffer is asked for its next chunk as soon as stage B has used it, kRing - 1 steps before that chunk's
-        // turn, so a wavefront has that many steps of work to cover the latency of the request.
-        struct Ids {
-            uint4 raw;
-            uint32_t mb;
-            uint64_t starts[8];      // row j: start bits of its positions 1 .. 63
-            uint32_t first[8];       // row j: byte offset of the message of its position 0 from message mb - 1
-        };
-        constexpr int kRing = 2;     // (the records live in scalar registers: there is room for two)
-        const uint32_t wave_u = (uint32_t)__builtin_amdgcn_readfirstlane((int)wave);
-        auto load_ids = [&](Ids& I, uint32_t c) {
-            if (c <= c1) {
-                I.raw = ids4[(uint64_t)c * (kIdChunk / 8) + lane];
-                I.mb = mbase[c];
-                const uint64_t* rec = starts + (uint64_t)c * kStartWords;
-#pragma unroll
-                for (int j = 0; j < 8; ++j) I.starts[j] = rec[j];
-#pragma unroll
-                for (int j = 0; j < 8; ++j) I.first[j] = reinterpret_cast<const uint32_t*>(rec + 8)[j];
-            }
-        };
-        // Stage B's result, waiting for stage C.  There are two of these, used in turn: copying one into the other
-        // at the end of a step would make the step wait for the messages it has just asked for.  For the same reason
-        // the loop below is written out once per combination of buffers.
-        struct Pending {
-            uint4 raw;
+        const uint32_t ca = e0 / kIdChunk, cb = e1 / kIdChunk;
+        const bool has_a = e0 % kIdChunk != 0, has_b = e1 % kIdChunk != 0 && !(has_a && ca == cb);
+        const bool do_a = has_a && wave == n_full % kGatherWaves, do_b = has_b && wave == (n_full + 1) % kGatherWaves;
+        if (do_a || do_b) {
+            const uint32_t c = do_a ? ca : cb;
+            const uint4 raw = ids4[(uint64_t)c * (kIdChunk / 8) + lane];
+            Starts S;
+            ask_starts(S, c);
+            uint32_t at[8];
+            distances(at, S);
+            uint32_t ok = 0;
             float val[8];
-            uint32_t ok;             // per-id validity bits of a checked chunk
-            bool fast;               // the chunk took the unchecked path (wavefront-uniform)
-        };
-        Pending X, Y;
-        X.ok = 0; X.fast = false; Y.ok = 0; Y.fast = false;
-        X.raw = make_uint4(0, 0, 0, 0); Y.raw = make_uint4(0, 0, 0, 0);
 #pragma unroll
-        for (int j = 0; j < 8; ++j) { X.val[j] = 0.0f; Y.val[j] = 0.0f; }
-
-        // ---- stage B on chunk c: lane l holds the ids at stream positions 64 j + l of the chunk, so for a fixed j
-        // the wavefront covers 64 consecutive ids (row j).  The message of the id in lane l is the message of the
-        // row's first id plus the messages begun at positions 1 .. l, which is what mbcnt counts in the row's word.
-        auto stage_b = [&](Pending& S, const Ids& I, uint32_t c) {
-            S.raw = I.raw;
-            S.ok = 0;
-            const uint32_t mb = I.mb;
-            const uint64_t first = (uint64_t)c * kIdChunk;
-            // mb >= 1: the chunk's first id then has a message at or before it
-            S.fast = first >= e0 && first + kIdChunk <= e1 && mb >= 1 && (uint64_t)mb + kIdChunk <= A.M;
-            if (S.fast) {
-                // messages mb - 1 .. mb + 511, inside [0, M): one base address for the chunk, 32-bit offsets from it
-                const char* near = reinterpret_cast<const char*>(A.msg) + ((uint64_t)mb << 2) - 4;
-#pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    const uint32_t before = __builtin_amdgcn_mbcnt_hi((uint32_t)(I.starts[j] >> 32),
-                                                                      __builtin_amdgcn_mbcnt_lo((uint32_t)I.starts[j], 0u));
-                    S.val[j] = *reinterpret_cast<const float*>(near + ((before << 2) + I.first[j]));
-                }
-            } else {
-                const uint32_t ebase = c * kIdChunk + lane;
-#pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    const uint32_t mi = mb - 1u + (I.first[j] >> 2) +
-                                        __builtin_amdgcn_mbcnt_hi((uint32_t)(I.starts[j] >> 32),
-                                                                  __builtin_amdgcn_mbcnt_lo((uint32_t)I.starts[j], 0u));
-                    const uint32_t e = ebase + 64 * j;
-                    const bool ok = e >= e0 && e < e1 && id_of(I.raw, j) < kAccSlots * kIdScale && mi < A.M;   // (mi wraps if no message precedes)
-                    S.ok |= (ok ? 1u : 0u) << j;
-                    S.val[j] = A.msg[ok ? mi : 0u];
-                }
+            for (int j = 0; j < 8; ++j) {
+                const uint32_t mi = S.mb - 1u + at[j] / 4, e = c * kIdChunk + lane + 64 * j;
+                const bool good = e >= e0 && e < e1 && id_of(raw, j) < kAccSlots * kIdScale && mi < A.M;   // (mi wraps if no message precedes)
+                ok |= (good ? 1u : 0u) << j;
+                val[j] = A.msg[good ? mi : 0u];
             }
-        };
-        // ---- stage C: the chunk's ids add their messages; leaves S empty.  An id is the byte offset of its row's
-        // accumulator divided by 8 / kIdScale, so any 16-bit value stays inside `acc` (the sink slot is its end).
-        auto stage_c = [&](Pending& S) {
-            if (S.fast) {
 #pragma unroll
-                for (int j = 0; j < 8; ++j) atomicAdd(acc_at(acc, id_of(S.raw, j) * (8 / kIdScale)), to_fixed(S.val[j]));
-            } else if (S.ok) {
-#pragma unroll
-                for (int j = 0; j < 8; ++j)
-                    if ((S.ok >> j) & 1u) atomicAdd(acc_at(acc, id_of(S.raw, j) * (8 / kIdScale)), to_fixed(S.val[j]));
-            }
-            S.fast = false; S.ok = 0;
-        };
-        // one step: B on chunk c out of buffer I into `fresh`, I asked for the chunk kRing steps on, C on `due`
-        uint32_t c = c0 + wave_u;
-        auto step = [&](Ids& I, Pending& fresh, Pending& due) -> bool {
-            if (c > c1) return false;
-            stage_b(fresh, I, c);
-            load_ids(I, c + kRing * kGatherWaves);
-            stage_c(due);
-            c += kGatherWaves;
-            return true;
-        };
-        Ids I0, I1;
-        I0.raw = I1.raw = make_uint4(0, 0, 0, 0);
-        I0.mb = I1.mb = 0;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) { I0.starts[j] = I1.starts[j] = 0; I0.first[j] = I1.first[j] = 0; }
-        load_ids(I0, c);
-        load_ids(I1, c + kGatherWaves);
-        while (step(I0, X, Y) && step(I1, Y, X)) {}
-        stage_c(X);          // drain: at most one of the two still holds a chunk
-        stage_c(Y);
+            for (int j = 0; j < 8; ++j)
+                if ((ok >> j) & 1u) atomicAdd(acc_at(acc, id_of(raw, j) * (8 / kIdScale)), to_fixed(val[j]));
+        }
     }
+    if (wave < n_full) {
+        uint32_t c = f0 + wave;
+        const uint32_t last = c + (n_full - 1 - wave) / kGatherWaves * kGatherWaves;       // this wavefront's last chunk
+        uint4 raw[2];
+        Starts S[2];
+        float val[2][8];
+        auto ahead = [&](uint32_t steps) { return c + steps * kGatherWaves < last ? c + steps * kGatherWaves : last; };
+        auto ask_ids = [&](uint4& r, uint32_t at) { r = ids4[(uint64_t)at * (kIdChunk / 8) + lane]; };
+        auto ask_messages = [&](float (&v)[8], const Starts& of) {
+            // (message mb - 1 is not touched by a chunk that begins a message at its first position: not below the array)
+            const char* near = reinterpret_cast<const char*>(A.msg) + ((uint64_t)of.mb << 2) - 4;
+            uint32_t at[8];
+            distances(at, of);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) v[j] = *reinterpret_cast<const float*>(near + at[j]);
+        };
+        auto add = [&](const uint4& r, const float (&v)[8]) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) atomicAdd(acc_at(acc, id_of(r, j) * (8 / kIdScale)), to_fixed(v[j]));
+        };
+        // one step, on a chunk whose messages were asked for in the step before
+        auto step = [&](int k) {
+            ask_messages(val[k ^ 1], S[k ^ 1]);                  // of the next chunk
+            ask_starts(S[k ^ 1], ahead(3));
+            __builtin_amdgcn_sched_barrier(0);
+            add(raw[k], val[k]);
+            __builtin_amdgcn_sched_barrier(0);
+            ask_ids(raw[k], ahead(2));
+            c += kGatherWaves;
+        };
+        ask_starts(S[0], c);
+        ask_ids(raw[0], c);
+        ask_ids(raw[1], ahead(1));
+        ask_messages(val[0], S[0]);
+        ask_starts(S[1], ahead(1));
+        ask_starts(S[0], ahead(2));
+        const uint32_t steps = (last - c) / kGatherWaves + 1;
+        for (uint32_t i = 0; i < steps / 2; ++i) {               // (one basic block: else requests sink to where they are used)
+            step(0);
+            step(1);
+        }
+        if (steps & 1) add(raw[0], val[0]);
+    }
+    if (t == p0) dangling_group(strand, threadIdx.x & ~63u, groups);
+    const uint32_t q = T.range;
+    const int64_t v0 = (int64_t)q * kRowsPerPart;
+    const uint32_t nrows = (uint32_t)(A.V - v0 < (int64_t)kRowsPerPart ? A.V - v0 : (int64_t)kRowsPerPart);
     __syncthreads();
     if constexpr (kDynamic)
-        if (t + 1 == span.y && threadIdx.x == 0) asked = ask_if_time(A.sched, G);   // covered by the row pass below
+        if (t + 1 == p1 && threadIdx.x == 0) asked = ask_if_time(A.sched, G);   // covered by the row pass below
 
     if (T.partial != kNoPartial) {
         // merged range: the sums go out as one row of partial sums; the next scatter sweep (or F) finishes the rows
-        float* out = A.partials + (size_t)T.partial * kRowsPerPart;
-        for (uint32_t i = threadIdx.x; i < kRowsPerPart; i += kGatherBlock) out[i] = (float)acc[i] * kFixInv;
+        float2* out = reinterpret_cast<float2*>(A.partials + (size_t)T.partial * kRowsPerPart);
+#pragma unroll 4
+        for (uint32_t i = threadIdx.x; i < kRowsPerPart / 2; i += kGatherBlock) {
+            const ulonglong2 two = reinterpret_cast<const ulonglong2*>(acc)[i];
+            out[i] = make_float2((float)two.x * kFixInv, (float)two.y * kFixInv);
+        }
         if (threadIdx.x == 0 && !final_pass) dnext[t] = 0.0f;
     } else {
     // direct range: fused vertex pass for its rows
-    const int64_t v0 = (int64_t)q * kRowsPerPart;
+    const float base = (1.0f - A.damping) / (float)A.V + A.damping * dangling_total(groups) / (float)A.V;
     float dangling = 0.0f;
     constexpr int kRowsPerThread = (kRowsPerPart + kGatherBlock - 1) / kGatherBlock;
     if (final_pass) {
@@ -799,7 +807,7 @@ void k_gather(DevArgs A, GateArg G, uint32_t tile0, uint32_t n_tiles, int parity
 #pragma unroll
         for (int k = 0; k < kRowsPerThread; ++k) {
             const uint32_t i = threadIdx.x + kGatherBlock * k;
-            inv[k] = i < nrows ? A.inv_out[v0 + i] : 1.0f;
+            inv[k] = A.inv_out[v0 + (i < nrows ? i : nrows - 1)];
         }
 #pragma unroll
         for (int k = 0; k < kRowsPerThread; ++k) {
@@ -813,7 +821,10 @@ void k_gather(DevArgs A, GateArg G, uint32_t tile0, uint32_t n_tiles, int parity
         if (threadIdx.x == 0) dnext[t] = total;
     }
     }
+    if (tile0 == 0 && blockIdx.x == 0 && local == 0 && t == p0 && !final_pass)   // slots no gather piece writes: the scatter tiles of the next
+        for (uint32_t i = A.n_pieces + threadIdx.x; i < A.n_dpart; i += kGatherBlock) dnext[i] = 0.0f;   // sweep fill theirs in, void pieces have none
     __syncthreads();                                             // the piece is done with acc
+    T = T_next;
     }       // pieces
     if constexpr (kDynamic) {
         if (threadIdx.x == 0) next_local = settle_next_tile(asked, A.sched, G, n_tiles);
@@ -827,15 +838,17 @@ void k_gather(DevArgs A, GateArg G, uint32_t tile0, uint32_t n_tiles, int parity
 }
 
 // ---- F ----
-// After the last iteration: r_K of kFinishRows rows of one merged range (partial sums of G_{K-1}) or of one empty
-// range (the base value) goes to ranks_out.
-constexpr uint32_t kFinishRows = 2048;
-__global__ __launch_bounds__(kBlock) void k_finish(DevArgs A, GateArg G, uint32_t tile0, int parity)
+// After the last iteration: r_K of the rows of one merged range (partial sums of G_{K-1}) or of one empty range (the base
+// value) goes to ranks_out, kFinishRows rows a workgroup, one or two workgroups a tile.
+__global__ __launch_bounds__(kBlock) void k_finish(DevArgs A, GateArg G, uint32_t part0, int parity)
 {
+    __shared__ float groups[kStrands / 64];
     if (!fr_gate_admit(G.gate, G.slot, G.need_ticks)) return;
-    const uint32_t t = tile0 + blockIdx.x;
-    const float D = dangling_total(A.dpart + (size_t)parity * A.n_dpart, A.n_dpart);
-    const float base = (1.0f - A.damping) / (float)A.V + A.damping * D / (float)A.V;
+    const uint32_t t = part0 + blockIdx.x;
+    for (uint32_t i = threadIdx.x; i < kStrands; i += kBlock)
+        dangling_group(dangling_strand(A.dpart + (size_t)parity * A.n_dpart, A.n_dpart, i), i & ~63u, groups);
+    __syncthreads();
+    const float base = (1.0f - A.damping) / (float)A.V + A.damping * dangling_total(groups) / (float)A.V;
     const uint32_t per_range = A.rows_per_part / kFinishRows;
     if (t / per_range < A.n_finish) {
         const uint32_t q = A.finish_ranges[t / per_range];
@@ -889,9 +902,10 @@ struct PrTask {
         case FR_PR_SEG_VERTEX: return L.Q;
         case FR_PR_SEG_SCATTER: return L.n_scatter;
         case FR_PR_SEG_GATHER: return L.n_gather;
-        default: return std::max<uint32_t>(1, L.n_finish * (L.rows_per_part / kFinishRows));
+        default: return std::max<uint32_t>(1, L.n_finish * (L.rows_per_part / finish_rows()));
         }
     }
+    uint32_t finish_rows() const { return finish_tile_rows(L.n_finish, L.rows_per_part); }
     uint64_t rows_of_q(uint32_t q) const
     {
         return std::min<uint64_t>(L.rows_per_part, (uint64_t)L.V - (uint64_t)q * L.rows_per_part);
@@ -935,7 +949,8 @@ int pr_launch(PrTask* p, uint32_t g, uint32_t tile0, uint32_t tile1, hipStream_t
         hipLaunchKernelGGL(k_vertex0, dim3(n), dim3(kBlock), 0, stream, args, G, tile0, K == 0 ? 1 : 0);
     } else if (kind == FR_PR_SEG_FINISH) {
         // after G_{K-1}: the dangling partials of r_{K-1} sit in set (K-1) & 1
-        hipLaunchKernelGGL(k_finish, dim3(n), dim3(kBlock), 0, stream, args, G, tile0, (int)((K - 1) & 1u));
+        const uint32_t parts = p->finish_rows() / kFinishRows;      // workgroups a tile
+        hipLaunchKernelGGL(k_finish, dim3(n * parts), dim3(kBlock), 0, stream, args, G, tile0 * parts, (int)((K - 1) & 1u));
     } else {
         const uint32_t k = (g - 1) / 2;
         if (kind == FR_PR_SEG_SCATTER) {    // S_k finishes rows of r_k with D_{k-1}: set (k-1) & 1
@@ -957,7 +972,7 @@ int pr_launch(PrTask* p, uint32_t g, uint32_t tile0, uint32_t tile1, hipStream_t
             const uint32_t grid = std::min(n, p->L.gather_slots);
             const bool dynamic = n > grid;
             auto go = [&](auto kernel) {
-                hipLaunchKernelGGL(kernel, dim3(grid), dim3(kGatherBlock), 0, stream, args, G, tile0, n, parity, final_pass, args.starts, args.mbase);
+                hipLaunchKernelGGL(kernel, dim3(grid), dim3(kGatherBlock), 0, stream, args, G, tile0, n, parity, final_pass, args.starts, args.mbase, args.gather_tiles, args.gather_pieces);
             };
             if (p->L.rows_per_part == kRowsLarge) { if (dynamic) go(k_gather<kRowsLarge, true>); else go(k_gather<kRowsLarge, false>); }
             else { if (dynamic) go(k_gather<kRowsSmall, true>); else go(k_gather<kRowsSmall, false>); }

@@ -195,11 +195,10 @@ __device__ __forceinline__ void read_chunk(ChunkKeys& K, uint32_t c, uint32_t E,
 }
 
 // One pass over the keys: message-start records, messages and repeated edges per chunk, messages per source (cnt, zero
-// before; integer atomics).  A chunk's record, kStartWords 64-bit words: words 0 .. 7 = for row j (stream positions 64 j ..
-// 64 j + 63 of the chunk) the start bits of positions 1 .. 63 in bits 0 .. 62 (bit l set: position l + 1 begins a message);
-// words 8 .. 11 = eight 32-bit words, for the first position of each row four times the distance of its message from
-// message mbase[c] - 1 (0 .. 2048: a byte offset into the messages).  The message of position l of row j is then:
-// mbase[c] - 1 + first[j] / 4 + (set bits below l in word j).  Repeated edges, adjacent in the stream, hit one accumulator
+// before; integer atomics).  A chunk's record, kStartWords 64-bit words: word j for row j (stream positions 64 j ..
+// 64 j + 63 of the chunk), bit l - 1 set if position l begins a message, bit 63 if position 0 does.  The message of position l
+// of row j is then: mbase[c] - 1 + (set bits of the words before j) + (bit 63 of word j) + (set bits below l in word j).
+// Repeated edges, adjacent in the stream, hit one accumulator
 // from neighbouring lanes, which the LDS serialises; the tile cutter counts them.  Bound by the atomics: 2^26 edges 0.3 ms
 // (a pass each for records, numbering, repeats and counts, the records 64 keys a thread: 1.9 ms).
 __global__ __launch_bounds__(kBlk) void k_chunk_facts(uint32_t E, int64_t V, uint32_t n_chunks, uint32_t src_mask, const uint64_t* __restrict__ keys,
@@ -217,13 +216,9 @@ __global__ __launch_bounds__(kBlk) void k_chunk_facts(uint32_t E, int64_t V, uin
     uint64_t* rec = starts + (uint64_t)c * kStartWords;
     uint32_t begun = 0, repeated = 0;
     uint64_t word = 0;
-    uint32_t first = 0;
 #pragma unroll
     for (int j = 0; j < kChunkRows; ++j) {
-        if (lane == (uint32_t)j) {
-            word = K.begins[j] >> 1;
-            first = (uint64_t)c * kIdChunk + 64 * j < E ? 4u * (begun + (uint32_t)(K.begins[j] & 1u)) : 0u;
-        }
+        if (lane == (uint32_t)j) word = K.begins[j] >> 1 | K.begins[j] << 63;
         begun += (uint32_t)__popcll(K.begins[j]);
         repeated += (uint32_t)__popcll(K.repeats[j]);
         if ((K.begins[j] >> lane) & 1u) {
@@ -231,10 +226,7 @@ __global__ __launch_bounds__(kBlk) void k_chunk_facts(uint32_t E, int64_t V, uin
             if ((int64_t)u < V) atomicAdd(&cnt[u], 1u);
         }
     }
-    if (lane < (uint32_t)kChunkRows) {
-        rec[lane] = word;
-        reinterpret_cast<uint32_t*>(rec + kChunkRows)[lane] = first;
-    }
+    if (lane < (uint32_t)kChunkRows) rec[lane] = word;
     if (lane == 0) { messages[c] = begun; rep[c] = repeated; }
 }
 
@@ -320,7 +312,9 @@ __device__ __forceinline__ uint32_t message_of(uint32_t e, const uint64_t* __res
 {
     const uint32_t c = e / kIdChunk, j = e % kIdChunk / 64, l = e % 64;
     const uint64_t* rec = starts + (uint64_t)c * kStartWords;
-    return mbase[c] - 1 + reinterpret_cast<const uint32_t*>(rec + kChunkRows)[j] / 4 + (uint32_t)__popcll(rec[j] & ((1ull << l) - 1));
+    uint32_t m = mbase[c] - 1;
+    for (uint32_t i = 0; i < j; ++i) m += (uint32_t)__popcll(rec[i]);
+    return m + (uint32_t)(rec[j] >> 63) + (uint32_t)__popcll(rec[j] & ((1ull << l) - 1));
 }
 
 // bins[t * Qe + j] = message range of the edges of range j whose source lies in scatter tile t.

@@ -53,7 +53,7 @@
 #include "pr_rules.h"
 
 constexpr uint32_t kIdChunk = 512;           // ids per wavefront step (8 per lane, 64 apart)
-constexpr uint32_t kStartWords = 12;         // 64-bit words of a chunk's message-start record
+constexpr uint32_t kStartWords = 8;          // 64-bit words of a chunk's message-start record
 constexpr int kKeyLocalBits = 15;            // sort key = range << (15 + bits of a source) | source << 15 | local row
 constexpr uint32_t kLocalMask = (1u << kKeyLocalBits) - 1;
 static_assert(kRowsLarge <= (1u << kKeyLocalBits) && kSrcLarge <= 65536, "id fields");
@@ -113,9 +113,8 @@ struct PrLayout {
     int32_t* perm = nullptr;         // [V] caller's id of new id v
     uint16_t* ids16 = nullptr;       // [n_chunks * kIdChunk] local row id times id_scale_for(rows_per_part);
                                      // each chunk stored transposed: stream position 64 j + lane at slot 8 lane + j
-    uint64_t* starts = nullptr;      // [n_chunks * kStartWords] per chunk: eight words of message-start bits (one per 64
-                                     // positions, shifted down by one) and, for the eight first positions, the byte offsets
-                                     // of their messages from message mbase[chunk] - 1
+    uint64_t* starts = nullptr;      // [n_chunks * kStartWords] per chunk a word per row of 64 positions: bit l - 1 says that
+                                     // position l begins a message, bit 63 that position 0 does
     uint16_t* src16 = nullptr;       // [M] source id relative to the first source of its scatter piece
     uint32_t* mbase = nullptr;       // [n_chunks + 1] messages that begin before each chunk
     uint2* bins = nullptr;           // [n_spieces * Qe] message range [x, y) of (scatter piece, range), piece-major

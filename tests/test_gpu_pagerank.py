@@ -155,6 +155,23 @@ def test_layout_of_edge_counts_around_its_runs(n, edges):
     _check(graphs.csr_from_edges(n, src, dst), iterations=4)
 
 
+# pieces of the gather sweep that begin and end inside a chunk of 512 edges, both in one chunk, or on its ends: three ranges of
+# 16384 + x, 8192 and `tail` edges (x rows of three in-edges, then two, then one); 32, 16 and 0 or 1 whole chunks for 16 wavefronts
+@pytest.mark.parametrize("x,tail", [(0, 100), (5, 100), (412, 100), (450, 100), (8, 1000), (511, 513)])
+def test_pieces_that_begin_and_end_inside_a_chunk(x, tail):
+    V = 8192 * 2 + 5000
+    degree = np.zeros(V, dtype=np.int64)
+    degree[:8192] = 2
+    degree[:x] += 1
+    degree[8192:16384] = 1
+    degree[16384:16384 + tail] = 1
+    rng = np.random.default_rng(x)
+    row = rng.permutation(V)                                     # (ids in any order)
+    dst = np.repeat(row, degree[np.arange(V)])
+    src = rng.integers(0, V, len(dst))
+    _check(graphs.csr_from_edges(V, src, dst), iterations=5)
+
+
 def test_partition_sizes_other_than_the_two_supported_are_refused():
     g = graphs.rmat_csr(10, 3000, seed=8)
     rp, col, od = _dev(g.row_ptr, torch.int32), _dev(g.col, torch.int32), _dev(g.out_degree, torch.int32)
