@@ -44,10 +44,35 @@ constexpr float kFixInv = 1.0f / 4611686018427387904.0f;
 constexpr float kMsgScale = 1073741824.0f;
 
 // ---- fixed-order reductions ----
+// (by moves between lanes of the vector unit: inside rows of 16 lanes, then row 0 into row 1 and row 2 into row 3, then the
+// lower half into the upper; six exchanges through the LDS unit take some 0.2 us)
+template <int kCtrl, int kRows>
+__device__ __forceinline__ int from_lane(int x)
+{
+    return __builtin_amdgcn_update_dpp(0, x, kCtrl, kRows, 0xf, false);      // 0 in lanes without a source
+}
+
 __device__ __forceinline__ float wave_sum(float x)
 {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) x += __shfl_xor(x, off, 64);
+    auto add = [&](int moved) { x += __int_as_float(moved); };
+    add(from_lane<0x111, 0xf>(__float_as_int(x)));       // row_shr 1, 2, 4, 8
+    add(from_lane<0x112, 0xf>(__float_as_int(x)));
+    add(from_lane<0x114, 0xf>(__float_as_int(x)));
+    add(from_lane<0x118, 0xf>(__float_as_int(x)));
+    add(from_lane<0x142, 0xa>(__float_as_int(x)));       // row_bcast 15 into rows 1 and 3
+    add(from_lane<0x143, 0xc>(__float_as_int(x)));       // row_bcast 31 into rows 2 and 3
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 63));
+}
+
+// Inclusive prefix sums over the lanes.
+__device__ __forceinline__ uint32_t wave_scan(uint32_t x)
+{
+    x += (uint32_t)from_lane<0x111, 0xf>((int)x);
+    x += (uint32_t)from_lane<0x112, 0xf>((int)x);
+    x += (uint32_t)from_lane<0x114, 0xf>((int)x);
+    x += (uint32_t)from_lane<0x118, 0xf>((int)x);
+    x += (uint32_t)from_lane<0x142, 0xa>((int)x);
+    x += (uint32_t)from_lane<0x143, 0xc>((int)x);
     return x;
 }
 
@@ -149,17 +174,47 @@ __device__ __forceinline__ float merged_sum(const DevArgs& A, RangeInfo info, ui
     float s[kLeaves];
 #pragma unroll
     for (int k = 0; k < kLeaves; ++k) s[k] = 0.0f;
-    // (all loads of a round, up to sixteen, are issued before the first is used)
-    for (uint32_t t0 = 0; t0 < nt; t0 += 16) {
-        float x[kLeaves];
+    // kDeep rounds of 16 at a time, then half as many, then what is left of one: sixteen loads or more are issued before the
+    // first is used (a round at a time, the 90 partial sums of a row of the heaviest range of 2^26 edges were six latencies
+    // one after the other).  The last round has two, four, eight or sixteen leaves: most merged ranges have two or three
+    // pieces, and sixteen loads a row instead of three made the scatter sweep of 2^24 / 2^28 7 us longer.
+    constexpr uint32_t kDeep = kLeaves >= 16 ? 1 : kLeaves >= 8 ? 2 : 4;
+    uint32_t t0 = 0;
+    auto rounds = [&](auto count) {
+        constexpr uint32_t R = decltype(count)::value;
+        float x[R][kLeaves];
 #pragma unroll
-        for (int k = 0; k < kLeaves; ++k) {
+        for (uint32_t j = 0; j < R; ++j)
+#pragma unroll
+            for (int k = 0; k < kLeaves; ++k) {
+                const uint32_t t = t0 + 16 * j + sub * kLeaves + k;
+                x[j][k] = p[(size_t)(j + 1 < R || t < nt ? t : nt - 1) << A.rows_shift];
+            }
+#pragma unroll
+        for (uint32_t j = 0; j < R; ++j)
+#pragma unroll
+            for (int k = 0; k < kLeaves; ++k) s[k] += j + 1 < R || t0 + 16 * j + sub * kLeaves + k < nt ? x[j][k] : 0.0f;
+        t0 += 16 * R;
+    };
+    while (t0 + 16 * (kDeep > 1 ? kDeep - 1 : 1) < nt) rounds(std::integral_constant<uint32_t, kDeep>{});
+    if constexpr (kDeep >= 4)
+        while (t0 + 16 < nt) rounds(std::integral_constant<uint32_t, 2>{});
+    auto rest = [&](auto count) {                // nt - t0 <= count: leaves 0 .. count - 1
+        constexpr int C = decltype(count)::value < kLeaves ? decltype(count)::value : kLeaves;
+        float x[C];
+#pragma unroll
+        for (int k = 0; k < C; ++k) {
             const uint32_t t = t0 + sub * kLeaves + k;
-            x[k] = t < nt ? p[(size_t)t << A.rows_shift] : 0.0f;
+            x[k] = p[(size_t)(t < nt ? t : nt - 1) << A.rows_shift];
         }
 #pragma unroll
-        for (int k = 0; k < kLeaves; ++k) s[k] += x[k];
-    }
+        for (int k = 0; k < C; ++k) s[k] += t0 + sub * kLeaves + k < nt ? x[k] : 0.0f;
+    };
+    const uint32_t left = t0 < nt ? nt - t0 : 0;
+    if (left > 8) rest(std::integral_constant<int, 16>{});
+    else if (left > 4) rest(std::integral_constant<int, 8>{});
+    else if (left > 2) rest(std::integral_constant<int, 4>{});
+    else if (left) rest(std::integral_constant<int, 2>{});
 #pragma unroll
     for (int w = 1; w < kLeaves; w <<= 1)
 #pragma unroll
@@ -392,28 +447,22 @@ __global__ void k_clear_sched(uint32_t* sched)
 // piece, and the next 64 groups are mostly in the same bin), groups of eight round-robin; which: scatter_in_runs.
 constexpr uint32_t kDescBatch = 1024;       // bins per batch
 
-// Exclusive prefix sums of one value per thread over the workgroup (kScatterBlock threads); out[i] = sum of the
-// values of threads < i for i <= kScatterBlock.  `wave_tot` holds kScatterWaves + 1 words.
-__device__ __forceinline__ void block_exclusive_scan(uint32_t value, uint32_t* out, uint32_t* wave_tot)
+// Exclusive prefix sums of one value per thread over the workgroup, in two halves with a barrier between them: the first
+// leaves every wavefront's total in wave_tot; the second returns the sum of the values of the threads before this one, and
+// the sum of all.
+__device__ __forceinline__ uint32_t scan_in_wave(uint32_t value, uint32_t* wave_tot)
 {
-    const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    uint32_t incl = value;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const uint32_t up = (uint32_t)__shfl_up((int)incl, off, 64);
-        if (lane >= (uint32_t)off) incl += up;
-    }
-    if (lane == 63) wave_tot[wave] = incl;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        uint32_t run = 0;
-        for (int w = 0; w < kScatterWaves; ++w) { const uint32_t x = wave_tot[w]; wave_tot[w] = run; run += x; }
-        wave_tot[kScatterWaves] = run;
-    }
-    __syncthreads();
-    out[threadIdx.x] = wave_tot[wave] + incl - value;
-    if (threadIdx.x == 0) out[kScatterBlock] = wave_tot[kScatterWaves];
-    __syncthreads();
+    const uint32_t incl = wave_scan(value);
+    if ((threadIdx.x & 63) == 63) wave_tot[threadIdx.x >> 6] = incl;
+    return incl - value;
+}
+__device__ __forceinline__ uint32_t scan_over_waves(uint32_t before_in_wave, const uint32_t* wave_tot, uint32_t* all)
+{
+    static_assert(kScatterWaves == 16, "the totals are one row of lanes");
+    const uint32_t lane = threadIdx.x & 63, wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const uint32_t incl = wave_scan(lane < kScatterWaves ? wave_tot[lane] : 0u);
+    *all = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+    return before_in_wave + (wave ? (uint32_t)__builtin_amdgcn_readlane((int)incl, (int)wave - 1) : 0u);
 }
 
 struct GroupRef {
@@ -421,7 +470,23 @@ struct GroupRef {
     uint32_t bin;     // its bin in the batch
 };
 
-// Group number k of the batch: its bin is the last one of [lo, hi) whose first group number is <= k (lo's is).
+// Group numbers k[0 .. n) of the batch: the bin of one is the last whose first group number is <= k.  The n searches go side by
+// side, a fixed number of steps each (one after the other, four searches among a thousand bins were forty reads of the LDS
+// in a row).  step0: the largest power of two below the number of bins; gpre holds the number of all groups behind its end.
+template <int kSearches>
+__device__ __forceinline__ void find_bins(const uint32_t (&k)[kSearches], const uint32_t* gpre, uint32_t step0, uint32_t (&bin)[kSearches])
+{
+#pragma unroll
+    for (int a = 0; a < kSearches; ++a) bin[a] = 0;
+    for (uint32_t step = step0; step; step >>= 1) {
+#pragma unroll
+        for (int a = 0; a < kSearches; ++a) {
+            const uint32_t at = bin[a] + step;
+            bin[a] = gpre[at] <= k[a] ? at : bin[a];
+        }
+    }
+}
+
 __device__ __forceinline__ uint32_t find_bin(uint32_t k, const uint32_t* gpre, uint32_t lo, uint32_t hi)
 {
     while (hi - lo > 1) {
@@ -486,12 +551,12 @@ __device__ __forceinline__ void emit_group(const GroupRef& ref, const uint2* des
 // the hand-out, which costs registers too, is left out).
 template <uint32_t kSrcPerPart, bool kPacked, bool kDynamic, bool kRuns>
 __global__ __launch_bounds__(kScatterBlock) __attribute__((amdgpu_waves_per_eu(kSrcPerPart == kSrcSmall ? 8 : 4, kSrcPerPart == kSrcSmall ? 8 : 4)))
-void k_scatter(DevArgs A, GateArg G, uint32_t tile0, uint32_t n_tiles, int parity, int first)
+void k_scatter(DevArgs A, GateArg G, uint32_t tile0, uint32_t n_tiles, int parity, int first, const ScatterTile* __restrict__ tiles)
 {
     __shared__ __align__(16) float slice[kSrcPerPart];
     __shared__ uint2 desc[kDescBatch];
     __shared__ uint32_t gpre[kScatterBlock + 1];          // groups before each bin of the batch; [kScatterBlock] = all
-    __shared__ uint32_t wave_tot[kScatterWaves + 1];
+    __shared__ uint32_t wave_tot[kScatterWaves];
     __shared__ float red[kScatterWaves];
     __shared__ float groups[kStrands / 64];
     __shared__ uint32_t next_local;
@@ -499,12 +564,20 @@ void k_scatter(DevArgs A, GateArg G, uint32_t tile0, uint32_t n_tiles, int parit
     static_assert(kScatterBlock == kStrands, "a thread per strand");
     if (!fr_gate_admit(G.gate, G.slot, kDynamic ? G.tile_ticks : G.need_ticks)) return;
     const uint32_t Qe = A.Qe;
-    float base = 0.0f;
-    if (!first) {
-        dangling_group(dangling_strand(A.dpart + (size_t)parity * A.n_dpart, A.n_dpart, threadIdx.x), threadIdx.x & ~63u, groups);
-        __syncthreads();
-        base = (1.0f - A.damping) / (float)A.V + A.damping * dangling_total(groups) / (float)A.V;
-    }
+    float strand = 0.0f, base = 0.0f;
+    if (!first) strand = dangling_strand(A.dpart + (size_t)parity * A.n_dpart, A.n_dpart, threadIdx.x);
+    bool summed = first;                          // base is known
+    auto base_value = [&] { return (1.0f - A.damping) / (float)A.V + A.damping * dangling_total(groups) / (float)A.V; };
+    // Where a workgroup does one tile of the small size the groups are numbered while the slice's values are not there yet, and
+    // the dangling partials put together behind the same barrier.  (The large size asks for its slice, 128 KB, first: 2^24 / 2^28
+    // 116.8 -> 113.6 us a sweep; and where tiles are handed out there are no registers for it.)
+    constexpr bool kNumberFirst = kSrcPerPart == kSrcSmall && !kDynamic;
+    if constexpr (!kNumberFirst)
+        if (!first) {
+            dangling_group(strand, threadIdx.x & ~63u, groups);
+            __syncthreads();
+            base = base_value();
+        }
     constexpr uint32_t kGroup = kRuns ? 4 : 8;
     // rows a thread reads per round while the slice is filled (the small size has 64 registers per lane)
     constexpr int kFillRound = kSrcPerPart == kSrcSmall ? 4 : 16;
@@ -514,6 +587,25 @@ void k_scatter(DevArgs A, GateArg G, uint32_t tile0, uint32_t n_tiles, int parit
         // the first batch of bin descriptors is asked for now and used after the slice is filled
         uint2 d_first = make_uint2(0, 0);
         if (threadIdx.x < Qe) d_first = A.bins[(uint64_t)t * Qe + threadIdx.x];
+        uint32_t total = 0, step0 = 0;            // groups of the batch; for the search among its bins
+        // the groups of a batch of bins are numbered (`then`: what is ready for the same barrier)
+        auto number_groups = [&](uint2 d, uint32_t nb, auto then) {
+            if (d.y > A.M) d.y = A.M;
+            if (d.x > d.y) d.x = d.y;
+            const uint32_t mine = threadIdx.x < nb && d.y > d.x ? (d.y - 1) / kGroup - d.x / kGroup + 1 : 0;
+            const uint32_t before = scan_in_wave(mine, wave_tot);
+            then();
+            __syncthreads();
+            gpre[threadIdx.x] = scan_over_waves(before, wave_tot, &total);
+            if (threadIdx.x == 0) gpre[kScatterBlock] = total;
+            desc[threadIdx.x] = d;
+            if constexpr (!kRuns) step0 = nb > 1 ? 1u << (31 - __builtin_clz(nb - 1)) : 0u;
+        };
+        if constexpr (kNumberFirst) {
+            number_groups(d_first, Qe < kDescBatch ? Qe : kDescBatch, [&] { if (!summed) dangling_group(strand, threadIdx.x & ~63u, groups); });
+            if (!summed) base = base_value();
+            summed = true;
+        }
         const uint32_t u0 = T.u0;
         const uint32_t n = T.u1 - T.u0 < kSrcPerPart ? T.u1 - T.u0 : kSrcPerPart;
         if (first) {
@@ -532,59 +624,81 @@ void k_scatter(DevArgs A, GateArg G, uint32_t tile0, uint32_t n_tiles, int parit
                 }
             }
         } else {
-            const float total = block_sum(fill_slice<kScatterBlock, kFillRound, kSrcPerPart == kSrcLarge>(A, u0, n, base, slice, first_info), red);
-            if (threadIdx.x == 0) A.dpart[(size_t)(parity ^ 1) * A.n_dpart + A.n_pieces + t] = total;
+            const float mass = wave_sum(fill_slice<kScatterBlock, kFillRound, kSrcPerPart == kSrcLarge>(A, u0, n, base, slice, first_info));
+            if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = mass;
         }
-        for (uint32_t qb = 0; qb < Qe; qb += kDescBatch) {
+        for (uint32_t qb = 0; qb == 0 || qb < Qe; qb += kDescBatch) {       // (once where there are no bins at all)
             const uint32_t nb = Qe - qb < kDescBatch ? Qe - qb : kDescBatch;
-            __syncthreads();                                     // slice filled / previous batch consumed
-            uint32_t groups = 0;
-            if (threadIdx.x < nb) {
-                uint2 d = qb == 0 ? d_first : A.bins[(uint64_t)t * Qe + qb + threadIdx.x];
-                if (d.y > A.M) d.y = A.M;
-                if (d.x > d.y) d.x = d.y;
-                desc[threadIdx.x] = d;
-                if (d.y > d.x) groups = (d.y - 1) / kGroup - d.x / kGroup + 1;
+            if (!kNumberFirst || qb) {
+                __syncthreads();                                 // previous batch consumed
+                uint2 d = d_first;
+                if (qb) d = threadIdx.x < nb ? A.bins[(uint64_t)t * Qe + qb + threadIdx.x] : make_uint2(0, 0);
+                number_groups(d, nb, [] {});
             }
-            block_exclusive_scan(groups, gpre, wave_tot);
-            const uint32_t total = gpre[kScatterBlock];
-            constexpr uint32_t kAhead = 4;                       // groups a thread has in flight, kApart numbers apart
-            constexpr uint32_t kApart = kRuns ? 64 : kScatterBlock;
-            // (runs are shorter where all wavefronts get some then)
-            const uint32_t ahead = !kRuns || total >= kAhead * kScatterBlock ? kAhead : (total + kScatterBlock - 1) / kScatterBlock;
-            const uint32_t k_first = kRuns ? (threadIdx.x / 64) * (ahead * 64) + threadIdx.x % 64 : threadIdx.x;
-            for (uint32_t k0 = k_first; k0 < total; k0 += ahead * kScatterBlock) {
-                // the question for the next tile goes out with the tile's last groups: put earlier, a workgroup on a
-                // heavy tile would book its next tile hundreds of microseconds before it is free to start it
-                if constexpr (kDynamic)
-                    if (threadIdx.x == 0 && last_piece && qb + kDescBatch >= Qe && k0 + ahead * kScatterBlock >= total)
-                        asked = ask_if_time(A.sched, G);
-                GroupRef ref[kAhead];
-                GroupSources<kGroup> raw[kAhead];
-                uint32_t bin = 0;
+            __syncthreads();                                     // slice filled, groups numbered
+            if (qb == 0 && !first && threadIdx.x == 0) {
+                float mass = 0.0f;
 #pragma unroll
-                for (uint32_t a = 0; a < kAhead; ++a) {
-                    const uint32_t k = k0 + a * kApart;
-                    ref[a] = GroupRef{0, 0};
-                    raw[a] = GroupSources<kGroup>{};
-                    if (a < ahead && k < total) {
-                        bin = !kRuns || a == 0 ? find_bin(k, gpre, 0, nb) : next_bin(k, gpre, bin, nb);
-                        ref[a] = GroupRef{(desc[bin].x / kGroup + (k - gpre[bin])) * kGroup, bin};
+                for (int w = 0; w < kScatterWaves; ++w) mass += red[w];
+                A.dpart[(size_t)(parity ^ 1) * A.n_dpart + A.n_pieces + t] = mass;
+            }
+            // the question for the next tile goes out with the tile's last groups: put earlier, a workgroup on a
+            // heavy tile would book its next tile hundreds of microseconds before it is free to start it
+            auto ask_with_last = [&](bool last_groups) {
+                if constexpr (kDynamic)
+                    if (threadIdx.x == 0 && last_piece && qb + kDescBatch >= Qe && last_groups) asked = ask_if_time(A.sched, G);
+            };
+            auto group_at = [&](uint32_t k, uint32_t bin) { return GroupRef{(desc[bin].x / kGroup + (k - gpre[bin])) * kGroup, bin}; };
+            if constexpr (!kRuns) {
+                constexpr uint32_t kAhead = 4;                   // groups a thread has in flight
+                for (uint32_t k0 = threadIdx.x; k0 < total; k0 += kAhead * kScatterBlock) {
+                    ask_with_last(k0 + kAhead * kScatterBlock >= total);
+                    uint32_t number[kAhead], bin[kAhead];
+                    GroupRef ref[kAhead];
+                    GroupSources<kGroup> raw[kAhead];
+#pragma unroll
+                    for (uint32_t a = 0; a < kAhead; ++a) number[a] = k0 + a * kScatterBlock < total ? k0 + a * kScatterBlock : k0;
+                    find_bins(number, gpre, step0, bin);
+#pragma unroll
+                    for (uint32_t a = 0; a < kAhead; ++a) {      // (behind the last group: one that is there)
+                        ref[a] = group_at(number[a], bin[a]);
                         raw[a] = load_group<kGroup>(A.src16, ref[a].m0);
                     }
-                }
 #pragma unroll
-                for (uint32_t a = 0; a < kAhead; ++a)
-                    if (a < ahead && k0 + a * kApart < total) emit_group<kGroup>(ref[a], desc, raw[a], slice, n, A.msg);
+                    for (uint32_t a = 0; a < kAhead; ++a)
+                        if (k0 + a * kScatterBlock < total) emit_group<kGroup>(ref[a], desc, raw[a], slice, n, A.msg);
+                }
+            } else {
+                // (runs are shorter where all wavefronts get some then)
+                constexpr uint32_t kAhead = 4;
+                const uint32_t ahead = total >= kAhead * kScatterBlock ? kAhead : (total + kScatterBlock - 1) / kScatterBlock;
+                for (uint32_t k0 = (threadIdx.x / 64) * (ahead * 64) + threadIdx.x % 64; k0 < total; k0 += ahead * kScatterBlock) {
+                    ask_with_last(k0 + ahead * kScatterBlock >= total);
+                    GroupRef ref[kAhead];
+                    GroupSources<kGroup> raw[kAhead];
+                    uint32_t bin = 0;
+#pragma unroll
+                    for (uint32_t a = 0; a < kAhead; ++a) {
+                        const uint32_t k = k0 + a * 64;
+                        ref[a] = GroupRef{0, 0};
+                        raw[a] = GroupSources<kGroup>{};
+                        if (a < ahead && k < total) {
+                            bin = a == 0 ? find_bin(k, gpre, 0, nb) : next_bin(k, gpre, bin, nb);
+                            ref[a] = group_at(k, bin);
+                            raw[a] = load_group<kGroup>(A.src16, ref[a].m0);
+                        }
+                    }
+#pragma unroll
+                    for (uint32_t a = 0; a < kAhead; ++a)
+                        if (a < ahead && k0 + a * 64 < total) emit_group<kGroup>(ref[a], desc, raw[a], slice, n, A.msg);
+                }
             }
         }
     };
     uint32_t local = xcd_runs(blockIdx.x, gridDim.x);
     do {
-        if (tile0 + local == 0 && !first && A.void_slot != kNoVoid && threadIdx.x == 0)       // (once per sweep)
-            A.dpart[(size_t)(parity ^ 1) * A.n_dpart + A.n_pieces + A.void_slot] = base * A.n_void_dangling;
         asked = kAskLater;
-        const uint4* rec = reinterpret_cast<const uint4*>(A.scatter_tiles + tile0 + local);
+        const uint4* rec = reinterpret_cast<const uint4*>(tiles + (tile0 + (uint32_t)__builtin_amdgcn_readfirstlane((int)local)));
         const uint4 span = rec[0];                               // x, y: the tile's pieces, worked on one after the other;
         const uint4 span_info = rec[1];                          // z, w: the sources of the first; then their range
         if constexpr (!kPacked) {
@@ -603,6 +717,8 @@ void k_scatter(DevArgs A, GateArg G, uint32_t tile0, uint32_t n_tiles, int parit
                 __syncthreads();                                 // the piece is done with slice and desc
             }
         }
+        if (tile0 + local == 0 && !first && A.void_slot != kNoVoid && threadIdx.x == 0)       // (once per sweep)
+            A.dpart[(size_t)(parity ^ 1) * A.n_dpart + A.n_pieces + A.void_slot] = base * A.n_void_dangling;
         if constexpr (kDynamic) {
             if (threadIdx.x == 0) next_local = settle_next_tile(asked, A.sched, G, n_tiles);
             __syncthreads();
@@ -957,7 +1073,7 @@ int pr_launch(PrTask* p, uint32_t g, uint32_t tile0, uint32_t tile1, hipStream_t
             const int parity = (int)((k + 1) & 1u), first = k == 0 ? 1 : 0;
             const uint32_t grid = std::min(n, p->L.scatter_slots);
             const bool packed = p->L.scatter_packed, dynamic = n > grid;
-            auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(grid), dim3(kScatterBlock), 0, stream, args, G, tile0, n, parity, first); };
+            auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(grid), dim3(kScatterBlock), 0, stream, args, G, tile0, n, parity, first, args.scatter_tiles); };
             const bool runs = scatter_in_runs(p->L.src_per_part, p->d.n_vertices, p->L.cus, dynamic);
             auto go_as = [&](auto packs) {
                 constexpr bool kPacked = decltype(packs)::value;
