@@ -389,8 +389,8 @@ int fr_pagerank_run_standalone(void* user, int32_t device_id, void* stream, uint
                                uint64_t* phase_ns_out);
 /*
  * A program that sets up standalone PageRank tasks one after the other (less than five seconds from one set-up to the
- * next) leaves set-up scratch with the library for the next one, at most 1/64 of the device's memory, also when every
- * task is destroyed.  It is given back when a context is made or destroyed, when an allocation of the library fails, after
+ * next) leaves set-up scratch with the library for the next one, at most 1/64 of the device's memory, and what a
+ * task of such a series held, at most 1/256, also when every task is destroyed.  It is given back when a context is made or destroyed, when an allocation of the library fails, after
  * five seconds without use at the next set-up, and by this call, which a program makes when it is done setting up
  * graphs and another allocator is to have the memory.  *bytes_out (may be NULL) receives the bytes given back.
  */

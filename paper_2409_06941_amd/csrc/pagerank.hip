@@ -1099,13 +1099,6 @@ int pr_launch(PrTask* p, uint32_t g, uint32_t tile0, uint32_t tile1, hipStream_t
     return FR_OK;
 }
 
-template <typename T>
-bool take(fr_alloc* a, T** out, uint64_t count)
-{
-    *out = static_cast<T*>(fr_alloc_device(a, (size_t)(count ? count : 1) * sizeof(T)));
-    return *out != nullptr;
-}
-
 int pr_init(void* user, fr_alloc* a, void* stream_v)
 {
     PrTask* p = static_cast<PrTask*>(user);
@@ -1121,9 +1114,10 @@ int pr_init(void* user, fr_alloc* a, void* stream_v)
     PrLayout& L = p->L;
     // dangling partials: one slot per range (V0), or one per gather piece followed by one per scatter piece
     p->n_dpart = std::max(L.Q, L.n_pieces + L.n_spieces);
-    if (!take(a, &p->msg, L.M) || !take(a, &p->contrib, (uint64_t)V) || !take(a, &p->dpart, 2ull * p->n_dpart) ||
-        !take(a, &p->partials, (uint64_t)L.n_partials * L.rows_per_part) || !take(a, &p->sched, 2))
-        return a->hip_error ? FR_ERR_HIP : FR_ERR_OOM;
+    Carve work;
+    work.add(&p->msg, L.M); work.add(&p->contrib, (uint64_t)V); work.add(&p->dpart, 2ull * p->n_dpart);
+    work.add(&p->partials, (uint64_t)L.n_partials * L.rows_per_part); work.add(&p->sched, 2);
+    if (!work.keep_apart(a)) return a->hip_error ? FR_ERR_HIP : FR_ERR_OOM;
     hipLaunchKernelGGL(k_clear_sched, dim3(1), dim3(64), 0, stream, p->sched);
     if (hipStreamSynchronize(stream) != hipSuccess) return FR_ERR_HIP;
     DevArgs& A = p->args;
@@ -1302,8 +1296,8 @@ int fr_pagerank_destroy(void* user)
     if (!p) return FR_ERR_ARG;
     if (p->registered) return FR_ERR_STATE;
     if (p->inited) {
-        (void)hipDeviceSynchronize();
-        fr_alloc_release(&p->own);
+        if (hipDeviceSynchronize() == hipSuccess) fr_alloc_hand_back(&p->own);
+        else fr_alloc_release(&p->own);
     }
     delete p;
     return FR_OK;

@@ -248,12 +248,14 @@ __device__ __forceinline__ uint32_t tile_of_source(const uint32_t* __restrict__ 
 // (2^22 vertices: the whole array is a 16 MB copy to memory the host has to touch first, and a walk over it.)
 constexpr uint64_t kHeadSources = 1u << 18, kFineSources = 16;
 __global__ __launch_bounds__(kBlk) void k_source_facts(uint64_t V, const uint32_t* __restrict__ cnt, const uint32_t* __restrict__ cum,
-                                                       uint64_t* __restrict__ sends, uint32_t* __restrict__ fine)
+                                                       uint64_t* __restrict__ sends, uint32_t* __restrict__ fine, uint32_t* __restrict__ all)
 {
     const uint64_t u = (uint64_t)blockIdx.x * kBlk + threadIdx.x;
     const uint64_t any = __ballot(u < V && cnt[u] != 0);
     if ((threadIdx.x & 63) == 0 && u < V) sends[u / 64] = any;
-    if (u >= kHeadSources && u < V && u % kFineSources == 0) fine[(u - kHeadSources) / kFineSources] = cum[u];
+    if (u >= V) return;
+    if (u >= kHeadSources && u % kFineSources == 0) fine[(u - kHeadSources) / kFineSources] = cum[u];
+    if (u == V - 1) *all = cum[u] + cnt[u];
 }
 
 __global__ __launch_bounds__(kBlk) void k_zero_u32(uint64_t n, uint32_t* p)
@@ -359,37 +361,6 @@ struct Scratch {
     }
 };
 
-// Several arrays in one block of the allocator, each on a 256-byte boundary: what they count as is what they would as
-// blocks of their own, at the price of one allocation (10 to 300 us each, and as much to give back).
-struct Carve {
-    uint64_t bytes = 0;
-    struct Part { void** where; uint64_t at; };
-    std::vector<Part> parts;
-    template <typename T>
-    void add(T** out, uint64_t count)
-    {
-        parts.push_back({reinterpret_cast<void**>(out), bytes});
-        bytes += ((count ? count : 1) * sizeof(T) + 255) / 256 * 256;
-    }
-    void place(void* base)
-    {
-        for (const Part& x : parts) *x.where = static_cast<char*>(base) + x.at;
-    }
-    bool keep(fr_alloc* a)
-    {
-        void* base = fr_alloc_device(a, (size_t)bytes);
-        if (base) place(base);
-        return base != nullptr;
-    }
-};
-
-template <typename T>
-bool keep(fr_alloc* a, T** out, uint64_t count)
-{
-    *out = static_cast<T*>(fr_alloc_device(a, (size_t)(count ? count : 1) * sizeof(T)));
-    return *out != nullptr;
-}
-
 }  // namespace
 
 #define PREP_HIP(expr)                                             \
@@ -438,7 +409,11 @@ int pr_build_layout(PrLayout* L, int64_t V, int64_t E, const int32_t* row_ptr, c
     // ---- vertices in order of falling in-degree; those without in-edges by falling out-degree
     // The keys' two buffers are taken first; while the second is unused, what is needed to order the vertices and to make
     // the keys lies in it, if it has room (E of about 4 V; else it has blocks of its own, given back as soon as they are done with).
-    if (!keep(a, &L->perm, (uint64_t)V) || !keep(a, &L->inv_out, (uint64_t)V)) PREP_NEED((void*)nullptr);
+    {
+        Carve kept;
+        kept.add(&L->perm, (uint64_t)V); kept.add(&L->inv_out, (uint64_t)V);
+        if (!kept.keep_apart(a)) PREP_NEED((void*)nullptr);
+    }
     int32_t* inv = nullptr;
     uint64_t* keys_a = nullptr;
     uint64_t* keys_b = nullptr;
@@ -530,8 +505,11 @@ int pr_build_layout(PrLayout* L, int64_t V, int64_t E, const int32_t* row_ptr, c
     // ---- scatter pieces: source intervals of about equal numbers of messages
     // (`cum`: messages before each of the first kHeadSources sources, then before every kFineSources-th; `sends`: a bit a source)
     const uint64_t n_head = std::min<uint64_t>((uint64_t)V, kHeadSources), n_fine = ((uint64_t)V - n_head + kFineSources - 1) / kFineSources;
-    std::vector<uint32_t> cum(n_head + n_fine, 0u), rep_host(L->n_chunks), mbase_host((size_t)L->n_chunks + 1, 0u);
-    std::vector<uint64_t> sends(((uint64_t)V + 63) / 64, 0ull);
+    const uint64_t n_words = ((uint64_t)V + 63) / 64;
+    const uint32_t *cum_head = nullptr, *cum_fine = nullptr, *rep_host = nullptr;
+    const uint64_t* sends = nullptr;
+    std::vector<uint64_t> facts;                       // the four of them, as they come from the device in one copy
+    std::vector<uint32_t> mbase_host((size_t)L->n_chunks + 1, 0u);
     {
         Carve kept;
         kept.add(&L->starts, (uint64_t)padded / kIdChunk * kStartWords); kept.add(&L->mbase, (uint64_t)L->n_chunks + 1);
@@ -545,9 +523,11 @@ int pr_build_layout(PrLayout* L, int64_t V, int64_t E, const int32_t* row_ptr, c
         PREP_HIP(rocprim::exclusive_scan(nullptr, bytes, cnt, cum_dev, 0u, (size_t)V, rocprim::plus<uint32_t>(), stream));
         PREP_HIP(rocprim::exclusive_scan(nullptr, bytes_m, messages, L->mbase, 0u, (size_t)L->n_chunks + 1, rocprim::plus<uint32_t>(), stream));
         Carve parts;
-        parts.add(&cnt, (uint64_t)V); parts.add(&cum_dev, (uint64_t)V); parts.add(&messages, (uint64_t)L->n_chunks + 1); parts.add(&rep, (uint64_t)L->n_chunks);
-        parts.add(&fine, n_fine); parts.add(&sends_dev, sends.size()); parts.add(&t, std::max(bytes, bytes_m));
-        void* block = tmp.take<uint8_t>(parts.bytes);
+        // (rep's last entry: the messages of all sources; the host takes everything up to the head of cum in one copy)
+        parts.add(&fine, n_fine); parts.add(&sends_dev, n_words); parts.add(&rep, (uint64_t)L->n_chunks + 1);
+        const uint64_t fact_bytes = parts.bytes + n_head * 4;
+        parts.add(&cum_dev, (uint64_t)V); parts.add(&cnt, (uint64_t)V); parts.add(&messages, (uint64_t)L->n_chunks + 1); parts.add(&t, std::max(bytes, bytes_m));
+        char* block = static_cast<char*>(static_cast<void*>(tmp.take<uint8_t>(parts.bytes)));
         PREP_NEED(block);
         parts.place(block);
         hipLaunchKernelGGL(k_zero_u32, dim3(blocks_for((uint64_t)V)), dim3(kBlk), 0, stream, (uint64_t)V, cnt);
@@ -555,26 +535,31 @@ int pr_build_layout(PrLayout* L, int64_t V, int64_t E, const int32_t* row_ptr, c
                            messages, rep, cnt);
         PREP_HIP(rocprim::exclusive_scan(t, bytes_m, messages, L->mbase, 0u, (size_t)L->n_chunks + 1, rocprim::plus<uint32_t>(), stream));
         PREP_HIP(rocprim::exclusive_scan(t, bytes, cnt, cum_dev, 0u, (size_t)V, rocprim::plus<uint32_t>(), stream));
-        hipLaunchKernelGGL(k_source_facts, dim3(blocks_for((uint64_t)V)), dim3(kBlk), 0, stream, (uint64_t)V, cnt, cum_dev, sends_dev, fine);
-        uint32_t last[2] = {0, 0};
-        PREP_HIP(hipMemcpyAsync(cum.data(), cum_dev, n_head * 4, hipMemcpyDeviceToHost, stream));
-        if (n_fine) PREP_HIP(hipMemcpyAsync(cum.data() + n_head, fine, n_fine * 4, hipMemcpyDeviceToHost, stream));
-        PREP_HIP(hipMemcpyAsync(sends.data(), sends_dev, sends.size() * 8, hipMemcpyDeviceToHost, stream));
-        PREP_HIP(hipMemcpyAsync(&last[0], cum_dev + (V - 1), 4, hipMemcpyDeviceToHost, stream));
-        PREP_HIP(hipMemcpyAsync(&last[1], cnt + (V - 1), 4, hipMemcpyDeviceToHost, stream));
-        PREP_HIP(hipMemcpyAsync(rep_host.data(), rep, (size_t)L->n_chunks * 4, hipMemcpyDeviceToHost, stream));
+        hipLaunchKernelGGL(k_source_facts, dim3(blocks_for((uint64_t)V)), dim3(kBlk), 0, stream, (uint64_t)V, cnt, cum_dev, sends_dev, fine, rep + L->n_chunks);
+        facts.resize(fact_bytes / 8 + 1);                 // (while the device works)
+        PREP_HIP(hipMemcpyAsync(facts.data(), block, fact_bytes, hipMemcpyDeviceToHost, stream));
         PREP_HIP(hipMemcpyAsync(mbase_host.data(), L->mbase, ((size_t)L->n_chunks + 1) * 4, hipMemcpyDeviceToHost, stream));
         PREP_HIP(hipStreamSynchronize(stream));
+        auto on_host = [&](const void* p) { return static_cast<const void*>(reinterpret_cast<const char*>(facts.data()) + (static_cast<const char*>(p) - block)); };
+        cum_head = static_cast<const uint32_t*>(on_host(cum_dev));
+        cum_fine = static_cast<const uint32_t*>(on_host(fine));
+        sends = static_cast<const uint64_t*>(on_host(sends_dev));
+        rep_host = static_cast<const uint32_t*>(on_host(rep));
+        const uint32_t sum = rep_host[L->n_chunks];
         tmp.drop(block);
         M = mbase_host[L->n_chunks];
-        if (last[0] + last[1] != M) return FR_ERR_ARG;
+        if (sum != M) return FR_ERR_ARG;
     } else {
+        facts.assign((n_head + n_fine) / 2 + 1 + n_words, 0ull);       // no messages, and no source that sends any
+        sends = facts.data();
+        cum_head = reinterpret_cast<const uint32_t*>(facts.data() + n_words);
+        cum_fine = cum_head + n_head;
         PREP_HIP(hipMemcpyAsync(L->mbase, mbase_host.data(), 4, hipMemcpyHostToDevice, stream));
     }
     // messages of the sources before u: any u up to kHeadSources, beyond it a multiple of kFineSources or V
     auto messages_before = [&](uint64_t u) -> uint64_t {
         if (u >= (uint64_t)V) return M;
-        return u < n_head ? cum[u] : cum[n_head + (u - n_head) / kFineSources];
+        return u < n_head ? cum_head[u] : cum_fine[(u - n_head) / kFineSources];
     };
     L->M = M;
 
@@ -747,7 +732,7 @@ int pr_build_layout(PrLayout* L, int64_t V, int64_t E, const int32_t* row_ptr, c
                 voids.push_back({lo, hi}); void_rows_before_void.push_back(rows);
                 rows += hi - lo;
             };
-            for (uint64_t k = first_voidable / 64; k < sends.size(); ++k) {
+            for (uint64_t k = first_voidable / 64; k < n_words; ++k) {
                 uint64_t w = sends[k];
                 if (k == first_voidable / 64) w &= ~0ull << (first_voidable % 64);
                 if (!w) continue;
@@ -758,13 +743,17 @@ int pr_build_layout(PrLayout* L, int64_t V, int64_t E, const int32_t* row_ptr, c
             void_rows_before_void.push_back(rows);
         }
         auto void_rows_before = [&](uint64_t u) -> uint64_t {        // rows of void runs among the sources before u
+            if (voids.empty() || u <= voids[0].first) return 0;
             const size_t k = (size_t)(std::upper_bound(voids.begin(), voids.end(), std::pair<uint64_t, uint64_t>(u, ~(uint64_t)0)) - voids.begin());   // runs starting at or before u
             if (k == 0) return 0;
             return void_rows_before_void[k - 1] + std::min(u, voids[k - 1].second) - voids[k - 1].first;
         };
+        // (asked for some 20 times a piece and cut: with a division and a search among the void runs each time most of the 1.7 ms
+        // that the device waited for the host's cuts on 2^22 vertices / 2^26 edges)
+        const int row_bits = rows_per_part == kRowsLarge ? 14 : 13;
         auto weight_before = [&](uint64_t u) -> uint64_t {
-            const uint64_t j = std::min<uint64_t>(u / rows_per_part, Q);
-            const uint64_t rows = rows_before[j] + (j < Q ? (u - j * rows_per_part) * per_row[j] : 0);
+            const uint64_t j = std::min<uint64_t>(u >> row_bits, Q);
+            const uint64_t rows = rows_before[j] + (j < Q ? (u - (j << row_bits)) * per_row[j] : 0);
             return kScatterMessageWeight * messages_before(u) + kScatterRowWeight * (rows - void_rows_before(u));
         };
         auto cut = [&](uint64_t target) {
