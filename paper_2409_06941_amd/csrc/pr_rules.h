@@ -1,4 +1,10 @@
 // The sizes of the partition-centric layout, and the rules that choose among its kernels.  Host code only.
+// (The times beside the rules are of the sweeps as they were when each line was drawn, both sides by the same kernels.  With the
+// present ones - a branch-free gather loop, side-by-side searches in the scatter sweep - the sums are 4 to 20 % less and the lines lie
+// where they were: us an iteration, as the rules say / with the other side of the gather's, of the scatter's:
+//   10^6 / 10^7 25.6 / 28.1 (two a unit) / 26.1; 2^16 / 2^20 on 64 units 17.2 / 17.4 / 17.9; uniform 2^17 / 2^21 on 128 18.9 / 18.8 / 19.9;
+//   2^20 / 2^24 on 64 60.5 / 62.1 (one a unit) / 65.8; 3 x 10^6 / 6 x 10^7 on 128 103.9 / 105.4 / 120.9;
+//   kMergeBalance 20, 29, 40: 2^18 / 2^22 22.3, 20.3, 21.0.)
 #ifndef FR_PR_RULES_H
 #define FR_PR_RULES_H
 

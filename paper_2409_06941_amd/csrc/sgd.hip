@@ -41,6 +41,7 @@ constexpr uint64_t kMostBytes = 128;              // per rating that the rounds'
 constexpr uint32_t kMaxBlocks = 1024;
 constexpr int64_t kMaxIds = (1ll << 27) - 1024;
 constexpr uint32_t kNoBatch = 0xffffffffu;
+constexpr uint32_t kFetchAheadBlocks = 128;       // from which on the next stratum's programs are read ahead (see k_sgd)
 constexpr int kMaxLds = (kMaxRounds + 3) * 2 * 16 + (2 * kBatch + 1) * 256;      // of a batch of 64 factors: 74 KB
 
 // A batch: a record of `stride` 16-byte words, the head and then the ids of its rows (users, then items with kItemRow set,
@@ -60,7 +61,8 @@ struct SgdArgs {
     const uint4* entries;
     float* P;
     float* Q;
-    uint32_t stride;             // 16-byte words of a record
+    uint32_t layout;             // 16-byte words of a record | blocks << 16 (in a word of its own the launch's arguments would end in
+                                 // another cache line, 0.2 us a launch)
     float gamma, gl;             // gl = gamma * lambda, rounded once
 };
 
@@ -153,17 +155,21 @@ typedef float float4_any __attribute__((ext_vector_type(4), aligned(4)));
 // side by side in one wavefront, laid out once by k_sgd_schedule.  All four wavefronts bring the batch's rows to LDS, the
 // first one works through the rounds, all four write the rows back.
 // What bounds it: the longest chain of a stratum (16.1 M ratings, 512 x 512 cells, 64 factors: 85 updates, where its largest
-// cell has 109 ratings and a mean cell 61), at 105 ns a round with 64 factors, 94 with 32, 80 with 16 (a cell that is one chain of
-// n ratings takes 2.2 us + n rounds): one wavefront's instructions, some forty, and the latency of the sum's dependent moves.
+// cell has 109 ratings and a mean cell 61), at 82 ns a round with 64 factors, 74 with 32, 56 with 16 (a cell that is one chain of
+// n ratings takes 2.5 us + n rounds): one wavefront's instructions, some forty, and the latency of the sum's dependent moves.
 // Hence 32 lanes with two factors each (90.7 rounds) and not 16 with four (87.5 rounds of half as many instructions again),
 // rows fetched from LDS a round ahead, before the stores of the round that is being computed, and the row of a chain handed on
-// in registers.  A stratum takes 15 us there, of which the rounds are some 9.5; the rest is fetching and storing 42 000 rows (21 MB) and the
-// launch.  An iteration of 512 strata takes 7.7 ms; one rating after the other straight from memory, as k_sgd_chain does it, it
-// took 21.9 ms (16 factors, 300 000 ratings in 64 x 64 cells: 0.46 and 1.9 ms).
+// in registers; and twelve rounds without a branch (six with 32 factors, where twelve are no better): at a loop's head the
+// wavefront waits for everything it has asked the LDS for, which every third round took 102, 89 and 75 ns a round.  A stratum
+// takes 14 us there, of which the rounds are some 7.5; the rest is fetching and storing 42 000 rows (21 MB) and the
+// launch.  An iteration of 512 strata takes 7.3 ms (8.3 with branches between the rounds and nothing read ahead); one rating after
+// the other straight from memory, as k_sgd_chain does it, it took 21.9 ms (16 factors, 300 000 ratings in 64 x 64 cells: 0.40, 0.45
+// and 1.9 ms).
 template <int F, int kLanes>
 __device__ __forceinline__ void run_rounds(LdsBytes entries, uint32_t rounds, float gamma, float gl)
 {
     constexpr int kN = F / kLanes, kSlots = 64 / kLanes;
+    constexpr uint32_t kUnroll = F == 32 ? 6 : 12;
     const uint32_t lane = threadIdx.x & 63, at = (lane % kLanes) * (kN * 4);
     const LdsBytes mine = entries + (lane / kLanes) * sizeof(SlotEntry);
     struct Turn { float rating; uint32_t p, q; };         // p, q: as in the entry, and addresses once the rows are asked for
@@ -205,7 +211,17 @@ __device__ __forceinline__ void run_rounds(LdsBytes entries, uint32_t rounds, fl
             q.v[k] = keep_q ? q2.v[k] : qn.v[k];
         }
     };
-    for (uint32_t r = 0; r < rounds;) {                   // (three more entries are there to be read)
+    // (three more entries are there to be read)
+    uint32_t r = 0;
+    for (; r + kUnroll <= rounds; r += kUnroll) {         // one basic block: at a loop's head the wavefront waits for all of the LDS
+#pragma unroll
+        for (uint32_t k = 0; k < kUnroll; k += 3) {
+            step(A, B, r + k);
+            step(B, C, r + k + 1);
+            step(C, A, r + k + 2);
+        }
+    }
+    while (r < rounds) {
         step(A, B, r);
         if (++r == rounds) break;
         step(B, C, r);
@@ -223,12 +239,13 @@ __global__ __launch_bounds__(kSgdBlock) void k_sgd(SgdArgs A, GateArg G, uint32_
     if (!fr_gate_admit(G.gate, G.slot, G.need_ticks)) return;
     constexpr uint32_t kSlots = 64 / lanes_for(F), kWords = F / 4;      // 16-byte words of a row
     constexpr int kDepth = F / 8 + 2;                                   // words in flight per thread: 160 rows or more at once
+    const uint32_t stride = A.layout & 0xffffu, blocks = A.layout >> 16;
     uint32_t b = cell0 + blockIdx.x;
     do {
-        const uint4* record = A.records + (uint64_t)b * A.stride;
+        const uint4* record = A.records + (uint64_t)b * stride;
         const uint32_t* ids = reinterpret_cast<const uint32_t*>(record + 1);
         const uint4 head = record[0];
-        const uint32_t most = (A.stride - 1) * 4 * kWords;              // words of the rows there can be
+        const uint32_t most = (stride - 1) * 4 * kWords;              // words of the rows there can be
         uint32_t id[kDepth];
         auto ask_ids = [&](uint32_t i0) {
 #pragma unroll
@@ -260,9 +277,31 @@ __global__ __launch_bounds__(kSgdBlock) void k_sgd(SgdArgs A, GateArg G, uint32_
             ask_ids(i0);
         }
         __syncthreads();
-        if (threadIdx.x < 64 && H.rounds) {                             // (a cell without ratings has no entries to read)
-            const LdsBytes at = reinterpret_cast<LdsBytes>((uint32_t)((n_rows + 1) * (F * 4)));
-            run_rounds<F, lanes_for(F)>(at, H.rounds, A.gamma, A.gl);
+        if (threadIdx.x < 64) {
+            if (H.rounds) {                                             // (a cell without ratings has no entries to read)
+                const LdsBytes at = reinterpret_cast<LdsBytes>((uint32_t)((n_rows + 1) * (F * 4)));
+                run_rounds<F, lanes_for(F)>(at, H.rounds, A.gamma, A.gl);
+            }
+        } else if (blocks >= kFetchAheadBlocks && b < blocks * blocks) {
+            // meanwhile the other wavefronts read what the next stratum's cell of this user block begins with - its record, its
+            // entries and its rows of P, which no other workgroup writes - so that the launch of that stratum, whose workgroup
+            // of this number runs on the same compute die, finds them in its L2.  From 128 blocks on, where a stratum's
+            // programs come from memory: ms an iteration, without -> with, 512 blocks 7.61 -> 7.32, 256 3.91 -> 3.77 (32 factors, two
+            // iterations) and 7.19 -> 6.84 (16, two), 128 2.20 -> 2.17 and 1.82 -> 1.69; 32 0.79 -> 0.82 (64, three)
+            const uint32_t after = b + blocks < blocks * blocks ? b + blocks : b + blocks - blocks * blocks;
+            const uint4* soon = A.records + (uint64_t)after * stride;
+            const uint32_t* soon_ids = reinterpret_cast<const uint32_t*>(soon + 1);
+            const uint4 soon_head = soon[0];
+            const uint32_t rounds = soon_head.y & 0xffffu, entry_words = rounds ? (rounds + 3) * kSlots : 0, words = (soon_head.z & 0xffffu) * kWords;
+            const uint64_t entry0 = (uint64_t)(soon_head.y >> 16) << 32 | soon_head.x;
+            uint32_t read = 0;
+            for (uint32_t i = threadIdx.x - 64; i < stride; i += kSgdBlock - 64) read ^= soon[i].x;
+            for (uint32_t i = threadIdx.x - 64; i < entry_words; i += kSgdBlock - 64) read ^= A.entries[entry0 + i].x;
+            for (uint32_t i = threadIdx.x - 64; i < words; i += kSgdBlock - 64) {
+                const uint32_t id = soon_ids[i / kWords];
+                if (!(id & kItemRow)) read ^= __float_as_uint(A.P[(size_t)id * F + (i % kWords) * 4]);
+            }
+            asm volatile("" :: "v"(read));                              // (the values are of no use, but the loads are to be made)
         }
         __syncthreads();
         for (uint32_t i0 = threadIdx.x; i0 < n_words; i0 += kDepth * kSgdBlock) {
@@ -785,7 +824,7 @@ int sgd_lay_out_rounds(SgdTask* p, fr_alloc* a, hipStream_t stream, const uint32
     (void)fr_alloc_free(a, before); (void)fr_alloc_free(a, size); (void)fr_alloc_free(a, place); (void)fr_alloc_free(a, more_dev);
     (void)fr_alloc_free(a, heads);
     if (F == 64) SGD_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_sgd<64>), hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLds));
-    p->args.records = records; p->args.entries = entries; p->args.stride = stride;
+    p->args.records = records; p->args.entries = entries; p->args.layout = stride | p->B << 16;
     return FR_OK;
 }
 

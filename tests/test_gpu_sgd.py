@@ -407,3 +407,32 @@ def test_rounds_of_a_batch_match_the_oracle(shape, B, F):
     P, Q, _ = _run(r, P0, Q0, F, 0.02, 0.03, 3, B)
     P32, Q32 = osgd.sgd(r.row_ptr, r.item, r.rating, P0, Q0, 0.02, 0.03, 3, B, ordered_fp32=True)
     assert _same_bits(P, P32) and _same_bits(Q, Q32)
+
+
+# rounds one after the other in pieces without a branch (of twelve, six with 32 factors, and of three behind them): chains of as
+# many ratings as there are rounds, on both sides of the pieces' ends
+@pytest.mark.parametrize("F", [16, 32, 64])
+@pytest.mark.parametrize("n", [2, 3, 4, 5, 6, 7, 11, 12, 13, 14, 17, 18, 23, 24, 25, 26, 127])
+def test_chains_of_any_length_match_the_oracle(n, F):
+    r = _dense([(0, i) for i in range(n)], 1, n, seed=n)
+    P0, Q0 = wl.initial_factors(1, n, F, seed=F)
+    P, Q, _ = _run(r, P0, Q0, F, 0.02, 0.03, 3, 1)
+    P32, Q32 = osgd.sgd(r.row_ptr, r.item, r.rating, P0, Q0, 0.02, 0.03, 3, 1, ordered_fp32=True)
+    assert _same_bits(P, P32) and _same_bits(Q, Q32)
+
+
+# from 128 blocks on the next stratum's programs are read ahead: the last stratum reads those of the first, cells without ratings
+# and of several batches among them; also on the other side of the line, and cell by cell
+@pytest.mark.parametrize("B,F,cells", [(127, 16, 0), (128, 16, 0), (128, 64, 50), (130, 32, 0)])
+def test_programs_read_ahead_leave_the_factors_alone(B, F, cells):
+    rng = np.random.default_rng(B)
+    n = 4000
+    pairs = set(zip(rng.integers(0, n, 150_000).tolist(), rng.integers(0, n, 150_000).tolist()))
+    pairs |= {(u, i) for u in range(30) for i in range(300)}                     # (cells of more than 128 ratings)
+    r = _dense(sorted(pairs), n, n, seed=B)
+    P0, Q0 = wl.initial_factors(n, n, F, seed=F)
+    print("case", B, F, cells, r.n_ratings, flush=True)
+    P, Q, info = _run(r, P0, Q0, F, 0.02, 0.03, 2, B, cells)
+    assert info.blocks == B
+    P32, Q32 = osgd.sgd(r.row_ptr, r.item, r.rating, P0, Q0, 0.02, 0.03, 2, B, ordered_fp32=True)
+    assert _same_bits(P, P32) and _same_bits(Q, Q32)
