@@ -974,7 +974,7 @@ int fr_destroy(fr_ctx* c)
     if (c->side) { (void)hipStreamSynchronize(c->side); (void)hipStreamDestroy(c->side); }
     if (c->tail_event) (void)hipEventDestroy(c->tail_event);
     if (c->gate) (void)hipFree(c->gate);
-    if (!c->host_only) g_pool.trim(true);                // (last: it waits for the device, and the worker is gone by now)
+    if (!c->host_only) trim_pools(true);                 // (last: it waits for the device, and the worker is gone by now)
     delete c;
     return FR_OK;
 }

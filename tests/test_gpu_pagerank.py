@@ -514,3 +514,17 @@ def test_a_limit_holds_for_kept_set_up_memory_too():
         t.fr_pagerank_destroy()
         held.append(fr.fr_scratch_release())
     assert held[1] >= held[0] + 8 * small.n_edges // 2, held
+
+
+def test_a_context_gives_back_what_a_series_left_when_it_is_destroyed():
+    # made before the series, so that only its end can have given back set-up scratch and what the tasks held
+    g = graphs.rmat_csr(16, 900_000, seed=47)
+    fr.fr_scratch_release()
+    ctx = fr.Context(device_id=0)
+    for _ in range(3):
+        _run(g, iterations=2)
+    ctx.fr_destroy()
+    assert fr.fr_scratch_release() == 0
+    for _ in range(3):
+        _run(g, iterations=2)
+    assert fr.fr_scratch_release() > 0                   # (a series does leave something)
