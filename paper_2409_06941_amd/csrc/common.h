@@ -25,7 +25,7 @@ struct fr_alloc {
 
 void fr_alloc_reset(fr_alloc* a, uint64_t limit, bool host_only, int device);
 void fr_alloc_release(fr_alloc* a);   // frees every block handed out
-void fr_alloc_hand_back(fr_alloc* a); // the same at the end of a task whose work is done: blocks of the layouts' pool go back to it
+void fr_alloc_hand_back(fr_alloc* a); // the same at the end of a task: waits for its device, and blocks of the layouts' pool go back to it
 // Memory a task holds until it ends (else as fr_alloc_scratch).
 void* fr_alloc_kept(fr_alloc* a, size_t bytes);
 bool fr_alloc_pools(const fr_alloc* a);      // does it get blocks of the pools?  (known once it has been asked for memory)

@@ -1295,10 +1295,7 @@ int fr_pagerank_destroy(void* user)
     PrTask* p = static_cast<PrTask*>(user);
     if (!p) return FR_ERR_ARG;
     if (p->registered) return FR_ERR_STATE;
-    if (p->inited) {
-        if (hipDeviceSynchronize() == hipSuccess) fr_alloc_hand_back(&p->own);
-        else fr_alloc_release(&p->own);
-    }
+    if (p->inited) fr_alloc_hand_back(&p->own);
     delete p;
     return FR_OK;
 }

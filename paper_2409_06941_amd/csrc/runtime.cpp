@@ -728,6 +728,15 @@ struct DeviceMemory {
     static void free(void* p) { (void)hipFree(p); }
     static uint64_t now_ns() { return ::now_ns(); }
     static uint64_t keep_at_most(int device) { return total_memory(device) / 64; }
+    static bool wait(int device)
+    {
+        int current = -1;
+        if (hipGetDevice(&current) != hipSuccess) return false;
+        if (current != device && hipSetDevice(device) != hipSuccess) return false;
+        const bool done = hipDeviceSynchronize() == hipSuccess;
+        if (current != device) (void)hipSetDevice(current);
+        return done;
+    }
 };
 ScratchPool<DeviceMemory> g_pool;
 // What a task of such a series held until it was destroyed, for the next one: 2^22 vertices / 2^26 edges, 350 MB in five blocks, to
@@ -760,7 +769,7 @@ void fr_alloc_release(fr_alloc* a)
 {
     for (const fr_alloc::Block& b : a->blocks) {
         if (a->host_only) std::free(b.ptr);
-        else (void)hipFree(b.ptr);           // (of the pool or not: the set-up that took it failed)
+        else (void)hipFree(b.ptr);           // (of a pool or not: what a pool is to keep has been handed to it before)
     }
     if (a->pooled) trim_pools(false);        // (a task of a context has no part in the pool, and is stopped under the context's lock)
     a->blocks.clear();
@@ -769,11 +778,7 @@ void fr_alloc_release(fr_alloc* a)
 
 void fr_alloc_hand_back(fr_alloc* a)
 {
-    for (fr_alloc::Block& b : a->blocks) {
-        if (!b.kept || !b.room || a->host_only) continue;
-        g_layouts.give(a->device, b.ptr, b.room);
-        b.ptr = nullptr;
-    }
+    if (!a->host_only) g_layouts.take_back(a->device, a->blocks);
     fr_alloc_release(a);                     // (freeing no block is nothing)
 }
 

@@ -1,5 +1,6 @@
 // Blocks of device memory kept between set-ups (see runtime.cpp for what they are kept for).  `Mem` is where they come from:
-//   free(p), now_ns(), and keep_at_most(device): bytes that may be kept on a device.
+//   free(p), now_ns(), keep_at_most(device): bytes that may be kept on a device, and, for take_back, wait(device): is that device
+//   done with all it was given?
 #ifndef FR_SCRATCH_POOL_H
 #define FR_SCRATCH_POOL_H
 
@@ -60,6 +61,19 @@ public:
             freed.add(remove(oldest < n_ ? oldest : 0));
         }
         kept_[n_++] = {device, ptr, room, Mem::now_ns()};
+    }
+
+    // A task has ended: its blocks marked `kept` go to the pool (and their ptr to NULL), once their device is done with them -
+    // theirs, which need not be the calling thread's current one.  Nothing is taken where that cannot be said.
+    template <class Blocks>
+    void take_back(int device, Blocks& blocks)
+    {
+        if (!Mem::wait(device)) return;
+        for (auto& b : blocks) {
+            if (!b.kept || !b.room) continue;
+            give(device, b.ptr, b.room);
+            b.ptr = nullptr;
+        }
     }
 
     // Gives back what has been kept for longer than kKeepNs, or all of it; bytes given back.

@@ -18,9 +18,32 @@ struct Mem {
     static void free(void* p) { g_freed.push_back((uint64_t)(uintptr_t)p); }
     static uint64_t now_ns() { return g_now; }
     static uint64_t keep_at_most(int) { return g_most; }
+    static bool wait(int device);
 };
+static std::vector<int> g_waited;              // devices that were waited for, and what was free to be taken on them then
+static bool g_wait_fails = false;
 static ScratchPool<Mem>* pool = new ScratchPool<Mem>();
+bool Mem::wait(int device)
+{
+    uint64_t room = 0;
+    if (void* p = pool->take(device, 1, ~0ull, &room)) { pool->give(device, p, room); g_waited.push_back(-1); }
+    g_waited.push_back(device);
+    return !g_wait_fails;
+}
+struct Block { void* ptr; uint64_t room; bool kept; };
 extern "C" {
+// a task that held block 1 (kept), 2 (scratch) and 3 (no block of the pool) ends; how many blocks are still its own
+int end_of_task(int device, int fails)
+{
+    std::vector<Block> blocks = {{(void*)1, 100, true}, {(void*)2, 100, false}, {(void*)3, 0, true}};
+    g_waited.clear();
+    g_wait_fails = fails != 0;
+    pool->take_back(device, blocks);
+    int own = 0;
+    for (const Block& b : blocks) own += b.ptr != nullptr;
+    return own;
+}
+int waited(uint64_t k) { return k < g_waited.size() ? g_waited[k] : -2; }
 void reset(uint64_t most) { delete pool; pool = new ScratchPool<Mem>(); g_now = 0; g_most = most; g_freed.clear(); }
 void set_now(uint64_t s) { g_now = s * 1000000000ull; }
 uint64_t take(int device, uint64_t bytes, uint64_t most) { uint64_t room = 0; return pool->take(device, bytes, most, &room) ? room : 0; }
@@ -105,6 +128,16 @@ def test_only_a_set_up_that_follows_another_takes_part(lib):
     assert not lib.begins(0) and not lib.begins(-1) and not lib.begins(64)
     lib.give(0, 1, 300); lib.give(1, 2, 400)
     assert lib.trim(0) == 0 and lib.trim(1) == 700 and lib.trim(1) == 0
+
+
+def test_what_a_task_held_is_kept_only_when_its_own_device_is_done_with_it(lib):
+    lib.reset(1000)
+    lib.waited.argtypes, lib.end_of_task.argtypes = [ctypes.c_uint64], [ctypes.c_int, ctypes.c_int]
+    assert lib.end_of_task(3, 0) == 2                             # (whichever device is current: only device 3 is asked about)
+    assert [lib.waited(k) for k in range(2)] == [3, -2]           # once, with nothing of the task's to be had before
+    assert lib.take(0, 1, 1000) == 0 and lib.take(3, 1, 1000) == 100 and lib.take(3, 1, 1000) == 0
+    assert lib.end_of_task(3, 1) == 3                             # a device in error: all blocks stay the task's, which frees them
+    assert lib.trim(1) == 0
 
 
 def test_memory_is_freed_outside_the_pools_lock(tmp_path_factory):
