@@ -356,9 +356,11 @@ typedef struct fr_pagerank_info_t {
     uint32_t sources_per_partition; /* most source vertices of a scatter tile                               */
     uint32_t partial_rows;        /* gather pieces of merged ranges (rows of fp32 partial sums)             */
     uint64_t bytes_resident;      /* booked against the limit after init (caller buffers included)          */
-    uint64_t bytes_peak;          /* highest amount booked during init (set-up scratch included): what a limit has to hold;
-                                     a standalone run without a limit below the device's memory may hold scratch blocks
-                                     up to a quarter larger than what is booked for them                    */
+    uint64_t bytes_peak;          /* highest amount booked during init (set-up scratch included): what a limit has to hold.
+                                     Both are what the task asked for.  A standalone run without a limit below the
+                                     device's memory that follows another one (see fr_scratch_release) may hold blocks
+                                     up to a quarter larger than that, scratch during its set-up and its arrays until
+                                     it is destroyed; one with a limit holds what is booked                  */
     uint32_t scatter_slots;       /* workgroups of a scatter launch / of a gather launch that run side by side on  */
     uint32_t gather_slots;        /* the stream's compute units: a step of more tiles runs in rounds, and plan_step
                                      cuts a step that does not reach its segment's end to whole rounds             */
@@ -390,9 +392,10 @@ int fr_pagerank_run_standalone(void* user, int32_t device_id, void* stream, uint
 /*
  * A program that sets up standalone PageRank tasks one after the other (less than five seconds from one set-up to the
  * next) leaves set-up scratch with the library for the next one, at most 1/64 of the device's memory, and what a
- * task of such a series held, at most 1/256, also when every task is destroyed.  It is given back when a context is made or destroyed, when an allocation of the library fails, after
- * five seconds without use at the next set-up, and by this call, which a program makes when it is done setting up
- * graphs and another allocator is to have the memory.  *bytes_out (may be NULL) receives the bytes given back.
+ * task of such a series held, at most 1/256, also when every task is destroyed.  Both are given back when a context is
+ * made or destroyed, when an allocation of the library fails, after five seconds without use at the next set-up, and by
+ * this call, which a program makes when it is done setting up graphs and another allocator is to have the memory.
+ * *bytes_out (may be NULL) receives the bytes given back.
  */
 int fr_scratch_release(uint64_t* bytes_out);
 /*

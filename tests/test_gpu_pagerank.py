@@ -528,3 +528,47 @@ def test_a_context_gives_back_what_a_series_left_when_it_is_destroyed():
     for _ in range(3):
         _run(g, iterations=2)
     assert fr.fr_scratch_release() > 0                   # (a series does leave something)
+
+
+def _set_up_and_destroy(csr, mem_limit=1 << 40, leaving=False):
+    """One task in a series: (bytes booked for its arrays, booked at most, the bytes of the blocks they lay in).  leaving: the
+    blocks, and set-up scratch, stay for the next task, else all that lies idle goes back."""
+    rp, col, od = csr
+    V, E = len(od), len(col)
+    ranks = torch.zeros(V, dtype=torch.float32, device="cuda")
+    torch.cuda.synchronize()
+    t = fr.PageRankTask(V, E, rp, col, od, ranks, iterations=2, mem_limit_bytes=mem_limit)
+    t.fr_pagerank_run_standalone(0, torch.cuda.current_stream())
+    info = t.fr_pagerank_info()
+    if not leaving:
+        fr.fr_scratch_release()                          # (what is released below is the arrays' alone)
+    t.fr_pagerank_destroy()
+    return info.bytes_resident - (4 * (V + 1) + 4 * E + 8 * V), info.bytes_peak, 0 if leaving else fr.fr_scratch_release()
+
+
+def _csr_on_gpu(V, degree, seed):
+    col = torch.randint(0, V, (V * degree,), dtype=torch.int32, device="cuda", generator=torch.Generator("cuda").manual_seed(seed))
+    return (torch.arange(V + 1, device="cuda") * degree).to(torch.int32), col, torch.bincount(col, minlength=V).to(torch.int32)
+
+
+def test_blocks_a_task_held_are_what_is_booked_and_without_a_limit_up_to_a_quarter_more():
+    big, small = _csr_on_gpu(1 << 16, 16, 1), _csr_on_gpu(1 << 16, 14, 2)
+    fr.fr_scratch_release()
+    _set_up_and_destroy(big)                             # (the next one is of a series, whatever ran before)
+    most, _, held = _set_up_and_destroy(big)
+    assert held == most                                  # nothing kept to be had: blocks of its own
+    _set_up_and_destroy(big, leaving=True)
+    booked, peak, held = _set_up_and_destroy(small)
+    assert booked < held <= min(most, booked + booked // 4)
+    _set_up_and_destroy(big, leaving=True)
+    assert _set_up_and_destroy(small, mem_limit=peak) == (booked, peak, booked)
+
+
+def test_what_tasks_held_is_kept_up_to_a_256th_of_the_device():
+    csr = _csr_on_gpu(1 << 22, 48, 3)                    # arrays of about 1.6 GB, in blocks of which each may be kept
+    most = torch.cuda.mem_get_info()[1] // 256
+    fr.fr_scratch_release()
+    for _ in range(2):
+        booked, _, held = _set_up_and_destroy(csr)
+    print("booked", booked, "held", held, "at most", most, flush=True)
+    assert 0 < held <= most < booked
