@@ -41,7 +41,6 @@ constexpr uint64_t kMostBytes = 128;              // per rating that the rounds'
 constexpr uint32_t kMaxBlocks = 1024;
 constexpr int64_t kMaxIds = (1ll << 27) - 1024;
 constexpr uint32_t kNoBatch = 0xffffffffu;
-constexpr uint32_t kFetchAheadBlocks = 128;       // from which on the next stratum's programs are read ahead (see k_sgd)
 constexpr int kMaxLds = (kMaxRounds + 3) * 2 * 16 + (2 * kBatch + 1) * 256;      // of a batch of 64 factors: 74 KB
 
 // A batch: a record of `stride` 16-byte words, the head and then the ids of its rows (users, then items with kItemRow set,
@@ -231,7 +230,9 @@ __device__ __forceinline__ void run_rounds(LdsBytes entries, uint32_t rounds, fl
     }
 }
 
-template <int F>
+// kAhead: the next stratum's programs are read ahead (a kernel of its own: the code for it is 1 to 2 % of a launch that has no use
+// for it, and its registers, 64 -> 72 with 16 factors, 10 to 19 % where eight small cells share a unit)
+template <int F, bool kAhead>
 __global__ __launch_bounds__(kSgdBlock) void k_sgd(SgdArgs A, GateArg G, uint32_t cell0)
 {
     // the rows begin at LDS address 0 (the kernel has no other LDS): an entry's offset is an address
@@ -282,12 +283,11 @@ __global__ __launch_bounds__(kSgdBlock) void k_sgd(SgdArgs A, GateArg G, uint32_
                 const LdsBytes at = reinterpret_cast<LdsBytes>((uint32_t)((n_rows + 1) * (F * 4)));
                 run_rounds<F, lanes_for(F)>(at, H.rounds, A.gamma, A.gl);
             }
-        } else if (blocks >= kFetchAheadBlocks && b < blocks * blocks) {
+        } else if (kAhead && b < blocks * blocks) {                     // (not for a cell's further batches)
             // meanwhile the other wavefronts read what the next stratum's cell of this user block begins with - its record, its
-            // entries and its rows of P, which no other workgroup writes - so that the launch of that stratum, whose workgroup
-            // of this number runs on the same compute die, finds them in its L2.  From 128 blocks on, where a stratum's
-            // programs come from memory: ms an iteration, without -> with, 512 blocks 7.61 -> 7.32, 256 3.91 -> 3.77 (32 factors, two
-            // iterations) and 7.19 -> 6.84 (16, two), 128 2.20 -> 2.17 and 1.82 -> 1.69; 32 0.79 -> 0.82 (64, three)
+            // entries and its rows of P, which no other workgroup writes - so that the launch of that stratum finds them in the
+            // L2 (whole strata: the workgroup of this number runs on the same compute die again) or in the cache behind it.
+            // Where it pays: sgd_reads_ahead.
             const uint32_t after = b + blocks < blocks * blocks ? b + blocks : b + blocks - blocks * blocks;
             const uint4* soon = A.records + (uint64_t)after * stride;
             const uint32_t* soon_ids = reinterpret_cast<const uint32_t*>(soon + 1);
@@ -730,6 +730,7 @@ struct SgdTask {
     uint64_t footprint_after = 0, footprint_peak = 0;
     SgdArgs args{};
     ChainArgs chain{};                    // keys: NULL if the ratings are worked on in rounds
+    uint32_t cus = 1;                     // compute units of the stream the task was set up on
     bool inited = false, registered = false;
     fr_alloc own;                         // used by the standalone run only
     int hip_error = 0;
@@ -743,7 +744,9 @@ int sgd_launch(SgdTask* p, uint32_t seg, uint32_t tile0, uint32_t tile1, hipStre
     if (tile1 <= tile0 || tile1 > p->B || seg >= p->n_segments()) return FR_ERR_ARG;
     const uint32_t s = seg % p->B, n = tile1 - tile0, cell0 = s * p->B + tile0;
     const int F = p->d.factors;
-    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(n), dim3(kSgdBlock), p->lds_bytes, stream, p->args, G, cell0); };
+    auto go = [&](auto kernel, auto ahead) {
+        hipLaunchKernelGGL(sgd_reads_ahead((uint64_t)p->d.n_ratings, p->B, n, p->cus) ? ahead : kernel, dim3(n), dim3(kSgdBlock), p->lds_bytes, stream, p->args, G, cell0);
+    };
     auto go_chain = [&](auto kernel) {
         const unsigned grid = (unsigned)(((uint64_t)n * F + kSgdBlock - 1) / kSgdBlock);
         hipLaunchKernelGGL(kernel, dim3(grid), dim3(kSgdBlock), 0, stream, p->chain, G, cell0, n);
@@ -752,9 +755,9 @@ int sgd_launch(SgdTask* p, uint32_t seg, uint32_t tile0, uint32_t tile1, hipStre
         if (F == 64) go_chain(k_sgd_chain<64>);
         else if (F == 32) go_chain(k_sgd_chain<32>);
         else go_chain(k_sgd_chain<16>);
-    } else if (F == 64) go(k_sgd<64>);
-    else if (F == 32) go(k_sgd<32>);
-    else go(k_sgd<16>);
+    } else if (F == 64) go(k_sgd<64, false>, k_sgd<64, true>);
+    else if (F == 32) go(k_sgd<32, false>, k_sgd<32, true>);
+    else go(k_sgd<16, false>, k_sgd<16, true>);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) { p->hip_error = (int)e; return FR_ERR_HIP; }
     return FR_OK;
@@ -823,7 +826,9 @@ int sgd_lay_out_rounds(SgdTask* p, fr_alloc* a, hipStream_t stream, const uint32
     SGD_HIP(hipStreamSynchronize(stream));
     (void)fr_alloc_free(a, before); (void)fr_alloc_free(a, size); (void)fr_alloc_free(a, place); (void)fr_alloc_free(a, more_dev);
     (void)fr_alloc_free(a, heads);
-    if (F == 64) SGD_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_sgd<64>), hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLds));
+    if (F == 64)
+        for (auto kernel : {k_sgd<64, false>, k_sgd<64, true>})
+            SGD_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLds));
     p->args.records = records; p->args.entries = entries; p->args.layout = stride | p->B << 16;
     return FR_OK;
 }
@@ -944,7 +949,8 @@ int sgd_init(void* user, fr_alloc* a, void* stream_v)
     p->chain = ChainArgs{};
     // Rounds, or where they do not pay, or the rounds' layout is out of proportion to the ratings or has no room in the task's
     // limit (or on the device), one rating after the other: that needs no more memory than the sort before it did.
-    bool rounds = sgd_rounds_pay((uint64_t)E, B, p->chain_ratings, F, fr_stream_cus(stream));
+    p->cus = fr_stream_cus(stream);
+    bool rounds = sgd_rounds_pay((uint64_t)E, B, p->chain_ratings, F, p->cus);
     if (rounds) {
         const size_t mark = fr_alloc_mark(a);
         int rc = sgd_lay_out_rounds(p, a, stream, cell_ptr, index, user_of);

@@ -421,18 +421,18 @@ def test_chains_of_any_length_match_the_oracle(n, F):
     assert _same_bits(P, P32) and _same_bits(Q, Q32)
 
 
-# from 128 blocks on the next stratum's programs are read ahead: the last stratum reads those of the first, cells without ratings
-# and of several batches among them; also on the other side of the line, and cell by cell
-@pytest.mark.parametrize("B,F,cells", [(127, 16, 0), (128, 16, 0), (128, 64, 50), (130, 32, 0)])
+# from 128 blocks and 16 ratings a cell on the next stratum's programs are read ahead: the last stratum reads those of the first,
+# cells without ratings and of several batches among them; also on the other side of the lines (127 blocks, launches of 30 cells)
+@pytest.mark.parametrize("B,F,cells", [(127, 16, 0), (128, 16, 0), (128, 64, 50), (128, 64, 30), (130, 32, 0)])
 def test_programs_read_ahead_leave_the_factors_alone(B, F, cells):
     rng = np.random.default_rng(B)
     n = 4000
-    pairs = set(zip(rng.integers(0, n, 150_000).tolist(), rng.integers(0, n, 150_000).tolist()))
+    pairs = set(zip(rng.integers(0, n, 290_000).tolist(), rng.integers(0, n, 290_000).tolist()))
     pairs |= {(u, i) for u in range(30) for i in range(300)}                     # (cells of more than 128 ratings)
     r = _dense(sorted(pairs), n, n, seed=B)
     P0, Q0 = wl.initial_factors(n, n, F, seed=F)
     print("case", B, F, cells, r.n_ratings, flush=True)
     P, Q, info = _run(r, P0, Q0, F, 0.02, 0.03, 2, B, cells)
-    assert info.blocks == B
+    assert info.blocks == B and r.n_ratings >= 16 * B * B
     P32, Q32 = osgd.sgd(r.row_ptr, r.item, r.rating, P0, Q0, 0.02, 0.03, 2, B, ordered_fp32=True)
     assert _same_bits(P, P32) and _same_bits(Q, Q32)

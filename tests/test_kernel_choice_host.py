@@ -21,9 +21,13 @@ def _compile(tmp_path_factory, name, code):
 def sgd(tmp_path_factory):
     L = _compile(tmp_path_factory, "sgd_rule", '''#include "sgd_rule.h"
 extern "C" int pay(uint64_t ratings, uint32_t B, uint64_t chain, int F, uint32_t cus) { return sgd_rounds_pay(ratings, B, chain, F, cus); }
+extern "C" int ahead(uint64_t ratings, uint32_t B, uint32_t n, uint32_t cus) { return sgd_reads_ahead(ratings, B, n, cus); }
 ''')
+    L.ahead.argtypes = [ctypes.c_uint64, ctypes.c_uint32, ctypes.c_uint32, ctypes.c_uint32]
     L.pay.argtypes = [ctypes.c_uint64, ctypes.c_uint32, ctypes.c_uint64, ctypes.c_int, ctypes.c_uint32]
-    return lambda ratings, B, chain, F, cus: bool(L.pay(ratings, B, int(chain * B), F, cus))
+    pay = lambda ratings, B, chain, F, cus: bool(L.pay(ratings, B, int(chain * B), F, cus))
+    pay.ahead = lambda ratings, B, cus, n=0: bool(L.ahead(ratings, B, n or B, cus))
+    return pay
 
 
 # (ratings, blocks, mean over the strata of their largest cell, factors, compute units, ms one after the other, ms in rounds)
@@ -57,6 +61,27 @@ def test_sgd_blocks_the_library_makes_are_worked_on_in_rounds(sgd):
                     assert sgd(ratings, B, 1.2 * mean, F, cus), (ratings, F, cus)
     assert not sgd(257, 1, 257, 16, 256)                        # beyond 256 ratings a cell on average
     assert not sgd(0, 4, 0, 16, 256) and not sgd(0, 1, 0, 64, 256)
+
+
+# (blocks, ratings a cell, compute units, ms of an iteration with the next stratum's programs read ahead, without)
+AHEAD_MEASURED = [
+    (256, 31, 32, 1.953, 1.658), (512, 7.7, 64, 3.627, 2.438), (512, 7.7, 32, 5.233, 3.507), (512, 7.7, 128, 2.458, 2.310), (1024, 15.3, 128, 9.347, 7.031),
+    (1024, 1.9, 256, 5.839, 4.999), (256, 245, 32, 6.744, 5.834), (512, 61, 24, 27.99, 25.73), (512, 61, 32, 21.79, 20.52), (128, 31, 24, 0.965, 0.897),
+    (128, 8.4, 256, 0.495, 0.438), (128, 16.8, 128, 0.529, 0.502), (384, 12.6, 256, 1.738, 1.651), (256, 7.8, 256, 1.106, 1.087), (512, 16.7, 128, 3.924, 3.749),
+    (128, 33.5, 32, 0.741, 0.726), (384, 25.1, 96, 3.119, 3.048), (512, 33, 96, 5.085, 4.765),
+    (512, 61, 256, 4.659, 5.262), (512, 49, 192, 6.169, 6.450), (256, 245, 256, 4.614, 4.905), (1024, 33, 256, 8.437, 9.373), (1024, 49, 256, 11.30, 12.38),
+    (512, 25, 256, 2.927, 3.253), (512, 33, 128, 3.562, 3.774), (384, 25.1, 128, 2.052, 2.131), (128, 25.2, 256, 0.554, 0.563), (256, 16.6, 256, 1.125, 1.169),
+    (256, 33, 96, 1.467, 1.546), (128, 123, 64, 1.196, 1.250), (128, 66, 96, 0.759, 0.807),
+]
+
+
+def test_programs_are_read_ahead_where_that_was_measured_to_be_faster(sgd):
+    for B, mean, cus, ahead, without in AHEAD_MEASURED:
+        assert sgd.ahead(int(mean * B * B), B, cus) == (ahead < without), (B, mean, cus)
+    assert not sgd.ahead(60 * 127 * 127, 127, 256) and not sgd.ahead(0, 128, 256) and not sgd.ahead(1 << 30, 1024, 1)
+    # parts of strata: 512 blocks of 61 and 49, 256 of 31 and 8 ratings a cell
+    assert sgd.ahead(61 << 18, 512, 256, 52) and sgd.ahead(61 << 18, 512, 64, 100) and not sgd.ahead(61 << 18, 512, 64) and not sgd.ahead(49 << 18, 512, 256, 20)
+    assert sgd.ahead(31 << 16, 256, 64, 52) and not sgd.ahead(31 << 16, 256, 256, 3) and not sgd.ahead(8 << 16, 256, 256, 52)
 
 
 @pytest.fixture(scope="module")
