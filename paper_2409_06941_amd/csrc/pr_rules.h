@@ -88,13 +88,4 @@ inline uint64_t least_scatter_weight(uint64_t all)
     return balance > kMinTileMessages ? balance : kMinTileMessages;
 }
 
-// Rows of a tile of the pass after the last iteration: 2048 while that makes at most 512 tiles, else 4096.  A workgroup has 2048
-// either way; the tile is what a plan charges, and the more of them run side by side the further their summed costs lie above
-// what the pass takes (2^21 vertices: 613 tiles of 2048 rows run in 26 us).
-constexpr uint32_t kFinishRows = 2048, kFinishRowsOfMany = 4096, kFinishTilesFew = 512;
-inline uint32_t finish_tile_rows(uint32_t n_finish, uint32_t rows_per_part)
-{
-    return (uint64_t)n_finish * (rows_per_part / kFinishRows) <= kFinishTilesFew ? kFinishRows : kFinishRowsOfMany;
-}
-
 #endif
