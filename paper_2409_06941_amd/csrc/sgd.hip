@@ -230,10 +230,12 @@ __device__ __forceinline__ void run_rounds(LdsBytes entries, uint32_t rounds, fl
     }
 }
 
-// kAhead: the next stratum's programs are read ahead (a kernel of its own: the code for it is 1 to 2 % of a launch that has no use
-// for it, and its registers, 64 -> 72 with 16 factors, 10 to 19 % where eight small cells share a unit)
-template <int F, bool kAhead>
-__global__ __launch_bounds__(kSgdBlock) void k_sgd(SgdArgs A, GateArg G, uint32_t cell0)
+// kAhead: the next stratum's programs are read ahead (a kernel of its own: its registers, 64 -> 72 with 16 factors, cost 10 to 19 %
+// where eight small cells share a unit).  kCells: workgroups that are to fit on a unit.  With 16 factors eight have 64 registers
+// a lane, two fewer than the rounds take without waits between their dependent moves (a wait a round, 1.8 % of an iteration of 20 011 x
+// 5003 ids and 300 000 ratings), seven have 72; with 32 and 64 factors the rounds take more than either.
+template <int F, bool kAhead, int kCells>
+__global__ __launch_bounds__(kSgdBlock) __attribute__((amdgpu_waves_per_eu(1, kCells))) void k_sgd(SgdArgs A, GateArg G, uint32_t cell0)
 {
     // the rows begin at LDS address 0 (the kernel has no other LDS): an entry's offset is an address
     extern __shared__ __align__(16) char lds[];
@@ -744,9 +746,8 @@ int sgd_launch(SgdTask* p, uint32_t seg, uint32_t tile0, uint32_t tile1, hipStre
     if (tile1 <= tile0 || tile1 > p->B || seg >= p->n_segments()) return FR_ERR_ARG;
     const uint32_t s = seg % p->B, n = tile1 - tile0, cell0 = s * p->B + tile0;
     const int F = p->d.factors;
-    auto go = [&](auto kernel, auto ahead) {
-        hipLaunchKernelGGL(sgd_reads_ahead((uint64_t)p->d.n_ratings, p->B, n, p->cus) ? ahead : kernel, dim3(n), dim3(kSgdBlock), p->lds_bytes, stream, p->args, G, cell0);
-    };
+    const bool reads_ahead = sgd_reads_ahead((uint64_t)p->d.n_ratings, p->B, n, p->cus);
+    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(n), dim3(kSgdBlock), p->lds_bytes, stream, p->args, G, cell0); };
     auto go_chain = [&](auto kernel) {
         const unsigned grid = (unsigned)(((uint64_t)n * F + kSgdBlock - 1) / kSgdBlock);
         hipLaunchKernelGGL(kernel, dim3(grid), dim3(kSgdBlock), 0, stream, p->chain, G, cell0, n);
@@ -755,9 +756,10 @@ int sgd_launch(SgdTask* p, uint32_t seg, uint32_t tile0, uint32_t tile1, hipStre
         if (F == 64) go_chain(k_sgd_chain<64>);
         else if (F == 32) go_chain(k_sgd_chain<32>);
         else go_chain(k_sgd_chain<16>);
-    } else if (F == 64) go(k_sgd<64, false>, k_sgd<64, true>);
-    else if (F == 32) go(k_sgd<32, false>, k_sgd<32, true>);
-    else go(k_sgd<16, false>, k_sgd<16, true>);
+    } else if (F == 64) go(reads_ahead ? k_sgd<64, true, 8> : k_sgd<64, false, 8>);
+    else if (F == 32) go(reads_ahead ? k_sgd<32, true, 8> : k_sgd<32, false, 8>);
+    else if (sgd_eight_cells_a_unit(n, p->cus)) go(k_sgd<16, false, 8>);           // (too many to read ahead)
+    else go(reads_ahead ? k_sgd<16, true, 7> : k_sgd<16, false, 7>);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) { p->hip_error = (int)e; return FR_ERR_HIP; }
     return FR_OK;
@@ -827,7 +829,7 @@ int sgd_lay_out_rounds(SgdTask* p, fr_alloc* a, hipStream_t stream, const uint32
     (void)fr_alloc_free(a, before); (void)fr_alloc_free(a, size); (void)fr_alloc_free(a, place); (void)fr_alloc_free(a, more_dev);
     (void)fr_alloc_free(a, heads);
     if (F == 64)
-        for (auto kernel : {k_sgd<64, false>, k_sgd<64, true>})
+        for (auto kernel : {k_sgd<64, false, 8>, k_sgd<64, true, 8>})
             SGD_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLds));
     p->args.records = records; p->args.entries = entries; p->args.layout = stride | p->B << 16;
     return FR_OK;

@@ -52,4 +52,8 @@ inline bool sgd_reads_ahead(uint64_t ratings, uint32_t B, uint32_t n, uint32_t c
     return mean >= 24 && stratum >= (n <= 3 * cus ? 6144 : 12288);
 }
 
+// Whether eight workgroups of a launch of `n` cells are to share a unit (64 registers a lane) rather than seven (72), with 16
+// factors: the eighth has work from eight cells a unit on.
+inline bool sgd_eight_cells_a_unit(uint32_t n, uint32_t cus) { return (uint64_t)n > 7ull * cus; }
+
 #endif

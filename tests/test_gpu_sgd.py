@@ -436,3 +436,26 @@ def test_programs_read_ahead_leave_the_factors_alone(B, F, cells):
     assert info.blocks == B and r.n_ratings >= 16 * B * B
     P32, Q32 = osgd.sgd(r.row_ptr, r.item, r.rating, P0, Q0, 0.02, 0.03, 2, B, ordered_fp32=True)
     assert _same_bits(P, P32) and _same_bits(Q, Q32)
+
+
+# 16 factors: up to seven cells a unit in a launch take one kernel, eight another
+@pytest.mark.parametrize("B,cells", [(56, 0), (57, 0), (64, 0), (64, 57), (64, 56)])
+def test_many_cells_on_few_units_match_the_oracle(B, cells):
+    rng = np.random.default_rng(B)
+    n = 900
+    pairs = set(zip(rng.integers(0, n, 90_000).tolist(), rng.integers(0, n, 90_000).tolist()))
+    pairs |= {(u, i) for u in range(20) for i in range(200)}                     # (cells of more than 128 ratings)
+    r = _dense(sorted(pairs), n, n, seed=B)
+    P0, Q0 = wl.initial_factors(n, n, 16, seed=3)
+    P, Q = _dev(P0), _dev(Q0)
+    print("case", B, cells, r.n_ratings, flush=True)
+    ctx = fr.Context(device_id=0, cu_count=8)
+    t = _task(r, P, Q, 16, 0.02, 0.03, 3, B)
+    try:
+        t.fr_sgd_run_standalone(0, ctx.fr_side_stream(), cells)
+        assert t.fr_sgd_info().blocks == B
+    finally:
+        t.fr_sgd_destroy()
+        ctx.fr_destroy()
+    P32, Q32 = osgd.sgd(r.row_ptr, r.item, r.rating, P0, Q0, 0.02, 0.03, 3, B, ordered_fp32=True)
+    assert _same_bits(P.cpu().numpy(), P32) and _same_bits(Q.cpu().numpy(), Q32)

@@ -21,11 +21,13 @@ def _compile(tmp_path_factory, name, code):
 def sgd(tmp_path_factory):
     L = _compile(tmp_path_factory, "sgd_rule", '''#include "sgd_rule.h"
 extern "C" int pay(uint64_t ratings, uint32_t B, uint64_t chain, int F, uint32_t cus) { return sgd_rounds_pay(ratings, B, chain, F, cus); }
+extern "C" int eight(uint32_t n, uint32_t cus) { return sgd_eight_cells_a_unit(n, cus); }
 extern "C" int ahead(uint64_t ratings, uint32_t B, uint32_t n, uint32_t cus) { return sgd_reads_ahead(ratings, B, n, cus); }
 ''')
     L.ahead.argtypes = [ctypes.c_uint64, ctypes.c_uint32, ctypes.c_uint32, ctypes.c_uint32]
     L.pay.argtypes = [ctypes.c_uint64, ctypes.c_uint32, ctypes.c_uint64, ctypes.c_int, ctypes.c_uint32]
     pay = lambda ratings, B, chain, F, cus: bool(L.pay(ratings, B, int(chain * B), F, cus))
+    pay.eight = lambda n, cus: bool(L.eight(n, cus))
     pay.ahead = lambda ratings, B, cus, n=0: bool(L.ahead(ratings, B, n or B, cus))
     return pay
 
@@ -82,6 +84,13 @@ def test_programs_are_read_ahead_where_that_was_measured_to_be_faster(sgd):
     # parts of strata: 512 blocks of 61 and 49, 256 of 31 and 8 ratings a cell
     assert sgd.ahead(61 << 18, 512, 256, 52) and sgd.ahead(61 << 18, 512, 64, 100) and not sgd.ahead(61 << 18, 512, 64) and not sgd.ahead(49 << 18, 512, 256, 20)
     assert sgd.ahead(31 << 16, 256, 64, 52) and not sgd.ahead(31 << 16, 256, 256, 3) and not sgd.ahead(8 << 16, 256, 256, 52)
+
+
+# (cells of a launch, compute units): eight workgroups a unit where the launch has that many, and never together with reading ahead
+@pytest.mark.parametrize("n,cus,want", [(1, 1, False), (7, 1, False), (8, 1, True), (56, 8, False), (57, 8, True), (64, 256, False), (512, 64, True), (512, 74, False), (1024, 146, True), (1024, 256, False)])
+def test_sgd_cells_that_share_a_unit(sgd, n, cus, want):
+    assert sgd.eight(n, cus) == want
+    assert not (want and any(sgd.ahead(mean << 20, 1024, cus, n) for mean in (2, 60, 1000)))
 
 
 @pytest.fixture(scope="module")
