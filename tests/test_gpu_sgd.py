@@ -232,6 +232,9 @@ def test_pagerank_and_sgd_queued_on_one_worker_run_one_after_the_other():
     Pr, Qr, _ = _run(r, P0, Q0, F, gamma, lam, K_sgd, B)                        # SGD reference bits
     rp, col, od = _dev(g.row_ptr, torch.int32), _dev(g.col, torch.int32), _dev(g.out_degree, torch.int32)
     ranks = torch.zeros(g.n_vertices, dtype=torch.float32, device="cuda")
+    once = fr.PageRankTask(g.n_vertices, g.n_edges, rp, col, od, ranks, iterations=2)    # a kernel's first launch in a process loads its code
+    once.fr_pagerank_run_standalone(0, torch.cuda.current_stream(), 1)
+    once.fr_pagerank_destroy()
     P, Q = _dev(P0), _dev(Q0)
     ctx = fr.Context(device_id=0, guard_ns=200_000, launch_cost_ns=20_000, max_chunk_ns=0, time_steps=1, mem_available_bytes=1 << 40)
     pr_task = fr.PageRankTask(g.n_vertices, g.n_edges, rp, col, od, ranks, iterations=K_pr, max_runs=1, mem_limit_bytes=1 << 30,
