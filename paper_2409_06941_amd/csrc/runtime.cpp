@@ -706,7 +706,7 @@ namespace {
 // memory that was free at first has been used: 2^22 vertices / 2^26 edges, made, run and destroyed over and over, take 8.4 ms
 // a graph with kept scratch and without it 10.0 for the first 120 and 40 from then on, with single ones of 0.1 to 2.6 s.
 // Only a program that sets up graph after graph gains by it, so only a set-up that begins within kKeepNs of the one before
-// takes part; then at most 1/64 of the device's memory and kBlocks blocks are kept.  There is no thread that watches their
+// takes part; then at most 1/64 of the device's memory and kKeptBlocks blocks are kept.  There is no thread that watches their
 // age: a block unused for kKeepNs is given back by the next set-up, or the next task with kept scratch that is destroyed; all are when a context
 // is made or destroyed, when an allocation of the library fails, and by fr_scratch_release.
 // (it never changes: asked for once a device)

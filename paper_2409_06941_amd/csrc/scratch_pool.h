@@ -13,10 +13,18 @@
 // holds for what is in use as well.
 inline uint64_t most_room(uint64_t limit, uint64_t total, uint64_t bytes) { return total && limit >= total ? bytes + bytes / 4 : bytes; }
 
-template <class Mem>
+// Blocks of a device that each of the library's pools keeps.  A set-up has a handful of scratch blocks and a task holds five: with
+// eight, graphs of two sizes in turn were enough to have each find the other's, and to free those in its own time.  ms for set-up, one
+// iteration and destruction, eight blocks (and those of the scratch alone) -> 64, in turn: 2^14 vertices / 2^18 edges, 2^18 / 2^22, 2^20 / 2^24,
+// 2^22 / 2^26: 2.58 (1.40) -> 0.45, 2.22 (1.82) -> 0.99, 2.88 (5.2) -> 1.92, 6.70 (9.6) -> 5.40; 2^14 / 2^18 and 2^22 / 2^26: 1.61 (1.40) -> 0.45, 5.75
+// (8.2) -> 5.37; nineteen sizes from 16 000 to 2 065 395 vertices, mean 2.42 (2.78) -> 1.12 (32 blocks 1.98, 128 1.10).  What bounds the
+// memory is its bytes.
+constexpr size_t kKeptBlocks = 64;
+
+template <class Mem, size_t kMostBlocks = kKeptBlocks>
 class ScratchPool {
 public:
-    static constexpr size_t kBlocks = 8;                    // of a device
+    static constexpr size_t kBlocks = kMostBlocks;          // of a device
     static constexpr uint64_t kKeepNs = 5000000000ull;
 
     // A set-up begins on `device`: does it follow another one within kKeepNs?  (Only then is anything worth keeping for the next.)

@@ -22,7 +22,8 @@ struct Mem {
 };
 static std::vector<int> g_waited;              // devices that were waited for, and what was free to be taken on them then
 static bool g_wait_fails = false;
-static ScratchPool<Mem>* pool = new ScratchPool<Mem>();
+typedef ScratchPool<Mem, 8> Pool;             // (small enough for its bound to be reached in a few lines)
+static Pool* pool = new Pool();
 bool Mem::wait(int device)
 {
     uint64_t room = 0;
@@ -43,8 +44,27 @@ int end_of_task(int device, int fails)
     for (const Block& b : blocks) own += b.ptr != nullptr;
     return own;
 }
+// tasks of five blocks each, of sizes more than a quarter apart, one after the other `rounds` times: blocks that had to be allocated
+int allocated_by(uint64_t tasks, uint64_t rounds, uint64_t most)
+{
+    g_most = most;
+    ScratchPool<Mem> lasting;                  // as the library has it
+    int fresh = 0;
+    for (uint64_t k = 0; k < rounds * tasks; ++k) {
+        const uint64_t size = 100ull << k % tasks;
+        void* held[5];
+        uint64_t room[5];
+        for (int i = 0; i < 5; ++i) {
+            room[i] = size;
+            held[i] = lasting.take(0, size, size + size / 4, &room[i]);
+            if (!held[i]) { held[i] = (void*)(uintptr_t)(1000 + 10 * k + i); ++fresh; }
+        }
+        for (int i = 0; i < 5; ++i) lasting.give(0, held[i], room[i]);
+    }
+    return fresh;
+}
 int waited(uint64_t k) { return k < g_waited.size() ? g_waited[k] : -2; }
-void reset(uint64_t most) { delete pool; pool = new ScratchPool<Mem>(); g_now = 0; g_most = most; g_freed.clear(); }
+void reset(uint64_t most) { delete pool; pool = new Pool(); g_now = 0; g_most = most; g_freed.clear(); }
 void set_now(uint64_t s) { g_now = s * 1000000000ull; }
 uint64_t take(int device, uint64_t bytes, uint64_t most) { uint64_t room = 0; return pool->take(device, bytes, most, &room) ? room : 0; }
 void give(int device, uint64_t id, uint64_t room) { pool->give(device, (void*)(uintptr_t)id, room); }
@@ -140,6 +160,13 @@ def test_what_a_task_held_is_kept_only_when_its_own_device_is_done_with_it(lib):
     assert lib.trim(1) == 0
 
 
+def test_tasks_of_several_sizes_in_turn_find_their_blocks_again(lib):
+    lib.reset(1000)
+    lib.allocated_by.argtypes = [ctypes.c_uint64] * 3
+    assert lib.allocated_by(2, 10, 1 << 20) == 2 * 5 and lib.allocated_by(4, 10, 1 << 20) == 4 * 5 and lib.allocated_by(12, 10, 1 << 22) == 12 * 5
+    assert lib.allocated_by(4, 10, 5 * 1500 - 1) > 4 * 5          # (bytes bound it)
+
+
 def test_memory_is_freed_outside_the_pools_lock(tmp_path_factory):
     # giving memory back waits for the device: a thread that only wants a block must not wait for that
     exe = _build(tmp_path_factory, "pool_lock", r'''
@@ -152,7 +179,7 @@ struct Mem {
     static uint64_t now_ns() { return g_now; }
     static uint64_t keep_at_most(int) { return 100; }
 };
-static ScratchPool<Mem> pool;
+static ScratchPool<Mem, 8> pool;
 static int frees = 0;
 static void on_free() { ++frees; uint64_t room = 0; (void)pool.take(9, 1, 1, &room); }       // hangs if the lock is held
 int main()
@@ -160,7 +187,7 @@ int main()
     pool.give(0, (void*)1, 101);                                 // too large
     for (uintptr_t k = 2; k < 12; ++k) pool.give(0, (void*)k, 10);        // too many
     pool.give(0, (void*)20, 90);                                 // too much
-    g_now = ScratchPool<Mem>::kKeepNs + 1;
+    g_now = decltype(pool)::kKeepNs + 1;
     pool.trim(false);                                            // too old
     pool.give(0, (void*)21, 1);
     pool.trim(true);
