@@ -1,10 +1,15 @@
 // The sizes of the partition-centric layout, and the rules that choose among its kernels.  Host code only.
-// (The times beside the rules are of the sweeps as they were when each line was drawn, both sides by the same kernels.  With the
-// present ones - a branch-free gather loop, side-by-side searches in the scatter sweep - the sums are 4 to 20 % less and the lines lie
-// where they were: us an iteration, as the rules say / with the other side of the gather's, of the scatter's:
-//   10^6 / 10^7 25.6 / 28.1 (two a unit) / 26.1; 2^16 / 2^20 on 64 units 17.2 / 17.4 / 17.9; uniform 2^17 / 2^21 on 128 18.9 / 18.8 / 19.9;
-//   2^20 / 2^24 on 64 60.5 / 62.1 (one a unit) / 65.8; 3 x 10^6 / 6 x 10^7 on 128 103.9 / 105.4 / 120.9;
-//   kMergeBalance 20, 29, 40: 2^18 / 2^22 22.3, 20.3, 21.0.)
+// (The times beside the rules are of the sweeps as they were when each line was drawn, both sides by the same kernels.  The present
+// ones - a branch-free gather loop, side-by-side searches in the scatter sweep - take 9 to 23 % less, and were measured again with either
+// side of gather_alone and of scatter_alone forced: 138 graphs, 8 to 20 edges a vertex, 8000 to 150 000 edges a unit, 16 to 256 units.
+//   scatter_alone: within 3 % of the faster side on 130, 5 % on 136; at worst 7.3 (uniform 3.2 x 10^6 / 2.6 x 10^7), where the other side
+//     of the rule elsewhere costs up to 38 % (uniform 2.4 x 10^6 / 1.9 x 10^7 on 128 units 64.6 -> 88.8).
+//   gather_alone: within 3 % on 109; the others are all on the side of two workgroups, on up to 64 units from 48 000 to 100 000 edges a
+//     unit: one would take us an iteration 22.9 -> 19.6 (skewed 153 600 / 3.1 x 10^6 on 64 units), 25.6 -> 23.4 (201 600 / 4.0 x 10^6), 32.1 -> 29.9
+//     (320 000 / 6.4 x 10^6), 21.9 -> 18.7 (76 800 / 1.5 x 10^6 on 32), 23.8 -> 21.2 (50 400 / 1.0 x 10^6 on 16), uniform ones of 48 000 and 63 000
+//     a unit 3 to 11 % less; at 100 000 uniform ones take 5 to 10 % more with one, at 150 000 all but a few do.  On 256 units: uniform 2.0 x 10^6 /
+//     1.6 x 10^7 51.6 -> 48.9.  So that line could lie higher on few units by now; the kernels before them are what it is drawn for.
+// kMergeBalance 20, 29, 40 with the present kernels: 2^18 / 2^22 22.3, 20.3, 21.0.)
 #ifndef FR_PR_RULES_H
 #define FR_PR_RULES_H
 
