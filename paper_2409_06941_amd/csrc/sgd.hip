@@ -154,14 +154,14 @@ typedef float float4_any __attribute__((ext_vector_type(4), aligned(4)));
 // side by side in one wavefront, laid out once by k_sgd_schedule.  All four wavefronts bring the batch's rows to LDS, the
 // first one works through the rounds, all four write the rows back.
 // What bounds it: the longest chain of a stratum (16.1 M ratings, 512 x 512 cells, 64 factors: 85 updates, where its largest
-// cell has 109 ratings and a mean cell 61), at 82 ns a round with 64 factors, 74 with 32, 56 with 16 (a cell that is one chain of
+// cell has 109 ratings and a mean cell 61), at 81 ns a round with 64 factors, 73 with 32, 55 with 16 (a cell that is one chain of
 // n ratings takes 2.5 us + n rounds): one wavefront's instructions, some forty, and the latency of the sum's dependent moves.
 // Hence 32 lanes with two factors each (90.7 rounds) and not 16 with four (87.5 rounds of half as many instructions again),
 // rows fetched from LDS a round ahead, before the stores of the round that is being computed, and the row of a chain handed on
 // in registers; and twelve rounds without a branch (six with 32 factors, where twelve are no better): at a loop's head the
 // wavefront waits for everything it has asked the LDS for, which every third round took 102, 89 and 75 ns a round.  A stratum
-// takes 14 us there, of which the rounds are some 7.5; the rest is fetching and storing 42 000 rows (21 MB) and the
-// launch.  An iteration of 512 strata takes 7.3 ms (8.3 with branches between the rounds and nothing read ahead); one rating after
+// takes 13 us there, of which the rounds are some 7.5; the rest is fetching and storing 42 000 rows (21 MB) and the
+// launch.  An iteration of 512 strata takes 6.5 to 7.3 ms (7.6 to 8.3 with branches between the rounds and nothing read ahead); one rating after
 // the other straight from memory, as k_sgd_chain does it, it took 21.9 ms (16 factors, 300 000 ratings in 64 x 64 cells: 0.40, 0.45
 // and 1.9 ms).
 template <int F, int kLanes>
