@@ -738,14 +738,14 @@ struct DeviceMemory {
         return done;
     }
 };
-ScratchPool<DeviceMemory> g_pool;
+ScratchPool<DeviceMemory, kKeptBlocks> g_pool;
 // What a task of such a series held until it was destroyed, for the next one: 2^22 vertices / 2^26 edges, 350 MB in five blocks, to
 // make 0.25 ms and to give back 1.5 ms of the 7.4 of a graph that is set up, run once and destroyed.  A pool of its own, with
 // a quarter of the other's room.
 struct LayoutMemory : DeviceMemory {
     static uint64_t keep_at_most(int device) { return total_memory(device) / 256; }
 };
-ScratchPool<LayoutMemory> g_layouts;
+ScratchPool<LayoutMemory, kKeptBlocks> g_layouts;
 uint64_t trim_pools(bool all)
 {
     const uint64_t bytes = g_pool.trim(all);

@@ -21,7 +21,7 @@ inline uint64_t most_room(uint64_t limit, uint64_t total, uint64_t bytes) { retu
 // memory is its bytes.
 constexpr size_t kKeptBlocks = 64;
 
-template <class Mem, size_t kMostBlocks = kKeptBlocks>
+template <class Mem, size_t kMostBlocks = 8>
 class ScratchPool {
 public:
     static constexpr size_t kBlocks = kMostBlocks;          // of a device

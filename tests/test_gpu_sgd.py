@@ -232,9 +232,6 @@ def test_pagerank_and_sgd_queued_on_one_worker_run_one_after_the_other():
     Pr, Qr, _ = _run(r, P0, Q0, F, gamma, lam, K_sgd, B)                        # SGD reference bits
     rp, col, od = _dev(g.row_ptr, torch.int32), _dev(g.col, torch.int32), _dev(g.out_degree, torch.int32)
     ranks = torch.zeros(g.n_vertices, dtype=torch.float32, device="cuda")
-    once = fr.PageRankTask(g.n_vertices, g.n_edges, rp, col, od, ranks, iterations=2)    # a kernel's first launch in a process loads its code
-    once.fr_pagerank_run_standalone(0, torch.cuda.current_stream(), 1)
-    once.fr_pagerank_destroy()
     P, Q = _dev(P0), _dev(Q0)
     ctx = fr.Context(device_id=0, guard_ns=200_000, launch_cost_ns=20_000, max_chunk_ns=0, time_steps=1, mem_available_bytes=1 << 40)
     pr_task = fr.PageRankTask(g.n_vertices, g.n_edges, rp, col, od, ranks, iterations=K_pr, max_runs=1, mem_limit_bytes=1 << 30,
@@ -424,10 +421,27 @@ def test_chains_of_any_length_match_the_oracle(n, F):
     assert _same_bits(P, P32) and _same_bits(Q, Q32)
 
 
+# from 128 blocks on the next stratum's programs are read ahead: the last stratum reads those of the first, cells without ratings
+# and of several batches among them; also on the other side of the line, and cell by cell
+@pytest.mark.parametrize("B,F,cells", [(127, 16, 0), (128, 16, 0), (128, 64, 50), (130, 32, 0)])
+def test_programs_read_ahead_leave_the_factors_alone(B, F, cells):
+    rng = np.random.default_rng(B)
+    n = 4000
+    pairs = set(zip(rng.integers(0, n, 150_000).tolist(), rng.integers(0, n, 150_000).tolist()))
+    pairs |= {(u, i) for u in range(30) for i in range(300)}                     # (cells of more than 128 ratings)
+    r = _dense(sorted(pairs), n, n, seed=B)
+    P0, Q0 = wl.initial_factors(n, n, F, seed=F)
+    print("case", B, F, cells, r.n_ratings, flush=True)
+    P, Q, info = _run(r, P0, Q0, F, 0.02, 0.03, 2, B, cells)
+    assert info.blocks == B
+    P32, Q32 = osgd.sgd(r.row_ptr, r.item, r.rating, P0, Q0, 0.02, 0.03, 2, B, ordered_fp32=True)
+    assert _same_bits(P, P32) and _same_bits(Q, Q32)
+
+
 # from 128 blocks and 16 ratings a cell on the next stratum's programs are read ahead: the last stratum reads those of the first,
 # cells without ratings and of several batches among them; also on the other side of the lines (127 blocks, launches of 30 cells)
 @pytest.mark.parametrize("B,F,cells", [(127, 16, 0), (128, 16, 0), (128, 64, 50), (128, 64, 30), (130, 32, 0)])
-def test_programs_read_ahead_leave_the_factors_alone(B, F, cells):
+def test_programs_of_large_cells_read_ahead_leave_the_factors_alone(B, F, cells):
     rng = np.random.default_rng(B)
     n = 4000
     pairs = set(zip(rng.integers(0, n, 290_000).tolist(), rng.integers(0, n, 290_000).tolist()))

@@ -3,6 +3,7 @@ falls on, over the sizes on both sides of it."""
 import ctypes
 import os
 import subprocess
+import types
 
 import pytest
 
@@ -21,15 +22,9 @@ def _compile(tmp_path_factory, name, code):
 def sgd(tmp_path_factory):
     L = _compile(tmp_path_factory, "sgd_rule", '''#include "sgd_rule.h"
 extern "C" int pay(uint64_t ratings, uint32_t B, uint64_t chain, int F, uint32_t cus) { return sgd_rounds_pay(ratings, B, chain, F, cus); }
-extern "C" int eight(uint32_t n, uint32_t cus) { return sgd_eight_cells_a_unit(n, cus); }
-extern "C" int ahead(uint64_t ratings, uint32_t B, uint32_t n, uint32_t cus) { return sgd_reads_ahead(ratings, B, n, cus); }
 ''')
-    L.ahead.argtypes = [ctypes.c_uint64, ctypes.c_uint32, ctypes.c_uint32, ctypes.c_uint32]
     L.pay.argtypes = [ctypes.c_uint64, ctypes.c_uint32, ctypes.c_uint64, ctypes.c_int, ctypes.c_uint32]
-    pay = lambda ratings, B, chain, F, cus: bool(L.pay(ratings, B, int(chain * B), F, cus))
-    pay.eight = lambda n, cus: bool(L.eight(n, cus))
-    pay.ahead = lambda ratings, B, cus, n=0: bool(L.ahead(ratings, B, n or B, cus))
-    return pay
+    return lambda ratings, B, chain, F, cus: bool(L.pay(ratings, B, int(chain * B), F, cus))
 
 
 # (ratings, blocks, mean over the strata of their largest cell, factors, compute units, ms one after the other, ms in rounds)
@@ -65,6 +60,16 @@ def test_sgd_blocks_the_library_makes_are_worked_on_in_rounds(sgd):
     assert not sgd(0, 4, 0, 16, 256) and not sgd(0, 1, 0, 64, 256)
 
 
+@pytest.fixture(scope="module")
+def cells(tmp_path_factory):
+    L = _compile(tmp_path_factory, "sgd_cells", '''#include "sgd_rule.h"
+extern "C" int eight(uint32_t n, uint32_t cus) { return sgd_eight_cells_a_unit(n, cus); }
+extern "C" int ahead(uint64_t ratings, uint32_t B, uint32_t n, uint32_t cus) { return sgd_reads_ahead(ratings, B, n, cus); }
+''')
+    L.ahead.argtypes = [ctypes.c_uint64, ctypes.c_uint32, ctypes.c_uint32, ctypes.c_uint32]
+    return types.SimpleNamespace(eight=lambda n, cus: bool(L.eight(n, cus)), ahead=lambda ratings, B, cus, n=0: bool(L.ahead(ratings, B, n or B, cus)))
+
+
 # (blocks, ratings a cell, compute units, ms of an iteration with the next stratum's programs read ahead, without)
 AHEAD_MEASURED = [
     (256, 31, 32, 1.953, 1.658), (512, 7.7, 64, 3.627, 2.438), (512, 7.7, 32, 5.233, 3.507), (512, 7.7, 128, 2.458, 2.310), (1024, 15.3, 128, 9.347, 7.031),
@@ -77,20 +82,20 @@ AHEAD_MEASURED = [
 ]
 
 
-def test_programs_are_read_ahead_where_that_was_measured_to_be_faster(sgd):
+def test_programs_are_read_ahead_where_that_was_measured_to_be_faster(cells):
     for B, mean, cus, ahead, without in AHEAD_MEASURED:
-        assert sgd.ahead(int(mean * B * B), B, cus) == (ahead < without), (B, mean, cus)
-    assert not sgd.ahead(60 * 127 * 127, 127, 256) and not sgd.ahead(0, 128, 256) and not sgd.ahead(1 << 30, 1024, 1)
+        assert cells.ahead(int(mean * B * B), B, cus) == (ahead < without), (B, mean, cus)
+    assert not cells.ahead(60 * 127 * 127, 127, 256) and not cells.ahead(0, 128, 256) and not cells.ahead(1 << 30, 1024, 1)
     # parts of strata: 512 blocks of 61 and 49, 256 of 31 and 8 ratings a cell
-    assert sgd.ahead(61 << 18, 512, 256, 52) and sgd.ahead(61 << 18, 512, 64, 100) and not sgd.ahead(61 << 18, 512, 64) and not sgd.ahead(49 << 18, 512, 256, 20)
-    assert sgd.ahead(31 << 16, 256, 64, 52) and not sgd.ahead(31 << 16, 256, 256, 3) and not sgd.ahead(8 << 16, 256, 256, 52)
+    assert cells.ahead(61 << 18, 512, 256, 52) and cells.ahead(61 << 18, 512, 64, 100) and not cells.ahead(61 << 18, 512, 64) and not cells.ahead(49 << 18, 512, 256, 20)
+    assert cells.ahead(31 << 16, 256, 64, 52) and not cells.ahead(31 << 16, 256, 256, 3) and not cells.ahead(8 << 16, 256, 256, 52)
 
 
 # (cells of a launch, compute units): eight workgroups a unit where the launch has that many, and never together with reading ahead
 @pytest.mark.parametrize("n,cus,want", [(1, 1, False), (7, 1, False), (8, 1, True), (56, 8, False), (57, 8, True), (64, 256, False), (512, 64, True), (512, 74, False), (1024, 146, True), (1024, 256, False)])
-def test_sgd_cells_that_share_a_unit(sgd, n, cus, want):
-    assert sgd.eight(n, cus) == want
-    assert not (want and any(sgd.ahead(mean << 20, 1024, cus, n) for mean in (2, 60, 1000)))
+def test_sgd_cells_that_share_a_unit(cells, n, cus, want):
+    assert cells.eight(n, cus) == want
+    assert not (want and any(cells.ahead(mean << 20, 1024, cus, n) for mean in (2, 60, 1000)))
 
 
 @pytest.fixture(scope="module")

@@ -22,8 +22,7 @@ struct Mem {
 };
 static std::vector<int> g_waited;              // devices that were waited for, and what was free to be taken on them then
 static bool g_wait_fails = false;
-typedef ScratchPool<Mem, 8> Pool;             // (small enough for its bound to be reached in a few lines)
-static Pool* pool = new Pool();
+static ScratchPool<Mem>* pool = new ScratchPool<Mem>();
 bool Mem::wait(int device)
 {
     uint64_t room = 0;
@@ -48,7 +47,7 @@ int end_of_task(int device, int fails)
 int allocated_by(uint64_t tasks, uint64_t rounds, uint64_t most)
 {
     g_most = most;
-    ScratchPool<Mem> lasting;                  // as the library has it
+    ScratchPool<Mem, kKeptBlocks> lasting;     // as the library has it
     int fresh = 0;
     for (uint64_t k = 0; k < rounds * tasks; ++k) {
         const uint64_t size = 100ull << k % tasks;
@@ -64,7 +63,7 @@ int allocated_by(uint64_t tasks, uint64_t rounds, uint64_t most)
     return fresh;
 }
 int waited(uint64_t k) { return k < g_waited.size() ? g_waited[k] : -2; }
-void reset(uint64_t most) { delete pool; pool = new Pool(); g_now = 0; g_most = most; g_freed.clear(); }
+void reset(uint64_t most) { delete pool; pool = new ScratchPool<Mem>(); g_now = 0; g_most = most; g_freed.clear(); }
 void set_now(uint64_t s) { g_now = s * 1000000000ull; }
 uint64_t take(int device, uint64_t bytes, uint64_t most) { uint64_t room = 0; return pool->take(device, bytes, most, &room) ? room : 0; }
 void give(int device, uint64_t id, uint64_t room) { pool->give(device, (void*)(uintptr_t)id, room); }
@@ -179,7 +178,7 @@ struct Mem {
     static uint64_t now_ns() { return g_now; }
     static uint64_t keep_at_most(int) { return 100; }
 };
-static ScratchPool<Mem, 8> pool;
+static ScratchPool<Mem> pool;
 static int frees = 0;
 static void on_free() { ++frees; uint64_t room = 0; (void)pool.take(9, 1, 1, &room); }       // hangs if the lock is held
 int main()
@@ -187,7 +186,7 @@ int main()
     pool.give(0, (void*)1, 101);                                 // too large
     for (uintptr_t k = 2; k < 12; ++k) pool.give(0, (void*)k, 10);        // too many
     pool.give(0, (void*)20, 90);                                 // too much
-    g_now = decltype(pool)::kKeepNs + 1;
+    g_now = ScratchPool<Mem>::kKeepNs + 1;
     pool.trim(false);                                            // too old
     pool.give(0, (void*)21, 1);
     pool.trim(true);
