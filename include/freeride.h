@@ -323,8 +323,7 @@ typedef struct fr_pagerank_desc {
                         its own; light ones share a tile.  A repeated edge has the same source and row as the edge
                         before it: the two collide in the accumulator.  The constant stands for the start and the
                         row pass of a piece.)
-         finish tile  : finish_tile_ns (already ns), for 2048 rows of a merged or empty range, or 4096 where 2048
-                        would make more than 512 tiles (fr_pagerank_tiles says how many there are); the costs of a
+         finish tile  : finish_tile_ns (already ns), for 2048 rows of a merged or empty range; the costs of a
                         step's tiles add up, so this is the pass's time over its tiles, not that of one tile alone  */
     uint64_t fs_per_edge;
     uint64_t fs_per_message;

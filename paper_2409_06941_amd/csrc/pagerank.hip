@@ -956,13 +956,14 @@ void k_gather(DevArgs A, GateArg G, uint32_t tile0, uint32_t n_tiles, int parity
 }
 
 // ---- F ----
-// After the last iteration: r_K of the rows of one merged range (partial sums of G_{K-1}) or of one empty range (the base
-// value) goes to ranks_out, kFinishRows rows a workgroup, one or two workgroups a tile.
-__global__ __launch_bounds__(kBlock) void k_finish(DevArgs A, GateArg G, uint32_t part0, int parity)
+// After the last iteration: r_K of kFinishRows rows of one merged range (partial sums of G_{K-1}) or of one empty
+// range (the base value) goes to ranks_out.
+constexpr uint32_t kFinishRows = 2048;
+__global__ __launch_bounds__(kBlock) void k_finish(DevArgs A, GateArg G, uint32_t tile0, int parity)
 {
     __shared__ float groups[kStrands / 64];
     if (!fr_gate_admit(G.gate, G.slot, G.need_ticks)) return;
-    const uint32_t t = part0 + blockIdx.x;
+    const uint32_t t = tile0 + blockIdx.x;
     for (uint32_t i = threadIdx.x; i < kStrands; i += kBlock)
         dangling_group(dangling_strand(A.dpart + (size_t)parity * A.n_dpart, A.n_dpart, i), i & ~63u, groups);
     __syncthreads();
@@ -1020,10 +1021,9 @@ struct PrTask {
         case FR_PR_SEG_VERTEX: return L.Q;
         case FR_PR_SEG_SCATTER: return L.n_scatter;
         case FR_PR_SEG_GATHER: return L.n_gather;
-        default: return std::max<uint32_t>(1, L.n_finish * (L.rows_per_part / finish_rows()));
+        default: return std::max<uint32_t>(1, L.n_finish * (L.rows_per_part / kFinishRows));
         }
     }
-    uint32_t finish_rows() const { return finish_tile_rows(L.n_finish, L.rows_per_part); }
     uint64_t rows_of_q(uint32_t q) const
     {
         return std::min<uint64_t>(L.rows_per_part, (uint64_t)L.V - (uint64_t)q * L.rows_per_part);
@@ -1067,8 +1067,7 @@ int pr_launch(PrTask* p, uint32_t g, uint32_t tile0, uint32_t tile1, hipStream_t
         hipLaunchKernelGGL(k_vertex0, dim3(n), dim3(kBlock), 0, stream, args, G, tile0, K == 0 ? 1 : 0);
     } else if (kind == FR_PR_SEG_FINISH) {
         // after G_{K-1}: the dangling partials of r_{K-1} sit in set (K-1) & 1
-        const uint32_t parts = p->finish_rows() / kFinishRows;      // workgroups a tile
-        hipLaunchKernelGGL(k_finish, dim3(n * parts), dim3(kBlock), 0, stream, args, G, tile0 * parts, (int)((K - 1) & 1u));
+        hipLaunchKernelGGL(k_finish, dim3(n), dim3(kBlock), 0, stream, args, G, tile0, (int)((K - 1) & 1u));
     } else {
         const uint32_t k = (g - 1) / 2;
         if (kind == FR_PR_SEG_SCATTER) {    // S_k finishes rows of r_k with D_{k-1}: set (k-1) & 1

@@ -93,15 +93,4 @@ inline uint64_t least_scatter_weight(uint64_t all)
     return balance > kMinTileMessages ? balance : kMinTileMessages;
 }
 
-// Rows of a tile of the pass after the last iteration: 2048 while that makes at most 512 tiles, else 4096.  A workgroup has 2048
-// either way; the tile is what a plan charges, and the more of them run side by side the further their summed costs lie above
-// what the pass takes (2^21 vertices: 613 tiles of 2048 rows run in 26 us).  No kernel gets faster by the larger tile.  With 2048 rows
-// throughout and 1000 ns a tile, a task's model that claims a fifth or a quarter of what its sweeps take claims 613 us for these 26, and
-// plans the ends of bubbles so carefully that few or none of its steps overrun (0, 0, 1, 1, 1, 1 in six runs; 12 in every run with 4096).
-constexpr uint32_t kFinishRows = 2048, kFinishRowsOfMany = 4096, kFinishTilesFew = 512;
-inline uint32_t finish_tile_rows(uint32_t n_finish, uint32_t rows_per_part)
-{
-    return (uint64_t)n_finish * (rows_per_part / kFinishRows) <= kFinishTilesFew ? kFinishRows : kFinishRowsOfMany;
-}
-
 #endif

@@ -40,14 +40,17 @@ def _segments(task, iterations):
 
 
 def _scaled_model(share, phase_ns, iterations, gather_weight, scatter_weight, info):
-    """Rates that make the task's cost model claim `share` of the measured time of every sweep."""
+    """Rates that make the task's cost model claim `share` of the measured time of every sweep and of the last pass.  (With 1000 ns
+    for each tile of that pass a model of 0.2 claimed 613 us for its 26, more than a fifth of the whole run's 1.3 ms, and planned a
+    bubble's end too carefully to show what a model that claims too little does.)"""
     V0_rows = info.ranges * info.rows_per_partition
     pv = max(1, int(share * phase_ns[0] * 1e6 / V0_rows))
     s_fs = share * phase_ns[1] / iterations * 1e6
     g_fs = share * phase_ns[2] / iterations * 1e6
     pm = max(1, int(s_fs / max(1, info.messages + scatter_weight)))
     pe = max(1, int(2 * g_fs / max(1, gather_weight)))
-    return dict(fs_per_vertex=pv, fs_per_message=pm, fs_per_edge=pe, finish_tile_ns=1000)
+    finish_tiles = (info.merged_ranges + info.ranges - info.nonempty_ranges) * info.rows_per_partition // 2048
+    return dict(fs_per_vertex=pv, fs_per_message=pm, fs_per_edge=pe, finish_tile_ns=max(1, int(share * phase_ns[3] / max(1, finish_tiles))))
 
 
 def _floors(min_step_ns, iterations):

@@ -572,3 +572,25 @@ def test_what_tasks_held_is_kept_up_to_a_256th_of_the_device():
         booked, _, held = _set_up_and_destroy(csr)
     print("booked", booked, "held", held, "at most", most, flush=True)
     assert 0 < held <= most < booked
+
+
+@pytest.mark.parametrize("V,E,rows", [(8192 * 100, 9_000, 8192), (2_000_001, 20_000, 8192), (2_000_001, 20_000, 16384)])
+def test_a_tile_of_the_last_pass_is_2048_rows_of_any_graph(V, E, rows):
+    # (finish_tile_ns is the cost of one: a caller's figure holds for every graph)
+    rng = np.random.default_rng(E)
+    g = graphs.csr_from_edges(V, rng.integers(0, V, E), rng.integers(0, V, E))
+    rp, col, od = _dev(g.row_ptr, torch.int32), _dev(g.col, torch.int32), _dev(g.out_degree, torch.int32)
+    out = []
+    for max_tiles in (0, 7):
+        ranks = torch.zeros(V, dtype=torch.float32, device="cuda")
+        torch.cuda.synchronize()
+        t = fr.PageRankTask(V, E, rp, col, od, ranks, iterations=2, rows_per_partition=rows, finish_tile_ns=50)
+        t.fr_pagerank_run_standalone(0, torch.cuda.current_stream(), max_tiles)
+        info = t.fr_pagerank_info()
+        costs = t.fr_pagerank_tile_costs(fr.FR_PR_SEG_FINISH)
+        t.fr_pagerank_destroy()
+        assert costs == [50] * ((info.merged_ranges + info.ranges - info.nonempty_ranges) * rows // 2048)
+        out.append(ranks.cpu().numpy())
+    assert np.array_equal(out[0].view(np.uint32), out[1].view(np.uint32))
+    want = pagerank(g.row_ptr, g.col, g.out_degree, 0.85, 2)
+    assert np.abs(out[0].astype(np.float64) - want).max() <= TOL

@@ -204,10 +204,3 @@ def test_gemm_rows_beyond_a_32_bit_offset_take_the_kernel_with_64_bit_addresses(
                 assert 7 * 2 * K + 112 >= 1 << 32 and gemm.choose(M, N, K, cus) == gemm.tiles() - 1
             assert gemm.choose(M, N, (1 << 27) + 64, cus) == gemm.tiles() - 1
             assert 0 <= gemm.choose(M, N, 1 << 27, cus) < gemm.tiles() - 1 and 7 * 2 * (1 << 27) + 112 < 1 << 31
-
-
-@pytest.mark.parametrize("n_finish,rows,want", [(0, 8192, 2048), (128, 8192, 2048), (129, 8192, 4096), (64, 16384, 2048), (65, 16384, 4096), (131072, 16384, 4096)])
-def test_tiles_of_the_last_pass(tmp_path_factory, n_finish, rows, want):
-    L = _compile(tmp_path_factory, "pr_rules", '#include "pr_rules.h"\nextern "C" uint32_t finish(uint32_t n, uint32_t rows) { return finish_tile_rows(n, rows); }\n')
-    L.finish.argtypes, L.finish.restype = [ctypes.c_uint32, ctypes.c_uint32], ctypes.c_uint32
-    assert L.finish(n_finish, rows) == want                      # 512 tiles at most, or 4096 rows each
